@@ -158,7 +158,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 T *__restrict__ out,   // dQ, dK or dV
                 T *__restrict__ out2,  // dV of the fused dK + dV pass, else unused
                 int S, int nR, int N, float c, float scale, uint32_t rsign, int causal, unsigned stat_bytes,
-                int group)
+                int group, int chunk_first, int chunk_heads)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using E = Elem<T>;
@@ -182,11 +182,18 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 5, l32 = lane & 31;
 
-    const int wg = remap_workgroup(blockIdx.x, N, false);
-    const int head = wg / nR;                     // head of the resident side: a query head (dQ pass) or a key/value head
     const int Gn = GRP ? group : 1;              // query heads per key/value head
-    // causal: query tiles get longer with their index, key tiles shorter; start the long ones first
-    const int rt = (causal && !KEYS_RES) ? nR - 1 - (wg - head * nR) : wg - head * nR;
+    int head, rt;                                 // head of the resident side (a query head in the dQ pass, else a key/value head) and tile
+    if (causal && chunk_heads > 0) {
+        // query tiles get longer with their index, key tiles shorter: the long ones of all heads first (causal_tile)
+        const CausalTile ct = causal_tile(blockIdx.x, nR, chunk_first, chunk_heads);
+        head = ct.head;
+        rt = KEYS_RES ? ct.level : nR - 1 - ct.level;
+    } else {
+        const int wg = remap_workgroup(blockIdx.x, N, false);
+        head = wg / nR;
+        rt = (causal && !KEYS_RES) ? nR - 1 - (wg - head * nR) : wg - head * nR;
+    }
     const size_t head_off = (size_t)head * (size_t)S * D;
     const T *r1 = (KEYS_RES ? k : q) + head_off;       // resident operands
     const T *r2 = (KEYS_RES ? v : dout) + head_off;

@@ -119,6 +119,36 @@ __device__ __forceinline__ int remap_workgroup(int id, int N, bool linear) {
     return x * base + (x < rem ? x : rem) + y;
 }
 
+// Order of the tiles under the causal mask, where the work of a tile grows (queries resident) or shrinks (keys
+// resident) with its index.  Every XCD starts the longest tiles of ALL its heads first ("level" 0 of each head, then
+// level 1, ...), so that what is left to start near the end are the shortest ones.  Head after head, each longest tile
+// first, the long tiles of the last heads start when most of the launch is over and the chip drains behind them: with
+// 64 heads of 16 tiles and 64 workgroups resident per XCD, 24 tile units instead of the 17 that the work amounts to.
+// Heads are taken in chunks of 8 * hg (hg per XCD; causal_chunks in sdpa_fwd_launch.h), of which the first may be short.
+// The heads of a chunk that eight does not divide (rem < 8) are dealt tile by tile, level by level, over all XCDs.
+// Returns the level in .level and the head in .head; with N = BH * nQ every pair is met exactly once.
+struct CausalTile { int head, level; };
+__device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int hg) {
+    const int x = id & 7;
+    int y = id >> 3;
+    int full = first >> 3, rem = first & 7, h0 = 0;
+    const int in_first = full * nQ + ((nQ * rem + 7 - x) >> 3);   // this XCD's share of the first chunk
+    if (y >= in_first) {
+        y -= in_first;
+        const int c = y / (hg * nQ);
+        y -= c * hg * nQ;
+        h0 = first + c * 8 * hg;
+        full = hg;
+        rem = 0;
+    }
+    // before level l this XCD has before(l) = l * full + ceil((l * rem - x) / 8) tiles of its own and dealt ones;
+    // the largest l with before(l) <= y is:
+    const int level = (8 * y + x) / (8 * full + rem);
+    const int i = y - (level * full + ((level * rem + 7 - x) >> 3));
+    const int dealt = ((x - level * rem) & 7);                    // of this level's rem dealt tiles, the one that is ours
+    return CausalTile{h0 + (i < full ? x * full + i : 8 * full + dealt), level};
+}
+
 // Hides how a register value was computed from the optimiser.  Used on loop-invariant LDS pointers:
 // left transparent, the compiler splits them into a common base and per-pointer offsets and re-adds the
 // two in front of every LDS read of the loop (one vector-ALU instruction per read).
@@ -153,7 +183,8 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 float tau, uint32_t qsign, int linear_grid, int causal,
                 int Skv_arg, int splits_arg, float *__restrict__ ws, int rows_per_head,
                 const int *__restrict__ kv_lens, int heads_per_batch,
-                const int *__restrict__ block_table, int max_blocks, int block_shift, int tile_rot)
+                const int *__restrict__ block_table, int max_blocks, int block_shift, int tile_rot,
+                int chunk_first, int chunk_heads, int batches)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses device-only types
     constexpr bool KV = KVM != 0, PAGED = KVM == 2;
@@ -188,13 +219,27 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     const int splits = KV ? splits_arg : 1;
     const int Sp = KV ? rows_per_head : S;        // query positions per query head (S = G * Sp rows when folded)
     const bool folded = KV && Sp != S;
-    const int wg = remap_workgroup(blockIdx.x, N, linear_grid != 0);
-    // query tile fastest, then split, then head: neighbours share one run of K/V tiles
-    const int hs = wg / nQ;
-    const int head = KV ? hs / splits : hs;
+    // query tile fastest, then split, then head: neighbours share one run of K/V tiles.  Under the causal mask the work
+    // of a query tile grows with its index, and the long ones of all heads are started first (causal_tile).
+    int hs, qt;
+    if (causal && !linear_grid && chunk_heads > 0) {
+        const CausalTile ct = causal_tile(blockIdx.x, nQ, chunk_first, chunk_heads);
+        hs = ct.head;
+        qt = nQ - 1 - ct.level;
+        if (KV && folded && Sp % TM == 0) {       // the last tile of every folded query head, then the one before it, ...
+            const int G_heads = S / Sp, per_head = Sp / TM;
+            qt = (ct.level % G_heads) * per_head + per_head - 1 - ct.level / G_heads;
+        }
+    } else {
+        const int wg = remap_workgroup(blockIdx.x, N, linear_grid != 0);
+        hs = wg / nQ;
+        qt = causal ? nQ - 1 - (wg - hs * nQ) : wg - hs * nQ;
+    }
+    int head = KV ? hs / splits : hs;
     const int sp = KV ? hs - head * splits : 0;
-    // under the causal mask the work of a query tile grows with its index: start the long ones first
-    const int qt = causal ? nQ - 1 - (wg - hs * nQ) : wg - hs * nQ;
+    // Cache entries differ in length: batch entries vary fastest over the workgroups, so that each XCD gets a share of
+    // every entry (head by head, the XCD with the longest entry finishes last).
+    if (KV && kv_lens != nullptr) head = (head % batches) * heads_per_batch + head / batches;
     const size_t head_off = (size_t)head * (size_t)S * D;
     const size_t kv_off = (size_t)head * (size_t)(KV ? Skv_arg : S) * D;
     // key rows of this head; S is the number of query rows

@@ -24,9 +24,34 @@ struct LaunchArgs {
     const int *block_table; // kv = 1: NULL, or pages of a paged cache (device, int32 [B][max_blocks]); k, v are then [pages][heads_per_batch][1 << block_shift][D]
     int max_blocks, block_shift;
     int tile_rot;      // kv = 1, dense cache: 1 = every workgroup starts its sweep over the unmasked tiles at a tile of its own
+    int batches;       // kv = 1: batch entries (BH / heads_per_batch)
     int rows_per_head; // kv = 1: query positions per query head; S / rows_per_head query heads are folded into the S rows
     hipStream_t stream;
 };
+
+// Chunks in which causal_tile (sdpa_fwd_kernel.h) takes the heads: heads per XCD and chunk (0: the plain order, head
+// after head), and heads of the first chunk.  `tiles` workgroups per head, `stream_bytes` of streamed operands per head.
+// From timings of every chunk size on 24 shapes (us, plain order -> this rule):
+//   * up to one workgroup per CU all of them start at once and the order is moot: the plain one, whose index arithmetic
+//     is shorter (0.3-0.5 us of 13-19 at nine heads of S = 1024);
+//   * up to two per CU: all heads in one chunk, so that a CU holds a long tile and a short one (BF16, 64 heads of
+//     S = 1024 at D = 128: 29.8 -> 27.4; nine heads of S = 4096: 78.3 -> 64.2);
+//   * beyond, eight heads per XCD, as long as the chunk streams at most 8 MiB per XCD, twice its L2 (64 heads of
+//     S = 2048, D = 96: 71.5 -> 60, D = 128: 89 -> 72; S = 4096, D = 128: 274 -> 248 with four heads; S = 8192: 962 ->
+//     930 with two and 982 with eight).
+struct CausalChunks { int first, heads; };
+inline CausalChunks causal_chunks(int heads, int tiles, long long stream_bytes)
+{
+    const long long n = (long long)heads * tiles;
+    int hg = (heads + 7) / 8;
+    if (n <= 256 || tiles == 1) return CausalChunks{heads, 0};
+    if (n > 512) {
+        const long long fit = stream_bytes > 0 ? (8ll << 20) / stream_bytes : 8;
+        const int most = fit > 8 ? 8 : fit < 1 ? 1 : (int)fit;
+        if (hg > most) hg = most;
+    }
+    return CausalChunks{heads - (heads - 1) / (8 * hg) * (8 * hg), hg};
+}
 
 // Rows of slack after the B*H*S entries of each backward statistics array: the keys-resident pass
 // reads them 4 rows at a time up to a tile past the last row of the last head.

@@ -457,6 +457,7 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     a.rows_per_head = Sq;
     a.kv_lens = kv_lens;
     a.heads_per_batch = Hkv;
+    a.batches = B;
     a.block_table = block_table;
     a.max_blocks = max_blocks;
     a.block_shift = block_shift;
