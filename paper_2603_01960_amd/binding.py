@@ -1,7 +1,9 @@
-"""ctypes binding of libtiled_sdpa.so: argument marshalling only.
+"""Python binding of libtiled_sdpa.so: argument marshalling only.
 
 Every step of the forward pass runs in the HIP kernels behind the C-ABI declared
 in include/tiled_sdpa.h.  PyTorch supplies device memory and the current stream.
+The tensor functions (sdpa, sdpa_kv, sdpa_paged, sdpa_backward) go through native
+code (csrc/torch_calls.cpp), the C-ABI itself is exposed through ctypes.
 There is no CPU fallback: if the library is missing, loading raises.
 """
 from __future__ import annotations
@@ -17,7 +19,9 @@ FLAG_CAUSAL = 8
 
 _PKG = Path(__file__).resolve().parent
 _LIB_PATH = _PKG / "libtiled_sdpa.so"
+_CALLS_PATH = _PKG / "_torch_calls.so"
 _lib = None
+_native = None
 
 EXPORTS = (
     "tiled_sdpa_fwd",
@@ -104,6 +108,30 @@ def load_library():
     return lib
 
 
+def _calls():
+    """The native tensor entry points (csrc/torch_calls.cpp)."""
+    global _native
+    if _native is None:
+        import torch  # noqa: F401  (its libraries have to be in the process first)
+
+        load_library()
+        if not _CALLS_PATH.exists():
+            raise FileNotFoundError(
+                f"{_CALLS_PATH} not found: build it with `python -m paper_2603_01960_amd.build` "
+                "(there is no fallback path)")
+        from . import _torch_calls
+
+        _native = _torch_calls
+    return _native
+
+
+def _checked(result):
+    """Result object of a native call, or its status code as an exception."""
+    if type(result) is int:
+        raise TiledSdpaError(result, status_string(result))
+    return result
+
+
 def version() -> int:
     return int(load_library().tiled_sdpa_version())
 
@@ -132,8 +160,8 @@ def tune_tile(q, k, v, causal: bool = False, scale=None, *, launches: int = 10, 
     out = torch.empty_like(q)
     tm, tn = ctypes.c_int(0), ctypes.c_int(0)
     ms = (ctypes.c_float * len(TILE_ORDER))()
-    guard, stream = _guard_and_stream(torch, q.device)
-    with guard:
+    with torch.cuda.device(q.device):
+        stream = torch.cuda.current_stream(q.device).cuda_stream
         st = load_library().tiled_sdpa_tune_tile(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), B, H, S, D,
                                                  math.nan if scale is None else float(scale),
                                                  F16 if q.dtype == torch.float16 else BF16, stream, flags, launches,
@@ -196,30 +224,6 @@ def tiled_sdpa_fwd(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, S, D, scale, dtype
                                              float(scale), dtype, stream))
 
 
-
-class _NoGuard:
-    def __enter__(self):
-        return self
-
-    def __exit__(self, *exc):
-        return False
-
-
-_NO_GUARD = _NoGuard()
-
-
-def _guard_and_stream(torch, device):
-    """(context manager that makes ``device`` current for the launch, raw handle of the stream that is
-    current on it).  A short call is dominated by host time, so the usual case -- the tensors live on
-    the current device -- takes no device switch and reads the raw stream handle directly."""
-    current = torch.cuda.current_device()
-    index = current if device.index is None else device.index
-    guard = _NO_GUARD if index == current else torch.cuda.device(index)
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    stream = raw(index) if raw is not None else torch.cuda.current_stream(index).cuda_stream
-    return guard, stream
-
-
 def tiled_sdpa_fwd_ex(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, S, D, scale, dtype, stream,
                       tile_m=0, tile_n=0, flags=0) -> int:
     return int(load_library().tiled_sdpa_fwd_ex(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, B, H, S, D,
@@ -271,56 +275,7 @@ def sdpa_kv(q, k, v, causal: bool = False, scale=None, *, splits: int = 0, retur
     ``kv_lens`` (int32 device tensor [B]): k, v are a cache of capacity Skv of which batch entry b holds
     kv_lens[b] valid rows (tiled_sdpa_fwd_kvcache); rows no key reaches come back as zeros.
     """
-    import torch
-
-    if causal:
-        flags |= FLAG_CAUSAL
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if not isinstance(t, torch.Tensor) or not t.is_cuda:
-            raise ValueError(f"{name} must be a device tensor")
-        if t.dim() != 4 or not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous [B, H, S, D]")
-    if q.dtype not in (torch.float16, torch.bfloat16) or k.dtype != q.dtype or v.dtype != q.dtype:
-        raise ValueError("q, k, v must share dtype float16 or bfloat16")
-    if k.shape != v.shape or q.shape[0] != k.shape[0] or q.shape[3] != k.shape[3]:
-        raise ValueError("q must be [B, H, Sq, D] and k, v [B, Hkv, Skv, D]")
-    if k.shape[1] == 0 or q.shape[1] % k.shape[1] != 0:
-        raise ValueError("the number of query heads must be a multiple of the number of key/value heads")
-    if k.device != q.device or v.device != q.device:
-        raise ValueError("q, k, v must be on one device")
-    if kv_lens is not None:
-        if (not isinstance(kv_lens, torch.Tensor) or kv_lens.dtype != torch.int32 or kv_lens.device != q.device
-                or kv_lens.shape != (q.shape[0],) or not kv_lens.is_contiguous()):
-            raise ValueError("kv_lens must be a contiguous int32 tensor [B] on the device of q")
-    B, H, Sq, D = q.shape
-    Hkv, Skv = k.shape[1], k.shape[2]
-    group = H // Hkv
-    out_shape = q.shape
-    dtype = F16 if q.dtype == torch.float16 else BF16
-    if out is None:
-        out = torch.empty(out_shape, dtype=q.dtype, device=q.device)
-    elif out.shape != out_shape or out.dtype != q.dtype or not out.is_contiguous() or out.device != q.device:
-        raise ValueError("out must match q in shape, dtype, device and be contiguous")
-    lse = torch.empty(out_shape[:3], dtype=torch.float32, device=q.device) if return_lse else None
-    tm, tn = tile if tile is not None else (0, 0)
-    # the library's heuristics see B * Hkv heads of group * Sq rows each
-    n = splits if splits else kv_default_splits(B, Hkv, group * Sq, Skv, D, dtype,
-                                                flags if group == 1 else flags & ~FLAG_CAUSAL)
-    need = kv_workspace_bytes(B, H, Sq, D, n)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    guard, stream = _guard_and_stream(torch, q.device)
-    with guard:
-        st = tiled_sdpa_fwd_kvcache(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                    lse.data_ptr() if lse is not None else None,
-                                    kv_lens.data_ptr() if kv_lens is not None else None,
-                                    B, H, Hkv, Sq, Skv, D, math.nan if scale is None else scale, dtype, stream,
-                                    tm, tn, flags, n, ws_ptr, ws_bytes)
-    if st != 0:
-        raise TiledSdpaError(st, status_string(st))
-    return (out, lse) if return_lse else out
+    return _checked(_calls().sdpa_kv(q, k, v, causal, scale, splits, return_lse, out, workspace, tile, flags, kv_lens))
 
 
 def tiled_sdpa_fwd_paged(q_ptr, k_ptr, v_ptr, o_ptr, lse_ptr, kv_lens_ptr, block_table_ptr, B, H, Hkv, Sq, max_blocks,
@@ -336,52 +291,8 @@ def sdpa_paged(q, k_pages, v_pages, kv_lens, block_table, causal: bool = False, 
     """Attention of q [B, H, Sq, D] over a paged cache: k_pages, v_pages [P, Hkv, block_rows, D],
     block_table int32 [B, max_blocks] (page of every block of every batch entry), kv_lens int32 [B]
     (valid key rows per entry).  See tiled_sdpa_fwd_paged; otherwise as :func:`sdpa_kv`."""
-    import torch
-
-    if causal:
-        flags |= FLAG_CAUSAL
-    for name, t in (("q", q), ("k_pages", k_pages), ("v_pages", v_pages)):
-        if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dim() != 4 or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous 4-d device tensor")
-    if q.dtype not in (torch.float16, torch.bfloat16) or k_pages.dtype != q.dtype or v_pages.dtype != q.dtype:
-        raise ValueError("q, k_pages, v_pages must share dtype float16 or bfloat16")
-    if k_pages.shape != v_pages.shape or k_pages.shape[3] != q.shape[3] or k_pages.device != q.device or v_pages.device != q.device:
-        raise ValueError("k_pages, v_pages must be [P, Hkv, block_rows, D] on the device of q")
-    B, H, Sq, D = q.shape
-    P, Hkv, block_rows = k_pages.shape[:3]
-    if Hkv == 0 or H % Hkv != 0:
-        raise ValueError("the number of query heads must be a multiple of the number of key/value heads")
-    for name, t, shape in (("kv_lens", kv_lens, (B,)), ("block_table", block_table, None)):
-        if (not isinstance(t, torch.Tensor) or t.dtype != torch.int32 or t.device != q.device or not t.is_contiguous()
-                or (shape is not None and tuple(t.shape) != shape)):
-            raise ValueError(f"{name} must be a contiguous int32 device tensor" + (f" {list(shape)}" if shape else ""))
-    if block_table.dim() != 2 or block_table.shape[0] != B:
-        raise ValueError("block_table must be [B, max_blocks]")
-    max_blocks = block_table.shape[1]
-    dtype = F16 if q.dtype == torch.float16 else BF16
-    if out is None:
-        out = torch.empty_like(q)
-    elif out.shape != q.shape or out.dtype != q.dtype or not out.is_contiguous() or out.device != q.device:
-        raise ValueError("out must match q in shape, dtype, device and be contiguous")
-    lse = torch.empty((B, H, Sq), dtype=torch.float32, device=q.device) if return_lse else None
-    tm, tn = tile if tile is not None else (0, 0)
-    group = H // Hkv
-    n = splits if splits else kv_default_splits(B, Hkv, group * Sq, max(1, max_blocks * block_rows), D, dtype,
-                                                flags & ~FLAG_CAUSAL)
-    need = kv_workspace_bytes(B, H, Sq, D, n)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    guard, stream = _guard_and_stream(torch, q.device)
-    with guard:
-        st = tiled_sdpa_fwd_paged(q.data_ptr(), k_pages.data_ptr(), v_pages.data_ptr(), out.data_ptr(),
-                                  lse.data_ptr() if lse is not None else None, kv_lens.data_ptr(),
-                                  block_table.data_ptr(), B, H, Hkv, Sq, max_blocks, block_rows, D,
-                                  math.nan if scale is None else scale, dtype, stream, tm, tn, flags, n, ws_ptr, ws_bytes)
-    if st != 0:
-        raise TiledSdpaError(st, status_string(st))
-    return (out, lse) if return_lse else out
+    return _checked(_calls().sdpa_paged(q, k_pages, v_pages, kv_lens, block_table, causal, scale, splits, return_lse, out,
+                                        workspace, tile, flags))
 
 
 def bwd_workspace_bytes(B: int, H: int, S: int) -> int:
@@ -402,43 +313,7 @@ def sdpa_backward(q, k, v, o, dout, lse, causal: bool = False, scale=None, *, wo
 
     Grouped heads: k, v [B, Hkv, S, D] with H a multiple of Hkv (the forward of ``sdpa_kv`` at Sq = Skv);
     dk, dv then have the shape of k and hold the sum over the query heads of each group."""
-    import torch
-
-    for name, t, like in (("q", q, q), ("k", k, k), ("v", v, k), ("o", o, q), ("dout", dout, q)):
-        if not isinstance(t, torch.Tensor) or not t.is_cuda:
-            raise ValueError(f"{name} must be a device tensor")
-        if t.dim() != 4 or not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous [B, H, S, D]")
-        if t.shape != like.shape or t.dtype != q.dtype or t.device != q.device:
-            raise ValueError("q, o, dout and k, v must agree in shape, dtype and device")
-    if q.dtype not in (torch.float16, torch.bfloat16):
-        raise ValueError("dtype must be float16 or bfloat16")
-    B, H, S, D = q.shape
-    Hkv = k.shape[1]
-    if k.shape[0] != B or k.shape[2:] != q.shape[2:] or Hkv == 0 or H % Hkv != 0:
-        raise ValueError("k, v must be [B, Hkv, S, D] with H a multiple of Hkv")
-    if lse.shape != (B, H, S) or lse.dtype != torch.float32 or not lse.is_contiguous() or lse.device != q.device:
-        raise ValueError("lse must be contiguous float32 [B, H, S] on the same device")
-    dtype = F16 if q.dtype == torch.float16 else BF16
-    if grads is None:
-        grads = (torch.empty_like(q), torch.empty_like(k), torch.empty_like(k))
-    for gname, t, like in zip(("dq", "dk", "dv"), grads, (q, k, k)):
-        if t.shape != like.shape or t.dtype != q.dtype or not t.is_contiguous() or t.device != q.device:
-            raise ValueError(f"{gname} must match {'q' if like is q else 'k'} in shape, dtype, device and be contiguous")
-    need = bwd_workspace_bytes(B, H, S)
-    if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_bytes = workspace.numel() * workspace.element_size()
-    guard, stream = _guard_and_stream(torch, q.device)
-    with guard:
-        st = int(load_library().tiled_sdpa_bwd_gqa(
-            q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), dout.data_ptr(),
-            lse.data_ptr(), grads[0].data_ptr(), grads[1].data_ptr(), grads[2].data_ptr(),
-            B, H, Hkv, S, D, math.nan if scale is None else float(scale), dtype,
-            FLAG_CAUSAL if causal else 0, workspace.data_ptr(), ws_bytes, stream))
-    if st != 0:
-        raise TiledSdpaError(st, status_string(st))
-    return grads
+    return _checked(_calls().sdpa_backward(q, k, v, o, dout, lse, causal, scale, workspace, grads))
 
 
 def sdpa(q, k, v, causal: bool = False, scale=None, *, return_lse: bool = False, out=None,
@@ -448,39 +323,4 @@ def sdpa(q, k, v, causal: bool = False, scale=None, *, return_lse: bool = False,
     Mirrors the functional API of Section 4.2.1 of the paper (scale defaults to 1/sqrt(D)).
     ``tile=(T_M, T_N)`` pins the schedule; ``out`` / ``lse_out`` let the caller own the outputs.
     """
-    import torch
-
-    if causal:
-        flags |= FLAG_CAUSAL
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if not isinstance(t, torch.Tensor) or not t.is_cuda:
-            raise ValueError(f"{name} must be a device tensor")
-        if t.dim() != 4:
-            raise ValueError(f"{name} must be [B, H, S, D]")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-    if q.dtype not in (torch.float16, torch.bfloat16) or k.dtype != q.dtype or v.dtype != q.dtype:
-        raise ValueError("q, k, v must share dtype float16 or bfloat16")
-    if q.shape != k.shape or q.shape != v.shape or k.device != q.device or v.device != q.device:
-        raise ValueError("q, k, v must have identical shape and device")
-    B, H, S, D = q.shape
-    dtype = F16 if q.dtype == torch.float16 else BF16
-    if out is None:
-        out = torch.empty_like(q)
-    elif out.shape != q.shape or out.dtype != q.dtype or not out.is_contiguous() or out.device != q.device:
-        raise ValueError("out must match q in shape, dtype, device and be contiguous")
-    lse = None
-    if return_lse:
-        lse = lse_out if lse_out is not None else torch.empty((B, H, S), dtype=torch.float32, device=q.device)
-        if lse.shape != (B, H, S) or lse.dtype != torch.float32 or not lse.is_contiguous():
-            raise ValueError("lse_out must be contiguous float32 [B, H, S]")
-    tm, tn = tile if tile is not None else (0, 0)
-    guard, stream = _guard_and_stream(torch, q.device)
-    with guard:
-        st = tiled_sdpa_fwd_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                               lse.data_ptr() if lse is not None else None,
-                               B, H, S, D, math.nan if scale is None else scale, dtype, stream,
-                               tm, tn, flags)
-    if st != 0:
-        raise TiledSdpaError(st, status_string(st))
-    return (out, lse) if return_lse else out
+    return _checked(_calls().sdpa(q, k, v, causal, scale, return_lse, out, lse_out, tile, flags))

@@ -1,4 +1,5 @@
-"""Build libtiled_sdpa.so (gfx950 only) from csrc/ with hipcc; objects compile in parallel.
+"""Build libtiled_sdpa.so (gfx950 only) from csrc/*.hip with hipcc, objects in parallel, and _torch_calls.so (the
+tensor entry points, host code only) from csrc/torch_calls.cpp with g++ against torch's headers.
 
 Usage: python -m paper_2603_01960_amd.build [--force]
 """
@@ -15,6 +16,8 @@ CSRC = PKG / "csrc"
 INCLUDE = PKG.parent / "include"
 OBJ = PKG / "_build"
 LIB = PKG / "libtiled_sdpa.so"
+CALLS_SRC = CSRC / "torch_calls.cpp"
+CALLS = PKG / "_torch_calls.so"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -56,12 +59,33 @@ def _compile(src: Path) -> Path:
     return obj
 
 
+def build_calls() -> Path:
+    """The CPython module behind the tensor functions of binding.py; links against LIB, which must exist."""
+    import sysconfig
+
+    import torch
+
+    root = Path(torch.__file__).resolve().parent
+    rocm = Path(HIPCC).resolve().parents[1]
+    tmp = CALLS.with_suffix(f".tmp{os.getpid()}.so")
+    # (the two definitions are what ROCm's and torch's headers expect of a host compiler other than hipcc)
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+                    "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    f"-I{INCLUDE}", f"-I{root / 'include'}", f"-I{root / 'include/torch/csrc/api/include'}",
+                    f"-I{rocm / 'include'}", f"-I{sysconfig.get_paths()['include']}",
+                    str(CALLS_SRC), "-o", str(tmp), f"-L{PKG}", f"-L{root / 'lib'}",
+                    "-ltiled_sdpa", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python",
+                    "-Wl,-rpath,$ORIGIN"], check=True)
+    os.replace(tmp, CALLS)
+    return CALLS
+
+
 def build(force: bool = True, jobs: int | None = None) -> Path:
     OBJ.mkdir(exist_ok=True)
     srcs = sources()
     headers = list(CSRC.glob("*.h")) + list(INCLUDE.glob("*.h"))
-    newest = max(p.stat().st_mtime for p in srcs + headers)
-    if not force and LIB.exists() and LIB.stat().st_mtime >= newest:
+    newest = max(p.stat().st_mtime for p in [*srcs, *headers, CALLS_SRC])
+    if not force and all(p.exists() and p.stat().st_mtime >= newest for p in (LIB, CALLS)):
         return LIB
     jobs = jobs or min(len(srcs), int(os.environ.get("MAX_JOBS", os.cpu_count() or 4)), 16)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -70,6 +94,7 @@ def build(force: bool = True, jobs: int | None = None) -> Path:
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc",
                     *map(str, objs), "-o", str(tmp)], check=True)
     os.replace(tmp, LIB)
+    build_calls()
     return LIB
 
 
