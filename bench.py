@@ -427,8 +427,8 @@ def bench_bwd(pkg, torch, args, flags):
                      "frac": round(tf / PEAK_MFMA_TFLOPS, 4),
                      # all four kernels of a call, FETCH_SIZE + WRITE_SIZE scaled (profiles/sdpa_bwd_C4_C2.md)
                      "traffic": 2515.7e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H) else None,
-                     "kernel": ("sdpa_bwd_prepare_kernel + sdpa_bwd_kernel<dK+dV> + sdpa_bwd_kernel<dQ>" if w.D == 64 else
-                                "sdpa_bwd_prepare_kernel + sdpa_bwd_kernel<dV> + sdpa_bwd_kernel<dK> + sdpa_bwd_kernel<dQ>"),
+                     "kernel": ("sdpa_bwd_kernel<dQ> + sdpa_bwd_kernel<dV> + sdpa_bwd_kernel<dK>" if w.D == 160 else
+                                "sdpa_bwd_kernel<dQ> + sdpa_bwd_kernel<dK+dV>"),
                      "ms_avg_all_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
                      # scores and dP are recomputed per pass: 7 products with the fused dK + dV pass of D = 64, else 8
                      "executed_mfma_flops_per_launch": flops * (7.0 if w.D == 64 else 8.0) / 5.0}}), flush=True)

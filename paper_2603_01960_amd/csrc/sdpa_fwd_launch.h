@@ -61,8 +61,8 @@ struct BwdLaunchArgs {
     const void *q, *k, *v, *o, *dout;
     const float *lse;        // natural-log LSE of the forward pass, [BH, S]
     void *dq, *dk, *dv;
-    float *delta, *lse2;     // workspace halves: [BH*S + slack] each
-    unsigned stat_bytes;     // bytes of one workspace half
+    float *stats;            // workspace, two halves of [BH*S + slack]: Delta, then LSE in log2 units
+    unsigned stat_bytes;     // bytes of one half
     int BH, S;               // query heads (B * H) and rows per head
     int group;               // query heads per key/value head (1: k, v, dk, dv have BH heads too; else BH / group)
     float c;                 // |scale| * log2(e)
@@ -84,7 +84,7 @@ int launch_bf16_d128(int tile_m, int tile_n, const LaunchArgs &a);
 int launch_bf16_d160(int tile_m, int tile_n, const LaunchArgs &a);
 
 
-// Backward pass: statistics kernel, then the dV, dK (keys resident) and dQ (queries resident) passes.
+// Backward pass: the dQ pass (queries resident; row statistics on the way), then dK and dV (keys resident).
 int launch_bwd_f16_d64(const BwdLaunchArgs &a);
 int launch_bwd_f16_d96(const BwdLaunchArgs &a);
 int launch_bwd_f16_d128(const BwdLaunchArgs &a);

@@ -563,8 +563,7 @@ int tiled_sdpa_bwd_gqa(const void *q, const void *k, const void *v, const void *
     a.q = q; a.k = k; a.v = v; a.o = o; a.dout = dout; a.lse = lse;
     a.dq = dq; a.dk = dk; a.dv = dv;
     const size_t half = (size_t)B * H * S + tsdpa::kBwdStatPad;
-    a.delta = (float *)workspace;
-    a.lse2 = (float *)workspace + half;
+    a.stats = (float *)workspace;
     a.stat_bytes = (unsigned)(half * sizeof(float));
     a.BH = B * H;
     a.S = S;
