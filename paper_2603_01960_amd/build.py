@@ -30,14 +30,17 @@ FLAGS = [
 
 # The forward kernels on 64-row K/V tiles (up to D = 128) are scheduled by LLVM's iterative ILP
 # strategy: measured 3-5 % faster than the default on every one of them.  The same strategy halves the
-# speed of the 32-row tile kernels (it lengthens live ranges past their 168-register budget) and does
-# not get through the backward kernels, so it is applied per translation unit and never elsewhere.
+# speed of the 32-row tile kernels (it lengthens live ranges past their 168-register budget).  The backward
+# kernels gain 1-5 % from it at D = 64, 96 and 160; at D = 128, where the fused dK + dV pass has two registers
+# left, it spills and loses 2-10 %.  So it is applied per translation unit and never elsewhere.
 ILP_SCHED = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
 
 
 def extra_flags(src: Path) -> list[str]:
     name = src.name
     if name.startswith("sdpa_fwd_") and name.endswith("_tn64.hip") and "_d160_" not in name:
+        return ILP_SCHED
+    if name.startswith("sdpa_bwd_") and not name.endswith("_d128.hip"):
         return ILP_SCHED
     return []
 

@@ -9,10 +9,14 @@ namespace tsdpa {
 
 // Tile shapes: 32*NW resident rows per workgroup, TS streamed rows per tile for the dQ / dK / dV / fused pass, the
 // wavefronts per SIMD its register budget is sized for, and whether its second resident operand stays in the LDS.
+// The passes are held by the clock on large problems, so that the choices are within a few per cent of each other
+// there: D = 128, dQ on 64-row tiles 1 % ahead of 32-row ones on large problems, 4 % at S = 1024 of nine heads; D = 96,
+// dQ on 32-row tiles at three wavefronts per SIMD 1-2 % ahead of 64-row ones at two; D = 64, the fused pass on 32-row
+// tiles 1-6 % behind.  D = 160 needs the resident operand in the LDS for two wavefronts per SIMD.
 template <int D> struct BwdShape;
 template <> struct BwdShape<64>  { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 2}, TS[4] = {64, 64, 64, 64}; static constexpr bool R2[4] = {0, 0, 0, 0}, FUSED_DKV = true; };
-template <> struct BwdShape<96>  { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 2}, TS[4] = {64, 32, 64, 32}; static constexpr bool R2[4] = {0, 0, 0, 0}, FUSED_DKV = true; };
-template <> struct BwdShape<128> { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 2}, TS[4] = {32, 32, 64, 32}; static constexpr bool R2[4] = {0, 0, 0, 1}, FUSED_DKV = true; };
+template <> struct BwdShape<96>  { static constexpr int NW = 4, WPS[4] = {3, 2, 2, 2}, TS[4] = {32, 32, 64, 32}; static constexpr bool R2[4] = {0, 0, 0, 0}, FUSED_DKV = true; };
+template <> struct BwdShape<128> { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 2}, TS[4] = {64, 32, 64, 32}; static constexpr bool R2[4] = {0, 0, 0, 1}, FUSED_DKV = true; };
 template <> struct BwdShape<160> { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 1}, TS[4] = {32, 32, 32, 32}; static constexpr bool R2[4] = {1, 1, 0, 0}, FUSED_DKV = false; };
 
 template <typename T, int D, int MODE, bool GRP, int NW>

@@ -370,9 +370,12 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             if constexpr (MODE == BWD_DK || FUSED) __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // One streamed tile, its successor's loads issued first: they land while this one is computed.  One loop body serves
+    // One streamed tile, its successor's loads issued early: they land while this one is computed.  One loop body serves
     // both slots (the pointers move by the slot distance and back) and both kinds of tile (only the weights branch), so
     // that the accumulators never meet at a join of two copies of the step.
+    // (a raised priority during the MFMA chains, as in the forward kernel, gains 2-4 % at D = 160; at the other head dims
+    // it gains 1-4 % on large problems and loses as much where a CU holds one workgroup)
+    constexpr bool PRIO = D == 160;
     int shift = TILE;                             // from the current slot to the other
     auto other_slot = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -387,18 +390,32 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     };
     auto tile = [&](int j, bool mask) __attribute__((always_inline)) {
         load_stats(j + 1, shift > 0 ? 1 : 0);
-        load_tile(j + 1, lds + (shift > 0 ? TILE : 0));
+        // The loads go out one at a time behind the MFMAs of the first products: back to back they hold the wavefront at
+        // the issue stage while the CU's address unit works through them (S = 1024 of nine heads: 69 -> 65.5 us at D =
+        // 128, 61 -> 55 at D = 96; 1-2 % where the CUs are full; level at D = 64)
+        const lds_ptr nxt = lds + (shift > 0 ? TILE : 0);
+        constexpr int HOOKS = NB * (NEED_DP ? 2 : 1) * KK;
+        auto spread = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = h * L / HOOKS; i < (h + 1) * L / HOOKS; ++i) load_part(j + 1, nxt, i);
+            __builtin_amdgcn_sched_barrier(0x786);              // MFMAs and loads keep this order
+        };
         const int trow0 = j * TS + g * 4;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {       // one 32-row block at a time: only its accumulators are live
             f32x16 sacc, dpacc;
-            products(0, nb, false, sacc, nothing);
-            if constexpr (NEED_DP) products(T2BASE, nb, true, dpacc, nothing);
+            if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
+            products(0, nb, false, sacc, [&](int kk) __attribute__((always_inline)) { spread(nb * (NEED_DP ? 2 : 1) * KK + kk); });
+            if constexpr (NEED_DP)
+                products(T2BASE, nb, true, dpacc, [&](int kk) __attribute__((always_inline)) { spread((nb * 2 + 1) * KK + kk); });
+            if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
             if (mask) weights(nb, trow0, sacc, dpacc, std::true_type{});
             else      weights(nb, trow0, sacc, dpacc, std::false_type{});
         }
+        if constexpr (PRIO) __builtin_amdgcn_s_setprio(2);
         accumulate(MODE == BWD_DV ? T2BASE : 0, xb, oacc);
         if constexpr (FUSED) accumulate(T2BASE, pb, oacc2);       // dV^T += dO^T P
+        if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
         TSDPA_WAIT_VMCNT0();
         __syncthreads();
         other_slot();
