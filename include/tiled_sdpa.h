@@ -128,8 +128,9 @@ int tiled_sdpa_tune_tile(const void *q, const void *k, const void *v, void *o,
  * over several workgroups: the KV-cache / decoding shapes that the paper names as future work
  * (Section 7), and the cure for shapes whose B*H*ceil(Sq/tile_m) workgroups cannot fill the GPU.
  * Each split runs the recurrence of Section 4.1.2 (Eqs. 2-4) over its own contiguous run of K/V
- * tiles and leaves its state (o, m, l) in the workspace; a second kernel combines the states with
- * the rescaling of Eqs. 3-4 and applies the final O_i = o_i / l_i.
+ * tiles and leaves its state (o, m, l) in the workspace; a second kernel (or, on a decoding step with few
+ * states per head, the workgroup that finishes last; o then holds its marks until the result replaces them)
+ * combines the states with the rescaling of Eqs. 3-4 and applies the final O_i = o_i / l_i.
  *
  *   q        : [B, H, Sq, D];  k, v : [B, H, Skv, D];  o : [B, H, Sq, D];  lse : NULL or FP32 [B, H, Sq].
  *              Layout, alignment, D, scale, dtype, stream as for tiled_sdpa_fwd.
@@ -142,7 +143,7 @@ int tiled_sdpa_tune_tile(const void *q, const void *k, const void *v, void *o,
  *   workspace: device memory for the split states, 16-byte aligned, at least
  *              tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, n) bytes, n being `splits` or, for splits = 0,
  *              the heuristic's value; ignored (may be NULL) when n = 1, where O is written directly.
- *              Owned by the caller; the library uses it only between the two kernels of this call, so
+ *              Owned by the caller; the library uses it only inside this call's kernels, so
  *              calls that may overlap on the GPU need distinct workspaces.  Its contents afterwards
  *              are unspecified.  More splits than there are K/V tiles are allowed (the surplus ones
  *              contribute nothing) but waste workspace.

@@ -1,0 +1,520 @@
+// Decoding steps: a few query rows (at most 32, the grouped query heads' rows together) against a long cache.
+//
+// Such a call is bound by reading the cache once, so the kernel is built around loads: each of a workgroup's four
+// wavefronts streams K/V tiles of its own (32 keys) through LDS slots of its own, with no barrier in the loop.  A
+// wavefront has one slot for K and one for V and refills each as soon as it has read it into registers: the next K tile
+// is requested before the scores of this one are computed, the next V tile before its output products, so that one or
+// two tiles per wavefront are always in flight; eight wavefronts per CU (64-80 KiB per workgroup from D = 128) keep
+// about 100 KB per CU in flight.  Scores and output are 16x16x32 MFMAs on 16 query rows (32: two of each): half the
+// matrix work of the 32x32 tiles on the same rows, and half the registers.  At the end the four states (o, m, l of
+// Eqs. 2-4) meet in the LDS.
+// The key range of a cache of capacity Skv is cut into `splits` runs of equal length whatever each entry holds; an entry
+// of fewer keys has fewer runs, so that workgroups do the same work each and the long entries do not finish last.
+// The forward kernel, which ran these shapes before (32 x 32 tiles, all wavefronts on the same tile, a barrier per tile, one
+// of its two wavefronts without rows), against this one, BF16, cold cache, us per call with the states' combination:
+// 8 key/value heads of 1024 keys 11.5 / 7.9, of 8192 keys 14.2 / 13.3; 32 heads of 8192 keys 34.1 / 27.5; 96 heads of 3000
+// keys at D = 96 36.4 / 24.2; 256 heads of 2048 keys 51.3 / 48.4 and of 200 ... 2048 keys 35.1 / 29.6; 256 heads of 8192
+// keys 187 / 177 (6.06 TB/s), of 2048 ... 8192 keys in pages 135.6 / 127.8.
+#pragma once
+#include <utility>
+
+#include "sdpa_fwd_kernel.h"
+#include "sdpa_fwd_launch.h"
+
+namespace tsdpa {
+
+constexpr int kDecodeTile = 32;                   // keys per tile
+constexpr int kDecodeMaxRows = 32;                // query rows per key/value head
+
+template <typename T> struct Elem16;
+template <> struct Elem16<_Float16> {
+    static __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+};
+template <> struct Elem16<__bf16> {
+    static __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+};
+
+// f(0), f(1), ..., f(N - 1) with the index as a compile-time constant (immediate offsets of the LDS reads below)
+template <typename F, int... I> __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
+template <int OFF> __device__ __forceinline__ void lds_fetch128(u32x4 &x, uint32_t addr)
+{
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(x) : "v"(addr), "n"(OFF) : "memory");
+}
+template <int OFF> __device__ __forceinline__ void lds_fetch_tr16(i16x4 &x, uint32_t addr)
+{
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(x) : "v"(addr), "n"(OFF) : "memory");
+}
+
+// LDS layout of a K or V tile: 32 rows of D values, unpadded; 16-byte chunks are permuted within each row.
+//   K (16 lanes read one chunk of 16 consecutive rows): as in the forward kernel.
+//   V (the transposing read has 32 lanes fetch the same 32 bytes of 8 consecutive rows): 32-byte block b of row r at
+//   b ^ vx(r), which puts eight consecutive rows on eight different 32-byte slots of the 256 bytes of the banks.
+template <int D> struct DecodeGeom {
+    static constexpr int ROW = D * 2, CPR = D / 8;
+    static constexpr int TILE = kDecodeTile * ROW;
+    static constexpr int UNITS = D / 16;          // direct-to-LDS load instructions (1 KiB each) per tile
+    static __host__ __device__ constexpr int kswz(int r) { return TileGeom<D, 32>::kswz(r); }
+    static __host__ __device__ constexpr int vx(int r) { return D == 128 ? ((r & 3) << 1) | ((r >> 2) & 1) : D == 64 ? (r >> 1) & 3 : (r >> 2) & 1; }
+    static constexpr int KP = D == 128 ? 4 : D == 64 ? 2 : CPR / 4;       // the lanes' offsets of K repeat every KP units
+    static constexpr int VP = D == 128 ? 2 : D == 64 ? 1 : CPR / 4;       // ... of V every VP
+    static constexpr int NKP = D == 128 ? 4 : D == 64 ? 2 : 1;            // row pointers: one per 64-byte step ks (or immediates)
+    static constexpr int NVP = D == 128 ? 8 : D == 64 ? 4 : 2;            // transposing pointers: one per 32-byte block db (or per parity)
+};
+
+// PAGED: a descriptor per tile (see the forward kernel's paged variant).
+template <typename T, int D, int NQ, int NW, bool PAGED>
+__global__ void __launch_bounds__(NW * 64, 2)
+sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
+                   T *o, float *__restrict__ lse, int S, int heads, float c, float tau, uint32_t qsign, int causal,
+                   int Skv_cap, int splits, float *ws, int rows_per_head,
+                   const int *__restrict__ kv_lens, int heads_per_batch,
+                   const int *__restrict__ block_table, int max_blocks, int block_shift, unsigned long long ticket)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    using E = Elem16<T>;
+    using vec8 = typename Elem<T>::vec8;
+    using vec4 = typename Elem<T>::vec4;
+    using G = DecodeGeom<D>;
+    constexpr int KS = D / 32, DB = D / 16, NU = G::UNITS;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const lds_ptr lds = (lds_ptr)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t = lane >> 4, l16 = lane & 15;
+
+    // Run fastest would put the runs of one long entry next to each other; run by run, each from another head on, a CU that
+    // gets several workgroups gets them from different entries.
+    const int sp = blockIdx.x / heads;
+    int head = blockIdx.x - sp * heads + (int)((long long)sp * heads / splits);
+    if (head >= heads) head -= heads;
+    int len = Skv_cap;
+    if (kv_lens != nullptr) {
+        const int x = kv_lens[head / heads_per_batch];
+        len = x < 0 ? 0 : (x < Skv_cap ? x : Skv_cap);
+    }
+
+    // ---- The runs' states are combined by whichever workgroup of the head is last to be done with its own, in run order
+    // whoever that is.  A workgroup writes its state, waits for the writes, marks it done, and looks at all the marks of its
+    // head: the last one finds them all; should two find them all, both write the same result.  Marks need no memory of
+    // their own and no cleared memory: they stand in the head's part of o, which nothing else uses before the result
+    // overwrites it, and a mark is the ticket of this very call, a 64-bit number that no other call has (the output of an
+    // earlier replay of the same graph, or whatever else o held, equals it with probability 2^-64).
+    // States and marks are written and read at agent scope, access by access: past the L2s, of which every XCD has its
+    // own.  (With plain accesses and release / acquire fences every workgroup writes back and invalidates its XCD's
+    // whole L2: 256 workgroups took 36 us instead of 15.)
+    auto put = [](float *at, float x, float y) __attribute__((always_inline)) {
+        const unsigned long long both = ((unsigned long long)__builtin_bit_cast(uint32_t, y) << 32) | __builtin_bit_cast(uint32_t, x);
+        __hip_atomic_store((unsigned long long *)at, both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    struct Pair { float x, y; };
+    auto get = [](const float *at) __attribute__((always_inline)) {
+        const unsigned long long both = __hip_atomic_load((unsigned long long *)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t lo = (uint32_t)both, hi = (uint32_t)(both >> 32);
+        return Pair{__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi)};
+    };
+    auto finish = [&]() __attribute__((always_inline)) {
+        unsigned long long *marks = (unsigned long long *)(o + (size_t)head * S * D);
+        TSDPA_WAIT_VMCNT0();
+        __syncthreads();
+        typedef TSDPA_LDS float *lds_f;
+        const lds_f wgt = (lds_f)lds;
+        if (wave == 0) {
+            if (lane == 0) (void)__hip_atomic_exchange(marks + sp, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            TSDPA_WAIT_VMCNT0();
+            bool done = true;
+#pragma unroll
+            for (int i = 0; i < 128; i += 64)
+                if (i + lane < splits) done &= __hip_atomic_load(marks + i + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ticket;
+            const bool all = __builtin_amdgcn_ballot_w64(!done) == 0;
+            if (lane == 0) wgt[0] = all ? 1.f : 0.f;
+        }
+        __syncthreads();
+        const bool last = wgt[0] != 0.f;
+        __syncthreads();
+        if (!last) return;
+        // weights of the runs per row, then the weighted sum of their o: [splits][S] weights in the LDS
+        const float *po = ws + (size_t)head * splits * S * D;
+        const float *pml = ws + (size_t)heads * splits * S * D + (size_t)head * splits * S * 2;
+        // one wavefront per row, a lane per run (and another 64 runs on)
+        for (int row = wave; row < S; row += NW) {
+            Pair st[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                st[i] = Pair{-INFINITY, 0.f};
+                if (lane + i * 64 < splits) st[i] = get(pml + ((lane + i * 64) * S + row) * 2);
+            }
+            float M = fmaxf(st[0].x, st[1].x);
+#pragma unroll
+            for (int w = 1; w < 64; w <<= 1) M = fmaxf(M, __shfl_xor(M, w, 64));
+            float L = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float w = st[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st[i].x - M);
+                if (lane + i * 64 < splits) wgt[(lane + i * 64) * S + row] = w;
+                L += w * st[i].y;
+            }
+#pragma unroll
+            for (int w = 1; w < 64; w <<= 1) L += __shfl_xor(L, w, 64);
+            if (lane == 0) {
+                wgt[splits * S + row] = L > 0.f ? 1.f / L : 0.f;       // (a row that no key reaches: O = 0, LSE = -inf)
+                if (lse != nullptr)
+                    lse[(size_t)head * S + row] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * 0.69314718055994530942f : -INFINITY;
+            }
+        }
+        __syncthreads();
+        // two columns per thread, eight runs' loads in flight
+        for (int x = tid; x < S * (D / 2); x += NW * 64) {
+            const int row = x / (D / 2);
+            float s0 = 0.f, s1 = 0.f;
+#pragma unroll 8
+            for (int s = 0; s < splits; ++s) {
+                const float w = wgt[s * S + row];
+                const Pair part = get(po + (size_t)s * S * D + (size_t)x * 2);
+                if (w > 0.f) {                            // (a run without keys has left its o unwritten)
+                    s0 += w * part.x;
+                    s1 += w * part.y;
+                }
+            }
+            const float inv = wgt[splits * S + row];
+            typedef T vec2 __attribute__((ext_vector_type(2)));
+            *(vec2 *)(o + (size_t)head * S * D + (size_t)x * 2) = vec2{(T)(s0 * inv), (T)(s1 * inv)};
+        }
+    };
+
+    // this workgroup's run of tiles: [t0, t0 + n)
+    const int run = ((Skv_cap + kDecodeTile - 1) / kDecodeTile + splits - 1) / splits;
+    const int t0 = sp * run;
+    const int nT = (len + kDecodeTile - 1) / kDecodeTile;
+    int n = nT - t0 < run ? nT - t0 : run;
+    if (n < 0) n = 0;
+    if (n == 0 && splits > 1) {                   // nothing to read: the state of no keys (the merge does not look at o then)
+        if (tid < S) {
+            put(ws + (size_t)heads * splits * S * D + ((size_t)(head * splits + sp) * S + tid) * 2, -INFINITY, 0.f);
+        }
+        if (ticket != 0) finish();
+        return;
+    }
+
+    // ---- tiles: HBM -> LDS.  Wavefront w takes the tiles w, w + 4, ... of the run, the run entered at a tile that depends on
+    // the workgroup: heads of a dense cache lie a power of two apart, and workgroups in step at the same distance from their
+    // start would keep hitting the same memory channels.
+    const lds_ptr kslot = lds + wave * 2 * G::TILE, vslot = kslot + G::TILE;
+    const size_t kv_off = (size_t)head * (size_t)Skv_cap * D;
+    const auto k_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(k + kv_off), (short)0, len * G::ROW, 0x00020000);
+    const auto v_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(v + kv_off), (short)0, len * G::ROW, 0x00020000);
+    const int *pages = nullptr;
+    int page_head = 0;
+    if constexpr (PAGED) {
+        const int b = head / heads_per_batch;
+        page_head = head - b * heads_per_batch;
+        pages = block_table + (size_t)b * max_blocks;
+    }
+    int kgoff[G::KP], vgoff[G::VP];
+#pragma unroll
+    for (int u = 0; u < G::KP; ++u) {
+        const int p = u * 64 + lane, r = p / G::CPR, cp = p % G::CPR;
+        kgoff[u] = r * G::ROW + ((cp ^ G::kswz(r)) << 4);
+    }
+#pragma unroll
+    for (int u = 0; u < G::VP; ++u) {
+        const int p = u * 64 + lane, r = p / G::CPR, cp = p % G::CPR;
+        vgoff[u] = r * G::ROW + ((cp ^ (G::vx(r) << 1)) << 4);
+    }
+    // where a tile lies: the whole head's descriptor and an offset (past the end for "no tile": nothing is fetched, zeros
+    // arrive), or a descriptor of the tile's valid rows within its page
+    struct Src { decltype(k_rsrc) kr, vr; int soff; };
+    auto page_of = [&](int tile) __attribute__((always_inline)) {
+        return __builtin_amdgcn_readfirstlane(pages[(tile * kDecodeTile) >> block_shift]);
+    };
+    auto src_of = [&](int tile, bool valid, int page) __attribute__((always_inline)) {
+        if constexpr (!PAGED) return Src{k_rsrc, v_rsrc, valid ? tile * G::TILE : nT * G::TILE};
+        else {
+            const int row0 = tile * kDecodeTile;
+            int rows = valid ? len - row0 : 0;
+            rows = rows < kDecodeTile ? rows : kDecodeTile;
+            const size_t first = (((size_t)page * heads_per_batch + page_head) << block_shift) + (row0 & ((1 << block_shift) - 1));
+            const unsigned long long byte0 = (unsigned long long)first * (unsigned long long)G::ROW;
+            const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)byte0), hi = __builtin_amdgcn_readfirstlane((unsigned)(byte0 >> 32));
+            const unsigned long long at = ((unsigned long long)hi << 32) | lo;
+            const int bytes = __builtin_amdgcn_readfirstlane(rows * G::ROW);
+            return Src{__builtin_amdgcn_make_buffer_rsrc((void *)((const char *)k + at), (short)0, bytes, 0x00020000),
+                       __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)v + at), (short)0, bytes, 0x00020000), 0};
+        }
+    };
+    auto load_k = [&](const Src &s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(s.kr, (TSDPA_LDS void *)(kslot + u * 1024), 16, kgoff[u % G::KP],
+                                                     s.soff + u / G::KP * (G::KP * 1024), 0, 0);
+    };
+    auto load_v = [&](const Src &s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(s.vr, (TSDPA_LDS void *)(vslot + u * 1024), 16, vgoff[u % G::VP],
+                                                     s.soff + u / G::VP * (G::VP * 1024), 0, 0);
+    };
+    const int mine = (n - wave + NW - 1) / NW;       // tiles of this wavefront (n - wave > -4)
+    const int rot = n > NW ? (int)((((unsigned)blockIdx.x * 2654435761u) >> 12) % (unsigned)n) : 0;
+    int cur = wave + rot;                         // within the run
+    if (cur >= n) cur -= n;
+    // the tile after `cur` (its index is only used while there is one)
+    auto advance = [&](int x) __attribute__((always_inline)) { x += NW; return x >= n ? x - n : x; };
+    // ---- Q rows as MFMA B-operands: lane holds Q[row nq*16 + l16][ks*32 + t*8 .. +7]
+    vec8 qf[NQ][KS];
+    int klim[NQ];                                 // key j contributes to this lane's row iff j <= klim
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq) {
+        const int row = nq * 16 + l16 < S ? nq * 16 + l16 : S - 1;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            u32x4 raw = *(const u32x4 *)(q + ((size_t)head * S + row) * D + ks * 32 + t * 8);
+            raw ^= qsign;
+            qf[nq][ks] = __builtin_bit_cast(vec8, raw);
+        }
+        klim[nq] = causal ? row % rows_per_head + len - rows_per_head : len - 1;
+    }
+
+    // the first tile's loads go out behind Q's (whose wait then leaves them on their way)
+    __builtin_amdgcn_sched_barrier(0);
+    int page_next = 0;                            // paged: page of this wavefront's next tile, looked up a tile ahead
+    if (mine > 0) {
+        if constexpr (PAGED) page_next = page_of(t0 + cur);
+        const Src s = src_of(t0 + cur, true, page_next);
+        load_k(s);
+        load_v(s);
+        if constexpr (PAGED) page_next = page_of(mine > 1 ? t0 + advance(cur) : t0);
+    }
+
+    f32x4 oacc[NQ][DB];
+    float m_ref[NQ], l_run[NQ];                   // as in the forward kernel: the lazy reference, this lane's share of the normaliser
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq) {
+        m_ref[nq] = -INFINITY;
+        l_run[nq] = 0.f;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) oacc[nq][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const float lazy_limit = __builtin_amdgcn_exp2f(tau);
+
+    // ---- LDS reads go through inline assembly with explicit waits: left to the compiler, which cannot tell the slots
+    // apart, the first of them waits for every outstanding load, the next tile's included
+    uint32_t kptr[G::NKP], vptr[G::NVP];
+#pragma unroll
+    for (int i = 0; i < G::NKP; ++i)
+        kptr[i] = __builtin_bit_cast(uint32_t, kslot) + l16 * G::ROW + (((4 * i + t) ^ G::kswz(l16)) << 4);
+    const int v_row = 4 * t + (l16 >> 2);
+#pragma unroll
+    for (int i = 0; i < G::NVP; ++i)
+        vptr[i] = __builtin_bit_cast(uint32_t, vslot) + v_row * G::ROW + ((i ^ G::vx(v_row)) << 5) + (lane & 3) * 8;
+
+    // weights of one tile and their sum, this lane's share
+    vec8 pb[NQ];
+    auto exponentials = [&](const f32x4 (&s)[2], int nq, int key0) __attribute__((always_inline)) {
+        float sum = 0.f;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][e], c, -m_ref[nq]));
+                if (key0 + b * 16 + e > klim[nq]) p = 0.f;
+                sum += p;
+                pb[nq][b * 4 + e] = (T)p;
+            }
+        return sum;
+    };
+
+    for (int i = 0; i < mine; ++i) {
+        const int next = advance(cur);
+        const bool more = i + 1 < mine;
+        const Src s = src_of(t0 + next, more, page_next);
+        if constexpr (PAGED) page_next = page_of(i + 2 < mine ? t0 + advance(next) : t0);
+        // K has landed when at most V's loads are outstanding
+        u32x4 kf[2][KS];
+        __builtin_amdgcn_s_waitcnt(0x0F70 | NU);
+        static_for<2 * KS>([&](auto x) __attribute__((always_inline)) {
+            constexpr int b = decltype(x)::value / KS, ks = decltype(x)::value % KS;
+            constexpr int off = b * 16 * G::ROW + (G::NKP == 1 ? ks * 64 : 0);
+            lds_fetch128<off>(kf[b][ks], kptr[G::NKP == 1 ? 0 : ks]);
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kf[b][ks]));      // (used after the wait)
+        load_k(s);
+        f32x4 sacc[NQ][2];
+#pragma unroll
+        for (int nq = 0; nq < NQ; ++nq)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                sacc[nq][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) sacc[nq][b] = E::mfma(__builtin_bit_cast(vec8, kf[b][ks]), qf[nq][ks], sacc[nq][b]);
+            }
+        const int key0 = (t0 + cur) * kDecodeTile + t * 4;
+#pragma unroll
+        for (int nq = 0; nq < NQ; ++nq) {
+            float ps = exponentials(sacc[nq], nq, key0);
+            if (__builtin_amdgcn_ballot_w64(!(ps <= lazy_limit)) != 0) {          // also inf (first tile) and NaN
+                // Eq. 2 for all rows of the wavefront: tile maximum, new reference, the rescale of Eqs. 3-4
+                float mx = -INFINITY;
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (key0 + b * 16 + e <= klim[nq]) mx = fmaxf(mx, sacc[nq][b][e]);
+                mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                const float m_tile = mx * c;
+                const bool grow = m_tile > m_ref[nq];      // (a row without keys so far: -inf or NaN, left alone)
+                const float alpha = grow ? __builtin_amdgcn_exp2f(m_ref[nq] - m_tile) : 1.f;
+                m_ref[nq] = grow ? m_tile : m_ref[nq];
+                l_run[nq] *= alpha;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) oacc[nq][db][e] *= alpha;
+                ps = exponentials(sacc[nq], nq, key0);
+            }
+            l_run[nq] += ps;
+        }
+        // V has landed when at most the next K's loads are outstanding
+        i16x4 vf[DB][2];
+        __builtin_amdgcn_s_waitcnt(0x0F70 | NU);
+        static_for<2 * DB>([&](auto x) __attribute__((always_inline)) {
+            constexpr int db = decltype(x)::value / 2, b = decltype(x)::value % 2;
+            constexpr int off = b * 16 * G::ROW + (G::NVP == 2 ? (db >> 1) * 64 : 0);
+            lds_fetch_tr16<off>(vf[db][b], vptr[G::NVP == 2 ? (db & 1) : db]);
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(vf[db][0]), "+v"(vf[db][1]));
+        load_v(s);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const i16x8 a = __builtin_shufflevector(vf[db][0], vf[db][1], 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+            for (int nq = 0; nq < NQ; ++nq) oacc[nq][db] = E::mfma(__builtin_bit_cast(vec8, a), pb[nq], oacc[nq][db]);
+        }
+        cur = next;
+    }
+
+    // ---- the four wavefronts' states, over the LDS (no load may still be on its way into it)
+    TSDPA_WAIT_VMCNT0();
+    __syncthreads();
+    typedef TSDPA_LDS float *lds_f;
+    const lds_f mem = (lds_f)lds;
+    float wgt[NQ];                                // this wavefront's weight 2^(m - M)
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq) {
+        float l = l_run[nq];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (t == 0) {
+            mem[((wave * NQ + nq) * 16 + l16) * 2] = m_ref[nq];
+            mem[((wave * NQ + nq) * 16 + l16) * 2 + 1] = l;
+        }
+    }
+    __syncthreads();
+    float M[NQ], L[NQ];
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq) {
+        M[nq] = -INFINITY;
+        L[nq] = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) M[nq] = fmaxf(M[nq], mem[((w * NQ + nq) * 16 + l16) * 2]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float m = mem[((w * NQ + nq) * 16 + l16) * 2];
+            L[nq] += (m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M[nq])) * mem[((w * NQ + nq) * 16 + l16) * 2 + 1];
+        }
+        wgt[nq] = m_ref[nq] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref[nq] - M[nq]);
+        // one split: the division by the normaliser on the way (no key at all: O = 0)
+        if (splits == 1) wgt[nq] *= L[nq] > 0.f ? 1.f / L[nq] : 0.f;
+    }
+    __syncthreads();
+    // [wave][row][D] floats
+#pragma unroll
+    for (int nq = 0; nq < NQ; ++nq)
+        if (nq * 16 + l16 < S)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                f32x4 part;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) part[e] = oacc[nq][db][e] * wgt[nq];
+                *(TSDPA_LDS f32x4 *)(lds + ((wave * NQ * 16 + nq * 16 + l16) * D + db * 16 + t * 4) * 4) = part;
+            }
+    __syncthreads();
+    if (wave == 0 && t == 0)
+#pragma unroll
+        for (int nq = 0; nq < NQ; ++nq) {
+            const int row = nq * 16 + l16;
+            if (row >= S) continue;
+            if (splits > 1) {
+                put(ws + (size_t)heads * splits * S * D + ((size_t)(head * splits + sp) * S + row) * 2, M[nq], L[nq]);
+            } else if (lse != nullptr) {
+                lse[(size_t)head * S + row] = L[nq] > 0.f ? (M[nq] + __builtin_amdgcn_logf(L[nq])) * 0.69314718055994530942f : -INFINITY;
+            }
+        }
+    for (int x = tid; x < S * (D / 4); x += NW * 64) {
+        f32x4 sum = *(TSDPA_LDS f32x4 *)(lds + x * 16);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += *(TSDPA_LDS f32x4 *)(lds + w * (NQ * 16 * D * 4) + x * 16);
+        if (splits > 1) {
+            float *part = ws + (size_t)(head * splits + sp) * S * D + (size_t)x * 4;
+            put(part, sum[0], sum[1]);
+            put(part + 2, sum[2], sum[3]);
+        } else {
+            vec4 out;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[e] = (T)sum[e];
+            *(vec4 *)(o + (size_t)head * S * D + (size_t)x * 4) = out;
+        }
+    }
+    if (ticket != 0) finish();
+#endif
+}
+
+template <typename T, int D, int NQ, int NW, bool PAGED> int launch_decode_one(const LaunchArgs &a)
+{
+    auto kern = sdpa_decode_kernel<T, D, NQ, NW, PAGED>;
+    constexpr int lds_bytes = NW * 2 * DecodeGeom<D>::TILE;
+    static_assert(NW * NQ * 16 * D * 4 <= lds_bytes, "the states of all wavefronts must fit");
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] {
+        attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    });
+    if (attr_err != hipSuccess) return (int)attr_err;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * a.splits)), dim3(NW * 64), lds_bytes, a.stream,
+                       (const T *)a.q, (const T *)a.k, (const T *)a.v, (T *)a.o, a.lse, a.S, a.BH, a.c, a.tau, a.qsign, a.causal,
+                       a.Skv, a.splits, a.ws, a.rows_per_head, a.kv_lens, a.heads_per_batch, a.block_table, a.max_blocks, a.block_shift, a.ticket);
+    return (int)hipGetLastError();
+}
+
+template <typename T, int D, int NQ> int launch_decode_rows(const LaunchArgs &a)
+{
+    // Up to one workgroup per CU: eight wavefronts each (two workgroups of four per CU hold as many beyond that): level on
+    // large caches, 256 heads of 2048 keys 52.5 -> 48.4 us
+    // (with less than a tile per wavefront to do, four)
+    if (a.BH * a.splits <= 256 && a.Skv / a.splits >= 8 * kDecodeTile)
+        return a.block_table ? launch_decode_one<T, D, NQ, 8, true>(a) : launch_decode_one<T, D, NQ, 8, false>(a);
+    return a.block_table ? launch_decode_one<T, D, NQ, 4, true>(a) : launch_decode_one<T, D, NQ, 4, false>(a);
+}
+
+template <typename T> int launch_decode(int D, const LaunchArgs &a)
+{
+    switch (D) {
+        case 64: return a.S <= 16 ? launch_decode_rows<T, 64, 1>(a) : launch_decode_rows<T, 64, 2>(a);
+        case 96: return a.S <= 16 ? launch_decode_rows<T, 96, 1>(a) : launch_decode_rows<T, 96, 2>(a);
+        case 128: return a.S <= 16 ? launch_decode_rows<T, 128, 1>(a) : launch_decode_rows<T, 128, 2>(a);
+        default: return a.S <= 16 ? launch_decode_rows<T, 160, 1>(a) : launch_decode_rows<T, 160, 2>(a);
+    }
+}
+
+}  // namespace tsdpa

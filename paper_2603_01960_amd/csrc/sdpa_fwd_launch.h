@@ -25,6 +25,7 @@ struct LaunchArgs {
     int max_blocks, block_shift;
     int tile_rot;      // kv = 1, dense cache: 1 = every workgroup starts its sweep over the unmasked tiles at a tile of its own
     int batches;       // kv = 1: batch entries (BH / heads_per_batch)
+    unsigned long long ticket; // decoding kernel, splits > 1: a number of this call alone (never 0) if it combines the runs itself, else 0
     int rows_per_head; // kv = 1: query positions per query head; S / rows_per_head query heads are folded into the S rows
     hipStream_t stream;
 };
@@ -83,6 +84,9 @@ int launch_bf16_d96(int tile_m, int tile_n, const LaunchArgs &a);
 int launch_bf16_d128(int tile_m, int tile_n, const LaunchArgs &a);
 int launch_bf16_d160(int tile_m, int tile_n, const LaunchArgs &a);
 
+// Decoding steps (a.S <= 32 query rows per key/value head; sdpa_decode_kernel.h).
+int launch_decode_f16(int D, const LaunchArgs &a);
+int launch_decode_bf16(int D, const LaunchArgs &a);
 
 // Backward pass: the dQ pass (queries resident; row statistics on the way), then dK and dV (keys resident).
 int launch_bwd_f16_d64(const BwdLaunchArgs &a);

@@ -2,10 +2,12 @@
 // See include/tiled_sdpa.h for the contract of every entry point.
 #include "tiled_sdpa.h"
 
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <limits>
 #include <mutex>
+#include <random>
 
 #include "sdpa_fwd_launch.h"
 #include "sdpa_merge_kernel.h"
@@ -132,6 +134,48 @@ int pick_splits(int BH, int Sq, int Skv, int tm, int tn)
     return (int)want;
 }
 
+// A 64-bit number that no other call of any process has had, as far as chance goes: a counter from a random start,
+// scrambled (the splitmix64 finaliser, a bijection) so that it looks like no data anybody would store.
+unsigned long long call_ticket()
+{
+    static std::atomic<unsigned long long> counter{[] {
+        std::random_device rd;
+        return ((unsigned long long)rd() << 32) ^ rd();
+    }()};
+    unsigned long long x = counter.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    x ^= x >> 31;
+    return x != 0 ? x : 1;
+}
+
+// Query rows per key/value head that the decoding kernel takes (its tile is not the caller's to choose).
+constexpr int kDecodeRows = 32;
+
+// Splits of a decoding step (BF16, cold cache, us; s = splits): one workgroup per CU in all, of runs of at least 128 keys.
+// From half as many key/value heads as CUs on, none: a pass is then as fast without the second look at the states (256
+// heads of 8192 keys: s1 177, s2 181, s4 185; lengths from a quarter of that: 127, 131-133, 130-132; 160 heads of 1024:
+// 18.0 / 22.5 / 23.5; 96 heads of 3000: 28.1 / 24.2 / 25.9; 32 heads of 8192: s4 30.9, s8 27.4, s16 28.5).
+int pick_splits_decode(int BH, int Skv)
+{
+    const int most = Skv > 256 ? (Skv + 127) / 128 : 1;
+    int want = BH >= 128 ? 1 : BH > 64 ? 2 : 256 / BH;
+    if (want > most) want = most;
+    if (want > TSDPA_MAX_SPLITS) want = TSDPA_MAX_SPLITS;
+    return want;
+}
+
+void pick_tile_kv(long long heads, int Sq, int Skv, int D, int *tm, int *tn);
+
+// Splits of a cache call whose tile is left to the library too.
+int default_splits(int BH, int rows, int Skv, int D)
+{
+    if (rows <= kDecodeRows) return pick_splits_decode(BH, Skv);
+    int tm, tn;
+    pick_tile_kv(BH, rows, Skv, D, &tm, &tn);
+    return pick_splits(BH, rows, Skv, tm, tn);
+}
+
 int validate_shape_kv(int B, int H, int Sq, int Skv, int D, int dtype, unsigned flags)
 {
     if (dtype != TSDPA_F16 && dtype != TSDPA_BF16) return TSDPA_ERR_BAD_DTYPE;
@@ -157,14 +201,12 @@ bool valid_tile_kv(int tm, int tn, bool paged)
 
 void pick_tile_kv(long long heads, int Sq, int Skv, int D, int *tm, int *tn)
 {
-    // (decoding shapes are bound by the cache read, not by the loop)
+    // (up to 32 rows the decoding kernel takes over, whose tile is its own)
     *tm = Sq <= 64 ? 64 : 128;
     *tn = Skv >= 512 ? 64 : 32;
     // D = 160: 32-row tiles are level or ahead (3-10 %) until the query block is long (2048 rows: 64-row tiles
-    // 2-5 % ahead) or its 128-row tiles are fewer than the CUs (15 % ahead at one head's 512 or 1024 rows);
-    // D = 96: a handful of query rows per key/value head read the cache 2-15 % faster in 32-row tiles
+    // 2-5 % ahead) or its 128-row tiles are fewer than the CUs (15 % ahead at one head's 512 or 1024 rows)
     if (D == 160) *tn = (Sq >= 2048 || (Sq >= 128 && Skv >= 512 && heads * ((Sq + 127) / 128) < 256)) ? 64 : 32;
-    if (D == 96 && Sq <= 16) *tn = 32;
 }
 
 }  // namespace
@@ -316,9 +358,11 @@ int tiled_sdpa_kv_default_splits(int B, int H, int Sq, int Skv, int D, int dtype
     if (!splits) return TSDPA_ERR_NULL_PTR;
     const int st = validate_shape_kv(B, H, Sq, Skv, D, dtype, flags);
     if (st != TSDPA_OK) return st;
-    int tm, tn;
-    pick_tile_kv((long long)B * H, Sq, Skv, D, &tm, &tn);
-    *splits = pick_splits(B * H, Sq, Skv, tm, tn);
+    if ((int64_t)B * H * Sq == 0) {
+        *splits = 1;
+        return TSDPA_OK;
+    }
+    *splits = default_splits(B * H, Sq, Skv, D);
     return TSDPA_OK;
 }
 
@@ -362,10 +406,9 @@ int tiled_sdpa_fwd_kvcache_static(const void *q, const void *k, const void *v, v
     if (splits < 0 || splits > TSDPA_MAX_SPLITS) return TSDPA_ERR_BAD_SPLITS;
     if ((int64_t)(H / Hkv) * Sq > (int64_t)std::numeric_limits<int>::max()) return TSDPA_ERR_BAD_SHAPE;
     if (splits == 0) {
-        int tm = tile_m, tn = tile_n;
-        if (tm == 0 && tn == 0) pick_tile_kv((long long)B * Hkv, (H / Hkv) * Sq, Skv, D, &tm, &tn);
-        else if (!valid_tile_kv(tm, tn, false)) return TSDPA_ERR_BAD_TILE;
-        splits = pick_splits(B * Hkv, (H / Hkv) * Sq, Skv, tm, tn);
+        if (tile_m == 0 && tile_n == 0) splits = default_splits(B * Hkv, (H / Hkv) * Sq, Skv, D);
+        else if (!valid_tile_kv(tile_m, tile_n, false)) return TSDPA_ERR_BAD_TILE;
+        else splits = pick_splits(B * Hkv, (H / Hkv) * Sq, Skv, tile_m, tile_n);
     }
     const unsigned long long need = tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits);
     if (need > (unsigned long long)TSDPA_STATIC_SCRATCH_BYTES) return TSDPA_ERR_STATIC_SCRATCH;
@@ -430,7 +473,7 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     if (std::isnan(scale)) scale = 1.0f / std::sqrt((float)D);
     if (std::isinf(scale)) return TSDPA_ERR_BAD_SCALE;
     if (splits < 0 || splits > TSDPA_MAX_SPLITS) return TSDPA_ERR_BAD_SPLITS;
-    if (splits == 0) splits = pick_splits(B * Hkv, rows, Skv, tile_m, tile_n);
+    if (splits == 0) splits = heuristic_tile ? default_splits(B * Hkv, rows, Skv, D) : pick_splits(B * Hkv, rows, Skv, tile_m, tile_n);
     // Long query blocks against a dense cache of one length, no mask, no split: the 256-row query tile of the
     // square problem, under the same conditions (with 256 such workgroups the 128-row tile has 512 and is not
     // split either, so the split count does not depend on this choice)
@@ -474,7 +517,14 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     a.stream = (hipStream_t)stream;
 
     int err;
-    if (dtype == TSDPA_F16) {
+    const bool decode = heuristic_tile && rows <= kDecodeRows;
+    // The decoding kernel combines the runs itself while they are few: a mark (8 bytes) per run must fit a head's part of o,
+    // and past about 64 states per head the one workgroup that does it is slower than the merge kernel's many (8 heads, 4
+    // rows: 8 runs of 128 keys 7.9 us against 10.5 with two kernels, 16 runs level, 32 runs of 256 keys 15.2 against 13.3)
+    if (decode && splits > 1 && splits <= rows * D / 4 && splits * rows <= 64) a.ticket = call_ticket();
+    if (decode) {
+        err = dtype == TSDPA_F16 ? tsdpa::launch_decode_f16(D, a) : tsdpa::launch_decode_bf16(D, a);
+    } else if (dtype == TSDPA_F16) {
         switch (D) {
             case 64: err = tsdpa::launch_f16_d64(tile_m, tile_n, a); break;
             case 96: err = tsdpa::launch_f16_d96(tile_m, tile_n, a); break;
@@ -490,13 +540,14 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
         }
     }
     if (err != 0) return TSDPA_ERR_LAUNCH;
+    if (a.ticket != 0) return TSDPA_OK;
     const size_t out_rows = (size_t)B * H * Sq;
-    // Which merge: with more than eight splits a thread that walks them waits for its loads in several
+    // Which merge: with more than eight splits (or after the decoding kernel, whose rows are few) a thread that walks them waits for its loads in several
     // batches, and when the rows are few (decoding) nothing else hides that: one workgroup per row, the
     // splits shared among eight threads (32 splits of 32 rows: 3.5 us against 12.5 us).  With thousands of
     // rows the walking threads are many enough to hide it themselves and launch an eighth of the threads
     // (8 splits of 8192 rows: 47 us per call against 55 us).
-    if (splits > 8 && out_rows <= 2048) {
+    if (splits > 1 && (splits > 8 || decode) && out_rows <= 2048) {
         static_assert(tsdpa::kMergeLanes * tsdpa::kMergePerLane >= TSDPA_MAX_SPLITS, "every split needs a thread");
         const dim3 block(D / 4, tsdpa::kMergeLanes);
         if (dtype == TSDPA_F16)

@@ -1,0 +1,51 @@
+"""The decoding kernel (at most 32 query rows per key/value head, tile left to the library) at the edges of its tiles (32 keys,
+16 query rows), of its wavefronts' shares (4 or 8 tiles per round) and of its runs, against the float64 oracle: the
+usual forward tolerances."""
+import pytest
+
+import test_sdpa_kv_gpu as kv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 96, 128, 160])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_row_and_key_counts_around_the_tiles(D, dtype):
+    for Sq in (1, 15, 16, 17, 32):
+        for Skv in (1, 31, 32, 33, 129, 257, 700):
+            q, k, v = kv.make_q_kv(1, 2, Sq, Skv, D, dtype, seed=4000 + 100 * Sq + Skv)
+            # one run (four or eight wavefronts), runs the kernel combines itself or leaves to the merge, empty runs
+            for splits in (1, 3, 40):
+                kv.check_kv(q, k, v, dtype, splits=splits, tag="decode")
+            if Skv >= Sq:
+                kv.check_kv(q, k, v, dtype, splits=2, causal=True, tag="decode causal")
+
+
+@pytest.mark.parametrize("splits", [0, 1, 2, 5])
+@pytest.mark.parametrize("D,G,Sq", [(64, 8, 1), (128, 4, 2), (160, 8, 4), (96, 1, 3)])
+def test_grouped_heads_lengths_and_pages(splits, D, G, Sq):
+    lens = [0, 1, 130, 513, 1000, 64, 999]
+    for causal in (False, True):
+        kv.check_kv_lens(len(lens), 2 * G, 2, Sq, 1000, D, "bf16", lens, causal, splits)
+        kv.check_paged(len(lens), 2 * G, 2, Sq, D, "bf16", lens, 64, causal, splits)
+
+
+def test_more_workgroups_than_fit_at_once():
+    # 600 key/value heads (four wavefronts each), 300 heads in two runs
+    q, k, v = kv.make_q_kv(100, 6, 1, 300, 64, "bf16", seed=4900)
+    kv.check_kv(q, k, v, "bf16", tag="many heads")
+    q, k, v = kv.make_q_kv(50, 6, 2, 300, 128, "f16", seed=4901)
+    kv.check_kv(q, k, v, "f16", splits=2, causal=True, tag="many heads, two runs")
+
+
+def test_output_buffer_holds_nothing_but_the_result():
+    """The runs' marks stand in the output until the result replaces them: whatever the buffer held before, an earlier result
+    of the same call included, must not matter."""
+    import torch
+    from paper_2603_01960_amd import binding
+    q, k, v = (t.cuda() for t in kv.make_q_kv(2, 3, 4, 2000, 128, "bf16", seed=4950))
+    ref = binding.sdpa_kv(q, k, v, splits=8)
+    for fill in (float("nan"), 0.0, 1.0):
+        out = torch.full_like(q, fill)
+        for _ in range(3):
+            assert torch.equal(binding.sdpa_kv(q, k, v, splits=8, out=out), ref)
