@@ -155,7 +155,8 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const float w = st[i].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st[i].x - M);
-                if (lane + i * 64 < splits) wgt[(lane + i * 64) * S + row] = w;
+                // (a run without keys, l = 0, has left its o unwritten: marked by a negative weight; a row of NaN scores has l = NaN)
+                if (lane + i * 64 < splits) wgt[(lane + i * 64) * S + row] = st[i].y == 0.f ? -1.f : w;
                 L += w * st[i].y;
             }
 #pragma unroll
@@ -175,7 +176,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
             for (int s = 0; s < splits; ++s) {
                 const float w = wgt[s * S + row];
                 const Pair part = get(po + (size_t)s * S * D + (size_t)x * 2);
-                if (w > 0.f) {                            // (a run without keys has left its o unwritten)
+                if (!(w < 0.f)) {
                     s0 += w * part.x;
                     s1 += w * part.y;
                 }

@@ -6,7 +6,7 @@
 // rescale by e^{m_old - m_new}, states over disjoint key ranges combine the same way:
 //     M = max_s m_s,   w_s = 2^(m_s - M),   L = sum_s w_s l_s,   O = (sum_s w_s o_s) / L,
 // and O_i = o_i / l_i as at the end of Section 4.1.2; LSE = (M + log2 L) ln 2.  A split that saw no
-// key of the row has (m, l) = (-inf, 0), weight 0, and an o that is not looked at.
+// key of the row has (m, l) = (-inf, 0), weight 0, and an o that is not looked at; a row of NaN scores has (-inf, NaN).
 //
 // Workspace layout (written by sdpa_fwd_kernel<..., KV = true>): o as float [BH][splits][S][D],
 // then (m, l) pairs as float [BH][splits][S][2].
@@ -57,7 +57,7 @@ sdpa_merge_kernel(const float *__restrict__ ws, T *__restrict__ o, float *__rest
         const float w = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[p * 2] - M);
         L += w * ml[p * 2 + 1];
         const f32x4 part = *(const f32x4 *)(ws + p * D + d4 * 4);
-        if (w > 0.f) acc += w * part;             // (a split without keys may have left its o unwritten)
+        if (ml[p * 2 + 1] != 0.f) acc += w * part; // (a split without keys, l = 0, may have left its o unwritten; a NaN row has l = NaN)
     }
     const float inv = L > 0.f ? 1.0f / L : 0.f;
     vec4 out;
@@ -117,7 +117,7 @@ sdpa_merge_wide_kernel(const float *__restrict__ ws, T *__restrict__ o, float *_
         // weight 0 for a split with m = -inf (it saw no key of the row, or does not exist)
         const float w = st[i][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st[i][0] - m_own);
         l_own += w * st[i][1];
-        if (w > 0.f) acc += w * part[i];          // (a split without keys may have left its o unwritten)
+        if (st[i][1] != 0.f) acc += w * part[i];  // (a split without keys, l = 0, may have left its o unwritten; a NaN row has l = NaN)
     }
     acc_sh[lane][d4] = acc;
     if (d4 == 0) ml_sh[lane] = f32x2{m_own, l_own};

@@ -49,3 +49,22 @@ def test_output_buffer_holds_nothing_but_the_result():
         out = torch.full_like(q, fill)
         for _ in range(3):
             assert torch.equal(binding.sdpa_kv(q, k, v, splits=8, out=out), ref)
+
+
+def test_nan_rows_stay_nan_however_the_runs_are_combined():
+    """A query row with a NaN has NaN weights: its output is NaN and no other row's is, whether one run, the kernel itself
+    or either merge kernel (few rows, many rows) makes the result; runs without keys (lens) change nothing."""
+    import torch
+    from paper_2603_01960_amd import binding
+    for B, Sq, splits in ((2, 4, 1), (2, 4, 8), (2, 4, 40), (700, 4, 3)):
+        q, k, v = (t.cuda() for t in kv.make_q_kv(B, 1, Sq, 400, 64, "bf16", seed=4970))
+        lens = torch.full((B,), 150, dtype=torch.int32, device="cuda")
+        for kv_lens in (None, lens):
+            ref = binding.sdpa_kv(q, k, v, splits=splits, kv_lens=kv_lens)
+            bad = q.clone()
+            bad[1, 0, 2, 5] = float("nan")
+            out = binding.sdpa_kv(bad, k, v, splits=splits, kv_lens=kv_lens)
+            assert out[1, 0, 2].isnan().all(), (B, splits)
+            out[1, 0, 2] = ref[1, 0, 2]
+            # (the NaN makes its wavefront raise every row's reference: other roundings of the weights, 2^-9 each)
+            torch.testing.assert_close(out.float(), ref.float(), rtol=1e-2, atol=1e-2)
