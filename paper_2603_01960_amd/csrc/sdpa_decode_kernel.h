@@ -16,8 +16,6 @@
 // keys at D = 96 36.4 / 24.2; 256 heads of 2048 keys 51.3 / 48.4 and of 200 ... 2048 keys 35.1 / 29.6; 256 heads of 8192
 // keys 187 / 177 (6.06 TB/s), of 2048 ... 8192 keys in pages 135.6 / 127.8.
 #pragma once
-#include <utility>
-
 #include "sdpa_fwd_kernel.h"
 #include "sdpa_fwd_launch.h"
 
@@ -34,22 +32,6 @@ template <> struct Elem16<__bf16> {
     static __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 };
 
-// f(0), f(1), ..., f(N - 1) with the index as a compile-time constant (immediate offsets of the LDS reads below)
-template <typename F, int... I> __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
-
-template <int OFF> __device__ __forceinline__ void lds_fetch128(u32x4 &x, uint32_t addr)
-{
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(x) : "v"(addr), "n"(OFF) : "memory");
-}
-template <int OFF> __device__ __forceinline__ void lds_fetch_tr16(i16x4 &x, uint32_t addr)
-{
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(x) : "v"(addr), "n"(OFF) : "memory");
-}
-
 // LDS layout of a K or V tile: 32 rows of D values, unpadded; 16-byte chunks are permuted within each row.
 //   K (16 lanes read one chunk of 16 consecutive rows): as in the forward kernel.
 //   V (the transposing read has 32 lanes fetch the same 32 bytes of 8 consecutive rows): 32-byte block b of row r at
@@ -65,6 +47,110 @@ template <int D> struct DecodeGeom {
     static constexpr int NKP = D == 128 ? 4 : D == 64 ? 2 : 1;            // row pointers: one per 64-byte step ks (or immediates)
     static constexpr int NVP = D == 128 ? 8 : D == 64 ? 4 : 2;            // transposing pointers: one per 32-byte block db (or per parity)
 };
+
+// The operand reads of one tile and the wait for them, in ONE block of inline assembly each: left to the compiler, which
+// cannot tell the slots apart, the first read waits for every outstanding load, the next tile's included.  (One block:
+// the compiler takes an output for written when its block ends, so none may still be on its way then; outputs are early
+// clobbers because the pointers are read until the last of them.)
+//   keys:   x[b][ks] = 16 bytes at kptr[NKP == 1 ? 0 : ks] + b * 16 * ROW (+ ks * 64 where one pointer serves every ks)
+//   values: x[db][b] = transposing read at vptr[NVP == 2 ? db & 1 : db] + b * 16 * ROW (+ (db >> 1) * 64 where two serve)
+#define TSDPA_RD_K(i, a, off) "ds_read_b128 %" #i ", %" #a " offset:" #off "\n\t"
+#define TSDPA_RD_V(i, a, off) "ds_read_b64_tr_b16 %" #i ", %" #a " offset:" #off "\n\t"
+#define TSDPA_RD_WAIT "s_waitcnt lgkmcnt(0)"
+template <int D> struct DecodeRead;
+template <> struct DecodeRead<64> {
+    static __device__ __forceinline__ void keys(u32x4 (&x)[2][2], const uint32_t (&p)[2])
+    {
+        asm volatile(TSDPA_RD_K(0, 4, 0) TSDPA_RD_K(1, 5, 0) TSDPA_RD_K(2, 4, 2048) TSDPA_RD_K(3, 5, 2048) TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1])
+                     : "v"(p[0]), "v"(p[1])
+                     : "memory");
+    }
+    static __device__ __forceinline__ void values(i16x4 (&x)[4][2], const uint32_t (&p)[4])
+    {
+        asm volatile(TSDPA_RD_V(0, 8, 0) TSDPA_RD_V(1, 8, 2048) TSDPA_RD_V(2, 9, 0) TSDPA_RD_V(3, 9, 2048)
+                     TSDPA_RD_V(4, 10, 0) TSDPA_RD_V(5, 10, 2048) TSDPA_RD_V(6, 11, 0) TSDPA_RD_V(7, 11, 2048) TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1]), "=&v"(x[2][0]), "=&v"(x[2][1]),
+                       "=&v"(x[3][0]), "=&v"(x[3][1])
+                     : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3])
+                     : "memory");
+    }
+};
+template <> struct DecodeRead<96> {
+    static __device__ __forceinline__ void keys(u32x4 (&x)[2][3], const uint32_t (&p)[1])
+    {
+        asm volatile(TSDPA_RD_K(0, 6, 0) TSDPA_RD_K(1, 6, 64) TSDPA_RD_K(2, 6, 128) TSDPA_RD_K(3, 6, 3072)
+                     TSDPA_RD_K(4, 6, 3136) TSDPA_RD_K(5, 6, 3200) TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[0][2]), "=&v"(x[1][0]), "=&v"(x[1][1]), "=&v"(x[1][2])
+                     : "v"(p[0])
+                     : "memory");
+    }
+    static __device__ __forceinline__ void values(i16x4 (&x)[6][2], const uint32_t (&p)[2])
+    {
+        asm volatile(TSDPA_RD_V(0, 12, 0) TSDPA_RD_V(1, 12, 3072) TSDPA_RD_V(2, 13, 0) TSDPA_RD_V(3, 13, 3072)
+                     TSDPA_RD_V(4, 12, 64) TSDPA_RD_V(5, 12, 3136) TSDPA_RD_V(6, 13, 64) TSDPA_RD_V(7, 13, 3136)
+                     TSDPA_RD_V(8, 12, 128) TSDPA_RD_V(9, 12, 3200) TSDPA_RD_V(10, 13, 128) TSDPA_RD_V(11, 13, 3200)
+                     TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1]), "=&v"(x[2][0]), "=&v"(x[2][1]),
+                       "=&v"(x[3][0]), "=&v"(x[3][1]), "=&v"(x[4][0]), "=&v"(x[4][1]), "=&v"(x[5][0]), "=&v"(x[5][1])
+                     : "v"(p[0]), "v"(p[1])
+                     : "memory");
+    }
+};
+template <> struct DecodeRead<128> {
+    static __device__ __forceinline__ void keys(u32x4 (&x)[2][4], const uint32_t (&p)[4])
+    {
+        asm volatile(TSDPA_RD_K(0, 8, 0) TSDPA_RD_K(1, 9, 0) TSDPA_RD_K(2, 10, 0) TSDPA_RD_K(3, 11, 0) TSDPA_RD_K(4, 8, 4096)
+                     TSDPA_RD_K(5, 9, 4096) TSDPA_RD_K(6, 10, 4096) TSDPA_RD_K(7, 11, 4096) TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[0][2]), "=&v"(x[0][3]), "=&v"(x[1][0]), "=&v"(x[1][1]),
+                       "=&v"(x[1][2]), "=&v"(x[1][3])
+                     : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3])
+                     : "memory");
+    }
+    static __device__ __forceinline__ void values(i16x4 (&x)[8][2], const uint32_t (&p)[8])
+    {
+        asm volatile(TSDPA_RD_V(0, 16, 0) TSDPA_RD_V(1, 16, 4096) TSDPA_RD_V(2, 17, 0) TSDPA_RD_V(3, 17, 4096)
+                     TSDPA_RD_V(4, 18, 0) TSDPA_RD_V(5, 18, 4096) TSDPA_RD_V(6, 19, 0) TSDPA_RD_V(7, 19, 4096)
+                     TSDPA_RD_V(8, 20, 0) TSDPA_RD_V(9, 20, 4096) TSDPA_RD_V(10, 21, 0) TSDPA_RD_V(11, 21, 4096)
+                     TSDPA_RD_V(12, 22, 0) TSDPA_RD_V(13, 22, 4096) TSDPA_RD_V(14, 23, 0) TSDPA_RD_V(15, 23, 4096)
+                     TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1]), "=&v"(x[2][0]), "=&v"(x[2][1]),
+                       "=&v"(x[3][0]), "=&v"(x[3][1]), "=&v"(x[4][0]), "=&v"(x[4][1]), "=&v"(x[5][0]), "=&v"(x[5][1]),
+                       "=&v"(x[6][0]), "=&v"(x[6][1]), "=&v"(x[7][0]), "=&v"(x[7][1])
+                     : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(p[4]), "v"(p[5]), "v"(p[6]), "v"(p[7])
+                     : "memory");
+    }
+};
+template <> struct DecodeRead<160> {
+    static __device__ __forceinline__ void keys(u32x4 (&x)[2][5], const uint32_t (&p)[1])
+    {
+        asm volatile(TSDPA_RD_K(0, 10, 0) TSDPA_RD_K(1, 10, 64) TSDPA_RD_K(2, 10, 128) TSDPA_RD_K(3, 10, 192)
+                     TSDPA_RD_K(4, 10, 256) TSDPA_RD_K(5, 10, 5120) TSDPA_RD_K(6, 10, 5184) TSDPA_RD_K(7, 10, 5248)
+                     TSDPA_RD_K(8, 10, 5312) TSDPA_RD_K(9, 10, 5376) TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[0][2]), "=&v"(x[0][3]), "=&v"(x[0][4]), "=&v"(x[1][0]),
+                       "=&v"(x[1][1]), "=&v"(x[1][2]), "=&v"(x[1][3]), "=&v"(x[1][4])
+                     : "v"(p[0])
+                     : "memory");
+    }
+    static __device__ __forceinline__ void values(i16x4 (&x)[10][2], const uint32_t (&p)[2])
+    {
+        asm volatile(TSDPA_RD_V(0, 20, 0) TSDPA_RD_V(1, 20, 5120) TSDPA_RD_V(2, 21, 0) TSDPA_RD_V(3, 21, 5120)
+                     TSDPA_RD_V(4, 20, 64) TSDPA_RD_V(5, 20, 5184) TSDPA_RD_V(6, 21, 64) TSDPA_RD_V(7, 21, 5184)
+                     TSDPA_RD_V(8, 20, 128) TSDPA_RD_V(9, 20, 5248) TSDPA_RD_V(10, 21, 128) TSDPA_RD_V(11, 21, 5248)
+                     TSDPA_RD_V(12, 20, 192) TSDPA_RD_V(13, 20, 5312) TSDPA_RD_V(14, 21, 192) TSDPA_RD_V(15, 21, 5312)
+                     TSDPA_RD_V(16, 20, 256) TSDPA_RD_V(17, 20, 5376) TSDPA_RD_V(18, 21, 256) TSDPA_RD_V(19, 21, 5376)
+                     TSDPA_RD_WAIT
+                     : "=&v"(x[0][0]), "=&v"(x[0][1]), "=&v"(x[1][0]), "=&v"(x[1][1]), "=&v"(x[2][0]), "=&v"(x[2][1]),
+                       "=&v"(x[3][0]), "=&v"(x[3][1]), "=&v"(x[4][0]), "=&v"(x[4][1]), "=&v"(x[5][0]), "=&v"(x[5][1]),
+                       "=&v"(x[6][0]), "=&v"(x[6][1]), "=&v"(x[7][0]), "=&v"(x[7][1]), "=&v"(x[8][0]), "=&v"(x[8][1]),
+                       "=&v"(x[9][0]), "=&v"(x[9][1])
+                     : "v"(p[0]), "v"(p[1])
+                     : "memory");
+    }
+};
+#undef TSDPA_RD_K
+#undef TSDPA_RD_V
+#undef TSDPA_RD_WAIT
 
 // PAGED: a descriptor per tile (see the forward kernel's paged variant).
 template <typename T, int D, int NQ, int NW, bool PAGED>
@@ -302,8 +388,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
     }
     const float lazy_limit = __builtin_amdgcn_exp2f(tau);
 
-    // ---- LDS reads go through inline assembly with explicit waits: left to the compiler, which cannot tell the slots
-    // apart, the first of them waits for every outstanding load, the next tile's included
+    // ---- pointers of the operand reads
     uint32_t kptr[G::NKP], vptr[G::NVP];
 #pragma unroll
     for (int i = 0; i < G::NKP; ++i)
@@ -337,16 +422,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
         // K has landed when at most V's loads are outstanding
         u32x4 kf[2][KS];
         __builtin_amdgcn_s_waitcnt(0x0F70 | NU);
-        static_for<2 * KS>([&](auto x) __attribute__((always_inline)) {
-            constexpr int b = decltype(x)::value / KS, ks = decltype(x)::value % KS;
-            constexpr int off = b * 16 * G::ROW + (G::NKP == 1 ? ks * 64 : 0);
-            lds_fetch128<off>(kf[b][ks], kptr[G::NKP == 1 ? 0 : ks]);
-        });
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kf[b][ks]));      // (used after the wait)
+        DecodeRead<D>::keys(kf, kptr);
         load_k(s);
         f32x4 sacc[NQ][2];
 #pragma unroll
@@ -387,14 +463,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
         // V has landed when at most the next K's loads are outstanding
         i16x4 vf[DB][2];
         __builtin_amdgcn_s_waitcnt(0x0F70 | NU);
-        static_for<2 * DB>([&](auto x) __attribute__((always_inline)) {
-            constexpr int db = decltype(x)::value / 2, b = decltype(x)::value % 2;
-            constexpr int off = b * 16 * G::ROW + (G::NVP == 2 ? (db >> 1) * 64 : 0);
-            lds_fetch_tr16<off>(vf[db][b], vptr[G::NVP == 2 ? (db & 1) : db]);
-        });
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(vf[db][0]), "+v"(vf[db][1]));
+        DecodeRead<D>::values(vf, vptr);
         load_v(s);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
