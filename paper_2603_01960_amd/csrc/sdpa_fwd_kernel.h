@@ -127,10 +127,17 @@ __device__ __forceinline__ int remap_workgroup(int id, int N, bool linear) {
 // Heads are taken in chunks of 8 * hg (hg per XCD; causal_chunks in sdpa_fwd_launch.h), of which the first may be short.
 // The heads of a chunk that eight does not divide (rem < 8) are dealt tile by tile, level by level, over all XCDs.
 // Returns the level in .level and the head in .head; with N = BH * nQ every pair is met exactly once.
+// `paired` (workgroups of the launch, where the order is wanted): up to two workgroups per CU (512) all of them start at
+// once, and the second one of a CU stays there whatever it does, so an XCD's workgroups past its first 32 come in reverse
+// order and the CU with the longest tile gets the shortest one beside it.  Forward, BF16, us: six heads of S = 8192
+// D = 64 88.2 -> 84.4, 96 115.3 -> 104.4, 128 138 -> 128, 160 174 -> 164; 30 of S = 2048 28.4 -> 27.1, 37.2 -> 34.0, 44.4 ->
+// 41.7, 55.8 -> 53.5; 64 of S = 1024 17.7 -> 17.1 ... 35.0 -> 33.7; level at S = 512.  The backward passes
+// gain 0-4 % at D = 128 and 160, and lose 0-2 % at D = 64 and 96, where it is not used.
 struct CausalTile { int head, level; };
-__device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int hg) {
+__device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int hg, int paired = 0) {
     const int x = id & 7;
     int y = id >> 3;
+    if (paired > 256 && paired <= 512 && y >= 32) y = ((paired - x + 7) >> 3) + 31 - y;
     int full = first >> 3, rem = first & 7, h0 = 0;
     const int in_first = full * nQ + ((nQ * rem + 7 - x) >> 3);   // this XCD's share of the first chunk
     if (y >= in_first) {
@@ -223,7 +230,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     // of a query tile grows with its index, and the long ones of all heads are started first (causal_tile).
     int hs, qt;
     if (causal && !linear_grid && chunk_heads > 0) {
-        const CausalTile ct = causal_tile(blockIdx.x, nQ, chunk_first, chunk_heads);
+        const CausalTile ct = causal_tile(blockIdx.x, nQ, chunk_first, chunk_heads, N);
         hs = ct.head;
         qt = nQ - 1 - ct.level;
         if (KV && folded && Sp % TM == 0) {       // the last tile of every folded query head, then the one before it, ...

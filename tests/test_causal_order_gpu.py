@@ -1,6 +1,6 @@
-"""The order in which workgroups take the tiles of a causal problem must not change a single bit: each launch below is
-large enough for the long-tiles-first order (more than 256 workgroups) and is held against calls that take the plain
-order (the linear-grid flag, or one head at a time).  Outputs start as NaN, so a tile nobody took shows."""
+"""The order in which workgroups take the tiles of a causal problem must not change what they compute (in the forward
+pass not a single bit): each launch below is large enough for the long-tiles-first order (more than 256 workgroups) and is
+held against calls that take the plain order (the linear-grid flag, or one head at a time).  Outputs start as NaN, so a tile nobody took shows."""
 import pytest
 import torch
 
@@ -14,7 +14,9 @@ def _normal(*shape, dtype=torch.bfloat16, seed=0):
 
 # (B, H, S): one chunk of heads with a remainder of eight; several chunks, the first short; chunks of one head per XCD
 # (K and V of a head beyond 8 MiB per eight heads); a ragged last tile
-@pytest.mark.parametrize("B,H,S,D", [(1, 53, 640, 64), (5, 21, 600, 64), (3, 11, 8192, 128), (1, 3, 16500, 64), (7, 17, 333, 96)])
+@pytest.mark.parametrize("B,H,S,D", [(1, 53, 640, 64), (5, 21, 600, 64), (3, 11, 8192, 128), (1, 3, 16500, 64), (7, 17, 333, 96),
+                                     # 257, 301 and 512 workgroups: the second one of a CU in reverse order
+                                     (1, 257, 100, 64), (1, 43, 850, 64), (1, 64, 1024, 160)])
 def test_forward_order(B, H, S, D):
     from paper_2603_01960_amd import binding
     q, k, v = (_normal(B, H, S, D, seed=i) for i in range(3))
@@ -58,6 +60,9 @@ def test_backward_order(B, H, Hkv, S, D):
             cut = lambda t, s: t[b:b + 1, s].contiguous()
             ref = binding.sdpa_backward(cut(q, hq), cut(k, slice(h, h + 1)), cut(v, slice(h, h + 1)), cut(o, hq), cut(dout, hq),
                                         cut(lse, hq), True)
-            assert torch.equal(grads[0][b, hq], ref[0][0])
-            assert torch.equal(grads[1][b, h], ref[1][0, 0]) and torch.equal(grads[2][b, h], ref[2][0, 0])
+            # a call on one head sums the same 16-bit products over tiles in another order (streams of tiles): FP32 sums that
+            # differ by about 1e-6 of their largest terms, rounded to neighbouring BF16 values at most (2^-7 of the value)
+            for got, want in ((grads[0][b, hq], ref[0][0]), (grads[1][b, h], ref[1][0, 0]), (grads[2][b, h], ref[2][0, 0])):
+                got, want = got.float(), want.float()
+                assert ((got - want).abs() <= want.abs() / 128 + 1e-4 * want.abs().max()).all()
     assert all(torch.isfinite(t.float()).all() for t in grads)
