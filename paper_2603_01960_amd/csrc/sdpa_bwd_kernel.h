@@ -88,6 +88,12 @@ enum { BWD_DQ = 0, BWD_DK = 1, BWD_DV = 2, BWD_DKV = 3 };
 // - Delta_i) scaled by P_ij, which is of order 1 exactly on such rows (on a row of n comparable keys it is of order 1/n).
 constexpr int kBwdShortRow = 64;
 
+// LDS of one stream of tiles: two slots per tensor and, in the keys-resident passes, of the row statistics.
+template <int D, int TS, int MODE> constexpr int bwd_stream_bytes() { return 4 * BwdGeom<D>::bytes(TS) + (MODE != BWD_DQ ? 2 * 2 * TS * 4 : 0); }
+// k-steps of a second resident operand kept in the LDS that stay in registers all the same: one at D = 160 in the
+// keys-resident pass, where all ten of them and the statistics would be 1 KiB too much for two workgroups per CU.
+template <int D, int MODE> constexpr int bwd_resident_regs() { return D == 160 && MODE != BWD_DQ ? 1 : 0; }
+
 // GRP: grouped heads, G query heads reading one key/value head (query head h the head h / G).  The
 // dQ pass then streams the K and V of its query head's group; the keys-resident passes run one
 // workgroup per (key/value head, key tile) and stream the Q and dO tiles of the G query heads of the
@@ -97,8 +103,8 @@ constexpr int kBwdShortRow = 64;
 // lane; each of its MFMAs then reads two operands from there.
 // The dQ pass runs first: it has the query rows, so it computes their statistics (Delta_i, and LSE_i in log2 units) in
 // its prologue and leaves them in `stats` for the keys-resident passes.
-template <typename T, int D, int NW, int TS, int WPS, int MODE, bool GRP, bool R2LDS>
-__global__ void __launch_bounds__(NW * 64, WPS)
+template <typename T, int D, int NW, int NS, int TS, int WPS, int MODE, bool GRP, bool R2LDS>
+__global__ void __launch_bounds__(NW * NS * 64, WPS)
 sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                 const T *__restrict__ dout, const T *__restrict__ o, const float *__restrict__ lse,
                 float *__restrict__ stats,   // Delta [B*H*S + slack], then LSE in log2 units likewise
@@ -124,20 +130,24 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     static_assert(TS * G::CPR % 64 == 0 && L >= 1 && (2 * U) % NW == 0, "tile pair does not divide over the workgroup");
     constexpr int NB = TS / 32, KK = D / 16, DB = D / 32;
     constexpr int TILE = G::bytes(TS), STATS = 2 * TS * 4;
+    constexpr int STREAM = bwd_stream_bytes<D, TS, MODE>();       // LDS of one stream: two slots per tensor, and of the statistics
+    constexpr int RK = R2LDS ? bwd_resident_regs<D, MODE>() : 0;  // k-steps of the second resident operand that stay in registers
     constexpr int ROW16 = G::bytes(16);           // LDS distance of rows 16 apart (the swizzles repeat every 16 rows)
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const lds_ptr lds = (lds_ptr)smem;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int stream = NS > 1 ? wave_id / NW : 0, wave = NS > 1 ? wave_id % NW : wave_id;
+    const lds_ptr slots = lds + stream * STREAM;
     const int g = lane >> 5, l32 = lane & 31;
 
     const int Gn = GRP ? group : 1;              // query heads per key/value head
     int head, rt;                                 // head of the resident side (a query head in the dQ pass, else a key/value head) and tile
     if (causal && chunk_heads > 0) {
         // query tiles get longer with their index, key tiles shorter: the long ones of all heads first (causal_tile)
-        const CausalTile ct = causal_tile(blockIdx.x, nR, chunk_first, chunk_heads);
+        const CausalTile ct = causal_tile(blockIdx.x, nR, chunk_first, chunk_heads, NS == 1 && D >= 128 ? N : 0);
         head = ct.head;
         rt = KEYS_RES ? ct.level : nR - 1 - ct.level;
     } else {
@@ -155,31 +165,31 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
 
     constexpr int T2BASE = 2 * TILE;              // T1 slot s at s*TILE, T2 slot s at T2BASE + s*TILE
     constexpr int STBASE = 4 * TILE;              // statistics slot s at STBASE + s*STATS (keys-resident passes)
-    constexpr int RBASE = STBASE + (KEYS_RES ? 2 * STATS : 0);      // second resident operand, 32 rows per wavefront
+    constexpr int RBASE = NS * STREAM;            // second resident operand, 32 rows per wavefront of a stream
 
     // ---- resident rows as MFMA B-operands: lane holds R[row l32][kk*16 + g*8 .. +7]; the sign of a
     // negative scale is folded into R1 so that c = |scale| * log2(e) applies to the scores
     const int r0 = rt * RM;
     const int rrow = r0 + wave * 32 + l32;
     const int rrow_c = rrow < S ? rrow : S - 1;
-    vec8 rf1[KK], rf2[R2LDS ? 1 : KK];
+    vec8 rf1[KK], rf2[R2LDS ? (RK > 0 ? RK : 1) : KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
         u32x4 raw = *(const u32x4 *)(r1 + (size_t)rrow_c * D + kk * 16 + g * 8);
         raw ^= rsign;
         rf1[kk] = __builtin_bit_cast(vec8, raw);
-        if constexpr (NEED_DP && !R2LDS) rf2[kk] = *(const vec8 *)(r2 + (size_t)rrow_c * D + kk * 16 + g * 8);
+        if (NEED_DP && (!R2LDS || kk < RK)) rf2[kk] = *(const vec8 *)(r2 + (size_t)rrow_c * D + kk * 16 + g * 8);
     }
     if constexpr (R2LDS) {
-        // this wavefront's 32 rows (rows >= S: zeros), waited for with its first tile
+        // this wavefront's 32 rows (rows >= S: zeros) in the order of the operand: k-step kk is one unit, lane after lane,
+        // so that one pointer and immediates serve all reads.  Waited for with the first tile.
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)r2, (short)0, S * G::GROW, 0x00020000);
         const int row0 = (r0 + wave * 32) * G::GROW;
 #pragma unroll
-        for (int u = 0; u < G::CPR / 2; ++u) {
-            const int p = u * 64 + lane, r = p / G::CPR, cp = p % G::CPR;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + RBASE + wave * G::bytes(32) + u * G::UNIT), 16,
-                                                     r * G::GROW + ((cp ^ G::swz(r)) << 4), row0, 0, 0);
-        }
+        for (int kk = RK; kk < KK; ++kk)
+            if (NS == 1 || kk % NS == stream)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + RBASE + (wave * (KK - RK) + kk - RK) * 1024), 16,
+                                                         l32 * G::GROW + g * 16, row0 + kk * 32, 0, 0);
     }
 
     // ---- range of streamed tiles, and the streamed rows [tlo, thi] that pair with this lane's row
@@ -203,7 +213,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
             const vec8 x = *(const vec8 *)(orow + kk * 16);
-            const vec8 y = R2LDS ? *(const vec8 *)(drow + kk * 16) : rf2[R2LDS ? 0 : kk];
+            const vec8 y = R2LDS && kk >= RK ? *(const vec8 *)(drow + kk * 16) : rf2[R2LDS && kk >= RK ? 0 : kk];
 #pragma unroll
             for (int e = 0; e < 8; ++e) delta_r += (float)x[e] * (float)y[e];
         }
@@ -237,9 +247,9 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     auto load_unit = [&](decltype(t1_rsrc) rsrc, lds_ptr dst, int unit, int voff, int soff) __attribute__((always_inline)) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(dst + unit * G::UNIT), 16, voff, soff, 0, 0);
     };
-    // load instruction i (of L) of tile j into slot `dst`
-    auto load_part = [&](int j, lds_ptr dst, int i) __attribute__((always_inline)) {
-        const int soff = (j < j1 ? j : nT) * TS * G::GROW;    // a tile past the range: outside the descriptor, zeros
+    // load instruction i (of L) of tile j (of the head the descriptors stand at) into slot `dst`
+    auto load_part = [&](int j, bool valid, lds_ptr dst, int i) __attribute__((always_inline)) {
+        const int soff = (valid ? j : nT) * TS * G::GROW;    // no such tile: outside the descriptor, zeros
         const int u = i * NW + wave;
         if constexpr (EVEN) {
             const int it = i % NLD;
@@ -254,17 +264,18 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             load_unit(first ? t1_rsrc : t2_rsrc, first ? dst : dst + T2BASE, first ? u : u - U, goff[i], soff);
         }
     };
-    auto load_tile = [&](int j, lds_ptr dst) __attribute__((always_inline)) {
+    auto load_tile = [&](int j, bool valid, lds_ptr dst) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < L; ++i) load_part(j, dst, i);
+        for (int i = 0; i < L; ++i) load_part(j, valid, dst, i);
     };
-    auto load_stats = [&](int j, int slot) __attribute__((always_inline)) {
+    // statistics of the rows from row0 on, counted over the heads of the group
+    auto load_stats = [&](int row0, int slot) __attribute__((always_inline)) {
         if constexpr (KEYS_RES) {
             if (wave == 0) {
 #pragma unroll
                 for (int it = 0; it < NST; ++it)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(stat_rsrc, (TSDPA_LDS void *)(lds + STBASE + slot * STATS + it * 256), 4,
-                                                             stat_goff[it], j * TS * 4, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(stat_rsrc, (TSDPA_LDS void *)(slots + STBASE + slot * STATS + it * 256), 4,
+                                                             stat_goff[it], row0 * 4, 0, 0);
             }
         }
     };
@@ -280,30 +291,27 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
 
     // ---- per-lane LDS read pointers (tile slot, nb, ks enter as immediate offsets)
     // row-wise: row l32 (+32*nb), chunk 2*kk + g
-    lds_ptr row_ptr[G::NRP], res_ptr[R2LDS ? G::NRP : 1];
+    lds_ptr row_ptr[G::NRP];
 #pragma unroll
     for (int i = 0; i < G::NRP; ++i) {
-        row_ptr[i] = lds + G::at(l32, 2 * G::rp_kk(i) + g);
+        row_ptr[i] = slots + G::at(l32, 2 * G::rp_kk(i) + g);
         TSDPA_OPAQUE(row_ptr[i]);
-        if constexpr (R2LDS) {
-            res_ptr[i] = row_ptr[i] + RBASE + wave * G::bytes(32);
-            TSDPA_OPAQUE(res_ptr[i]);
-        }
     }
+    const lds_ptr res_ptr = lds + RBASE + wave * (KK - RK) * 1024 + lane * 16;
     // transposing: row g*4 + (lane%16)/4 (+ multiples of 8), bytes db*64 + ((lane/16)%2)*32 + (lane%4)*8 of the row
     const int t_row = g * 4 + ((lane & 15) >> 2), t_chunk = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
     lds_ptr tr_lo[G::NTP], tr_hi[D == 128 ? 1 : G::NTP];       // rows t_row (+16k) and t_row + 8 (+16k)
 #pragma unroll
     for (int i = 0; i < G::NTP; ++i) {
-        tr_lo[i] = lds + G::at(t_row, i * 4 + t_chunk) + (lane & 1) * 8;
+        tr_lo[i] = slots + G::at(t_row, i * 4 + t_chunk) + (lane & 1) * 8;
         TSDPA_OPAQUE(tr_lo[i]);
         if constexpr (D != 128) {                 // (at D = 128 eight rows on is two units on, swizzled alike)
-            tr_hi[i] = lds + G::at(t_row + 8, i * 4 + t_chunk) + (lane & 1) * 8;
+            tr_hi[i] = slots + G::at(t_row + 8, i * 4 + t_chunk) + (lane & 1) * 8;
             TSDPA_OPAQUE(tr_hi[i]);
         }
     }
 
-    lds_ptr st_ptr = lds + STBASE + g * 16;       // statistics of rows g*4 ... g*4 + 3 (+8k) of the current tile
+    lds_ptr st_ptr = slots + STBASE + g * 16;       // statistics of rows g*4 ... g*4 + 3 (+8k) of the current tile
 
     // acc[i] = <T_row, R_col>, row = nb*32 + (i/4)*8 + g*4 + i%4 of the tile, col = this lane's row
     auto products = [&](int slot, int nb, bool second, f32x16 &acc, auto &&after_mfma) __attribute__((always_inline)) {
@@ -314,8 +322,8 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             const u32x4 raw = lds_read128(row_ptr[G::rp(kk)] + slot + nb * 2 * ROW16 + G::rp_imm(kk));
             vec8 b;
             if (!second) b = rf1[kk];
-            else if constexpr (R2LDS) b = __builtin_bit_cast(vec8, lds_read128(res_ptr[G::rp(kk)] + G::rp_imm(kk)));
-            else b = rf2[kk];
+            else if (R2LDS && kk >= RK) b = __builtin_bit_cast(vec8, lds_read128(res_ptr + (kk - RK) * 1024));
+            else b = rf2[R2LDS && kk >= RK ? 0 : kk];
             acc = E::mfma(__builtin_bit_cast(vec8, raw), b, acc);
             after_mfma(kk);
         }
@@ -388,16 +396,16 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         if constexpr (KEYS_RES) st_ptr += shift > 0 ? STATS : -STATS;
         shift = -shift;
     };
-    auto tile = [&](int j, bool mask) __attribute__((always_inline)) {
-        load_stats(j + 1, shift > 0 ? 1 : 0);
+    auto tile = [&](int j, bool mask, int next_j, int next_row, bool next_valid) __attribute__((always_inline)) {
+        load_stats(next_row, shift > 0 ? 1 : 0);
         // The loads go out one at a time behind the MFMAs of the first products: back to back they hold the wavefront at
         // the issue stage while the CU's address unit works through them (S = 1024 of nine heads: 69 -> 65.5 us at D =
         // 128, 61 -> 55 at D = 96; 1-2 % where the CUs are full; level at D = 64)
-        const lds_ptr nxt = lds + (shift > 0 ? TILE : 0);
+        const lds_ptr nxt = slots + (shift > 0 ? TILE : 0);
         constexpr int HOOKS = NB * (NEED_DP ? 2 : 1) * KK;
         auto spread = [&](int h) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = h * L / HOOKS; i < (h + 1) * L / HOOKS; ++i) load_part(j + 1, nxt, i);
+            for (int i = h * L / HOOKS; i < (h + 1) * L / HOOKS; ++i) load_part(next_j, next_valid, nxt, i);
             __builtin_amdgcn_sched_barrier(0x786);              // MFMAs and loads keep this order
         };
         const int trow0 = j * TS + g * 4;
@@ -416,9 +424,6 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         accumulate(MODE == BWD_DV ? T2BASE : 0, xb, oacc);
         if constexpr (FUSED) accumulate(T2BASE, pb, oacc2);       // dV^T += dO^T P
         if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
-        TSDPA_WAIT_VMCNT0();
-        __syncthreads();
-        other_slot();
     };
     // a tile needs the mask if it reaches past row S-1 or (causal) crosses the diagonal of any of this workgroup's rows
     auto needs_mask = [&](int j) __attribute__((always_inline)) -> bool {
@@ -432,7 +437,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         if (r0 < kBwdShortRow && (causal || S <= kBwdShortRow)) {
             float sum = 0.f;
             for (int j = 0; j * TS < kBwdShortRow && j < j1; ++j) {
-                load_tile(j, lds);
+                load_tile(j, true, slots);
                 TSDPA_WAIT_VMCNT0();
                 __syncthreads();
 #pragma unroll
@@ -451,29 +456,107 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             sum = pair_sum(sum);
             if (rrow < kBwdShortRow) delta_r = sum;
         }
-        if (g == 0 && rrow < S) {
+        if (stream == 0 && g == 0 && rrow < S) {
             stats[(size_t)head * S + rrow] = delta_r;
             *(float *)((char *)stats + stat_bytes + ((size_t)head * S + rrow) * 4) = lse_r;
         }
     }
-    for (int gq = 0; gq < (KEYS_RES ? Gn : 1); ++gq) {
-        if (GRP && KEYS_RES && gq > 0) {
+    constexpr bool HEADS = GRP && KEYS_RES;
+    auto to_head = [&](int h) __attribute__((always_inline)) {     // descriptors of head h of the group
+        t1_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(t1 + (size_t)h * S * D), (short)0, S * G::GROW, 0x00020000);
+        t2_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(t2 + (size_t)h * S * D), (short)0, S * G::GROW, 0x00020000);
+    };
+    if constexpr (NS == 1) {
+        for (int h = 0; h < (HEADS ? Gn : 1); ++h) {
             // next query head of the group: its Q, dO and statistics (the last barrier of the previous head's
             // loop has every wavefront past its last LDS read and every outstanding load landed)
-            t1 += (size_t)S * D;
-            t2 += (size_t)S * D;
-            t1_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)t1, (short)0, S * G::GROW, 0x00020000);
-            t2_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)t2, (short)0, S * G::GROW, 0x00020000);
-#pragma unroll
-            for (int it = 0; it < NST; ++it) stat_goff[it] += S * 4;
+            if (HEADS && h > 0) to_head(h);
+            // (into the slot that the pointers stand at)
+            load_stats(h * S + j0 * TS, shift > 0 ? 0 : 1);
+            load_tile(j0, true, slots + (shift > 0 ? 0 : TILE));
+            TSDPA_WAIT_VMCNT0();
+            __syncthreads();
+            for (int j = j0; j < j1; ++j) {
+                tile(j, needs_mask(j), j + 1, h * S + (j + 1) * TS, j + 1 < j1);
+                TSDPA_WAIT_VMCNT0();
+                __syncthreads();
+                other_slot();
+            }
         }
-        if (j0 >= j1) break;
-        // (into the slot that the pointers stand at)
-        load_stats(j0, shift > 0 ? 0 : 1);
-        load_tile(j0, lds + (shift > 0 ? 0 : TILE));
+    } else {
+        // The tiles of this stream: every NS-th of the sequence (head of the group, tile), the next one's loads always a
+        // step ahead, also across heads.
+        const int nj = j1 - j0;
+        int jn = j0 + stream, hn = 0;             // tile whose loads go out next, and its head within the group
+        auto settle = [&]() __attribute__((always_inline)) {
+            if constexpr (HEADS) {
+                bool moved = false;
+                while (jn >= j1 && hn < Gn) {
+                    jn -= nj;
+                    ++hn;
+                    moved = true;
+                }
+                if (moved && hn < Gn) to_head(hn);
+            }
+        };
+        auto valid = [&]() __attribute__((always_inline)) -> bool { return HEADS ? hn < Gn : jn < j1; };
+        settle();
+        load_stats(hn * S + jn * TS, 0);
+        load_tile(jn, valid(), slots);
+        int j = jn;
+        bool here = valid();
+        jn += NS;
+        settle();
         TSDPA_WAIT_VMCNT0();
         __syncthreads();
-        for (int j = j0; j < j1; ++j) tile(j, needs_mask(j));
+        const int steps = ((HEADS ? Gn * nj : nj) + NS - 1) / NS;
+        for (int step = 0; step < steps; ++step) {
+            if (here) tile(j, needs_mask(j), jn, hn * S + jn * TS, valid());
+            TSDPA_WAIT_VMCNT0();
+            if constexpr (NW > 1) __syncthreads();    // (a wavefront that streams alone waits for nobody)
+            other_slot();
+            j = jn;
+            here = valid();
+            jn += NS;
+            settle();
+        }
+    }
+
+    // ---- the streams' sums, added in the order of the streams by the wavefronts of the first one
+    if constexpr (NS > 1) {
+        auto gather = [&](f32x16 (&acc)[DB]) __attribute__((always_inline)) {
+            __syncthreads();                      // (the region's last readers are through)
+            const lds_ptr at = lds + wave * (32 * D * 4) + lane * 16;
+            constexpr int DIST = NW * 32 * D * 4;
+            if (stream > 0) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        f32x4 part;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) part[e] = acc[db][q4 * 4 + e];
+                        *(TSDPA_LDS f32x4 *)(at + (stream - 1) * DIST + (db * 4 + q4) * 1024) = part;
+                    }
+            }
+            __syncthreads();
+            if (stream == 0) {
+#pragma unroll
+                for (int s = 0; s < NS - 1; ++s)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db)
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4) {
+                            const f32x4 part = *(TSDPA_LDS f32x4 *)(at + s * DIST + (db * 4 + q4) * 1024);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[db][q4 * 4 + e] += part[e];
+                        }
+            }
+        };
+        gather(oacc);
+        if constexpr (FUSED) gather(oacc2);
+        __syncthreads();
+        if (stream != 0) return;
     }
 
     // ---- store: out^T tiles are turned through LDS (as the forward kernel's O) and written as whole
@@ -507,14 +590,15 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
 #endif
 }
 
-// LDS of one instantiation: slots and statistics during the loop (and the resident operand kept there), one 32 x D block
-// per wavefront for the output transpose after it.
-template <int D, int NW, int TS, int MODE, bool R2LDS> constexpr int bwd_lds_bytes()
+// LDS of one instantiation: slots and statistics of every stream during the loop (and the resident operand kept there), then
+// the sums of the streams, then one 32 x D block per wavefront of a stream for the output transpose.
+template <int D, int NW, int NS, int TS, int MODE, bool R2LDS> constexpr int bwd_lds_bytes()
 {
-    using G = BwdGeom<D>;
-    const int loop = 4 * G::bytes(TS) + (MODE != BWD_DQ ? 2 * 2 * TS * 4 : 0) + (R2LDS ? NW * G::bytes(32) : 0);
-    const int stage = NW * 32 * G::OROW;
-    return loop > stage ? loop : stage;
+    const int loop = NS * bwd_stream_bytes<D, TS, MODE>() + (R2LDS ? NW * (D / 16 - bwd_resident_regs<D, MODE>()) * 1024 : 0);
+    const int sums = (NS - 1) * NW * 32 * D * 4;
+    const int stage = NW * 32 * BwdGeom<D>::OROW;
+    const int most = loop > sums ? loop : sums;
+    return most > stage ? most : stage;
 }
 
 }  // namespace tsdpa
