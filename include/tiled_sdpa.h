@@ -95,15 +95,16 @@ int tiled_sdpa_fwd(const void *q, const void *k, const void *v, void *o, float *
  * {32,64,128} (128 not at D = 160), or (tile_m, tile_n) = (256, 64), which is not in the paper's grid: eight
  * wavefronts share every K/V tile, the fastest schedule on this GPU for long sequences at D >= 96 without the
  * causal mask.
- * tile_m = tile_n = 0 selects the built-in shape heuristic, which is what tiled_sdpa_fwd uses.  The
+ * tile_m = tile_n = 0 selects the built-in shape heuristic, which is what tiled_sdpa_fwd uses; where workgroups would be
+ * few it also splits the key tiles over several streams inside a workgroup, which explicit tiles never do.  The
  * result does not depend on the tile choice beyond rounding order.
  */
 int tiled_sdpa_fwd_ex(const void *q, const void *k, const void *v, void *o, float *lse,
                       int B, int H, int S, int D, float scale, int dtype, void *stream,
                       int tile_m, int tile_n, unsigned flags);
 
-/* The (tile_m, tile_n) the heuristic picks for a shape and flags (only TSDPA_FLAG_CAUSAL matters);
- * returns a status code. */
+/* The (tile_m, tile_n) the heuristic picks for a shape and flags (only TSDPA_FLAG_CAUSAL matters), that of the form
+ * without streams; returns a status code. */
 int tiled_sdpa_default_tile(int B, int H, int S, int D, int dtype, unsigned flags, int *tile_m, int *tile_n);
 
 /*

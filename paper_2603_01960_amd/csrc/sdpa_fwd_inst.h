@@ -21,14 +21,17 @@ constexpr int kLdsPerCU = 160 * 1024;
 // halves and move them back and forth (or to scratch) inside the loop.
 template <int D, int NW, int TN> constexpr int waves_per_simd() { return (TN == 32 && D <= 128) ? 3 : 2; }
 
-template <typename T, int D, int NW, int TN, int KV = 0>     // 0 square, 1 dense cache, 2 paged cache
+template <typename T, int D, int NW, int TN, int KV = 0, int NS = 1>     // KV: 0 square, 1 dense cache, 2 paged cache; NS streams
 int launch_one(const LaunchArgs &a)
 {
-    constexpr int WPS = waves_per_simd<D, NW, TN>();
-    auto kern = sdpa_fwd_kernel<T, D, NW, TN, WPS, KV>;
-    // K/V tile slots during the loop, one 32 x D block per wavefront for the output transpose after it
-    constexpr int stage_bytes = NW * 32 * TileGeom<D, TN>::OROW;
-    constexpr int lds_bytes = TileGeom<D, TN>::LDS_BYTES > stage_bytes ? TileGeom<D, TN>::LDS_BYTES : stage_bytes;
+    constexpr int WPS = NS > 1 ? 2 : waves_per_simd<D, NW, TN>();
+    auto kern = sdpa_fwd_kernel<T, D, NW, stream_tile(TN, NS), WPS, KV>;
+    // K/V tile slots during the loop; then the states of all streams but the first, and one 32 x D block per wavefront for the
+    // output transpose
+    constexpr int stage_bytes = NW * 32 * TileGeom<D, TN>::OROW, state_bytes = (NS - 1) * NW * (32 * D * 4 + 512);
+    constexpr int after_bytes = stage_bytes > state_bytes ? stage_bytes : state_bytes;
+    constexpr int lds_bytes = NS * TileGeom<D, TN>::LDS_BYTES > after_bytes ? NS * TileGeom<D, TN>::LDS_BYTES : after_bytes;
+    static_assert(lds_bytes <= kLdsPerCU, "LDS of a CU");
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -41,7 +44,7 @@ int launch_one(const LaunchArgs &a)
     const int N = heads * nQ;
     // (entries of different lengths: eight heads per XCD and chunk whatever they stream, for the balance between them)
     const CausalChunks chunks = causal_chunks(heads, nQ, a.kv_lens ? 0 : (long long)(KV ? a.Skv : a.S) * D * 2 * (long long)sizeof(T));
-    hipLaunchKernelGGL(kern, dim3(N), dim3(NW * 64), lds_bytes, a.stream,
+    hipLaunchKernelGGL(kern, dim3(N), dim3(NW * NS * 64), lds_bytes, a.stream,
                        (const T *)a.q, (const T *)a.k, (const T *)a.v, (T *)a.o, a.lse,
                        a.S, nQ, N, a.c, a.tau, a.qsign, a.linear_grid, a.causal,
                        a.Skv, a.splits, a.ws, a.rows_per_head, a.kv_lens, a.heads_per_batch,
@@ -68,6 +71,8 @@ int launch_dispatch_tn64(int tile_m, const LaunchArgs &a)
     return tile_m == 64 ? launch_one<T, D, 2, 64>(a) : launch_one<T, D, 4, 64>(a);
 }
 
+// Streams (a.streams > 1, the square problem): tile_m / 32 wavefronts each, 32-row K/V tiles; the forms that pick_streams
+// (tiled_sdpa.hip) chooses from.
 using LaunchTn64 = int (*)(int tile_m, const LaunchArgs &a);
 
 template <typename T, int D>
@@ -75,6 +80,23 @@ int launch_dispatch(int tile_m, int tile_n, const LaunchArgs &a, LaunchTn64 tn64
 {
     if (tile_n == 64) return tn64(tile_m, a);
     const int key = tile_m * 1000 + tile_n;
+    if (a.streams > 1) {
+        switch (tile_m * 10 + a.streams) {
+            case 324: return launch_one<T, D, 1, 32, 0, 4>(a);
+            case 642: return launch_one<T, D, 2, 32, 0, 2>(a);
+            case 1282: return launch_one<T, D, 4, 32, 0, 2>(a);
+            case 643:
+                if constexpr (D == 160) return launch_one<T, D, 2, 32, 0, 3>(a);
+                break;
+            case 644:
+                if constexpr (D < 160) return launch_one<T, D, 2, 32, 0, 4>(a);
+                break;
+            case 328:
+                if constexpr (D == 64) return launch_one<T, D, 1, 32, 0, 8>(a);
+                break;
+        }
+        return (int)hipErrorInvalidValue;
+    }
     if (a.kv && a.block_table != nullptr) {
         switch (key) {
             case 64032: return launch_one<T, D, 2, 32, 2>(a);

@@ -183,8 +183,13 @@ __device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int
 // KVM: 0 = the paper's square problem, 1 = the general kernel over a dense cache, 2 = over a paged cache
 // (an instantiation of its own: the per-tile descriptors cost scalar registers in the loop, which the
 // latency-bound small decoding shapes of the dense path would pay for too).
-template <typename T, int D, int NW, int TN, int WPS, int KVM>
-__global__ void __launch_bounds__(NW * 64, WPS)  // WPS = wavefronts per SIMD the register budget is sized for
+// TILE: rows T_N of a K/V tile, plus 1000 * (NS - 1).  NS > 1 (square problem only): NS streams of NW wavefronts each work on
+// the same query rows; stream s takes the tiles s, s + NS, ... into LDS slots of its own, and the streams' states (o, m,
+// l of Eqs. 2-4) are combined through the LDS at the end, in their order.  For launches of few workgroups: the chain of tiles
+// that a wavefront waits through is NS times shorter, and with NW = 1 nothing waits at a barrier.
+constexpr int stream_tile(int tn, int ns) { return tn + 1000 * (ns - 1); }
+template <typename T, int D, int NW, int TILE, int WPS, int KVM>
+__global__ void __launch_bounds__(NW * (1 + TILE / 1000) * 64, WPS)  // WPS = wavefronts per SIMD the register budget is sized for
 sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                 T *__restrict__ o, float *__restrict__ lse, int S, int nQ, int N, float c,
                 float tau, uint32_t qsign, int linear_grid, int causal,
@@ -195,6 +200,8 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses device-only types
     constexpr bool KV = KVM != 0, PAGED = KVM == 2;
+    constexpr int TN = TILE % 1000, NS = 1 + TILE / 1000;
+    static_assert(NS == 1 || !KV, "streams are a form of the square problem");
     using E = Elem<T>;
     using vec8 = typename E::vec8;
     using vec4 = typename E::vec4;
@@ -217,10 +224,10 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     constexpr int NB = TNS / 32, KK = D / 16, DB = D / 32;
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const lds_ptr lds = (lds_ptr)smem;
-
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int stream = NS > 1 ? wave_id / NW : 0, wave = NS > 1 ? wave_id % NW : wave_id;
+    const lds_ptr lds = (lds_ptr)smem + stream * G::LDS_BYTES;     // slots of this stream
     const int g = lane >> 5, l32 = lane & 31;
 
     const int splits = KV ? splits_arg : 1;
@@ -592,8 +599,10 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     // tiles below nfull need no mask: they run in pairs through the unmasked step; the few tiles
     // left (the diagonal band under the causal mask, the ragged tail, an odd one out) take the
     // masked path, which is also correct for a tile that turns out to need no mask
-    const int fast_n = (t1 < nfull ? t1 : nfull) - t0;
-    const int fast_end = t0 + (fast_n > 0 ? fast_n & ~1 : 0);
+    // (in a stream the same with its own tiles: counted from its first, in steps of NS)
+    const int s0 = t0 + stream;
+    const int fast_n = NS > 1 ? ((t1 < nfull ? t1 : nfull) - s0 + NS - 1) / NS : (t1 < nfull ? t1 : nfull) - t0;
+    const int fast_end = s0 + (fast_n > 0 ? (fast_n & ~1) * NS : 0);
     // Dense cache with one query tile per head (decoding): every workgroup streams another head, and
     // heads lie a power of two apart, so workgroups that all start at their tile 0 and advance in step
     // keep hitting the same memory channels.  The order of the unmasked tiles is free (Eqs. 2-4 do not
@@ -608,7 +617,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         const int blk0 = (t0 * TN) >> block_shift;
         page_next = __builtin_amdgcn_readfirstlane(pages[blk0 < max_blocks ? blk0 : 0]);
     }
-    if constexpr (KVM == 0) {
+    if constexpr (KVM == 0 && NS == 1) {
         // A wavefront whose 32 rows all lie past the end of the sequence (the last query tile of a ragged S)
         // has nothing to compute or store: it only takes its share of the tile loads and keeps the
         // workgroup's barriers, leaving its SIMD's matrix and vector slots to the wavefronts that have rows.
@@ -627,9 +636,9 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             return;
         }
     }
-    load_tiles(t0 + rot, lds + KSLOT0, lds + VSLOT0);
+    load_tiles(s0 + rot, lds + KSLOT0, lds + VSLOT0);
     TSDPA_WAIT_VMCNT0();
-    __syncthreads();
+    if constexpr (NW > 1) __syncthreads();        // (a wavefront that streams alone waits for nobody)
 
     // tile j, followed by tile jn: PAR (alternating) selects the slots, MASK the masked code path
     auto step = [&](int j, int jn, auto par_tag, auto mask_tag) __attribute__((always_inline)) {
@@ -677,9 +686,9 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             __builtin_amdgcn_s_setprio(0);
         }
         TSDPA_WAIT_VMCNT0();
-        __syncthreads();
+        if constexpr (NW > 1) __syncthreads();
     };
-    int j = t0;
+    int j = s0;
     if constexpr (KVM == 1) {
         // unmasked tiles in rotated order: t0+rot ... fast_end-1, t0 ... t0+rot-1, then on to fast_end
         int cur = t0 + rot;
@@ -694,15 +703,20 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             cur = n2;
         }
     } else {
-        for (; j < fast_end; j += 2) {
-            step(j, j + 1, P0{}, std::false_type{});
-            step(j + 1, j + 2, P1{}, std::false_type{});
+        for (; j < fast_end; j += 2 * NS) {
+            step(j, j + NS, P0{}, std::false_type{});
+            step(j + NS, j + 2 * NS, P1{}, std::false_type{});
         }
     }
-    for (; j < t1; ++j) {
-        if ((j - t0) & 1) step(j, j + 1, P1{}, std::true_type{});
-        else              step(j, j + 1, P0{}, std::true_type{});
+    bool odd = false;                             // (the unmasked tiles were an even number)
+    for (; j < t1; j += NS) {
+        if (odd) step(j, j + NS, P1{}, std::true_type{});
+        else     step(j, j + NS, P0{}, std::true_type{});
+        odd = !odd;
     }
+    // (a stream has the others' number of tiles or one less)
+    if constexpr (NS > 1 && NW > 1)
+        if ((t1 - s0 + NS - 1) / NS < (t1 - t0 + NS - 1) / NS) __syncthreads();
     }
 
     // ---- O_i = o_i / l_i (Section 4.1.2), rounded once to the 16-bit output type.  The accumulators
@@ -710,7 +724,65 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     // through LDS: each wavefront writes its 32 x D block into its own LDS region (16-byte chunks
     // XOR-swizzled by row against bank conflicts) and reads it back as whole rows, so that every global
     // store instruction writes complete, contiguous rows (16 B per lane) instead of 8-byte pieces.
-    const float l_tot = pair_sum(l_run);
+    float l_tot = pair_sum(l_run);
+    if constexpr (NS > 1) {
+        // ---- one state from the streams': o, m, l of all but the first go through the LDS, lane by lane
+        constexpr int STATE = 32 * D * 4 + 512;   // bytes per wavefront: [o chunk][lane] x 16, then [lane] x (m, l)
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        __syncthreads();
+        const lds_ptr at = (lds_ptr)smem + wave * STATE + lane * 16;
+        if (stream > 0) {
+            const lds_ptr mine = at + (stream - 1) * (NW * STATE);
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    f32x4 part;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) part[e] = oacc[db][q4 * 4 + e];
+                    *(TSDPA_LDS f32x4 *)(mine + (db * 4 + q4) * 1024) = part;
+                }
+            *(TSDPA_LDS f32x2 *)(mine - lane * 8 + 32 * D * 4) = f32x2{m_ref, l_tot};
+        }
+        __syncthreads();
+        if (stream == 0) {
+            f32x2 ml[NS];
+            ml[0] = f32x2{m_ref, l_tot};
+            float M = m_ref;
+#pragma unroll
+            for (int s = 1; s < NS; ++s) {
+                ml[s] = *(TSDPA_LDS f32x2 *)(at + (s - 1) * (NW * STATE) - lane * 8 + 32 * D * 4);
+                M = fmaxf(M, ml[s][0]);
+            }
+            // weight 0 for a stream that saw no key of the row (m = -inf); stream 0 always sees key 0
+            float w[NS];
+            l_tot = 0.f;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                w[s] = ml[s][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[s][0] - M);
+                l_tot += w[s] * ml[s][1];
+            }
+            m_ref = M;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    f32x4 sum;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] = w[0] * oacc[db][q4 * 4 + e];
+#pragma unroll
+                    for (int s = 1; s < NS; ++s) {
+                        const f32x4 part = *(TSDPA_LDS f32x4 *)(at + (s - 1) * (NW * STATE) + (db * 4 + q4) * 1024);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[e] += w[s] * part[e];
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) oacc[db][q4 * 4 + e] = sum[e];
+                }
+        }
+        __syncthreads();                          // (the output transpose below reuses the region)
+        if (stream != 0) return;
+    }
     if (KV && splits > 1) {
         // partial state of this split: the accumulators as they are (a lane owns query row qrow and
         // groups of 4 consecutive columns), then the reference m and the normaliser l

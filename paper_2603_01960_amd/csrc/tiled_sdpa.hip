@@ -98,6 +98,42 @@ void pick_tile(int BH, int S, int D, bool causal, int *tm, int *tn)
     }
 }
 
+// Streams of K/V tiles per workgroup of the square problem, and the query rows that go with them (1: the plain form on
+// pick_tile's tile).  Up to one workgroup of 128 rows per CU a SIMD has one wavefront or none, which waits through the
+// whole chain of tiles alone; streams cut the chain, fewer rows make more workgroups.  From timings of every form on 680
+// shapes (4 ... 512 such workgroups, S = 64 ... 8192, BF16; mean gain of this choice over them 16-38 % by head dim and
+// mask, within 0.2-2 % of the best form; us, plain -> chosen): 32 workgroups, S = 512 8.1 -> 5.8 (D = 64), 10.1 -> 7.2 (D = 96
+// causal); 64 workgroups, S = 1024 12.8 -> 7.5, S = 8192 78.7 -> 26.7 (D = 64), 94.4 -> 36.2 (D = 96 causal); 128
+// workgroups, S = 4096 41.5 -> 24.5 (D = 64), 59.6 -> 35.0 (D = 128 causal); 160 workgroups, S = 4096 causal 41.8 -> 23.3
+// (D = 64); 256 workgroups, S = 2048 causal 28.2 -> 21.4 (D = 96); without the mask, where nothing is uneven, 3-8 % there.
+int pick_streams(long long BH, int S, int D, bool causal, int *tm)
+{
+    const long long n = BH * ((S + 127) / 128);      // workgroups of the plain form
+    const int chain = (S + 31) / 32;
+    auto form = [&](int rows, int streams) { *tm = rows; return streams; };
+    // (the plain 64 x 32 tile spills in its masked step at D = 128: one key tile per stream, 12.2 -> 8.5 with 512 heads)
+    if (chain == 2 && causal && D == 128 && n <= 512) return form(64, 2);
+    if (chain <= 2 || n > 400) return 1;
+    if (n <= 64) {
+        if (!causal && chain <= 4) return 1;
+        return D == 64 && chain >= 64 ? form(32, 8) : form(32, 4);
+    }
+    if (n <= 128) {
+        if (causal && D == 64 && chain >= 16) return form(32, 4);
+        if (causal && D == 160 && chain >= 64) return form(32, 4);
+        if (chain <= 4) return causal && D != 128 ? form(64, 2) : 1;
+        return chain >= 32 ? form(64, D == 160 ? 3 : 4) : form(64, 2);
+    }
+    if (n <= 256) {
+        if (!causal) return chain < 32 ? 1 : D == 64 ? form(64, 2) : form(128, 2);
+        if (chain >= 64 && n <= 192) return D == 64 ? form(32, 4) : form(64, D == 160 ? 3 : 4);
+        if (chain >= 64 && D == 64) return form(64, 4);
+        return chain >= 8 ? form(64, 2) : 1;
+    }
+    if (!causal || chain < (n <= 320 ? 32 : 64)) return 1;
+    return D == 64 && chain >= 128 ? form(64, 4) : form(64, 2);
+}
+
 int validate_shape(int B, int H, int S, int D, int dtype)
 {
     if (dtype != TSDPA_F16 && dtype != TSDPA_BF16) return TSDPA_ERR_BAD_DTYPE;
@@ -305,14 +341,18 @@ int tiled_sdpa_fwd_ex(const void *q, const void *k, const void *v, void *o, floa
     if (!q || !k || !v || !o) return TSDPA_ERR_NULL_PTR;
     const uintptr_t bits = (uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o;
     if ((bits & 15u) != 0 || ((uintptr_t)lse & 3u) != 0) return TSDPA_ERR_MISALIGNED;
-    if (tile_m == 0 && tile_n == 0)
-        pick_tile(B * H, S, D, (flags & TSDPA_FLAG_CAUSAL) != 0, &tile_m, &tile_n);
-    else if (!valid_tile(tile_m, tile_n, D))
+    int streams = 1;
+    if (tile_m == 0 && tile_n == 0) {
+        streams = pick_streams((long long)B * H, S, D, (flags & TSDPA_FLAG_CAUSAL) != 0, &tile_m);
+        if (streams > 1) tile_n = 32;
+        else pick_tile(B * H, S, D, (flags & TSDPA_FLAG_CAUSAL) != 0, &tile_m, &tile_n);
+    } else if (!valid_tile(tile_m, tile_n, D))
         return TSDPA_ERR_BAD_TILE;
     if (std::isnan(scale)) scale = 1.0f / std::sqrt((float)D);
     if (std::isinf(scale)) return TSDPA_ERR_BAD_SCALE;
 
     tsdpa::LaunchArgs a{};
+    a.streams = streams;
     a.q = q;
     a.k = k;
     a.v = v;
