@@ -11,7 +11,7 @@
 // Passes over the S x S score plane, all instances of ONE kernel template, so that no sum crosses workgroups (no
 // atomics, deterministic results):
 //   * BWD_DQ: a workgroup owns 32*NW query rows (Q and dO rows resident), streams K and V tiles; it also computes the
-//     statistics of its rows (Delta, LSE in log2 units) for the passes after it;
+//     statistics of its rows (-Delta, LSE in log2 units) for the passes after it;
 //   * BWD_DKV: a workgroup owns 32*NW key rows (K and V rows resident), streams Q and dO tiles; two accumulators;
 //   * BWD_DK, BWD_DV: its two halves as passes of their own (D = 160, where two accumulators do not fit).
 // With R the resident and T the streamed rows, a pass computes, per streamed tile,
@@ -107,7 +107,7 @@ template <typename T, int D, int NW, int NS, int TS, int WPS, int MODE, bool GRP
 __global__ void __launch_bounds__(NW * NS * 64, WPS)
 sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                 const T *__restrict__ dout, const T *__restrict__ o, const float *__restrict__ lse,
-                float *__restrict__ stats,   // Delta [B*H*S + slack], then LSE in log2 units likewise
+                float *__restrict__ stats,   // -Delta [B*H*S + slack], then LSE in log2 units likewise
                 T *__restrict__ out,   // dQ, dK or dV
                 T *__restrict__ out2,  // dV of the fused dK + dV pass, else unused
                 int S, int nR, int N, float c, float scale, uint32_t rsign, int causal, unsigned stat_bytes,
@@ -313,10 +313,29 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
 
     lds_ptr st_ptr = slots + STBASE + g * 16;       // statistics of rows g*4 ... g*4 + 3 (+8k) of the current tile
 
-    // acc[i] = <T_row, R_col>, row = nb*32 + (i/4)*8 + g*4 + i%4 of the tile, col = this lane's row
-    auto products = [&](int slot, int nb, bool second, f32x16 &acc, auto &&after_mfma) __attribute__((always_inline)) {
+    // -Delta of the lane's row as an accumulator to start from (not at D = 96, whose dQ pass has no 16 registers left)
+    constexpr bool DELTA16 = MODE == BWD_DQ && D != 96;
+    f32x16 minus_delta;
+    if constexpr (DELTA16) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+        for (int i = 0; i < 16; ++i) minus_delta[i] = 0.f;
+    }
+    // acc[i] = <T_row, R_col>, row = nb*32 + (i/4)*8 + g*4 + i%4 of the tile, col = this lane's row.  The second product
+    // starts from -Delta of the query row where that costs nothing: one vector instruction per element less in the weights.
+    auto products = [&](int slot, int nb, bool second, f32x16 &acc, auto &&after_mfma) __attribute__((always_inline)) {
+        if (second && KEYS_RES) {
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const f32x4 md = *(TSDPA_LDS f32x4 *)(st_ptr + (TS + nb * 32 + r4 * 8) * 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[r4 * 4 + e] = md[e];
+            }
+        } else if (second && DELTA16) {
+            acc = minus_delta;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+        }
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
             const u32x4 raw = lds_read128(row_ptr[G::rp(kk)] + slot + nb * 2 * ROW16 + G::rp_imm(kk));
@@ -355,11 +374,8 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         constexpr bool MASK = decltype(mask_tag)::value;
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-            f32x4 st_lse, st_delta;
-            if constexpr (KEYS_RES) {
-                st_lse = *(TSDPA_LDS f32x4 *)(st_ptr + (nb * 32 + r4 * 8) * 4);
-                if constexpr (NEED_DP) st_delta = *(TSDPA_LDS f32x4 *)(st_ptr + (TS + nb * 32 + r4 * 8) * 4);
-            }
+            f32x4 st_lse;
+            if constexpr (KEYS_RES) st_lse = *(TSDPA_LDS f32x4 *)(st_ptr + (nb * 32 + r4 * 8) * 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int i = r4 * 4 + e;
@@ -369,10 +385,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], c, -l2));        // P
                 if constexpr (FUSED) pb[nb][i >> 3][i & 7] = (T)(masked ? 0.f : p);
                 float x = p;
-                if constexpr (NEED_DP) {
-                    const float dl = KEYS_RES ? st_delta[e] : delta_r;
-                    x *= dpacc[i] - dl;                                                   // dS
-                }
+                if constexpr (NEED_DP) x *= KEYS_RES || DELTA16 ? dpacc[i] : dpacc[i] - delta_r;      // dS
                 xb[nb][i >> 3][i & 7] = (T)(masked ? 0.f : x);
             }
             if constexpr (MODE == BWD_DK || FUSED) __builtin_amdgcn_sched_barrier(0);
@@ -456,8 +469,13 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             sum = pair_sum(sum);
             if (rrow < kBwdShortRow) delta_r = sum;
         }
+        if constexpr (DELTA16) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) minus_delta[i] = -delta_r;
+            TSDPA_OPAQUE(minus_delta);            // (left transparent, it is built again for every block)
+        }
         if (stream == 0 && g == 0 && rrow < S) {
-            stats[(size_t)head * S + rrow] = delta_r;
+            stats[(size_t)head * S + rrow] = -delta_r;
             *(float *)((char *)stats + stat_bytes + ((size_t)head * S + rrow) * 4) = lse_r;
         }
     }
