@@ -3,6 +3,7 @@
 #include <mutex>
 
 #include "sdpa_bwd_kernel.h"
+#include "sdpa_bwd_short_kernel.h"
 #include "sdpa_fwd_launch.h"
 
 namespace tsdpa {
@@ -128,6 +129,20 @@ int launch_bwd_pass(const BwdLaunchArgs &a)
     return launch_bwd_pass_nw<T, D, MODE, GRP, Sh::NW, 1, Sh::TS[MODE], Sh::WPS[MODE]>(a);
 }
 
+// Short sequences of one query head per key/value head in one launch (sdpa_bwd_short_kernel.h), D = 64 and 96 (two accumulators
+// beside both resident operands do not fit above).  us per call, passes -> one launch: D = 64, S = 32 10.7 -> 6.5 (60 heads),
+// 19.4 -> 9.5 (768); S = 64 21.2 -> 14.9 (768); S = 128 11.3 -> 9.5 (60), 32.3 -> 25.2 (768); S = 197 25.5 -> 18.7 (200),
+// 67.6 -> 56.6 (768) but 14.8 -> 16.7 (60), where the passes spread a head over more CUs; D = 96, S = 64 12.3 -> 10.1 (60), 27.1 ->
+// 19.6 (768); S = 128 43.8 -> 34.9 (768); S = 256 31.4 -> 28.2 (200), 115 -> 101 (768) but 46.7 -> 52.1 (300): a second
+// round of one workgroup per CU that is mostly empty.
+inline bool bwd_in_one_launch(int D, int heads, int S)
+{
+    if (S <= (D == 64 ? 128 : 64)) return true;
+    if (heads < 110) return false;
+    if (D == 64 || S <= 128) return true;
+    return heads % 256 == 0 || heads * 10 >= (heads + 255) / 256 * 256 * 7;
+}
+
 template <typename T, int D, bool GRP>
 int launch_bwd_passes(const BwdLaunchArgs &a)
 {
@@ -146,6 +161,10 @@ int launch_bwd_passes(const BwdLaunchArgs &a)
 template <typename T, int D>
 int launch_bwd(const BwdLaunchArgs &a)
 {
+    if constexpr (D <= 96) {
+        if (a.group == 1 && a.S <= 256 && bwd_in_one_launch(D, a.BH, a.S))
+            return a.S <= 64 ? launch_bwd_short_nw<T, D, 2>(a) : a.S <= 128 ? launch_bwd_short_nw<T, D, 4>(a) : launch_bwd_short_nw<T, D, 8>(a);
+    }
     // one query head per key/value head keeps the kernels without the loop over a group
     return a.group == 1 ? launch_bwd_passes<T, D, false>(a) : launch_bwd_passes<T, D, true>(a);
 }

@@ -27,6 +27,9 @@ def _reference(q, k, v, dout, causal):
 # (B * Hkv, G, S): at most 64, 128, 256 and 400 workgroups of 128 rows on short, medium and long chains; more streams than tiles;
 # chains that continue into the next query head of a group
 CASES = [(1, 1, 65), (3, 1, 96), (2, 1, 97), (5, 1, 300), (2, 1, 2049), (1, 8, 33), (3, 4, 70), (2, 3, 161), (70, 1, 200), (24, 1, 520),
+         # whole heads in one workgroup (D = 64, 96): one to eight 32-row blocks, full and ragged
+         (3, 1, 1), (2, 1, 16), (5, 1, 32), (4, 1, 33), (2, 1, 64), (3, 1, 100), (2, 1, 128), (130, 1, 129), (120, 1, 160), (256, 1, 197),
+         (112, 1, 224), (115, 1, 255), (111, 1, 256),
          (7, 1, 2100), (35, 2, 257), (45, 1, 515), (25, 1, 1030), (16, 4, 513), (13, 1, 2050), (20, 1, 2048)]
 
 
