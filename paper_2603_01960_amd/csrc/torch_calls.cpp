@@ -127,8 +127,16 @@ Tile as_tile(PyObject *obj)
     return t;
 }
 
+// Lets other Python threads run while the allocator or the launch may block (a full queue, say, that waits for a host function
+// of another thread).
+struct NoGil {
+    PyThreadState *state = PyEval_SaveThread();
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+
 at::Tensor empty(at::IntArrayRef size, at::ScalarType type, const at::Tensor &like)
 {
+    const NoGil without;
     return at::Tensor(at::detail::empty_cuda(size, type, like.device(), std::nullopt));
 }
 
@@ -143,6 +151,13 @@ struct Launch {
         stream = (void *)c10::hip::getCurrentHIPStream(index).stream();
     }
 };
+
+// (the arguments are evaluated before the lock is let go)
+template <typename... P, typename... A> int without_gil(int (*call)(P...), A... args)
+{
+    const NoGil without;
+    return call(args...);
+}
 
 void *data(const at::Tensor &t) { return t.data_ptr(); }
 
@@ -256,7 +271,7 @@ PyObject *call_sdpa(PyObject *, PyObject *const *args, Py_ssize_t n)
             }
         }
         const Launch on(q);
-        const int st = tiled_sdpa_fwd_ex(data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr,
+        const int st = without_gil(tiled_sdpa_fwd_ex, data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr,
                                          (int)s[0], (int)s[1], (int)s[2], (int)s[3], scale, element_type(q), on.stream,
                                          tile.m, tile.n, flags);
         return result(st, args[6], out, with_lse, args[7], lse);
@@ -278,7 +293,7 @@ PyObject *call_sdpa_kv(PyObject *, PyObject *const *args, Py_ssize_t n)
         const at::Tensor &q = heads_tensor(args[0], "q"), &k = heads_tensor(args[1], "k"), &v = heads_tensor(args[2], "v");
         const unsigned flags = as_flags(args[10], args[3]);
         const float scale = as_scale(args[4]);
-        int splits = as_int(args[5]);
+        int splits = args[5] == Py_None ? 0 : as_int(args[5]);
         const bool with_lse = as_bool(args[6]);
         const Tile tile = as_tile(args[9]);
         same_type(q, k, v);
@@ -305,7 +320,7 @@ PyObject *call_sdpa_kv(PyObject *, PyObject *const *args, Py_ssize_t n)
         }
         const Workspace ws(args[8], tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits), q);
         const Launch on(q);
-        const int st = tiled_sdpa_fwd_kvcache(data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr, lens,
+        const int st = without_gil(tiled_sdpa_fwd_kvcache, data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr, lens,
                                               B, H, Hkv, Sq, Skv, D, scale, dtype, on.stream, tile.m, tile.n, flags, splits,
                                               ws.ptr, ws.bytes);
         return result(st, args[7], out, with_lse, Py_None, lse);
@@ -328,7 +343,7 @@ PyObject *call_sdpa_paged(PyObject *, PyObject *const *args, Py_ssize_t n)
         const at::Tensor &q = *tensors[0], &k = *tensors[1], &v = *tensors[2];
         const unsigned flags = as_flags(args[12], args[5]);
         const float scale = as_scale(args[6]);
-        int splits = as_int(args[7]);
+        int splits = args[7] == Py_None ? 0 : as_int(args[7]);
         const bool with_lse = as_bool(args[8]);
         const Tile tile = as_tile(args[11]);
         if ((q.scalar_type() != at::kHalf && q.scalar_type() != at::kBFloat16) || k.scalar_type() != q.scalar_type() ||
@@ -358,7 +373,7 @@ PyObject *call_sdpa_paged(PyObject *, PyObject *const *args, Py_ssize_t n)
         }
         const Workspace ws(args[10], tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits), q);
         const Launch on(q);
-        const int st = tiled_sdpa_fwd_paged(data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr,
+        const int st = without_gil(tiled_sdpa_fwd_paged, data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr,
                                             (const int *)data(lens), (const int *)data(table), B, H, Hkv, Sq, max_blocks,
                                             block_rows, D, scale, dtype, on.stream, tile.m, tile.n, flags, splits, ws.ptr, ws.bytes);
         return result(st, args[9], out, with_lse, Py_None, lse);
@@ -401,7 +416,7 @@ PyObject *call_sdpa_backward(PyObject *, PyObject *const *args, Py_ssize_t n)
                                                 "dv must match k in shape, dtype, device and be contiguous"};
             PyObject *seq = PySequence_Fast(args[9], "grads must be (dq, dk, dv)");
             if (!seq) throw PyFail{};
-            if (PySequence_Fast_GET_SIZE(seq) != 3) {
+            if (PySequence_Fast_GET_SIZE(seq) < 3) {
                 Py_DECREF(seq);
                 fail("grads must be (dq, dk, dv)");
             }
@@ -420,7 +435,7 @@ PyObject *call_sdpa_backward(PyObject *, PyObject *const *args, Py_ssize_t n)
         const int B = (int)s[0], H = (int)s[1], S = (int)s[2], D = (int)s[3];
         const Workspace ws(args[8], tiled_sdpa_bwd_workspace_bytes(B, H, S), q);
         const Launch on(q);
-        const int st = tiled_sdpa_bwd_gqa(data(q), data(k), data(v), data(o), data(dout), (const float *)data(lse), data(grad[0]),
+        const int st = without_gil(tiled_sdpa_bwd_gqa, data(q), data(k), data(v), data(o), data(dout), (const float *)data(lse), data(grad[0]),
                                           data(grad[1]), data(grad[2]), B, H, (int)t[1], S, D, scale, dtype, flags, ws.ptr,
                                           ws.bytes, on.stream);
         if (st != TSDPA_OK) return PyLong_FromLong(st);

@@ -68,3 +68,17 @@ def test_nan_rows_stay_nan_however_the_runs_are_combined():
             out[1, 0, 2] = ref[1, 0, 2]
             # (the NaN makes its wavefront raise every row's reference: other roundings of the weights, 2^-9 each)
             torch.testing.assert_close(out.float(), ref.float(), rtol=1e-2, atol=1e-2)
+
+
+def test_arguments_that_leave_a_choice_open():
+    """splits=None is the library's choice, as 0; of a longer `grads` the first three are used."""
+    import torch
+    from paper_2603_01960_amd import binding
+    q, k, v = (t.cuda() for t in kv.make_q_kv(1, 2, 64, 64, 64, "f16", seed=4980))
+    ref = binding.sdpa_kv(q, k, v)
+    assert torch.equal(binding.sdpa_kv(q, k, v, splits=None), ref)
+    o, lse = binding.sdpa(q, k, v, return_lse=True)
+    want = binding.sdpa_backward(q, k, v, o, q, lse)
+    grads = [torch.empty_like(t) for t in (q, k, v)] + [None]
+    assert binding.sdpa_backward(q, k, v, o, q, lse, grads=grads) is grads
+    assert all(torch.equal(a, b) for a, b in zip(grads, want))
