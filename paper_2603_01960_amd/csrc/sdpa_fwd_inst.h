@@ -71,8 +71,28 @@ int launch_dispatch_tn64(int tile_m, const LaunchArgs &a)
     return tile_m == 64 ? launch_one<T, D, 2, 64>(a) : launch_one<T, D, 4, 64>(a);
 }
 
-// Streams (a.streams > 1, the square problem): tile_m / 32 wavefronts each, 32-row K/V tiles; the forms that pick_streams
+// Streams (a.streams > 1): tile_m / 32 wavefronts each, 32-row K/V tiles; the forms that pick_streams
 // (tiled_sdpa.hip) chooses from.
+template <typename T, int D, int KV>
+int launch_streams(int tile_m, const LaunchArgs &a)
+{
+    switch (tile_m * 10 + a.streams) {
+        case 324: return launch_one<T, D, 1, 32, KV, 4>(a);
+        case 642: return launch_one<T, D, 2, 32, KV, 2>(a);
+        case 1282: return launch_one<T, D, 4, 32, KV, 2>(a);
+        case 643:
+            if constexpr (D == 160) return launch_one<T, D, 2, 32, KV, 3>(a);
+            break;
+        case 644:
+            if constexpr (D < 160) return launch_one<T, D, 2, 32, KV, 4>(a);
+            break;
+        case 328:
+            if constexpr (D == 64 && KV == 0) return launch_one<T, D, 1, 32, KV, 8>(a);
+            break;
+    }
+    return (int)hipErrorInvalidValue;
+}
+
 using LaunchTn64 = int (*)(int tile_m, const LaunchArgs &a);
 
 template <typename T, int D>
@@ -81,21 +101,8 @@ int launch_dispatch(int tile_m, int tile_n, const LaunchArgs &a, LaunchTn64 tn64
     if (tile_n == 64) return tn64(tile_m, a);
     const int key = tile_m * 1000 + tile_n;
     if (a.streams > 1) {
-        switch (tile_m * 10 + a.streams) {
-            case 324: return launch_one<T, D, 1, 32, 0, 4>(a);
-            case 642: return launch_one<T, D, 2, 32, 0, 2>(a);
-            case 1282: return launch_one<T, D, 4, 32, 0, 2>(a);
-            case 643:
-                if constexpr (D == 160) return launch_one<T, D, 2, 32, 0, 3>(a);
-                break;
-            case 644:
-                if constexpr (D < 160) return launch_one<T, D, 2, 32, 0, 4>(a);
-                break;
-            case 328:
-                if constexpr (D == 64) return launch_one<T, D, 1, 32, 0, 8>(a);
-                break;
-        }
-        return (int)hipErrorInvalidValue;
+        if (!a.kv) return launch_streams<T, D, 0>(tile_m, a);
+        return a.block_table ? launch_streams<T, D, 2>(tile_m, a) : launch_streams<T, D, 1>(tile_m, a);
     }
     if (a.kv && a.block_table != nullptr) {
         switch (key) {

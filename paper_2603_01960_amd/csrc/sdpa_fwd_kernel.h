@@ -183,7 +183,7 @@ __device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int
 // KVM: 0 = the paper's square problem, 1 = the general kernel over a dense cache, 2 = over a paged cache
 // (an instantiation of its own: the per-tile descriptors cost scalar registers in the loop, which the
 // latency-bound small decoding shapes of the dense path would pay for too).
-// TILE: rows T_N of a K/V tile, plus 1000 * (NS - 1).  NS > 1 (square problem only): NS streams of NW wavefronts each work on
+// TILE: rows T_N of a K/V tile, plus 1000 * (NS - 1).  NS > 1: NS streams of NW wavefronts each work on
 // the same query rows; stream s takes the tiles s, s + NS, ... into LDS slots of its own, and the streams' states (o, m,
 // l of Eqs. 2-4) are combined through the LDS at the end, in their order.  For launches of few workgroups: the chain of tiles
 // that a wavefront waits through is NS times shorter, and with NW = 1 nothing waits at a barrier.
@@ -201,7 +201,6 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses device-only types
     constexpr bool KV = KVM != 0, PAGED = KVM == 2;
     constexpr int TN = TILE % 1000, NS = 1 + TILE / 1000;
-    static_assert(NS == 1 || !KV, "streams are a form of the square problem");
     using E = Elem<T>;
     using vec8 = typename E::vec8;
     using vec4 = typename E::vec4;
@@ -380,7 +379,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             // latency is not paid in front of every tile
             if (tensor == k) {
                 page_now = page_next;
-                const int nblk = (row0 + TN) >> block_shift;
+                const int nblk = (row0 + NS * TN) >> block_shift;      // (of this stream's next tile)
                 // (the value is the same in every lane; said explicitly, or the descriptor built from it is
                 // taken for lane-dependent and every load is wrapped in a loop over distinct descriptors)
                 page_next = nblk == blk ? page_now : __builtin_amdgcn_readfirstlane(pages[nblk < max_blocks ? nblk : 0]);
@@ -608,13 +607,13 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     // keep hitting the same memory channels.  The order of the unmasked tiles is free (Eqs. 2-4 do not
     // care), so each workgroup starts its sweep at a tile of its own and wraps around.
     int rot = 0;
-    if constexpr (KVM == 1) {
+    if constexpr (KVM == 1 && NS == 1) {
         const int nf = fast_end - t0;
         if (tile_rot != 0 && nf > 2) rot = (int)((((unsigned)hs * 2654435761u) >> 12) % (unsigned)nf);
     }
     if (!KV || t0 < t1) {   // a split past the diagonal has no tile: its state stays (o, m, l) = (0, -inf, 0)
     if constexpr (PAGED) {
-        const int blk0 = (t0 * TN) >> block_shift;
+        const int blk0 = (s0 * TN) >> block_shift;
         page_next = __builtin_amdgcn_readfirstlane(pages[blk0 < max_blocks ? blk0 : 0]);
     }
     if constexpr (KVM == 0 && NS == 1) {
@@ -689,7 +688,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         if constexpr (NW > 1) __syncthreads();
     };
     int j = s0;
-    if constexpr (KVM == 1) {
+    if constexpr (KVM == 1 && NS == 1) {
         // unmasked tiles in rotated order: t0+rot ... fast_end-1, t0 ... t0+rot-1, then on to fast_end
         int cur = t0 + rot;
         for (; j < fast_end; j += 2) {
@@ -754,7 +753,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 ml[s] = *(TSDPA_LDS f32x2 *)(at + (s - 1) * (NW * STATE) - lane * 8 + 32 * D * 4);
                 M = fmaxf(M, ml[s][0]);
             }
-            // weight 0 for a stream that saw no key of the row (m = -inf); stream 0 always sees key 0
+            // weight 0 for a stream that saw no key of the row (m = -inf)
             float w[NS];
             l_tot = 0.f;
 #pragma unroll

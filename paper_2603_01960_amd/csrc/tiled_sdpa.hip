@@ -203,10 +203,39 @@ int pick_splits_decode(int BH, int Skv)
 
 void pick_tile_kv(long long heads, int Sq, int Skv, int D, int *tm, int *tn);
 
+// The same for a block of queries against a cache (rows = query rows per key/value head, grouped heads folded; Skv the
+// capacity).  Such a call used to be split over the key range only, with a whole state of rows x D floats per split through
+// memory and at least sixteen 64-row tiles per split: 24 to 64 workgroups that each waited through their tiles alone.  BF16,
+// us, splits alone -> streams (with the splits of default_splits): 8 workgroups of 128 rows, 512 keys 8.7 -> 5.9 (D = 64), 12.1 ->
+// 8.5 (128), 15.4 -> 10.3 (160); 4096 keys 19.3 -> 10.0, 25.8 -> 14.0, 30.8 -> 18.6; 32 of them, 2048 keys 20.1 -> 13.2, 27.3 ->
+// 18.2, 37.0 -> 22.0; 64, 2048 keys 21.8 -> 13.1, 30.4 -> 18.8, 40.8 -> 24.1; 128, 2048 keys 25.6 -> 16.9, 35.0 -> 26.5, 46.6
+// -> 36.9; 160, 2048 keys 30.8 -> 25.2, 40.2 -> 36.9, 51.4 -> 45.6.  With many keys per workgroup (16384 from 16 workgroups on,
+// 8192 from 32) the plain form's 128 rows per tile load win back what the shorter chain gains.
+int pick_streams_kv(long long heads, int rows, int Skv, int D, int *tm)
+{
+    if (rows <= kDecodeRows) return 1;
+    const long long n = heads * (((long long)rows + 127) / 128), n32 = heads * (((long long)rows + 31) / 32);
+    auto form = [&](int r, int streams) { *tm = r; return streams; };
+    if (n <= 64) {
+        const bool pays = Skv <= 4096 ? Skv > 64 : n32 <= 32 || (Skv <= 8192 && (D == 64 || (D <= 128 && n32 <= 128)));
+        return pays ? form(32, 4) : 1;
+    }
+    if (Skv > 4096 || Skv <= 256) return 1;
+    if (n <= 128) return Skv < 1024 ? form(64, 2) : form(64, D == 160 ? 3 : 4);
+    return n <= (Skv < 1024 ? 160 : 192) ? form(64, 2) : 1;
+}
+
 // Splits of a cache call whose tile is left to the library too.
 int default_splits(int BH, int rows, int Skv, int D)
 {
     if (rows <= kDecodeRows) return pick_splits_decode(BH, Skv);
+    int tile_m;
+    if (pick_streams_kv(BH, rows, Skv, D, &tile_m) > 1) {
+        // one workgroup per CU in all, once a stream has sixteen tiles to share (the states of a split cost a second kernel)
+        const long long wg = (long long)BH * ((rows + tile_m - 1) / tile_m);
+        const long long want = tile_m > 32 || Skv < 2048 ? 1 : 256 / wg;
+        return want < 1 ? 1 : want > 16 ? 16 : (int)want;
+    }
     int tm, tn;
     pick_tile_kv(BH, rows, Skv, D, &tm, &tn);
     return pick_splits(BH, rows, Skv, tm, tn);
@@ -558,6 +587,14 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
 
     int err;
     const bool decode = heuristic_tile && rows <= kDecodeRows;
+    if (heuristic_tile && !decode) {
+        int rows_per_wg;
+        a.streams = pick_streams_kv((long long)B * Hkv, rows, Skv, D, &rows_per_wg);
+        if (a.streams > 1) {
+            tile_m = rows_per_wg;
+            tile_n = 32;
+        }
+    }
     // The decoding kernel combines the runs itself while they are few: a mark (8 bytes) per run must fit a head's part of o,
     // and past about 64 states per head the one workgroup that does it is slower than the merge kernel's many (8 heads, 4
     // rows: 8 runs of 128 keys 7.9 us against 10.5 with two kernels, 16 runs level, 32 runs of 256 keys 15.2 against 13.3)
@@ -584,10 +621,11 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     const size_t out_rows = (size_t)B * H * Sq;
     // Which merge: with more than eight splits (or after the decoding kernel, whose rows are few) a thread that walks them waits for its loads in several
     // batches, and when the rows are few (decoding) nothing else hides that: one workgroup per row, the
-    // splits shared among eight threads (32 splits of 32 rows: 3.5 us against 12.5 us).  With thousands of
+    // splits shared among eight threads (32 splits of 32 rows: 3.5 us against 12.5 us; 8 splits of 1024 rows at D = 64 and
+    // 128 2-3 us less for the call, level at D = 160).  With thousands of
     // rows the walking threads are many enough to hide it themselves and launch an eighth of the threads
     // (8 splits of 8192 rows: 47 us per call against 55 us).
-    if (splits > 1 && (splits > 8 || decode) && out_rows <= 2048) {
+    if (splits > 1 && (splits > 8 || decode || (splits >= 4 && out_rows * D <= 131072)) && out_rows <= 2048) {
         static_assert(tsdpa::kMergeLanes * tsdpa::kMergePerLane >= TSDPA_MAX_SPLITS, "every split needs a thread");
         const dim3 block(D / 4, tsdpa::kMergeLanes);
         if (dtype == TSDPA_F16)
