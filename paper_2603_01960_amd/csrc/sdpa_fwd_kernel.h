@@ -707,11 +707,9 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             step(j + NS, j + 2 * NS, P1{}, std::false_type{});
         }
     }
-    bool odd = false;                             // (the unmasked tiles were an even number)
     for (; j < t1; j += NS) {
-        if (odd) step(j, j + NS, P1{}, std::true_type{});
-        else     step(j, j + NS, P0{}, std::true_type{});
-        odd = !odd;
+        if (((j - s0) / NS) & 1) step(j, j + NS, P1{}, std::true_type{});
+        else                     step(j, j + NS, P0{}, std::true_type{});
     }
     // (a stream has the others' number of tiles or one less)
     if constexpr (NS > 1 && NW > 1)
