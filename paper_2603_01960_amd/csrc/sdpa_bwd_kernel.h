@@ -28,6 +28,8 @@
 // dK and dV as two passes (8 products), D = 160 ran one wavefront per SIMD, and the statistics had kernels of their own.
 // BF16, 64 heads, S = 8192, ms per call before / now: D = 64 3.73 / 3.63, D = 96 6.27 / 5.08, D = 128 7.88 / 6.38,
 // D = 160 12.9 / 10.7; S = 2048 causal, us: D = 64 205 / 145, D = 96 335 / 198, D = 128 428 / 253, D = 160 644 / 425.
+// Since then the dP accumulators start from -Delta, the operand kept in the LDS lies in operand order, and at D = 160 two
+// workgroups of the dK pass share a CU: 64 heads, S = 4096, us, D = 64 931 / 907, D = 128 1628 / 1612, D = 160 2657 / 2385.
 // The MFMA formulation is the forward kernel's:
 // transposed accumulators (a lane owns one resident row), P and dS handed to the second product
 // straight from the accumulator registers as B-operands, the streamed tile read row-wise for the
@@ -101,6 +103,9 @@ template <int D, int MODE> constexpr int bwd_resident_regs() { return D == 160 &
 // and dV are.  GRP = false is G = 1 with that loop gone.
 // R2LDS: the second resident operand (dO in the dQ pass, V otherwise) stays in the LDS instead of D/4 registers per
 // lane; each of its MFMAs then reads two operands from there.
+// NS: streams.  NS groups of NW wavefronts share the resident rows and take every NS-th tile of the chain each (over the
+// heads of a group), in LDS slots of their own; at the end their sums are added in the order of the streams.  For passes
+// of few workgroups, whose wavefronts would wait through the whole chain alone (the choice and its figures: pick_bwd_form).
 // The dQ pass runs first: it has the query rows, so it computes their statistics (Delta_i, and LSE_i in log2 units) in
 // its prologue and leaves them in `stats` for the keys-resident passes.
 template <typename T, int D, int NW, int NS, int TS, int WPS, int MODE, bool GRP, bool R2LDS>
