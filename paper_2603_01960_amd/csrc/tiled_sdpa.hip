@@ -213,7 +213,10 @@ void pick_tile_kv(long long heads, int Sq, int Skv, int D, int *tm, int *tn);
 // 8192 from 32) the plain form's 128 rows per tile load win back what the shorter chain gains.
 int pick_streams_kv(long long heads, int rows, int Skv, int D, int *tm)
 {
-    if (rows <= kDecodeRows) return 1;
+    // (the decoding kernel below that, and on 17 to 32 rows of many heads or very long caches: 8 heads of 32 rows, 1000 keys
+    // D = 64 9.1 us there, 7.3 here, 62 heads D = 160 22.9 / 14.6, 62 of 4096 keys D = 128 28.8 / 24.7, but 128 of 4096 51.6 / 66,
+    // ... and few heads of few keys at D = 160 11.7 / 13.4)
+    if (rows <= 16 || (rows <= kDecodeRows && (heads > 64 || (D == 160 && heads <= 16 && Skv < 2048)))) return 1;
     const long long n = heads * (((long long)rows + 127) / 128), n32 = heads * (((long long)rows + 31) / 32);
     auto form = [&](int r, int streams) { *tm = r; return streams; };
     if (n <= 64) {
@@ -228,9 +231,10 @@ int pick_streams_kv(long long heads, int rows, int Skv, int D, int *tm)
 // Splits of a cache call whose tile is left to the library too.
 int default_splits(int BH, int rows, int Skv, int D)
 {
-    if (rows <= kDecodeRows) return pick_splits_decode(BH, Skv);
     int tile_m;
-    if (pick_streams_kv(BH, rows, Skv, D, &tile_m) > 1) {
+    const bool streams = pick_streams_kv(BH, rows, Skv, D, &tile_m) > 1;
+    if (rows <= kDecodeRows && !streams) return pick_splits_decode(BH, Skv);
+    if (streams) {
         // one workgroup per CU in all, once a stream has sixteen tiles to share (the states of a split cost a second kernel)
         const long long wg = (long long)BH * ((rows + tile_m - 1) / tile_m);
         const long long want = tile_m > 32 || Skv < 2048 ? 1 : 256 / wg;
@@ -586,8 +590,7 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     a.stream = (hipStream_t)stream;
 
     int err;
-    const bool decode = heuristic_tile && rows <= kDecodeRows;
-    if (heuristic_tile && !decode) {
+    if (heuristic_tile) {
         int rows_per_wg;
         a.streams = pick_streams_kv((long long)B * Hkv, rows, Skv, D, &rows_per_wg);
         if (a.streams > 1) {
@@ -595,6 +598,7 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
             tile_n = 32;
         }
     }
+    const bool decode = heuristic_tile && rows <= kDecodeRows && a.streams <= 1;
     // The decoding kernel combines the runs itself while they are few: a mark (8 bytes) per run must fit a head's part of o,
     // and past about 64 states per head the one workgroup that does it is slower than the merge kernel's many (8 heads, 4
     // rows: 8 runs of 128 keys 7.9 us against 10.5 with two kernels, 16 runs level, 32 runs of 256 keys 15.2 against 13.3)

@@ -34,6 +34,10 @@ def test_more_workgroups_than_fit_at_once():
     # 600 key/value heads (four wavefronts each), 300 heads in two runs
     q, k, v = kv.make_q_kv(100, 6, 1, 300, 64, "bf16", seed=4900)
     kv.check_kv(q, k, v, "bf16", tag="many heads")
+    # (17 to 32 rows stay with this kernel from 65 heads on)
+    for D in (64, 96, 128, 160):
+        q, k, v = kv.make_q_kv(11, 6, 17 + D // 32 * 3, 300, D, "bf16", seed=4902)
+        kv.check_kv(q, k, v, "bf16", splits=D // 64, causal=True, tag="many heads of many rows")
     q, k, v = kv.make_q_kv(50, 6, 2, 300, 128, "f16", seed=4901)
     kv.check_kv(q, k, v, "f16", splits=2, causal=True, tag="many heads, two runs")
 
