@@ -185,7 +185,8 @@ unsigned long long call_ticket()
     return x != 0 ? x : 1;
 }
 
-// Query rows per key/value head that the decoding kernel takes (its tile is not the caller's to choose).
+// Most query rows per key/value head that the decoding kernel takes (its tile is not the caller's to choose); above 16
+// rows pick_streams_kv may send a call elsewhere.
 constexpr int kDecodeRows = 32;
 
 // Splits of a decoding step (BF16, cold cache, us; s = splits): one workgroup per CU in all, of runs of at least 128 keys.
