@@ -248,7 +248,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
 #pragma unroll
             for (int w = 1; w < 64; w <<= 1) L += __shfl_xor(L, w, 64);
             if (lane == 0) {
-                wgt[splits * S + row] = L > 0.f ? 1.f / L : 0.f;       // (a row that no key reaches: O = 0, LSE = -inf)
+                wgt[splits * S + row] = M == -INFINITY ? 0.f : 1.f / L;      // (a row that no key reaches: O = 0, LSE = -inf)
                 if (lse != nullptr)
                     lse[(size_t)head * S + row] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * 0.69314718055994530942f : -INFINITY;
             }
@@ -381,7 +381,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
     float m_ref[NQ], l_run[NQ];                   // as in the forward kernel: the lazy reference, this lane's share of the normaliser
 #pragma unroll
     for (int nq = 0; nq < NQ; ++nq) {
-        m_ref[nq] = -INFINITY;
+        m_ref[nq] = klim[nq] >= t0 * kDecodeTile ? kNoWeight : -INFINITY;
         l_run[nq] = 0.f;
 #pragma unroll
         for (int db = 0; db < DB; ++db) oacc[nq][db] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -437,7 +437,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
 #pragma unroll
         for (int nq = 0; nq < NQ; ++nq) {
             float ps = exponentials(sacc[nq], nq, key0);
-            if (__builtin_amdgcn_ballot_w64(!(ps <= lazy_limit)) != 0) {          // also inf (first tile) and NaN
+            if (__builtin_amdgcn_ballot_w64(!(ps <= lazy_limit)) != 0) {          // also inf (first score) and NaN
                 // Eq. 2 for all rows of the wavefront: tile maximum, new reference, the rescale of Eqs. 3-4
                 float mx = -INFINITY;
 #pragma unroll
@@ -448,7 +448,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
                 mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
                 mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
                 const float m_tile = mx * c;
-                const bool grow = m_tile > m_ref[nq];      // (a row without keys so far: -inf or NaN, left alone)
+                const bool grow = m_tile > m_ref[nq];      // (a row without finite scores so far: -inf or NaN, left alone)
                 const float alpha = grow ? __builtin_amdgcn_exp2f(m_ref[nq] - m_tile) : 1.f;
                 m_ref[nq] = grow ? m_tile : m_ref[nq];
                 l_run[nq] *= alpha;
@@ -505,7 +505,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
         }
         wgt[nq] = m_ref[nq] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref[nq] - M[nq]);
         // one split: the division by the normaliser on the way (no key at all: O = 0)
-        if (splits == 1) wgt[nq] *= L[nq] > 0.f ? 1.f / L[nq] : 0.f;
+        if (splits == 1) wgt[nq] *= M[nq] == -INFINITY ? 0.f : 1.f / L[nq];
     }
     __syncthreads();
     // [wave][row][D] floats

@@ -156,6 +156,12 @@ __device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int
     return CausalTile{h0 + (i < full ? x * full + i : 8 * full + dealt), level};
 }
 
+// The reference m of a row that has keys but no weight yet.  Finite, so that scores of -inf (an overflowing product) in
+// front of a row's first finite one get weight 2^(-inf) = 0: against -inf they would be -inf + inf, a NaN that no later
+// tile removes.  Any finite score overflows the exponential against it, which raises the reference.  (m, l) = (kNoWeight, 0)
+// is thus a row whose scores were all -inf, (-inf, 0) a row that no key reaches.
+constexpr float kNoWeight = -__FLT_MAX__;
+
 // Hides how a register value was computed from the optimiser.  Used on loop-invariant LDS pointers:
 // left transparent, the compiler splits them into a common base and per-pointer offsets and re-adds the
 // two in front of every LDS read of the loop (one vector-ALU instruction per read).
@@ -445,14 +451,14 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     // Online-softmax state (Eqs. 2-4), all in the log2 domain of s*c.  m_ref is the reference the
     // exponentials are taken against.  It is not the running maximum of Eq. 2 but a stale one: a tile's
     // weights p = 2^(s*c - m_ref) are computed first, and only if this lane's sum of them exceeds
-    // 2^tau (some score lies far above the reference; always so on a row's first tile, where m_ref is
-    // -inf) is the tile maximum taken, the reference raised to it, the state rescaled (Eqs. 3-4) and
+    // 2^tau (some score lies far above the reference; always so on a row's first finite score, before which m_ref is
+    // kNoWeight) is the tile maximum taken, the reference raised to it, the state rescaled (Eqs. 3-4) and
     // the weights recomputed.  With a stale reference the weights of a row are merely scaled by a common
     // factor <= 2^tau, which cancels in o/l and in m_ref + log2(l); in return the common case needs
     // neither the maximum nor the rescale.  tau = 0 raises the reference on every new maximum (any
     // weight above 1 makes the sum exceed 1), which is Eq. 2 literally, at the price of recomputing
     // most tiles.
-    float m_ref = -INFINITY;
+    float m_ref = !KV || klim >= t0 * TN ? kNoWeight : -INFINITY;      // (-inf: no key of this run reaches the row)
     const float lazy_limit = __builtin_amdgcn_exp2f(tau);
     float l_run = 0.f;         // this lane's share of the normaliser (lane^32 holds the rest)
 
@@ -526,8 +532,8 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         mx = pair_max(mx);
         const float m_tile = mx * c;
         const bool row_over = pair_max(over ? 1.f : 0.f) > 0.f;
-        // rows that keep m_ref are left alone (also one whose keys so far were all masked: m_ref = -inf,
-        // m_tile = -inf or NaN)
+        // rows that keep m_ref are left alone (also one whose keys so far were all masked or scored -inf: m_tile = -inf
+        // or NaN)
         const bool grow = row_over && m_tile > m_ref;
         const float alpha = grow ? __builtin_amdgcn_exp2f(m_ref - m_tile) : 1.0f;
         m_ref = grow ? m_tile : m_ref;
@@ -581,7 +587,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     // sum added to l_run
     auto softmax_tile = [&](int row0, auto mask_tag) __attribute__((always_inline)) {
         float ps = exponentials(sacc, row0, pb, mask_tag);
-        const bool over = !(ps <= lazy_limit);               // also catches inf (first tile) and NaN
+        const bool over = !(ps <= lazy_limit);               // also catches inf (first score) and NaN
         if (__builtin_amdgcn_ballot_w64(over) != 0) {        // wavefront-uniform and rare
             raise_reference(sacc, row0, mask_tag, over);
             ps = exponentials(sacc, row0, pb, mask_tag);
@@ -751,7 +757,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 ml[s] = *(TSDPA_LDS f32x2 *)(at + (s - 1) * (NW * STATE) - lane * 8 + 32 * D * 4);
                 M = fmaxf(M, ml[s][0]);
             }
-            // weight 0 for a stream that saw no key of the row (m = -inf)
+            // (m = -inf in all streams or in none: a row that no key of the run reaches)
             float w[NS];
             l_tot = 0.f;
 #pragma unroll
@@ -803,12 +809,11 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         }
         return;
     }
-    // a row that no key reaches (empty cache entry, causal limit before the first key) has l = 0: O = 0, LSE = -inf
+    // a row that no key reaches (empty cache entry, causal limit before the first key): O = 0, LSE = -inf
     // (only the cache variants can have such a row: in the square problem every row sees key 0)
-    const bool no_key = KV && !(l_tot > 0.f);
-    const float inv = no_key ? 0.f : 1.0f / l_tot;
+    const float inv = KV && m_ref == -INFINITY ? 0.f : 1.0f / l_tot;
     if (lse != nullptr && g == 0 && qrow < S)
-        lse[(size_t)head * S + qrow] = no_key ? -INFINITY : (m_ref + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994530942f;
+        lse[(size_t)head * S + qrow] = KV && !(l_tot > 0.f) ? -INFINITY : (m_ref + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994530942f;
     // (the launcher sizes the dynamic LDS for the larger of the tile slots and this staging area)
     {
         constexpr int OCPR = G::OROW / 16, CMASK = OCPR - 1;   // chunks per staging row: a power of two

@@ -6,7 +6,8 @@
 // rescale by e^{m_old - m_new}, states over disjoint key ranges combine the same way:
 //     M = max_s m_s,   w_s = 2^(m_s - M),   L = sum_s w_s l_s,   O = (sum_s w_s o_s) / L,
 // and O_i = o_i / l_i as at the end of Section 4.1.2; LSE = (M + log2 L) ln 2.  A split that saw no
-// key of the row has (m, l) = (-inf, 0), weight 0, and an o that is not looked at; a row of NaN scores has (-inf, NaN).
+// key of the row has (m, l) = (-inf, 0), weight 0, and an o that is not looked at; one that saw only scores of -inf or NaN
+// has the lowest finite m and l = 0 or NaN (O is NaN if all splits are like that).
 //
 // Workspace layout (written by sdpa_fwd_kernel<..., KV = true>): o as float [BH][splits][S][D],
 // then (m, l) pairs as float [BH][splits][S][2].
@@ -59,7 +60,7 @@ sdpa_merge_kernel(const float *__restrict__ ws, T *__restrict__ o, float *__rest
         const f32x4 part = *(const f32x4 *)(ws + p * D + d4 * 4);
         if (ml[p * 2 + 1] != 0.f) acc += w * part; // (a split without keys, l = 0, may have left its o unwritten; a NaN row has l = NaN)
     }
-    const float inv = L > 0.f ? 1.0f / L : 0.f;
+    const float inv = M == -INFINITY ? 0.f : 1.0f / L;
     vec4 out;
 #pragma unroll
     for (int e = 0; e < 4; ++e) out[e] = (T)(acc[e] * inv);
@@ -136,7 +137,7 @@ sdpa_merge_wide_kernel(const float *__restrict__ ws, T *__restrict__ o, float *_
         out_acc += w * acc_sh[y][d4];
     }
     // M is -inf only for a row that no key reaches: all weights 0, O = 0, LSE = -inf
-    const float inv = L > 0.f ? 1.0f / L : 0.f;
+    const float inv = M == -INFINITY ? 0.f : 1.0f / L;
     vec4 out;
 #pragma unroll
     for (int e = 0; e < 4; ++e) out[e] = (T)(out_acc[e] * inv);
