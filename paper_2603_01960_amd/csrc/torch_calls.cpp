@@ -209,12 +209,15 @@ struct Workspace {
     at::Tensor held;
     void *ptr = nullptr;
     unsigned long long bytes = 0;
-    // the caller's buffer (any contiguous device tensor), or `need` bytes of torch's
+    // the caller's buffer, or `need` bytes of torch's.  The kernels write to it as to one range of bytes: it has to be that,
+    // and on the device of the call (of a call that needs none it is not looked at)
     Workspace(PyObject *obj, unsigned long long need, const at::Tensor &like)
     {
         if (obj != Py_None) {
             if (!THPVariable_Check(obj)) fail("workspace must be a device tensor");
             held = THPVariable_Unpack(obj);
+            if (need > 0 && (held.device() != like.device() || !held.is_non_overlapping_and_dense()))
+                fail("workspace must be a dense tensor on the device of q");
         } else if (need > 0) {
             held = empty({(int64_t)need}, at::kByte, like);
         } else {
@@ -262,10 +265,11 @@ PyObject *call_sdpa(PyObject *, PyObject *const *args, Py_ssize_t n)
         at::Tensor lse;
         if (with_lse) {
             if (args[7] != Py_None) {
-                if (!THPVariable_Check(args[7])) fail("lse_out must be contiguous float32 [B, H, S]");
+                static const char text[] = "lse_out must be contiguous float32 [B, H, S] on the device of q";
+                if (!THPVariable_Check(args[7])) fail(text);
                 lse = THPVariable_Unpack(args[7]);
-                if (lse.sizes() != s.slice(0, 3) || lse.scalar_type() != at::kFloat || !lse.is_contiguous())
-                    fail("lse_out must be contiguous float32 [B, H, S]");
+                if (lse.sizes() != s.slice(0, 3) || lse.scalar_type() != at::kFloat || !lse.is_contiguous() || lse.device() != q.device())
+                    fail(text);
             } else {
                 lse = empty(s.slice(0, 3), at::kFloat, q);
             }
