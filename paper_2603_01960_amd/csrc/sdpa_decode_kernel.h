@@ -8,8 +8,13 @@
 // about 100 KB per CU in flight.  Scores and output are 16x16x32 MFMAs on 16 query rows (32: two of each): half the
 // matrix work of the 32x32 tiles on the same rows, and half the registers.  At the end the four states (o, m, l of
 // Eqs. 2-4) meet in the LDS.
-// The key range of a cache of capacity Skv is cut into `splits` runs of equal length whatever each entry holds; an entry
-// of fewer keys has fewer runs, so that workgroups do the same work each and the long entries do not finish last.
+// The keys of the longest entry are cut into `splits` runs of equal length, and the other entries into runs of that length;
+// an entry of fewer keys has fewer runs, so that workgroups do the same work each and the long entries do not finish last.
+// (Runs that are a share of the CAPACITY, as they were, leave most workgroups without keys while little of a large cache is
+// filled: BF16, us, capacity 32768, such runs / these: 4 entries of 8 heads, 819 ... 3276 keys, D = 128 in pages 24.3 / 12.9, D =
+// 160 34.6 / 15.3; 2457 ... 9830 keys 43.5 / 22.4, 56.3 / 28.2; 1 entry of 8 heads, 655 keys, D = 128 10.8 / 8.5; a full
+// cache is level.  A share of each entry's OWN keys is level with these but for large entries of unequal length: 8192 ... 32768
+// keys, D = 160 84 / 77.)
 // The forward kernel, which ran these shapes before (32 x 32 tiles, all wavefronts on the same tile, a barrier per tile, one
 // of its two wavefronts without rows), against this one, BF16, cold cache, us per call with the states' combination:
 // 8 key/value heads of 1024 keys 11.5 / 7.9, of 8192 keys 14.2 / 13.3; 32 heads of 8192 keys 34.1 / 27.5; 96 heads of 3000
@@ -158,7 +163,7 @@ __global__ void __launch_bounds__(NW * 64, 2)
 sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                    T *o, float *__restrict__ lse, int S, int heads, float c, float tau, uint32_t qsign, int causal,
                    int Skv_cap, int splits, float *ws, int rows_per_head,
-                   const int *__restrict__ kv_lens, int heads_per_batch,
+                   const int *__restrict__ kv_lens, int heads_per_batch, int batches,
                    const int *__restrict__ block_table, int max_blocks, int block_shift, unsigned long long ticket)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -179,9 +184,23 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
     int head = blockIdx.x - sp * heads + (int)((long long)sp * heads / splits);
     if (head >= heads) head -= heads;
     int len = Skv_cap;
+    int longest = len;                            // keys of the longest entry (of more than 64 entries: of this one)
     if (kv_lens != nullptr) {
-        const int x = kv_lens[head / heads_per_batch];
-        len = x < 0 ? 0 : (x < Skv_cap ? x : Skv_cap);
+        const int b = head / heads_per_batch;
+        auto clamped = [&](int x) __attribute__((always_inline)) { return x < 0 ? 0 : (x < Skv_cap ? x : Skv_cap); };
+        if (splits > 1 && batches > 1 && batches <= 64) {
+            const int own = clamped(lane < batches ? kv_lens[lane] : 0);
+            len = __builtin_amdgcn_readlane(own, b);
+            // the maximum over the lanes, in the last one: within rows of 16 lanes, then across them
+            longest = own;
+#define TSDPA_MAX_STEP(ctrl, rows) { const int y = __builtin_amdgcn_update_dpp(0, longest, ctrl, rows, 0xf, false); longest = longest > y ? longest : y; }
+            TSDPA_MAX_STEP(0x111, 0xf) TSDPA_MAX_STEP(0x112, 0xf) TSDPA_MAX_STEP(0x114, 0xf) TSDPA_MAX_STEP(0x118, 0xf)      // row_shr
+            TSDPA_MAX_STEP(0x142, 0xa) TSDPA_MAX_STEP(0x143, 0xc)                                                          // row_bcast
+#undef TSDPA_MAX_STEP
+            longest = __builtin_amdgcn_readlane(longest, 63);
+        } else {
+            len = longest = clamped(kv_lens[b]);
+        }
     }
 
     // ---- The runs' states are combined by whichever workgroup of the head is last to be done with its own, in run order
@@ -274,9 +293,12 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
     };
 
     // this workgroup's run of tiles: [t0, t0 + n)
-    const int run = ((Skv_cap + kDecodeTile - 1) / kDecodeTile + splits - 1) / splits;
-    const int t0 = sp * run;
     const int nT = (len + kDecodeTile - 1) / kDecodeTile;
+    // (not below four tiles: one for each of four wavefronts.  Runs of a single tile, six entries of 8 heads and 12 rows with 25
+    // ... 102 keys each: 14.0 us against 12.6 at D = 160, 10.5 against 9.7 at D = 64)
+    int run = ((longest + kDecodeTile - 1) / kDecodeTile + splits - 1) / splits;
+    if (run < 4) run = 4;
+    const int t0 = sp * run;
     int n = nT - t0 < run ? nT - t0 : run;
     if (n < 0) n = 0;
     if (n == 0 && splits > 1) {                   // nothing to read: the state of no keys (the merge does not look at o then)
@@ -563,7 +585,7 @@ template <typename T, int D, int NQ, int NW, bool PAGED> int launch_decode_one(c
     if (attr_err != hipSuccess) return (int)attr_err;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.BH * a.splits)), dim3(NW * 64), lds_bytes, a.stream,
                        (const T *)a.q, (const T *)a.k, (const T *)a.v, (T *)a.o, a.lse, a.S, a.BH, a.c, a.tau, a.qsign, a.causal,
-                       a.Skv, a.splits, a.ws, a.rows_per_head, a.kv_lens, a.heads_per_batch, a.block_table, a.max_blocks, a.block_shift, a.ticket);
+                       a.Skv, a.splits, a.ws, a.rows_per_head, a.kv_lens, a.heads_per_batch, a.batches, a.block_table, a.max_blocks, a.block_shift, a.ticket);
     return (int)hipGetLastError();
 }
 

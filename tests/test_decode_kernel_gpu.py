@@ -30,6 +30,18 @@ def test_grouped_heads_lengths_and_pages(splits, D, G, Sq):
         kv.check_paged(len(lens), 2 * G, 2, Sq, D, "bf16", lens, 64, causal, splits)
 
 
+@pytest.mark.parametrize("entries", [2, 63, 64, 65])
+def test_runs_follow_the_longest_entry(entries):
+    """Runs are cut by the longest of up to 64 entries, by each entry's own length beyond: the longest one first, last and in the
+    middle, lengths around four tiles per run, most of the capacity unused."""
+    for splits in (2, 5, 40):
+        for at, most in ((0, 1500), (entries - 1, 128 * splits - 63), (entries // 2, 128 * splits + 1)):
+            lens = [(11 * i) % 97 for i in range(entries)]
+            lens[at] = min(most, 2900)
+            kv.check_kv_lens(entries, 4, 2, 1, 3000, 64, "bf16", lens, True, splits)
+            kv.check_paged(entries, 2, 2, 3, 128, "f16", lens, 64, False, splits)
+
+
 def test_more_workgroups_than_fit_at_once():
     # 600 key/value heads (four wavefronts each), 300 heads in two runs
     q, k, v = kv.make_q_kv(100, 6, 1, 300, 64, "bf16", seed=4900)
