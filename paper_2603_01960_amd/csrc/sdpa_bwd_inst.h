@@ -38,12 +38,12 @@ int launch_bwd_pass_nw(const BwdLaunchArgs &a)
     // one workgroup per (head of the resident side, tile of its rows): query heads in the dQ pass, key/value heads otherwise
     const int heads = MODE == BWD_DQ ? a.BH : a.BH / a.group;
     const int N = heads * nR;
-    const CausalChunks chunks = causal_chunks(heads, nR, (long long)(MODE == BWD_DQ ? 1 : a.group) * a.S * D * 2 * (long long)sizeof(T));
+    const TileOrder order = tile_order(heads, nR, (long long)(MODE == BWD_DQ ? 1 : a.group) * a.S * D * 2 * (long long)sizeof(T));
     void *out = MODE == BWD_DQ ? a.dq : (MODE == BWD_DV ? a.dv : a.dk);
     hipLaunchKernelGGL(kern, dim3(N), dim3(NW * NS * 64), lds_bytes, a.stream,
                        (const T *)a.q, (const T *)a.k, (const T *)a.v, (const T *)a.dout, (const T *)a.o, a.lse, a.stats,
                        (T *)out, (T *)(MODE == BWD_DKV ? a.dv : nullptr), a.S, nR, N, a.c, a.scale, a.rsign, a.causal, a.stat_bytes, a.group,
-                       chunks.first, chunks.heads);
+                       order);
     return (int)hipGetLastError();
 }
 

@@ -116,7 +116,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 T *__restrict__ out,   // dQ, dK or dV
                 T *__restrict__ out2,  // dV of the fused dK + dV pass, else unused
                 int S, int nR, int N, float c, float scale, uint32_t rsign, int causal, unsigned stat_bytes,
-                int group, int chunk_first, int chunk_heads)
+                int group, TileOrder order)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using E = Elem<T>;
@@ -148,16 +148,20 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     const lds_ptr slots = lds + stream * STREAM;
     const int g = lane >> 5, l32 = lane & 31;
 
+    // (the arguments of the prologue all at once, as in the forward kernel)
+    asm volatile("" : : "s"(q), "s"(k), "s"(v), "s"(dout), "s"(order.by_tiles.mul), "s"(order.by_tiles.shift), "s"(order.first),
+                 "s"(order.heads), "s"(order.by_chunk.mul), "s"(order.by_chunk.shift), "s"(order.by_first.mul), "s"(order.by_first.shift),
+                 "s"(order.by_full.mul), "s"(order.by_full.shift), "s"(S), "s"(causal));
     const int Gn = GRP ? group : 1;              // query heads per key/value head
     int head, rt;                                 // head of the resident side (a query head in the dQ pass, else a key/value head) and tile
-    if (causal && chunk_heads > 0) {
+    if (causal && order.heads > 0) {
         // query tiles get longer with their index, key tiles shorter: the long ones of all heads first (causal_tile)
-        const CausalTile ct = causal_tile(blockIdx.x, nR, chunk_first, chunk_heads, NS == 1 && D >= 128 ? N : 0);
+        const CausalTile ct = causal_tile(blockIdx.x, nR, order, NS == 1 && D >= 128 ? N : 0);
         head = ct.head;
         rt = KEYS_RES ? ct.level : nR - 1 - ct.level;
     } else {
         const int wg = remap_workgroup(blockIdx.x, N, false);
-        head = wg / nR;
+        head = divide(wg, order.by_tiles);
         rt = (causal && !KEYS_RES) ? nR - 1 - (wg - head * nR) : wg - head * nR;
     }
     const size_t head_off = (size_t)head * (size_t)S * D;

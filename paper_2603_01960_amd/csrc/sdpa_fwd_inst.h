@@ -43,12 +43,12 @@ int launch_one(const LaunchArgs &a)
     const int heads = a.BH * (KV ? a.splits : 1);
     const int N = heads * nQ;
     // (entries of different lengths: eight heads per XCD and chunk whatever they stream, for the balance between them)
-    const CausalChunks chunks = causal_chunks(heads, nQ, a.kv_lens ? 0 : (long long)(KV ? a.Skv : a.S) * D * 2 * (long long)sizeof(T));
+    const TileOrder order = tile_order(heads, nQ, a.kv_lens ? 0 : (long long)(KV ? a.Skv : a.S) * D * 2 * (long long)sizeof(T));
     hipLaunchKernelGGL(kern, dim3(N), dim3(NW * NS * 64), lds_bytes, a.stream,
                        (const T *)a.q, (const T *)a.k, (const T *)a.v, (T *)a.o, a.lse,
                        a.S, nQ, N, a.c, a.tau, a.qsign, a.linear_grid, a.causal,
                        a.Skv, a.splits, a.ws, a.rows_per_head, a.kv_lens, a.heads_per_batch,
-                       a.block_table, a.max_blocks, a.block_shift, a.tile_rot, chunks.first, chunks.heads, a.batches);
+                       a.block_table, a.max_blocks, a.block_shift, a.tile_rot, order, a.batches);
     return (int)hipGetLastError();
 }
 

@@ -24,6 +24,8 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "sdpa_fwd_launch.h"
+
 namespace tsdpa {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -133,16 +135,19 @@ __device__ __forceinline__ int remap_workgroup(int id, int N, bool linear) {
 // D = 64 88.2 -> 84.4, 96 115.3 -> 104.4, 128 138 -> 128, 160 174 -> 164; 30 of S = 2048 28.4 -> 27.1, 37.2 -> 34.0, 44.4 ->
 // 41.7, 55.8 -> 53.5; 64 of S = 1024 17.7 -> 17.1 ... 35.0 -> 33.7; level at S = 512.  The backward passes
 // gain 0-4 % at D = 128 and 160, and lose 0-2 % at D = 64 and 96, where it is not used.
+__device__ __forceinline__ int divide(int n, const Divisor &d) { return (int)(__umulhi(2u * (unsigned)n, d.mul) >> d.shift); }
 struct CausalTile { int head, level; };
-__device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int hg, int paired = 0) {
+__device__ __forceinline__ CausalTile causal_tile(int id, int nQ, const TileOrder &order, int paired = 0) {
+    const int first = order.first, hg = order.heads;
     const int x = id & 7;
     int y = id >> 3;
     if (paired > 256 && paired <= 512 && y >= 32) y = ((paired - x + 7) >> 3) + 31 - y;
     int full = first >> 3, rem = first & 7, h0 = 0;
     const int in_first = full * nQ + ((nQ * rem + 7 - x) >> 3);   // this XCD's share of the first chunk
-    if (y >= in_first) {
+    const bool later = y >= in_first;              // (than the first chunk)
+    if (later) {
         y -= in_first;
-        const int c = y / (hg * nQ);
+        const int c = divide(y, order.by_chunk);
         y -= c * hg * nQ;
         h0 = first + c * 8 * hg;
         full = hg;
@@ -150,7 +155,7 @@ __device__ __forceinline__ CausalTile causal_tile(int id, int nQ, int first, int
     }
     // before level l this XCD has before(l) = l * full + ceil((l * rem - x) / 8) tiles of its own and dealt ones;
     // the largest l with before(l) <= y is:
-    const int level = (8 * y + x) / (8 * full + rem);
+    const int level = divide(8 * y + x, later ? order.by_full : order.by_first);     // (8 * full + rem)
     const int i = y - (level * full + ((level * rem + 7 - x) >> 3));
     const int dealt = ((x - level * rem) & 7);                    // of this level's rem dealt tiles, the one that is ours
     return CausalTile{h0 + (i < full ? x * full + i : 8 * full + dealt), level};
@@ -202,7 +207,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 int Skv_arg, int splits_arg, float *__restrict__ ws, int rows_per_head,
                 const int *__restrict__ kv_lens, int heads_per_batch,
                 const int *__restrict__ block_table, int max_blocks, int block_shift, int tile_rot,
-                int chunk_first, int chunk_heads, int batches)
+                TileOrder order, int batches)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses device-only types
     constexpr bool KV = KVM != 0, PAGED = KVM == 2;
@@ -238,11 +243,16 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     const int splits = KV ? splits_arg : 1;
     const int Sp = KV ? rows_per_head : S;        // query positions per query head (S = G * Sp rows when folded)
     const bool folded = KV && Sp != S;
+    // The arguments that the prologue needs, all at once (each group of them that is left to be read where it is first used is
+    // another wait for the scalar cache).
+    asm volatile("" : : "s"(q), "s"(k), "s"(v), "s"(order.by_tiles.mul), "s"(order.by_tiles.shift), "s"(order.first), "s"(order.heads),
+                 "s"(order.by_chunk.mul), "s"(order.by_chunk.shift), "s"(order.by_first.mul), "s"(order.by_first.shift),
+                 "s"(order.by_full.mul), "s"(order.by_full.shift), "s"(S), "s"(causal));
     // query tile fastest, then split, then head: neighbours share one run of K/V tiles.  Under the causal mask the work
     // of a query tile grows with its index, and the long ones of all heads are started first (causal_tile).
     int hs, qt;
-    if (causal && !linear_grid && chunk_heads > 0) {
-        const CausalTile ct = causal_tile(blockIdx.x, nQ, chunk_first, chunk_heads, N);
+    if (causal && !linear_grid && order.heads > 0) {
+        const CausalTile ct = causal_tile(blockIdx.x, nQ, order, N);
         hs = ct.head;
         qt = nQ - 1 - ct.level;
         if (KV && folded && Sp % TM == 0) {       // the last tile of every folded query head, then the one before it, ...
@@ -251,7 +261,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         }
     } else {
         const int wg = remap_workgroup(blockIdx.x, N, linear_grid != 0);
-        hs = wg / nQ;
+        hs = divide(wg, order.by_tiles);
         qt = causal ? nQ - 1 - (wg - hs * nQ) : wg - hs * nQ;
     }
     int head = KV ? hs / splits : hs;

@@ -40,7 +40,7 @@ struct LaunchArgs {
 //     S = 1024 at D = 128: 29.8 -> 27.4; nine heads of S = 4096: 78.3 -> 64.2);
 //   * beyond, eight heads per XCD, as long as the chunk streams at most 8 MiB per XCD, twice its L2 (64 heads of
 //     S = 2048, D = 96: 71.5 -> 60, D = 128: 89 -> 72; S = 4096, D = 128: 274 -> 248 with four heads; S = 8192: 962 ->
-//     930 with two and 982 with eight).
+//     930 with two and 982 with eight). 
 struct CausalChunks { int first, heads; };
 inline CausalChunks causal_chunks(int heads, int tiles, long long stream_bytes)
 {
@@ -53,6 +53,33 @@ inline CausalChunks causal_chunks(int heads, int tiles, long long stream_bytes)
         if (hg > most) hg = most;
     }
     return CausalChunks{heads - (heads - 1) / (8 * hg) * (8 * hg), hg};
+}
+
+// Division by a number known at launch, for n < 2^31: n * mul >> (31 + shift) with mul = ceil(2^(31 + shift) / d) and shift =
+// ceil(log2 d).  (mul * d exceeds 2^(31 + shift) by less than d <= 2^shift, so the quotient is n / d plus less than 2^-shift <=
+// 1 / d.)  In the kernels' prologues: a division by a variable is a serial chain of some thirty instructions.  With these
+// divisions and the arguments read at once the plain forward forms are back at what they took before the causal order came (us,
+// before it / with variable divisions / now, no mask: 200 heads of S = 768 D = 128 73.2 / 74.1 / 72.9, 1586 of S = 131 D = 160
+// 72.4 / 73.6 / 72.2, 937 of S = 178 D = 96 28.9 / 29.4 / 28.8; the backward passes of 8 heads of S = 1024 gain 0.5-1 us).
+struct Divisor { uint32_t mul, shift; };
+inline Divisor divisor(uint32_t d)
+{
+    uint32_t shift = 0;
+    while ((1ull << shift) < d) ++shift;
+    return Divisor{(uint32_t)(((1ull << (31 + shift)) + d - 1) / d), shift};
+}
+
+// What a kernel needs to find its workgroup's head and tile: `tiles` per head, and the chunks of the causal order.
+struct TileOrder {
+    Divisor by_tiles;
+    int first, heads;          // CausalChunks
+    Divisor by_chunk, by_first, by_full;    // heads * tiles, first, 8 * heads
+};
+inline TileOrder tile_order(int heads, int tiles, long long stream_bytes)
+{
+    const CausalChunks c = causal_chunks(heads, tiles, stream_bytes);
+    auto by = [](long long d) { return divisor((uint32_t)(d > 0 ? d : 1)); };
+    return TileOrder{by(tiles), c.first, c.heads, by((long long)c.heads * tiles), by(c.first), by(8ll * c.heads)};
 }
 
 // Rows of slack after the B*H*S entries of each backward statistics array: the keys-resident pass
