@@ -28,7 +28,7 @@ int main()
     bool ok = true;
     auto check = [&](uint32_t d) {
         const uint64_t last = ((1ull << 31) - 1) / d * d;
-        for (uint64_t m : {(uint64_t)0, (uint64_t)d, 2ull * d, last / 2 / d * d, last - d, last})
+        for (uint64_t m : {(uint64_t)0, (uint64_t)d, 2 * (uint64_t)d, last / 2 / d * d, last - d, last})
             for (int64_t e : {-1, 0, 1}) if ((int64_t)m + e >= 0) ok = exact(d, m + e) && ok;
         ok = exact(d, (1ull << 31) - 1) && ok;
         for (int i = 0; i < 8; ++i) ok = exact(d, rng() >> 33) && ok;
