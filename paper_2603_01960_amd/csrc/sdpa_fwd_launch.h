@@ -40,16 +40,16 @@ struct LaunchArgs {
 //     S = 1024 at D = 128: 29.8 -> 27.4; nine heads of S = 4096: 78.3 -> 64.2);
 //   * beyond, eight heads per XCD, as long as the chunk streams at most 8 MiB per XCD, twice its L2 (64 heads of
 //     S = 2048, D = 96: 71.5 -> 60, D = 128: 89 -> 72; S = 4096, D = 128: 274 -> 248 with four heads; S = 8192: 962 ->
-//     930 with two and 982 with eight). 
+//     930 with two and 982 with eight).  Up to three per CU sixteen heads where the caller found it so (`wide`).
 struct CausalChunks { int first, heads; };
-inline CausalChunks causal_chunks(int heads, int tiles, long long stream_bytes)
+inline CausalChunks causal_chunks(int heads, int tiles, long long stream_bytes, bool wide)
 {
     const long long n = (long long)heads * tiles;
     int hg = (heads + 7) / 8;
     if (n <= 256 || tiles == 1) return CausalChunks{heads, 0};
     if (n > 512) {
         const long long fit = stream_bytes > 0 ? (8ll << 20) / stream_bytes : 8;
-        const int most = fit > 8 ? 8 : fit < 1 ? 1 : (int)fit;
+        const int most = wide && n <= 768 ? 16 : fit > 8 ? 8 : fit < 1 ? 1 : (int)fit;
         if (hg > most) hg = most;
     }
     return CausalChunks{heads - (heads - 1) / (8 * hg) * (8 * hg), hg};
@@ -75,9 +75,9 @@ struct TileOrder {
     int first, heads;          // CausalChunks
     Divisor by_chunk, by_first, by_full;    // heads * tiles, first, 8 * heads
 };
-inline TileOrder tile_order(int heads, int tiles, long long stream_bytes)
+inline TileOrder tile_order(int heads, int tiles, long long stream_bytes, bool wide = false)
 {
-    const CausalChunks c = causal_chunks(heads, tiles, stream_bytes);
+    const CausalChunks c = causal_chunks(heads, tiles, stream_bytes, wide);
     auto by = [](long long d) { return divisor((uint32_t)(d > 0 ? d : 1)); };
     return TileOrder{by(tiles), c.first, c.heads, by((long long)c.heads * tiles), by(c.first), by(8ll * c.heads)};
 }

@@ -15,8 +15,11 @@ def _normal(*shape, dtype=torch.bfloat16, seed=0):
 # (B, H, S): one chunk of heads with a remainder of eight; several chunks, the first short; chunks of one head per XCD
 # (K and V of a head beyond 8 MiB per eight heads); a ragged last tile
 @pytest.mark.parametrize("B,H,S,D", [(1, 53, 640, 64), (5, 21, 600, 64), (3, 11, 8192, 128), (1, 3, 16500, 64), (7, 17, 333, 96),
-                                     # 257, 301 and 512 workgroups: the second one of a CU in reverse order
-                                     (1, 257, 100, 64), (1, 43, 850, 64), (1, 64, 1024, 160)])
+                                     # 258, 301 and 512 workgroups: the second one of a CU in reverse order
+                                     (1, 129, 200, 64), (1, 43, 850, 64), (1, 64, 1024, 160),
+                                     # 513 ... 768 workgroups, up to three tiles per head: chunks of sixteen heads per XCD, a short
+                                     # first one; two tiles of equal work: head after head; one tile per head: likewise
+                                     (1, 231, 384, 64), (1, 257, 300, 96), (1, 256, 257, 128), (1, 300, 171, 96), (1, 257, 100, 64)])
 def test_forward_order(B, H, S, D):
     from paper_2603_01960_amd import binding
     q, k, v = (_normal(B, H, S, D, seed=i) for i in range(3))
