@@ -140,7 +140,8 @@ int tiled_sdpa_tune_tile(const void *q, const void *k, const void *v, void *o,
  *              row i only if j <= i + Skv - Sq.  It needs Skv >= Sq.  The other flags as above.
  *   tile_m   : 64 or 128;  tile_n : 32 or 64;  or (256, 64) (not with a paged cache);  both 0 = heuristic.
  *   splits   : workgroups per (head, query tile) along the key axis, 1..TSDPA_MAX_SPLITS; 0 = the
- *              value tiled_sdpa_kv_default_splits reports for this shape and these flags.
+ *              value tiled_sdpa_kv_default_splits reports for this shape and these flags, or with an explicit
+ *              tile the value of tiled_sdpa_kv_tile_splits where the workspace is large enough for it.
  *   workspace: device memory for the split states, 16-byte aligned, at least
  *              tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, n) bytes, n being `splits` or, for splits = 0,
  *              the heuristic's value; ignored (may be NULL) when n = 1, where O is written directly.
@@ -264,6 +265,10 @@ int tiled_sdpa_fwd_paged(const void *q, const void *k_pages, const void *v_pages
 
 /* Splits the heuristic picks (1 when the query tiles alone fill the GPU); returns a status code. */
 int tiled_sdpa_kv_default_splits(int B, int H, int Sq, int Skv, int D, int dtype, unsigned flags, int *splits);
+/* The same for a call with an explicit tile (both 0: the value above).  The two differ where the heuristic would
+ * take the decoding kernel or streams, which explicit tiles never do.  TSDPA_ERR_BAD_TILE for a tile the cache entry points
+ * do not offer. */
+int tiled_sdpa_kv_tile_splits(int B, int H, int Sq, int Skv, int D, int dtype, unsigned flags, int tile_m, int tile_n, int *splits);
 
 /* Workspace bytes tiled_sdpa_fwd_kv needs for `splits` >= 1 (a value from tiled_sdpa_kv_default_splits,
  * or the caller's own): B*H*splits*Sq*(D+2) floats.  0 for splits <= 1 or negative arguments. */

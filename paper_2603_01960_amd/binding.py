@@ -37,6 +37,7 @@ EXPORTS = (
     "tiled_sdpa_fwd_kvcache_static",
     "tiled_sdpa_fwd_paged",
     "tiled_sdpa_kv_default_splits",
+    "tiled_sdpa_kv_tile_splits",
     "tiled_sdpa_kv_workspace_bytes",
     "tiled_sdpa_probe_mfma",
     "tiled_sdpa_probe_hbm_read",
@@ -77,6 +78,8 @@ def load_library():
                                       ci, vp, ctypes.c_ulonglong]
     lib.tiled_sdpa_kv_default_splits.restype = ci
     lib.tiled_sdpa_kv_default_splits.argtypes = [ci, ci, ci, ci, ci, ci, ctypes.c_uint, ctypes.POINTER(ci)]
+    lib.tiled_sdpa_kv_tile_splits.restype = ci
+    lib.tiled_sdpa_kv_tile_splits.argtypes = [ci, ci, ci, ci, ci, ci, ctypes.c_uint, ci, ci, ctypes.POINTER(ci)]
     lib.tiled_sdpa_kv_workspace_bytes.restype = ctypes.c_ulonglong
     lib.tiled_sdpa_kv_workspace_bytes.argtypes = [ci, ci, ci, ci, ci]
     lib.tiled_sdpa_bwd.restype = ci

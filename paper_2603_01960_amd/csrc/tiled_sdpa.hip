@@ -440,6 +440,15 @@ int tiled_sdpa_kv_default_splits(int B, int H, int Sq, int Skv, int D, int dtype
     return TSDPA_OK;
 }
 
+int tiled_sdpa_kv_tile_splits(int B, int H, int Sq, int Skv, int D, int dtype, unsigned flags, int tile_m, int tile_n, int *splits)
+{
+    const int st = tiled_sdpa_kv_default_splits(B, H, Sq, Skv, D, dtype, flags, splits);
+    if (st != TSDPA_OK || (int64_t)B * H * Sq == 0 || (tile_m == 0 && tile_n == 0)) return st;
+    if (!valid_tile_kv(tile_m, tile_n, false)) return TSDPA_ERR_BAD_TILE;
+    *splits = pick_splits(B * H, Sq, Skv, tile_m, tile_n);
+    return TSDPA_OK;
+}
+
 int tiled_sdpa_fwd_kv(const void *q, const void *k, const void *v, void *o, float *lse,
                       int B, int H, int Sq, int Skv, int D, float scale, int dtype, void *stream,
                       int tile_m, int tile_n, unsigned flags,
@@ -547,7 +556,15 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     if (std::isnan(scale)) scale = 1.0f / std::sqrt((float)D);
     if (std::isinf(scale)) return TSDPA_ERR_BAD_SCALE;
     if (splits < 0 || splits > TSDPA_MAX_SPLITS) return TSDPA_ERR_BAD_SPLITS;
-    if (splits == 0) splits = heuristic_tile ? default_splits(B * Hkv, rows, Skv, D) : pick_splits(B * Hkv, rows, Skv, tile_m, tile_n);
+    if (splits == 0) {
+        splits = default_splits(B * Hkv, rows, Skv, D);
+        if (!heuristic_tile) {
+            // the tile's own count, unless the workspace holds the states of the default count only (a caller may have sized it by
+            // tiled_sdpa_kv_default_splits, which speaks of forms that an explicit tile never takes)
+            const int own = pick_splits(B * Hkv, rows, Skv, tile_m, tile_n);
+            if (own <= splits || (workspace && workspace_bytes >= tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, own))) splits = own;
+        }
+    }
     // Long query blocks against a dense cache of one length, no mask, no split: the 256-row query tile of the
     // square problem, under the same conditions (with 256 such workgroups the 128-row tile has 512 and is not
     // split either, so the split count does not depend on this choice)

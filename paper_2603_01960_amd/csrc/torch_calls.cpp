@@ -282,11 +282,13 @@ PyObject *call_sdpa(PyObject *, PyObject *const *args, Py_ssize_t n)
     });
 }
 
-// The split count of a call that leaves it to the library (which sees B * Hkv heads of G * Sq rows each).
-int heuristic_splits(int B, int H, int Hkv, int Sq, int Skv, int D, int dtype, unsigned flags, bool drop_causal, int *splits)
+// The split count of a call that leaves it to the library (which sees B * Hkv heads of G * Sq rows each).  A tile that the library
+// does not offer is for the call itself to refuse, after the checks that come before that one.
+int heuristic_splits(int B, int H, int Hkv, int Sq, int Skv, int D, int dtype, unsigned flags, bool drop_causal, Tile tile, int *splits)
 {
-    return tiled_sdpa_kv_default_splits(B, Hkv, (int)((int64_t)(H / Hkv) * Sq), Skv, D, dtype,
-                                        drop_causal ? flags & ~(unsigned)TSDPA_FLAG_CAUSAL : flags, splits);
+    const int st = tiled_sdpa_kv_tile_splits(B, Hkv, (int)((int64_t)(H / Hkv) * Sq), Skv, D, dtype,
+                                             drop_causal ? flags & ~(unsigned)TSDPA_FLAG_CAUSAL : flags, tile.m, tile.n, splits);
+    return st == TSDPA_ERR_BAD_TILE ? TSDPA_OK : st;
 }
 
 // sdpa_kv(q, k, v, causal, scale, splits, return_lse, out, workspace, tile, flags, kv_lens)
@@ -319,7 +321,7 @@ PyObject *call_sdpa_kv(PyObject *, PyObject *const *args, Py_ssize_t n)
         at::Tensor out = output(args[7], q, "out must match q in shape, dtype, device and be contiguous"), lse;
         if (with_lse) lse = empty(s.slice(0, 3), at::kFloat, q);
         if (splits == 0) {
-            const int st = heuristic_splits(B, H, Hkv, Sq, Skv, D, dtype, flags, H != Hkv, &splits);
+            const int st = heuristic_splits(B, H, Hkv, Sq, Skv, D, dtype, flags, H != Hkv, tile, &splits);
             if (st != TSDPA_OK) return PyLong_FromLong(st);
         }
         const Workspace ws(args[8], tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits), q);
@@ -372,7 +374,7 @@ PyObject *call_sdpa_paged(PyObject *, PyObject *const *args, Py_ssize_t n)
         if (splits == 0) {
             const int64_t rows = (int64_t)max_blocks * block_rows;
             if (rows > std::numeric_limits<int>::max()) return PyLong_FromLong(TSDPA_ERR_BAD_SHAPE);
-            const int st = heuristic_splits(B, H, Hkv, Sq, rows > 1 ? (int)rows : 1, D, dtype, flags, true, &splits);
+            const int st = heuristic_splits(B, H, Hkv, Sq, rows > 1 ? (int)rows : 1, D, dtype, flags, true, tile, &splits);
             if (st != TSDPA_OK) return PyLong_FromLong(st);
         }
         const Workspace ws(args[10], tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits), q);
