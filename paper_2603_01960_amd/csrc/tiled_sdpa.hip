@@ -3,6 +3,7 @@
 #include "tiled_sdpa.h"
 
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <limits>
@@ -174,9 +175,13 @@ int pick_splits(int BH, int Sq, int Skv, int tm, int tn)
 // scrambled (the splitmix64 finaliser, a bijection) so that it looks like no data anybody would store.
 unsigned long long call_ticket()
 {
-    static std::atomic<unsigned long long> counter{[] {
-        std::random_device rd;
-        return ((unsigned long long)rd() << 32) ^ rd();
+    static std::atomic<unsigned long long> counter{[]() noexcept {
+        try {
+            std::random_device rd;
+            return ((unsigned long long)rd() << 32) ^ rd();
+        } catch (...) {          // no random source: the time in nanoseconds, and where the loader put this library
+            return (unsigned long long)std::chrono::system_clock::now().time_since_epoch().count() ^ ((unsigned long long)(uintptr_t)&kVersion << 24);
+        }
     }()};
     unsigned long long x = counter.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
     x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
