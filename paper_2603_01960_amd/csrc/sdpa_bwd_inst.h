@@ -140,7 +140,7 @@ inline bool bwd_in_one_launch(int D, int heads, int S)
     if (S <= (D == 64 ? 128 : 64)) return true;
     if (heads < 110) return false;
     if (D == 64 || S <= 128) return true;
-    return heads % 256 == 0 || heads * 10 >= (heads + 255) / 256 * 256 * 7;
+    return heads * 10 >= (heads + 255) / 256 * 256 * 7;
 }
 
 template <typename T, int D, bool GRP>

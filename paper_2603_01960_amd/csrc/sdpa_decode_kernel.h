@@ -27,7 +27,6 @@
 namespace tsdpa {
 
 constexpr int kDecodeTile = 32;                   // keys per tile
-constexpr int kDecodeMaxRows = 32;                // query rows per key/value head
 
 template <typename T> struct Elem16;
 template <> struct Elem16<_Float16> {

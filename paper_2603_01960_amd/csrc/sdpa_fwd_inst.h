@@ -79,15 +79,17 @@ int launch_dispatch_tn64(int tile_m, const LaunchArgs &a)
     return tile_m == 64 ? launch_one<T, D, 2, 64>(a) : launch_one<T, D, 4, 64>(a);
 }
 
-// Streams (a.streams > 1): tile_m / 32 wavefronts each, 32-row K/V tiles; the forms that pick_streams
-// (tiled_sdpa.hip) chooses from.
+// Streams (a.streams > 1): tile_m / 32 wavefronts each, 32-row K/V tiles; the forms that pick_streams and
+// pick_streams_kv (tiled_sdpa.hip) choose from.
 template <typename T, int D, int KV>
 int launch_streams(int tile_m, const LaunchArgs &a)
 {
     switch (tile_m * 10 + a.streams) {
         case 324: return launch_one<T, D, 1, 32, KV, 4>(a);
         case 642: return launch_one<T, D, 2, 32, KV, 2>(a);
-        case 1282: return launch_one<T, D, 4, 32, KV, 2>(a);
+        case 1282:
+            if constexpr (KV == 0) return launch_one<T, D, 4, 32, KV, 2>(a);
+            break;
         case 643:
             if constexpr (D == 160) return launch_one<T, D, 2, 32, KV, 3>(a);
             break;
