@@ -25,3 +25,13 @@ def test_dense_caches(D, dtype):
         q, k, v = kv.make_q_kv(B, H, Sq, Skv, D, dtype, seed=9000 + Sq)
         kv.check_kv(q, k, v, dtype, causal=True, tag="streams causal")
         kv.check_kv(q, k, v, dtype, tag="streams")
+
+
+@pytest.mark.parametrize("D,dtype", [(64, "bf16"), (96, "f16"), (128, "bf16"), (160, "f16")])
+def test_causal_order_of_streams(D, dtype):
+    """More than 256 workgroups of 64 rows: the long-tiles-first order beside streams; whole and folded heads, an entry of every
+    length."""
+    q, k, v = kv.make_q_kv(1, 70, 256, 1100, D, dtype, seed=9100)
+    kv.check_kv(q, k, v, dtype, causal=True, tag="streams, ordered")
+    kv.check_kv_lens(35, 8, 2, 64, 1024, D, dtype, [(31 * i) % 1025 for i in range(35)], True, 0)
+    kv.check_kv_lens(24, 12, 3, 50, 1100, D, dtype, [1100 - 45 * i for i in range(24)], True, 2)
