@@ -365,7 +365,12 @@ def bench_kv(pkg, torch, args, tile, flags):
     if roofline["bound"] == "hbm" and not args.no_ceilings:
         roofline["hbm_read_ceiling_GBs"] = hbm_read_ceiling(pkg, torch)
         roofline["frac_of_hbm_read_ceiling"] = round(roofline["achieved"] / roofline["hbm_read_ceiling_GBs"], 4)
-    roofline.update({"traffic": None, "kernel": "sdpa_fwd_kernel<KV> + sdpa_merge_kernel" if splits > 1 else "sdpa_fwd_kernel<KV>",
+    rows = G * Sq                       # (17 to 32 rows: the decoding kernel where the heads are many)
+    kernel = ("sdpa_fwd_kernel<KV>" if tile or rows > 32 else "sdpa_decode_kernel" if rows <= 16 or B * Hkv > 64 else
+              "sdpa_decode_kernel or sdpa_fwd_kernel<KV>")
+    if splits > 1:                      # (the decoding kernel combines up to 64 states per head itself)
+        kernel += " + sdpa_merge_kernel" if rows > 16 or splits * rows > 64 or tile else ""
+    roofline.update({"traffic": None, "kernel": kernel,
                      "ms_avg_both_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
                      "compulsory_hbm_bytes_per_launch": comp_bytes})
     print(json.dumps({
@@ -378,8 +383,20 @@ def bench_kv(pkg, torch, args, tile, flags):
         "roofline": roofline}), flush=True)
 
 
+def bwd_kernels(D, heads, S, grouped):
+    """(kernels of a backward call, products of S x S x D that they execute per query head): one launch for short sequences of
+    whole heads (bwd_in_one_launch of csrc/sdpa_bwd_inst.h), else scores and dP once per pass: 7 products, 8 at D = 160."""
+    if D <= 96 and not grouped and S <= 256:
+        rounds = -(-heads // 256)
+        if S <= (128 if D == 64 else 64) or (heads >= 110 and (D == 64 or S <= 128 or 10 * heads >= 7 * 256 * rounds)):
+            return "sdpa_bwd_short_kernel", 5
+    if D == 160:
+        return "sdpa_bwd_kernel<dQ> + sdpa_bwd_kernel<dV> + sdpa_bwd_kernel<dK>", 8
+    return "sdpa_bwd_kernel<dQ> + sdpa_bwd_kernel<dK+dV>", 7
+
+
 def bench_bwd(pkg, torch, args, flags):
-    """One JSON line for tiled_sdpa_bwd on a workload (its three kernels timed as one step; the forward
+    """One JSON line for tiled_sdpa_bwd on a workload (its kernels timed as one step; the forward
     pass that provides o and lse, the gradients and the workspace are set up outside the timed region)."""
     from paper_2603_01960_amd.workloads import WORKLOADS, Workload, make_qkv, make_workload
     if args.shape:
@@ -417,6 +434,7 @@ def bench_bwd(pkg, torch, args, flags):
     # five S x S x D products (scores, dP, dV, dK, dQ) of 2*B*H*S^2*D flops each; half under the causal mask
     flops = 2.5 * w.flops * (0.5 if causal else 1.0)
     tf = flops / (ms * 1e-3) / 1e12
+    kernels, products = bwd_kernels(w.D, w.B * w.H, w.S, Hkv != w.H)
     print(json.dumps({
         "metric": "SDPA backward TFLOP/s (10*B*H*S^2*D / t)", "value": round(flops / (wall_ms * 1e-3) / 1e12, 2),
         "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(wall_ms, 5),
@@ -425,13 +443,10 @@ def bench_bwd(pkg, torch, args, flags):
                                f"{'' if Hkv == w.H else f' (kv heads {Hkv})'} S={w.S} D={w.D} {dtype}"},
         "roofline": {"bound": "mfma", "achieved": round(tf, 2), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tf / PEAK_MFMA_TFLOPS, 4),
-                     # all four kernels of a call, FETCH_SIZE + WRITE_SIZE scaled (profiles/sdpa_bwd_C4_C2.md)
-                     "traffic": 2515.7e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H) else None,
-                     "kernel": ("sdpa_bwd_kernel<dQ> + sdpa_bwd_kernel<dV> + sdpa_bwd_kernel<dK>" if w.D == 160 else
-                                "sdpa_bwd_kernel<dQ> + sdpa_bwd_kernel<dK+dV>"),
-                     "ms_avg_all_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
-                     # scores and dP are recomputed per pass: 7 products with the fused dK + dV pass of D = 64, else 8
-                     "executed_mfma_flops_per_launch": flops * (7.0 if w.D == 64 else 8.0) / 5.0}}), flush=True)
+                     # both kernels of a call, FETCH_SIZE + WRITE_SIZE scaled (profiles/sdpa_bwd_C4_C2.md)
+                     "traffic": 1621.4e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H) else None,
+                     "kernel": kernels, "ms_avg_all_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
+                     "executed_mfma_flops_per_launch": flops * products / 5.0}}), flush=True)
 
 
 TOL = {"f16": 2e-3, "bf16": 1.6e-2}     # max-abs error against the float64 oracle (the task's stated tolerances)
