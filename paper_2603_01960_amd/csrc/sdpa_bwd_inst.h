@@ -38,7 +38,7 @@ int launch_bwd_pass_nw(const BwdLaunchArgs &a)
     // one workgroup per (head of the resident side, tile of its rows): query heads in the dQ pass, key/value heads otherwise
     const int heads = MODE == BWD_DQ ? a.BH : a.BH / a.group;
     const int N = heads * nR;
-    const TileOrder order = tile_order(heads, nR, (long long)(MODE == BWD_DQ ? 1 : a.group) * a.S * D * 2 * (long long)sizeof(T));
+    const TileOrder order = tile_order(heads, nR, a.causal != 0, (long long)(MODE == BWD_DQ ? 1 : a.group) * a.S * D * 2 * (long long)sizeof(T));
     void *out = MODE == BWD_DQ ? a.dq : (MODE == BWD_DV ? a.dv : a.dk);
     hipLaunchKernelGGL(kern, dim3(N), dim3(NW * NS * 64), lds_bytes, a.stream,
                        (const T *)a.q, (const T *)a.k, (const T *)a.v, (const T *)a.dout, (const T *)a.o, a.lse, a.stats,

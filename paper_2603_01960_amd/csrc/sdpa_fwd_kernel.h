@@ -203,11 +203,11 @@ template <typename T, int D, int NW, int TILE, int WPS, int KVM>
 __global__ void __launch_bounds__(NW * (1 + TILE / 1000) * 64, WPS)  // WPS = wavefronts per SIMD the register budget is sized for
 sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                 T *__restrict__ o, float *__restrict__ lse, int S, int nQ, int N, float c,
-                float tau, uint32_t qsign, int linear_grid, int causal,
+                float tau, uint32_t qsign, int linear_grid, int causal, TileOrder order,      // (128 bytes up to here: two lines)
                 int Skv_arg, int splits_arg, float *__restrict__ ws, int rows_per_head,
                 const int *__restrict__ kv_lens, int heads_per_batch,
                 const int *__restrict__ block_table, int max_blocks, int block_shift, int tile_rot,
-                TileOrder order, int batches)
+                int batches)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses device-only types
     constexpr bool KV = KVM != 0, PAGED = KVM == 2;

@@ -64,22 +64,29 @@ inline CausalChunks causal_chunks(int heads, int tiles, long long stream_bytes, 
 struct Divisor { uint32_t mul, shift; };
 inline Divisor divisor(uint32_t d)
 {
-    uint32_t shift = 0;
-    while ((1ull << shift) < d) ++shift;
+    const uint32_t shift = d <= 1 ? 0 : 32 - __builtin_clz(d - 1);
     return Divisor{(uint32_t)(((1ull << (31 + shift)) + d - 1) / d), shift};
 }
 
-// What a kernel needs to find its workgroup's head and tile: `tiles` per head, and the chunks of the causal order.
+// What a kernel needs to find its workgroup's head and tile: `tiles` per head, and the chunks of the causal order (heads = 0
+// where it is not taken; the divisors after it are then not looked at).
 struct TileOrder {
     Divisor by_tiles;
     int first, heads;          // CausalChunks
     Divisor by_chunk, by_first, by_full;    // heads * tiles, first, 8 * heads
 };
-inline TileOrder tile_order(int heads, int tiles, long long stream_bytes, bool wide = false)
+inline TileOrder tile_order(int heads, int tiles, bool causal, long long stream_bytes, bool wide = false)
 {
+    TileOrder order{divisor((uint32_t)tiles), heads, 0, {}, {}, {}};
+    if (!causal) return order;
     const CausalChunks c = causal_chunks(heads, tiles, stream_bytes, wide);
-    auto by = [](long long d) { return divisor((uint32_t)(d > 0 ? d : 1)); };
-    return TileOrder{by(tiles), c.first, c.heads, by((long long)c.heads * tiles), by(c.first), by(8ll * c.heads)};
+    if (c.heads == 0) return order;
+    order.first = c.first;
+    order.heads = c.heads;
+    order.by_chunk = divisor((uint32_t)(c.heads * tiles));
+    order.by_first = divisor((uint32_t)c.first);
+    order.by_full = divisor((uint32_t)(8 * c.heads));
+    return order;
 }
 
 // Rows of slack after the B*H*S entries of each backward statistics array: the keys-resident pass
