@@ -13,7 +13,7 @@
 // then (m, l) pairs as float [BH][splits][S][2].
 //
 // Two kernels.  sdpa_merge_kernel: one thread produces 4 consecutive output columns and walks the
-// splits itself, eight loads in flight at a time; right for up to eight splits, and for any split count
+// splits itself, four of them in flight at a time; right for up to eight splits, and for any split count
 // when the rows are many (a long prefill chunk), where the other threads hide the waiting.
 // sdpa_merge_wide_kernel: one workgroup per output row, kMergeLanes threads per column group that
 // take every kMergeLanes-th split each and combine through the LDS; for the many splits of a decoding
@@ -31,6 +31,7 @@ sdpa_merge_kernel(const float *__restrict__ ws, T *__restrict__ o, float *__rest
                   int BH, int S, int D, int splits)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef T vec4 __attribute__((ext_vector_type(4)));
     const int d4n = D / 4;
@@ -43,22 +44,39 @@ sdpa_merge_kernel(const float *__restrict__ ws, T *__restrict__ o, float *__rest
     const float *ml = ws + rows * splits * D;
     const size_t first = (bh * splits) * S + row; // split s sits s*S rows further on
 
-    // both loops are chains of independent loads: unrolled so that eight of them are in flight at a time
-    // (with many splits and few rows this kernel is pure load latency)
+    // independent loads: unrolled so that eight of them are in flight at a time (this kernel is mostly load latency)
     float M = -INFINITY;
 #pragma unroll 8
     for (int s = 0; s < splits; ++s) M = fmaxf(M, ml[(first + (size_t)s * S) * 2]);
     float L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int s = 0; s < splits; ++s) {
-        const size_t p = first + (size_t)s * S;
-        // 0 for a split with m = -inf; M itself is -inf only for a row that no key reaches (an empty
-        // cache entry, or a causal limit before the first key): all weights 0, O = 0, LSE = -inf
-        const float w = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[p * 2] - M);
-        L += w * ml[p * 2 + 1];
-        const f32x4 part = *(const f32x4 *)(ws + p * D + d4 * 4);
-        if (ml[p * 2 + 1] != 0.f) acc += w * part; // (a split without keys, l = 0, may have left its o unwritten; a NaN row has l = NaN)
+    // four splits at a time, all their loads before the first use: stated by hand, because a load that only a condition needs is
+    // moved behind that condition, and the walk becomes a chain of load latencies (BF16, 4096 rows of D = 160 against
+    // 16384 ... 32768 keys in pages: the call 90.4 us with each load behind a condition, 82.8 so)
+    for (int s0 = 0; s0 < splits; s0 += 4) {
+        f32x2 st[4];
+        f32x4 part[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const size_t p = first + (size_t)(s0 + i < splits ? s0 + i : splits - 1) * S;
+            st[i] = *(const f32x2 *)(ml + p * 2);
+            part[i] = *(const f32x4 *)(ws + p * D + d4 * 4);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(st[i]), "+v"(part[i]));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (s0 + i >= splits) break;
+            // 0 for a split with m = -inf; M itself is -inf only for a row that no key reaches (an empty
+            // cache entry, or a causal limit before the first key): all weights 0, O = 0, LSE = -inf
+            const float e = __builtin_amdgcn_exp2f(st[i][0] - M), w = M == -INFINITY ? 0.f : e;
+            L += w * st[i][1];
+            // (a split without keys, l = 0, may have left its o unwritten; a NaN row has l = NaN)
+            const f32x4 sum = acc + w * part[i];
+            const bool keys = st[i][1] != 0.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] = keys ? sum[c] : acc[c];
+        }
     }
     const float inv = M == -INFINITY ? 0.f : 1.0f / L;
     vec4 out;
