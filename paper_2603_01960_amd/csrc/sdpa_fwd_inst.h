@@ -46,7 +46,11 @@ int launch_one(const LaunchArgs &a)
     // Square problem, plain form, up to three workgroups per CU (768), up to three tiles per head or D = 64: sixteen heads per XCD and chunk instead of eight
     // (us, plain order / eight / sixteen: 231 heads of S = 384 D = 64 14.7 / 15.4 / 13.6, D = 96 18.6 / 19.1 / 17.7; 224 of S =
     // 364 D = 160 29.5 / 28.7 / 26.2; with more tiles eight are ahead: 130 of S = 640 D = 128 29.2 / 25.9 / 27.4).
-    TileOrder order = tile_order(heads, nQ, a.causal != 0, a.kv_lens ? 0 : (long long)(KV ? a.Skv : a.S) * D * 2 * (long long)sizeof(T),
+    // (against a cache the tiles of a head are uneven by the queries' share of the keys only; below a twelfth of the capacity
+    // the plain order: 32 entries of 286 queries, 8192 ... 16384 keys, D = 64 587 -> 550 us, 300 queries of 16384 keys D = 96 575 ->
+    // 562, where 1024 queries of 2048 keys go 47.6 -> 44.2 with the causal order, 2048 of 8192 222.6 -> 215.6)
+    const bool uneven = a.causal != 0 && (!KV || (long long)a.rows_per_head * 12 >= a.Skv);
+    TileOrder order = tile_order(heads, nQ, uneven, a.kv_lens ? 0 : (long long)(KV ? a.Skv : a.S) * D * 2 * (long long)sizeof(T),
                                  !KV && NS == 1 && (nQ <= 3 || D == 64));
     // Two tiles of about the same work (33 ... 64 rows in the second: two wavefronts of six steps against four of four) in up to
     // two rounds: there is no long one to start first, and the plain order keeps a head's tiles together (576 heads of S = 171,
@@ -56,7 +60,7 @@ int launch_one(const LaunchArgs &a)
                        (const T *)a.q, (const T *)a.k, (const T *)a.v, (T *)a.o, a.lse,
                        a.S, nQ, N, a.c, a.tau, a.qsign, a.linear_grid, a.causal, order,
                        a.Skv, a.splits, a.ws, a.rows_per_head, a.kv_lens, a.heads_per_batch,
-                       a.block_table, a.max_blocks, a.block_shift, a.tile_rot, a.batches);
+                       a.block_table, a.max_blocks, a.block_shift, a.tile_rot, a.batches, divisor((uint32_t)(KV ? a.batches : 1)));
     return (int)hipGetLastError();
 }
 

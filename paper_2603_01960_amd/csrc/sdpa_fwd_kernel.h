@@ -207,7 +207,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 int Skv_arg, int splits_arg, float *__restrict__ ws, int rows_per_head,
                 const int *__restrict__ kv_lens, int heads_per_batch,
                 const int *__restrict__ block_table, int max_blocks, int block_shift, int tile_rot,
-                int batches)
+                int batches, Divisor by_batches)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses device-only types
     constexpr bool KV = KVM != 0, PAGED = KVM == 2;
@@ -267,8 +267,13 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     int head = KV ? hs / splits : hs;
     const int sp = KV ? hs - head * splits : 0;
     // Cache entries differ in length: batch entries vary fastest over the workgroups, so that each XCD gets a share of
-    // every entry (head by head, the XCD with the longest entry finishes last).
-    if (KV && kv_lens != nullptr) head = (head % batches) * heads_per_batch + head / batches;
+    // every entry (head by head, the XCD with the longest entry finishes last).  Not with one query tile per head, where nobody
+    // shares a head's keys: BF16, 32 entries of 16 heads, 64 queries, 410 ... 4096 keys in pages, 126 us head by head, 133 dealt
+    // (with 16 tiles per head, 4 entries of 8 heads, 4096 ... 8192 keys, 217 / 187).
+    if (KV && kv_lens != nullptr && nQ > 1) {
+        const int h = divide(head, by_batches);
+        head = (head - h * batches) * heads_per_batch + h;
+    }
     const size_t head_off = (size_t)head * (size_t)S * D;
     const size_t kv_off = (size_t)head * (size_t)(KV ? Skv_arg : S) * D;
     // key rows of this head; S is the number of query rows
