@@ -43,15 +43,16 @@ int launch_one(const LaunchArgs &a)
     const int heads = a.BH * (KV ? a.splits : 1);
     const int N = heads * nQ;
     // (entries of different lengths: eight heads per XCD and chunk whatever they stream, for the balance between them)
-    // Square problem, plain form, up to three workgroups per CU (768), up to three tiles per head or D = 64: sixteen heads per XCD and chunk instead of eight
-    // (us, plain order / eight / sixteen: 231 heads of S = 384 D = 64 14.7 / 15.4 / 13.6, D = 96 18.6 / 19.1 / 17.7; 224 of S =
-    // 364 D = 160 29.5 / 28.7 / 26.2; with more tiles eight are ahead: 130 of S = 640 D = 128 29.2 / 25.9 / 27.4).
+    // Square problem, plain form, up to three workgroups per CU (768), up to three tiles per head or D = 64: sixteen heads per XCD
+    // and chunk instead of eight (us, plain order / eight / sixteen: 231 heads of S = 384 D = 64 14.7 / 15.4 / 13.6, D = 96 18.6 /
+    // 19.1 / 17.7; 224 of S = 364 D = 160 29.5 / 28.7 / 26.2; with more tiles eight are ahead: 130 of S = 640 D = 128 29.2 / 25.9 /
+    // 27.4; so they are with up to four tiles and little over two workgroups per CU: 190 of S = 384 D = 64 13.7 / 12.0 / 12.9).
     // (against a cache the tiles of a head are uneven by the queries' share of the keys only; below a twelfth of the capacity
     // the plain order: 32 entries of 286 queries, 8192 ... 16384 keys, D = 64 587 -> 550 us, 300 queries of 16384 keys D = 96 575 ->
     // 562, where 1024 queries of 2048 keys go 47.6 -> 44.2 with the causal order, 2048 of 8192 222.6 -> 215.6)
     const bool uneven = a.causal != 0 && (!KV || (long long)a.rows_per_head * 12 >= a.Skv);
     TileOrder order = tile_order(heads, nQ, uneven, a.kv_lens ? 0 : (long long)(KV ? a.Skv : a.S) * D * 2 * (long long)sizeof(T),
-                                 !KV && NS == 1 && (nQ <= 3 || D == 64));
+                                 !KV && NS == 1 && (nQ <= 4 ? N > (D <= 96 ? 576 : 520) && (nQ <= 3 || D == 64) : D == 64));
     // Two tiles of about the same work (33 ... 64 rows in the second: two wavefronts of six steps against four of four) in up to
     // two rounds: there is no long one to start first, and the plain order keeps a head's tiles together (576 heads of S = 171,
     // D = 64 14.7 -> 14.4, D = 96 19.0 -> 17.6, D = 160 30.9 -> 30.5; 700 of S = 185 2 % at D = 96; beyond two rounds 1-8 % behind)
