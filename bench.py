@@ -99,7 +99,8 @@ def parse_args():
                     help="also write the tile sweep and the per-configuration summary as CSV rows with status and "
                          "status_detail columns (unsupported cells are recorded, not dropped: Section 5 of the paper)")
     ap.add_argument("--no-tune", dest="tune", action="store_false",
-                    help="take the library's heuristic tile; by default the tile is picked with tiled_sdpa_tune_tile "
+                    help="take the library's heuristic (the faster choice for problems of few workgroups, where it runs streams that "
+                         "no explicit tile has); by default the tile is picked with tiled_sdpa_tune_tile "
                          "(the paper's per-shape schedule search, Table 1 and Sections 5.5-5.6) before and outside the timed region")
     ap.add_argument("--no-sweep-tiles", dest="sweep_tiles", action="store_false",
                     help="skip the sweep over every (T_M, T_N) of the workload (the schedule knobs of the paper's Table 1)")

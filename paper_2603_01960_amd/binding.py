@@ -269,7 +269,7 @@ def sdpa_kv(q, k, v, causal: bool = False, scale=None, *, splits: int = 0, retur
             out=None, workspace=None, tile=None, flags: int = 0, kv_lens=None):
     """Attention of q [B, H, Sq, D] over k, v [B, H, Skv, D] (KV-cache / decoding shapes), the key range
     split over ``splits`` workgroups per query tile (0 = heuristic).  Under ``causal`` the queries are
-    the last Sq positions of the sequence.  ``workspace`` (any contiguous device tensor of enough bytes)
+    the last Sq positions of the sequence.  ``workspace`` (any dense tensor of enough bytes on q's device)
     is allocated through torch when not given and needed.
 
     Grouped heads: k, v may be [B, Hkv, Skv, D] with H = G * Hkv, query head h reading key/value head

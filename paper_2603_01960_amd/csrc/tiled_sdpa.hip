@@ -505,8 +505,8 @@ int tiled_sdpa_fwd_kvcache_static(const void *q, const void *k, const void *v, v
         ws = static_scratch_ptr();
         if (ws == nullptr) return TSDPA_ERR_STATIC_SCRATCH;
     }
-    // every word of the split states that the merge kernel reads is written by the attention kernel of
-    // the same call (a split without tiles stores (0, -inf, 0)), so nothing has to be cleared
+    // every word of the split states that the combination uses is written by the attention kernel of the same call ((m, l) of
+    // every split; o of those with l != 0), so nothing has to be cleared
     return fwd_kv_impl(q, k, v, o, lse, kv_lens, nullptr, 0, 0, B, H, Hkv, Sq, Skv, D, scale, dtype, stream, tile_m,
                        tile_n, flags, splits, ws, need);
 }
