@@ -35,3 +35,12 @@ def test_causal_order_of_streams(D, dtype):
     kv.check_kv(q, k, v, dtype, causal=True, tag="streams, ordered")
     kv.check_kv_lens(35, 8, 2, 64, 1024, D, dtype, [(31 * i) % 1025 for i in range(35)], True, 0)
     kv.check_kv_lens(24, 12, 3, 50, 1100, D, dtype, [1100 - 45 * i for i in range(24)], True, 2)
+
+
+@pytest.mark.parametrize("splits", [2, 3, 4, 5, 8, 9, 17])
+def test_merge_of_many_rows(splits):
+    """More than 2048 rows: the merge that walks the splits four at a time, with every remainder; under the mask some splits
+    have no key of a row."""
+    for D, dtype in ((64, "f16"), (160, "bf16")):
+        q, k, v = kv.make_q_kv(3, 1, 700, 900, D, dtype, seed=9200 + splits)
+        kv.check_kv(q, k, v, dtype, splits=splits, causal=splits % 2 == 0, tag="merge, many rows")
