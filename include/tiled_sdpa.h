@@ -294,10 +294,10 @@ unsigned long long tiled_sdpa_kv_workspace_bytes(int B, int H, int Sq, int D, in
  * Kernels enqueued on `stream`: dQ, which also leaves the row statistics in the workspace (Delta_i = <dO_i, O_i> and
  * LSE_i in log2 units; for query rows that see at most 64 keys -- S <= 64, or the first 64 rows under the causal mask --
  * Delta_i by its definition sum_j P_ij dP_ij in FP32, because on such rows the rounding of the 16-bit o inside
- * <dO_i, O_i> is not attenuated by small P_ij); then the keys-resident gradients (one fused dK + dV pass at D = 64, 96
- * and 128, a dV pass and a dK pass at D = 160).  Sequences of up to 256 rows at D = 64 and 96 with H = Hkv may take one
- * kernel for all of it, which leaves the workspace alone.  No sum crosses workgroups, so results are deterministic.  Validation order: dtype, D, shape, empty problem, null
- * pointers, alignment, scale, workspace, launch.
+ * <dO_i, O_i> is not attenuated by small P_ij); then dK and dV in one pass over resident keys.  Sequences of up to 256 rows
+ * at D = 64 and 96 with H = Hkv may take one kernel for all of it, which leaves the workspace alone.  No sum crosses
+ * workgroups, so results are deterministic.  Validation order: dtype, D, shape, empty problem, null pointers, alignment,
+ * scale, workspace, launch.
  */
 int tiled_sdpa_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
                    const float *lse, void *dq, void *dk, void *dv,

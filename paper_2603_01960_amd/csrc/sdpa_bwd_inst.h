@@ -3,22 +3,23 @@
 #include <mutex>
 
 #include "sdpa_bwd_kernel.h"
+#include "sdpa_bwd_pair_kernel.h"
 #include "sdpa_bwd_short_kernel.h"
 #include "sdpa_fwd_launch.h"
 
 namespace tsdpa {
 
-// Tile shapes: 32*NW resident rows per workgroup, TS streamed rows per tile for the dQ / dK / dV / fused pass, the
+// Tile shapes: 32*NW resident rows per workgroup, TS streamed rows per tile for the dQ and the dK + dV pass, the
 // wavefronts per SIMD its register budget is sized for, and whether its second resident operand stays in the LDS.
 // The passes are held by the clock on large problems, so that the choices are within a few per cent of each other
 // there: D = 128, dQ on 64-row tiles 1 % ahead of 32-row ones on large problems, 4 % at S = 1024 of nine heads; D = 96,
-// dQ on 32-row tiles at three wavefronts per SIMD 1-2 % ahead of 64-row ones at two; D = 64, the fused pass on 32-row
+// dQ on 32-row tiles at three wavefronts per SIMD 1-2 % ahead of 64-row ones at two; D = 64, dK + dV on 32-row
 // tiles 1-6 % behind.  D = 160 needs the resident operand in the LDS for two wavefronts per SIMD.
 template <int D> struct BwdShape;
-template <> struct BwdShape<64>  { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 2}, TS[4] = {64, 64, 64, 64}; static constexpr bool R2[4] = {0, 0, 0, 0}, FUSED_DKV = true; };
-template <> struct BwdShape<96>  { static constexpr int NW = 4, WPS[4] = {3, 2, 2, 2}, TS[4] = {32, 32, 64, 32}; static constexpr bool R2[4] = {0, 0, 0, 0}, FUSED_DKV = true; };
-template <> struct BwdShape<128> { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 2}, TS[4] = {64, 32, 64, 32}; static constexpr bool R2[4] = {0, 0, 0, 1}, FUSED_DKV = true; };
-template <> struct BwdShape<160> { static constexpr int NW = 4, WPS[4] = {2, 2, 2, 1}, TS[4] = {32, 32, 32, 32}; static constexpr bool R2[4] = {1, 1, 0, 0}, FUSED_DKV = false; };
+template <> struct BwdShape<64>  { static constexpr int NW = 4, WPS[2] = {2, 2}, TS[2] = {64, 64}; static constexpr bool R2[2] = {0, 0}; };
+template <> struct BwdShape<96>  { static constexpr int NW = 4, WPS[2] = {3, 2}, TS[2] = {32, 32}; static constexpr bool R2[2] = {0, 0}; };
+template <> struct BwdShape<128> { static constexpr int NW = 4, WPS[2] = {2, 2}, TS[2] = {64, 32}; static constexpr bool R2[2] = {0, 1}; };
+template <> struct BwdShape<160> { static constexpr int NW = 4, WPS[2] = {2, 2}, TS[2] = {32, 32}; static constexpr bool R2[2] = {1, 0}; };
 
 template <typename T, int D, int MODE, bool GRP, int NW, int NS, int TS, int WPS>
 int launch_bwd_pass_nw(const BwdLaunchArgs &a)
@@ -39,7 +40,7 @@ int launch_bwd_pass_nw(const BwdLaunchArgs &a)
     const int heads = MODE == BWD_DQ ? a.BH : a.BH / a.group;
     const int N = heads * nR;
     const TileOrder order = tile_order(heads, nR, a.causal != 0, (long long)(MODE == BWD_DQ ? 1 : a.group) * a.S * D * 2 * (long long)sizeof(T));
-    void *out = MODE == BWD_DQ ? a.dq : (MODE == BWD_DV ? a.dv : a.dk);
+    void *out = MODE == BWD_DQ ? a.dq : a.dk;
     hipLaunchKernelGGL(kern, dim3(N), dim3(NW * NS * 64), lds_bytes, a.stream,
                        (const T *)a.q, (const T *)a.k, (const T *)a.v, (const T *)a.dout, (const T *)a.o, a.lse, a.stats,
                        (T *)out, (T *)(MODE == BWD_DKV ? a.dv : nullptr), a.S, nR, N, a.c, a.scale, a.rsign, a.causal, a.stat_bytes, a.group,
@@ -79,8 +80,7 @@ inline BwdForm pick_bwd_form(int D, bool causal, bool keys_resident, long long n
     if (n <= 256) {
         if (!causal) return chain >= (keys_resident ? 16 : 32) ? BwdForm{4, 2} : plain;
         if (chain >= 64) return D == 64 ? BwdForm{1, 4} : BwdForm{2, D == 160 ? 3 : 4};
-        if (chain >= (D == 160 ? 32 : 16)) return BwdForm{2, 2};
-        return D == 160 && keys_resident && chain >= 16 ? BwdForm{4, 2} : plain;
+        return chain >= (D == 160 ? 32 : 16) ? BwdForm{2, 2} : plain;
     }
     if (n <= 400 && causal && chain >= 64) return D == 160 || (D == 128 && keys_resident) ? BwdForm{4, 2} : BwdForm{2, 2};
     return plain;
@@ -143,19 +143,30 @@ inline bool bwd_in_one_launch(int D, int heads, int S)
     return heads * 10 >= (heads + 255) / 256 * 256 * 7;
 }
 
+// Pairs and streams of the dK + dV pass at D = 160, by the workgroups of 128 keys and the 32-row steps of their chains; from
+// timings of four forms on 200 shapes (BF16, us).  Few workgroups: one pair and two streams (S = 2187 of one head 99.5 with
+// four pairs, 62.2), as many as fit; up to 150, and to 400 whose chains run over a group's heads: two of both (two
+// entries of 16 heads over 4, S = 4096: 10-15 %).  Else two pairs, two workgroups per CU, 2-10 % ahead of four on causal
+// and short problems; four pairs, which read a tile once for 128 keys, 3-4 % ahead on long ones without the mask (32 heads,
+// S = 8192: 2084 / 2002).
+template <typename T, int D, bool GRP>
+int launch_bwd_pairs(const BwdLaunchArgs &a)
+{
+    const long long nk = (long long)(a.BH / a.group) * ((a.S + 127) / 128), chain = (long long)a.group * ((a.S + 31) / 32);
+    if (chain > 3 && nk <= 75) return launch_bwd_pair<T, D, 1, 2, true>(a);
+    if (chain > 3 && (nk <= 153 || (nk <= 400 && chain > 140))) return launch_bwd_pair<T, D, 2, 2, true>(a);
+    if (!a.causal && a.S >= 600 && nk >= 430) return launch_bwd_pair<T, D, 4, 1, GRP>(a);
+    return launch_bwd_pair<T, D, 2, 1, GRP>(a);
+}
+
 template <typename T, int D, bool GRP>
 int launch_bwd_passes(const BwdLaunchArgs &a)
 {
-    // the dQ pass leaves the statistics of the query rows for the others
-    int err = launch_bwd_pass<T, D, BWD_DQ, GRP>(a);
+    // the dQ pass leaves the statistics of the query rows for the other
+    const int err = launch_bwd_pass<T, D, BWD_DQ, GRP>(a);
     if (err != 0) return err;
-    if constexpr (BwdShape<D>::FUSED_DKV) {
-        return launch_bwd_pass<T, D, BWD_DKV, GRP>(a);
-    } else {
-        err = launch_bwd_pass<T, D, BWD_DV, GRP>(a);
-        if (err != 0) return err;
-        return launch_bwd_pass<T, D, BWD_DK, GRP>(a);
-    }
+    if constexpr (D == 160) return launch_bwd_pairs<T, D, GRP>(a);
+    else return launch_bwd_pass<T, D, BWD_DKV, GRP>(a);
 }
 
 template <typename T, int D>

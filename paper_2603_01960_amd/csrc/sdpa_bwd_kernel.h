@@ -8,18 +8,18 @@
 //     dS_ij = P_ij (dP_ij - Delta_i),   Delta_i = <dO_i, O_i>   (= sum_j P_ij dP_ij)
 //     dQ_i  = scale * sum_j dS_ij k_j,  dK_j = scale * sum_i dS_ij q_i
 //
-// Passes over the S x S score plane, all instances of ONE kernel template, so that no sum crosses workgroups (no
-// atomics, deterministic results):
+// Two passes over the S x S score plane, instances of ONE template, so that no sum crosses workgroups (no atomics,
+// deterministic results):
 //   * BWD_DQ: a workgroup owns 32*NW query rows (Q and dO rows resident), streams K and V tiles; it also computes the
 //     statistics of its rows (-Delta, LSE in log2 units) for the passes after it;
-//   * BWD_DKV: a workgroup owns 32*NW key rows (K and V rows resident), streams Q and dO tiles; two accumulators;
-//   * BWD_DK, BWD_DV: its two halves as passes of their own (D = 160, where two accumulators do not fit).
+//   * BWD_DKV: a workgroup owns 32*NW key rows (K and V rows resident), streams Q and dO tiles; two accumulators (D = 160,
+//     where they do not fit one wavefront: sdpa_bwd_pair_kernel.h).
 // With R the resident and T the streamed rows, a pass computes, per streamed tile,
-//     acc[t][r]  = <T1_t, R1_r>  (scores)        acc2[t][r] = <T2_t, R2_r>  (dP; not in BWD_DV)
+//     acc[t][r]  = <T1_t, R1_r>  (scores)        acc2[t][r] = <T2_t, R2_r>  (dP)
 //     out^T[d][r] += sum_t T1[t][d] dS[t][r]     (dQ^T or dK^T)
 //     out^T[d][r] += sum_t T2[t][d] P[t][r]      (dV^T)
 // (T1, T2, R1, R2) = (K, V, Q, dO) or (Q, dO, K, V).  The scores and dP are thus computed twice (7 S x S x D products
-// against the 5 of the formulas; 8 at D = 160): the price of summing nothing across workgroups.
+// against the 5 of the formulas): the price of summing nothing across workgroups.
 // What bounds it: the matrix pipe and the clock under its power limit; what decides is that every pass fits 256
 // registers per lane (two wavefronts per SIMD, of which one does matrix work while the other is in its exponentials).
 // That took three things: the step exists ONCE in the loop (with copies of it for the two LDS slots and for masked
@@ -28,8 +28,8 @@
 // dK and dV as two passes (8 products), D = 160 ran one wavefront per SIMD, and the statistics had kernels of their own.
 // BF16, 64 heads, S = 8192, ms per call before / now: D = 64 3.73 / 3.63, D = 96 6.27 / 5.08, D = 128 7.88 / 6.38,
 // D = 160 12.9 / 10.7; S = 2048 causal, us: D = 64 205 / 145, D = 96 335 / 198, D = 128 428 / 253, D = 160 644 / 425.
-// Since then the dP accumulators start from -Delta, the operand kept in the LDS lies in operand order, and at D = 160 two
-// workgroups of the dK pass share a CU: 64 heads, S = 4096, us, D = 64 931 / 907, D = 128 1628 / 1612, D = 160 2657 / 2385.
+// Since then the dP accumulators start from -Delta and the operand kept in the LDS lies in operand order: 64 heads, S =
+// 4096, us, D = 64 931 / 907, D = 128 1628 / 1612.
 // The MFMA formulation is the forward kernel's:
 // transposed accumulators (a lane owns one resident row), P and dS handed to the second product
 // straight from the accumulator registers as B-operands, the streamed tile read row-wise for the
@@ -80,9 +80,9 @@ template <int D> struct BwdGeom {
     static constexpr int LCP = D == 64 ? 2 : D == 128 ? 1 : CPR / 4;
 };
 
-// BWD_DKV is the dK and dV passes in one (scores and P computed once for both): two output accumulators, which fits
-// 256 registers per lane (two wavefronts per SIMD) up to D = 128.
-enum { BWD_DQ = 0, BWD_DK = 1, BWD_DV = 2, BWD_DKV = 3 };
+// BWD_DKV: scores and P computed once for dK and dV; two output accumulators, which fit 256 registers per lane (two
+// wavefronts per SIMD) up to D = 128.
+enum { BWD_DQ = 0, BWD_DKV = 1 };
 
 // Delta_i of query rows that see at most this many keys (the first rows under the causal mask; every row of a sequence
 // of up to so many) is taken from its definition  Delta_i = sum_j P_ij dP_ij  in FP32.  <dO_i, O_i> equals it only in
@@ -92,9 +92,6 @@ constexpr int kBwdShortRow = 64;
 
 // LDS of one stream of tiles: two slots per tensor and, in the keys-resident passes, of the row statistics.
 template <int D, int TS, int MODE> constexpr int bwd_stream_bytes() { return 4 * BwdGeom<D>::bytes(TS) + (MODE != BWD_DQ ? 2 * 2 * TS * 4 : 0); }
-// k-steps of a second resident operand kept in the LDS that stay in registers all the same: one at D = 160 in the
-// keys-resident pass, where all ten of them and the statistics would be 1 KiB too much for two workgroups per CU.
-template <int D, int MODE> constexpr int bwd_resident_regs() { return D == 160 && MODE != BWD_DQ ? 1 : 0; }
 
 // GRP: grouped heads, G query heads reading one key/value head (query head h the head h / G).  The
 // dQ pass then streams the K and V of its query head's group; the keys-resident passes run one
@@ -108,15 +105,15 @@ template <int D, int MODE> constexpr int bwd_resident_regs() { return D == 160 &
 // of few workgroups, whose wavefronts would wait through the whole chain alone (the choice and its figures: pick_bwd_form).
 // The dQ pass runs first: it has the query rows, so it computes their statistics (Delta_i, and LSE_i in log2 units) in
 // its prologue and leaves them in `stats` for the keys-resident passes.
-template <typename T, int D, int NW, int NS, int TS, int WPS, int MODE, bool GRP, bool R2LDS>
-__global__ void __launch_bounds__(NW * NS * 64, WPS)
-sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
-                const T *__restrict__ dout, const T *__restrict__ o, const float *__restrict__ lse,
-                float *__restrict__ stats,   // -Delta [B*H*S + slack], then LSE in log2 units likewise
-                T *__restrict__ out,   // dQ, dK or dV
-                T *__restrict__ out2,  // dV of the fused dK + dV pass, else unused
-                int S, int nR, int N, float c, float scale, uint32_t rsign, int causal, unsigned stat_bytes,
-                int group, TileOrder order)
+template <typename T, int D, int NW, int NS, int TS, int MODE, bool GRP, bool R2LDS, bool HAVE_STATS>
+__device__ __forceinline__ void
+bwd_pass(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
+         const T *__restrict__ dout, const T *__restrict__ o, const float *__restrict__ lse,
+         float *__restrict__ stats,   // -Delta [B*H*S + slack], then LSE in log2 units likewise
+         T *__restrict__ out,   // dQ or dK
+         T *__restrict__ out2,  // dV of the keys-resident pass, else unused
+         int S, int nR, int N, float c, float scale, uint32_t rsign, int causal, unsigned stat_bytes,
+         int group, const TileOrder &order, const int block)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using E = Elem<T>;
@@ -124,9 +121,8 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     using vec4 = typename E::vec4;
     using G = BwdGeom<D>;
     constexpr bool KEYS_RES = MODE != BWD_DQ;
-    constexpr bool NEED_DP = MODE != BWD_DV;      // dP product and Delta
     constexpr bool FUSED = MODE == BWD_DKV;       // P kept next to dS, second accumulator for dV
-    static_assert(NEED_DP || !R2LDS, "the dV pass has no second resident operand");
+    static_assert(!KEYS_RES || D != 160, "the keys-resident pass of D = 160 is sdpa_bwd_pair_kernel");
     constexpr int RM = NW * 32;                   // resident rows per workgroup
     constexpr int U = TS * G::CPR / 64;           // units per streamed tile of one tensor
     constexpr int L = 2 * U / NW;                 // load instructions per wavefront per tile pair (T1, T2)
@@ -136,7 +132,6 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     constexpr int NB = TS / 32, KK = D / 16, DB = D / 32;
     constexpr int TILE = G::bytes(TS), STATS = 2 * TS * 4;
     constexpr int STREAM = bwd_stream_bytes<D, TS, MODE>();       // LDS of one stream: two slots per tensor, and of the statistics
-    constexpr int RK = R2LDS ? bwd_resident_regs<D, MODE>() : 0;  // k-steps of the second resident operand that stay in registers
     constexpr int ROW16 = G::bytes(16);           // LDS distance of rows 16 apart (the swizzles repeat every 16 rows)
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -156,11 +151,11 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     int head, rt;                                 // head of the resident side (a query head in the dQ pass, else a key/value head) and tile
     if (causal && order.heads > 0) {
         // query tiles get longer with their index, key tiles shorter: the long ones of all heads first (causal_tile)
-        const CausalTile ct = causal_tile(blockIdx.x, nR, order, NS == 1 && D >= 128 ? N : 0);
+        const CausalTile ct = causal_tile(block, nR, order, NS == 1 && D >= 128 && !HAVE_STATS ? N : 0);
         head = ct.head;
         rt = KEYS_RES ? ct.level : nR - 1 - ct.level;
     } else {
-        const int wg = remap_workgroup(blockIdx.x, N, false);
+        const int wg = remap_workgroup(block, N, false);
         head = divide(wg, order.by_tiles);
         rt = (causal && !KEYS_RES) ? nR - 1 - (wg - head * nR) : wg - head * nR;
     }
@@ -181,13 +176,13 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     const int r0 = rt * RM;
     const int rrow = r0 + wave * 32 + l32;
     const int rrow_c = rrow < S ? rrow : S - 1;
-    vec8 rf1[KK], rf2[R2LDS ? (RK > 0 ? RK : 1) : KK];
+    vec8 rf1[KK], rf2[R2LDS ? 1 : KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
         u32x4 raw = *(const u32x4 *)(r1 + (size_t)rrow_c * D + kk * 16 + g * 8);
         raw ^= rsign;
         rf1[kk] = __builtin_bit_cast(vec8, raw);
-        if (NEED_DP && (!R2LDS || kk < RK)) rf2[kk] = *(const vec8 *)(r2 + (size_t)rrow_c * D + kk * 16 + g * 8);
+        if constexpr (!R2LDS) rf2[kk] = *(const vec8 *)(r2 + (size_t)rrow_c * D + kk * 16 + g * 8);
     }
     if constexpr (R2LDS) {
         // this wavefront's 32 rows (rows >= S: zeros) in the order of the operand: k-step kk is one unit, lane after lane,
@@ -195,9 +190,9 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)r2, (short)0, S * G::GROW, 0x00020000);
         const int row0 = (r0 + wave * 32) * G::GROW;
 #pragma unroll
-        for (int kk = RK; kk < KK; ++kk)
+        for (int kk = 0; kk < KK; ++kk)
             if (NS == 1 || kk % NS == stream)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + RBASE + (wave * (KK - RK) + kk - RK) * 1024), 16,
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + RBASE + (wave * KK + kk) * 1024), 16,
                                                          l32 * G::GROW + g * 16, row0 + kk * 32, 0, 0);
     }
 
@@ -215,14 +210,17 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     // streamed into the LDS with each tile.  The descriptor spans both arrays, slack included; rows >= S of a head pick
     // up the next head's values or whatever the slack holds, and are masked.
     float lse_r = 0.f, delta_r = 0.f;
-    if constexpr (!KEYS_RES) {
+    if constexpr (!KEYS_RES && HAVE_STATS) {
+        delta_r = -stats[(size_t)head * S + rrow_c];
+        lse_r = *(const float *)((const char *)stats + stat_bytes + ((size_t)head * S + rrow_c) * 4);
+    } else if constexpr (!KEYS_RES) {
         lse_r = lse[(size_t)head * S + rrow_c] * 1.44269504088896340736f;
         // Delta = <dO, O>: the lane's half of the row, then the partner's (rows that see few keys: see below)
         const T *orow = o + head_off + (size_t)rrow_c * D + g * 8, *drow = r2 + (size_t)rrow_c * D + g * 8;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
             const vec8 x = *(const vec8 *)(orow + kk * 16);
-            const vec8 y = R2LDS && kk >= RK ? *(const vec8 *)(drow + kk * 16) : rf2[R2LDS && kk >= RK ? 0 : kk];
+            const vec8 y = R2LDS ? *(const vec8 *)(drow + kk * 16) : rf2[R2LDS ? 0 : kk];
 #pragma unroll
             for (int e = 0; e < 8; ++e) delta_r += (float)x[e] * (float)y[e];
         }
@@ -306,7 +304,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         row_ptr[i] = slots + G::at(l32, 2 * G::rp_kk(i) + g);
         TSDPA_OPAQUE(row_ptr[i]);
     }
-    const lds_ptr res_ptr = lds + RBASE + wave * (KK - RK) * 1024 + lane * 16;
+    const lds_ptr res_ptr = lds + RBASE + wave * KK * 1024 + lane * 16;
     // transposing: row g*4 + (lane%16)/4 (+ multiples of 8), bytes db*64 + ((lane/16)%2)*32 + (lane%4)*8 of the row
     const int t_row = g * 4 + ((lane & 15) >> 2), t_chunk = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
     lds_ptr tr_lo[G::NTP], tr_hi[D == 128 ? 1 : G::NTP];       // rows t_row (+16k) and t_row + 8 (+16k)
@@ -350,8 +348,8 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             const u32x4 raw = lds_read128(row_ptr[G::rp(kk)] + slot + nb * 2 * ROW16 + G::rp_imm(kk));
             vec8 b;
             if (!second) b = rf1[kk];
-            else if (R2LDS && kk >= RK) b = __builtin_bit_cast(vec8, lds_read128(res_ptr + (kk - RK) * 1024));
-            else b = rf2[R2LDS && kk >= RK ? 0 : kk];
+            else if (R2LDS) b = __builtin_bit_cast(vec8, lds_read128(res_ptr + kk * 1024));
+            else b = rf2[R2LDS ? 0 : kk];
             acc = E::mfma(__builtin_bit_cast(vec8, raw), b, acc);
             after_mfma(kk);
         }
@@ -394,10 +392,10 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], c, -l2));        // P
                 if constexpr (FUSED) pb[nb][i >> 3][i & 7] = (T)(masked ? 0.f : p);
                 float x = p;
-                if constexpr (NEED_DP) x *= KEYS_RES || DELTA16 ? dpacc[i] : dpacc[i] - delta_r;      // dS
+                x *= KEYS_RES || DELTA16 ? dpacc[i] : dpacc[i] - delta_r;     // dS
                 xb[nb][i >> 3][i & 7] = (T)(masked ? 0.f : x);
             }
-            if constexpr (MODE == BWD_DK || FUSED) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (FUSED) __builtin_amdgcn_sched_barrier(0);
         }
     };
     // One streamed tile, its successor's loads issued early: they land while this one is computed.  One loop body serves
@@ -424,7 +422,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         // the issue stage while the CU's address unit works through them (S = 1024 of nine heads: 69 -> 65.5 us at D =
         // 128, 61 -> 55 at D = 96; 1-2 % where the CUs are full; level at D = 64)
         const lds_ptr nxt = slots + (shift > 0 ? TILE : 0);
-        constexpr int HOOKS = NB * (NEED_DP ? 2 : 1) * KK;
+        constexpr int HOOKS = NB * 2 * KK;
         auto spread = [&](int h) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = h * L / HOOKS; i < (h + 1) * L / HOOKS; ++i) load_part(next_j, next_valid, nxt, i);
@@ -435,15 +433,14 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         for (int nb = 0; nb < NB; ++nb) {       // one 32-row block at a time: only its accumulators are live
             f32x16 sacc, dpacc;
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(1);
-            products(0, nb, false, sacc, [&](int kk) __attribute__((always_inline)) { spread(nb * (NEED_DP ? 2 : 1) * KK + kk); });
-            if constexpr (NEED_DP)
-                products(T2BASE, nb, true, dpacc, [&](int kk) __attribute__((always_inline)) { spread((nb * 2 + 1) * KK + kk); });
+            products(0, nb, false, sacc, [&](int kk) __attribute__((always_inline)) { spread(nb * 2 * KK + kk); });
+            products(T2BASE, nb, true, dpacc, [&](int kk) __attribute__((always_inline)) { spread((nb * 2 + 1) * KK + kk); });
             if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
             if (mask) weights(nb, trow0, sacc, dpacc, std::true_type{});
             else      weights(nb, trow0, sacc, dpacc, std::false_type{});
         }
         if constexpr (PRIO) __builtin_amdgcn_s_setprio(2);
-        accumulate(MODE == BWD_DV ? T2BASE : 0, xb, oacc);
+        accumulate(0, xb, oacc);
         if constexpr (FUSED) accumulate(T2BASE, pb, oacc2);       // dV^T += dO^T P
         if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
     };
@@ -456,7 +453,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     if constexpr (!KEYS_RES) {
         // rows that see at most kBwdShortRow keys: Delta from its definition, before the pass proper.  Such rows are among
         // the first kBwdShortRow of a head, their keys too.
-        if (r0 < kBwdShortRow && (causal || S <= kBwdShortRow)) {
+        if (!HAVE_STATS && r0 < kBwdShortRow && (causal || S <= kBwdShortRow)) {
             float sum = 0.f;
             for (int j = 0; j * TS < kBwdShortRow && j < j1; ++j) {
                 load_tile(j, true, slots);
@@ -483,7 +480,7 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
             for (int i = 0; i < 16; ++i) minus_delta[i] = -delta_r;
             TSDPA_OPAQUE(minus_delta);            // (left transparent, it is built again for every block)
         }
-        if (stream == 0 && g == 0 && rrow < S) {
+        if (!HAVE_STATS && stream == 0 && g == 0 && rrow < S) {
             stats[(size_t)head * S + rrow] = -delta_r;
             *(float *)((char *)stats + stat_bytes + ((size_t)head * S + rrow) * 4) = lse_r;
         }
@@ -612,16 +609,27 @@ sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
         }
     };
     // (the launcher sizes the dynamic LDS for the larger of the tile slots and this staging area)
-    store(oacc, MODE == BWD_DV ? 1.0f : scale, out);
+    store(oacc, scale, out);
     if constexpr (FUSED) store(oacc2, 1.0f, out2);   // same staging region: it is private to the wavefront, whose LDS operations complete in order
 #endif
+}
+
+template <typename T, int D, int NW, int NS, int TS, int WPS, int MODE, bool GRP, bool R2LDS>
+__global__ void __launch_bounds__(NW * NS * 64, WPS)
+sdpa_bwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ dout,
+                const T *__restrict__ o, const float *__restrict__ lse, float *__restrict__ stats, T *__restrict__ out,
+                T *__restrict__ out2, int S, int nR, int N, float c, float scale, uint32_t rsign, int causal,
+                unsigned stat_bytes, int group, TileOrder order)
+{
+    bwd_pass<T, D, NW, NS, TS, MODE, GRP, R2LDS, false>(q, k, v, dout, o, lse, stats, out, out2, S, nR, N, c, scale, rsign,
+                                                        causal, stat_bytes, group, order, blockIdx.x);
 }
 
 // LDS of one instantiation: slots and statistics of every stream during the loop (and the resident operand kept there), then
 // the sums of the streams, then one 32 x D block per wavefront of a stream for the output transpose.
 template <int D, int NW, int NS, int TS, int MODE, bool R2LDS> constexpr int bwd_lds_bytes()
 {
-    const int loop = NS * bwd_stream_bytes<D, TS, MODE>() + (R2LDS ? NW * (D / 16 - bwd_resident_regs<D, MODE>()) * 1024 : 0);
+    const int loop = NS * bwd_stream_bytes<D, TS, MODE>() + (R2LDS ? NW * (D / 16) * 1024 : 0);
     const int sums = (NS - 1) * NW * 32 * D * 4;
     const int stage = NW * 32 * BwdGeom<D>::OROW;
     const int most = loop > sums ? loop : sums;
