@@ -391,9 +391,8 @@ def bwd_kernels(D, heads, S, grouped):
         rounds = -(-heads // 256)
         if S <= (128 if D == 64 else 64) or (heads >= 110 and (D == 64 or S <= 128 or 10 * heads >= 7 * 256 * rounds)):
             return "sdpa_bwd_short_kernel", 5
-    if D == 160:
-        return "sdpa_bwd_kernel<dQ> + sdpa_bwd_pair_kernel", 7
-    return "sdpa_bwd_kernel<dQ> + sdpa_bwd_kernel<dK+dV>", 7
+    # (one grid after the statistics, or launches of their own: pick_bwd_joint of csrc/sdpa_bwd_inst.h)
+    return "sdpa_bwd_joint_kernel, or sdpa_bwd_kernel<dQ> + " + ("sdpa_bwd_pair_kernel" if D == 160 else "sdpa_bwd_kernel<dK+dV>"), 7
 
 
 def bench_bwd(pkg, torch, args, flags):

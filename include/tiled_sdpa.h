@@ -291,10 +291,11 @@ unsigned long long tiled_sdpa_kv_workspace_bytes(int B, int H, int Sq, int D, in
  *   workspace        : device memory, 16-byte aligned, at least tiled_sdpa_bwd_workspace_bytes(B, H, S)
  *                      bytes (two FP32 values per query row); caller-owned, used only during this call's
  *                      kernels, so calls that may overlap on the GPU need distinct workspaces.
- * Kernels enqueued on `stream`: dQ, which also leaves the row statistics in the workspace (Delta_i = <dO_i, O_i> and
+ * Kernels enqueued on `stream`: dQ, which also leaves the row statistics in the workspace, or a kernel for these alone (Delta_i = <dO_i, O_i> and
  * LSE_i in log2 units; for query rows that see at most 64 keys -- S <= 64, or the first 64 rows under the causal mask --
  * Delta_i by its definition sum_j P_ij dP_ij in FP32, because on such rows the rounding of the 16-bit o inside
- * <dO_i, O_i> is not attenuated by small P_ij); then dK and dV in one pass over resident keys.  Sequences of up to 256 rows
+ * <dO_i, O_i> is not attenuated by small P_ij); then dK and dV in one pass over resident keys, in one grid with dQ where
+ * that was not computed before.  Sequences of up to 256 rows
  * at D = 64 and 96 with H = Hkv may take one kernel for all of it, which leaves the workspace alone.  No sum crosses
  * workgroups, so results are deterministic.  Validation order: dtype, D, shape, empty problem, null pointers, alignment,
  * scale, workspace, launch.

@@ -3,7 +3,7 @@
 #include <mutex>
 
 #include "sdpa_bwd_kernel.h"
-#include "sdpa_bwd_pair_kernel.h"
+#include "sdpa_bwd_joint_kernel.h"
 #include "sdpa_bwd_short_kernel.h"
 #include "sdpa_fwd_launch.h"
 
@@ -48,41 +48,31 @@ int launch_bwd_pass_nw(const BwdLaunchArgs &a)
     return (int)hipGetLastError();
 }
 
-// Wavefronts along the resident rows and streams of a pass whose plain form (128 resident rows, one stream) has `n`
-// workgroups, each with a chain of `chain` 32-row steps (over all query heads of its group).  Up to one such workgroup per CU
+// Wavefronts along the resident rows and streams of a pass launched by itself at D = 96 and 128 whose plain form (128 resident
+// rows, one stream) has `n` workgroups, each with a chain of `chain` 32-row steps (over all query heads of its group).  (At D = 64 and
+// 160 only large problems launch the passes by themselves: pick_bwd_joint.)  Up to one such workgroup per CU
 // a SIMD has one wavefront or none and waits through every chain alone; streams shorten the chain, fewer resident rows make
 // more workgroups of it.  The lines between the cases are those of timings of every form on 560 shapes (16 ... 400 workgroups,
 // chains of 4 ... 256), where this choice is within 0.7 % of the best one on average:
 //   * up to 64 workgroups: one wavefront of 32 rows and its private tiles per stream, as many streams as the LDS holds
-//     (BF16, us per call with the one pass changed: 8 query heads per key/value head, S = 512, D = 64 104 -> 33, D = 128
-//     150 -> 66; S = 2048 of one head 75.9 -> 45.0);
+//     (BF16, us per call with the one pass changed, D = 128: 8 query heads per key/value head, S = 512, 150 -> 66);
 //   * up to 128: 64 rows, four streams on long chains (D = 128, S = 2048: 121 -> 97 us in the dQ pass), two on short ones;
-//     under the causal mask the 32-row form, whose uneven workgroups pack better, where its LDS lets two share a CU (D = 64)
-//     or the chain is long;
-//   * up to 256: under the mask 64 rows and two ... four streams (D = 160, four query heads per key/value head, S = 2048:
-//     540 -> 379 us), without it, where nothing is uneven, 128 rows and two streams on long chains (3-12 %);
+//     under the causal mask the 32-row form, whose uneven workgroups pack better, where the chain is long;
+//   * up to 256: under the mask 64 rows and two ... four streams, without it, where nothing is uneven, 128 rows and two streams on
+//     long chains (3-12 %);
 //   * up to 400, under the mask, long chains: 5-15 %.  Beyond, and on short chains, the plain form.
 struct BwdForm { int nw, ns; };
 inline BwdForm pick_bwd_form(int D, bool causal, bool keys_resident, long long n, long long chain)
 {
     const BwdForm plain{4, 1};
     if (chain <= 2) return plain;
-    if (n <= 64) {
-        if (D == 160) return BwdForm{1, 3};
-        if (!keys_resident && chain <= 8) return BwdForm{2, 2};
-        return BwdForm{1, D == 64 && chain >= 64 ? 8 : 4};
-    }
-    if (n <= 128) {
-        if (causal && chain >= (D == 64 ? 16 : D == 160 ? 64 : 128)) return BwdForm{1, D == 160 ? 3 : 4};
-        if (D == 160) return BwdForm{2, chain >= 64 ? 3 : 2};
-        return BwdForm{2, chain >= 32 ? 4 : 2};
-    }
+    if (n <= 64) return !keys_resident && chain <= 8 ? BwdForm{2, 2} : BwdForm{1, 4};
+    if (n <= 128) return causal && chain >= 128 ? BwdForm{1, 4} : BwdForm{2, chain >= 32 ? 4 : 2};
     if (n <= 256) {
         if (!causal) return chain >= (keys_resident ? 16 : 32) ? BwdForm{4, 2} : plain;
-        if (chain >= 64) return D == 64 ? BwdForm{1, 4} : BwdForm{2, D == 160 ? 3 : 4};
-        return chain >= (D == 160 ? 32 : 16) ? BwdForm{2, 2} : plain;
+        return chain >= 64 ? BwdForm{2, 4} : chain >= 16 ? BwdForm{2, 2} : plain;
     }
-    if (n <= 400 && causal && chain >= 64) return D == 160 || (D == 128 && keys_resident) ? BwdForm{4, 2} : BwdForm{2, 2};
+    if (n <= 400 && causal && chain >= 64) return D == 128 && keys_resident ? BwdForm{4, 2} : BwdForm{2, 2};
     return plain;
 }
 
@@ -107,20 +97,14 @@ int launch_bwd_pass(const BwdLaunchArgs &a)
 {
     using Sh = BwdShape<D>;
     const long long heads = MODE == BWD_DQ ? a.BH : a.BH / a.group;
-    const BwdForm f = pick_bwd_form(D, a.causal != 0, MODE != BWD_DQ, heads * ((a.S + 127) / 128),
-                                    (long long)(MODE == BWD_DQ ? 1 : a.group) * ((a.S + 31) / 32));
-    // (the forms with streams have the loop over a group compiled in: one instantiation for both)
-    if (f.ns > 1) {
-        if (f.nw == 4) return launch_bwd_pass_nw<T, D, MODE, true, 4, 2, 32, 2>(a);
-        if (f.nw == 2 && f.ns == 2) return launch_bwd_pass_nw<T, D, MODE, true, 2, 2, 32, 2>(a);
-        if constexpr (D == 160) {
-            if (f.nw == 2) return launch_bwd_pass_nw<T, D, MODE, true, 2, 3, 32, 2>(a);
-            return launch_bwd_pass_nw<T, D, MODE, true, 1, 3, 32, 2>(a);
-        } else {
-            if (f.nw == 2) return launch_bwd_pass_nw<T, D, MODE, true, 2, 4, 32, 2>(a);
-            if constexpr (D == 64)
-                if (f.ns == 8) return launch_bwd_pass_nw<T, D, MODE, true, 1, 8, 32, 2>(a);
-            return launch_bwd_pass_nw<T, D, MODE, true, 1, 4, 32, 2>(a);
+    if constexpr (D == 96 || D == 128) {
+        const BwdForm f = pick_bwd_form(D, a.causal != 0, MODE != BWD_DQ, heads * ((a.S + 127) / 128),
+                                        (long long)(MODE == BWD_DQ ? 1 : a.group) * ((a.S + 31) / 32));
+        // (the forms with streams have the loop over a group compiled in: one instantiation for both)
+        if (f.ns > 1) {
+            if (f.nw == 4) return launch_bwd_pass_nw<T, D, MODE, true, 4, 2, 32, 2>(a);
+            if (f.nw == 1) return launch_bwd_pass_nw<T, D, MODE, true, 1, 4, 32, 2>(a);
+            return f.ns == 2 ? launch_bwd_pass_nw<T, D, MODE, true, 2, 2, 32, 2>(a) : launch_bwd_pass_nw<T, D, MODE, true, 2, 4, 32, 2>(a);
         }
     }
     if constexpr (D == 128) {
@@ -143,19 +127,16 @@ inline bool bwd_in_one_launch(int D, int heads, int S)
     return heads * 10 >= (heads + 255) / 256 * 256 * 7;
 }
 
-// Pairs and streams of the dK + dV pass at D = 160, by the workgroups of 128 keys and the 32-row steps of their chains; from
-// timings of four forms on 200 shapes (BF16, us).  Few workgroups: one pair and two streams (S = 2187 of one head 99.5 with
-// four pairs, 62.2), as many as fit; up to 150, and to 400 whose chains run over a group's heads: two of both (two
-// entries of 16 heads over 4, S = 4096: 10-15 %).  Else two pairs, two workgroups per CU, 2-10 % ahead of four on causal
-// and short problems; four pairs, which read a tile once for 128 keys, 3-4 % ahead on long ones without the mask (32 heads,
-// S = 8192: 2084 / 2002).
+// The dK + dV pass at D = 160 as a launch of its own (large problems: pick_bwd_joint).  Two pairs, two workgroups per CU, 2-10 %
+// ahead of four on causal and short problems; four pairs, which read a tile once for 128 keys, 3-4 % ahead on long ones without the
+// mask (32 heads of S = 8192, us: 2084 / 2002); two pairs and two streams where up to 400 tiles of 128 keys have chains that run
+// over a group's heads (four entries of 16 heads over 4, S = 2048, causal: 374 / 305).
 template <typename T, int D, bool GRP>
 int launch_bwd_pairs(const BwdLaunchArgs &a)
 {
     const long long nk = (long long)(a.BH / a.group) * ((a.S + 127) / 128), chain = (long long)a.group * ((a.S + 31) / 32);
-    if (chain > 3 && nk <= 75) return launch_bwd_pair<T, D, 1, 2, true>(a);
-    if (chain > 3 && (nk <= 153 || (nk <= 400 && chain > 140))) return launch_bwd_pair<T, D, 2, 2, true>(a);
-    if (!a.causal && a.S >= 600 && nk >= 430) return launch_bwd_pair<T, D, 4, 1, GRP>(a);
+    if (nk <= 400 && chain > 140) return launch_bwd_pair<T, D, 2, 2, true>(a);
+    if (!a.causal && a.S >= 600) return launch_bwd_pair<T, D, 4, 1, GRP>(a);
     return launch_bwd_pair<T, D, 2, 1, GRP>(a);
 }
 
@@ -169,6 +150,118 @@ int launch_bwd_passes(const BwdLaunchArgs &a)
     else return launch_bwd_pass<T, D, BWD_DKV, GRP>(a);
 }
 
+// The form of the joint grid: wavefronts along the rows and streams of the dQ pass, then of the dK + dV pass (D = 160: pairs and
+// streams), as four digits; 0: the passes as launches of their own.  `nk`: workgroups of 128 keys; n: those and the ones of 128
+// queries; `chain`: the 32-row steps of a workgroup of keys, over the query heads of its group; work: their product.  The lines are
+// those of timings of a dozen forms on 1100 shapes (BF16; drawn over the whole range, and the neighbourhood of the lines), where
+// this choice is 1.9, 1.7, 2.8 and 1.8 % from the best of all forms on average at D = 64, 96, 128 and 160, and 1.12, 1.11,
+// 1.12 and 1.15 (there against pairs in a launch of their own) times as fast as the passes apart.  What decides:
+//   * few workgroups: a wavefront per 32 keys with tiles of its own (..14; D = 160 ..12), whose chains are the shortest; where a group's heads
+//     make them long, eight streams at D = 64 (2418);
+//   * more of them: workgroups that share tiles, 64 keys in two or four streams (4122, 2222, 2424, 4224) or 128 (2241, 4141, 4120);
+//   * many workgroups of ungrouped heads: the passes apart, which are level there and save reading O and dO once more.  Grouped
+//     heads keep the joint grid longer: their few long chains of keys drain beside the many short ones of the queries.
+// Us, passes apart / here: D = 64, 260 tiles of 128 (S = 1236, causal) 50.6 / 34.3; D = 96, one head S = 1159 25.9 / 17.2; D = 128, six
+// heads over 2 of S = 1024, causal 66.9 / 50.6; D = 160, 8 heads over 2 of S = 1346 139 / 86.
+inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
+{
+    const long long tiles = (S + 127) / 128, nk = heads / group * tiles, n = nk + heads * tiles;
+    const long long chain = (long long)group * ((S + 31) / 32), work = nk * chain;
+    if (D == 64 && group == 1) {
+        if (S <= 256) return n <= 330 || (n <= 440 && S <= 190) ? 4122 : causal ? 2241 : 0;
+        if (causal) {
+            if (n <= 220 && chain >= 30) return 1414;
+            return n <= 150 ? 2214 : n <= 514 ? 2222 : n <= 1850 ? 2241 : 0;
+        }
+        if (n <= 240) return n <= 170 ? 2214 : 4122;
+        if (n <= 950) return S <= 600 ? 4122 : 2241;
+        return S >= 1600 && n <= 1850 ? 2241 : 0;
+    }
+    if (D == 64) {
+        if (!causal) return nk > 100 ? 4122 : nk <= 32 && chain > 80 ? 2418 : 2214;
+        if (nk <= 48) return chain <= 36 || S <= 256 ? 2214 : 2418;
+        if (S <= 850) return nk <= 170 && n <= 1540 ? 4114 : 4122;
+        return nk <= 68 && n <= 1540 ? 2418 : n <= 1540 && chain <= 290 ? 2214 : nk <= 180 ? 4114 : 4122;
+    }
+    if (D == 96 && group == 1) {
+        if (n <= (causal ? 70 : 90)) return 2214;
+        if (causal) {
+            if (n <= 216 && chain >= 30) return 2424;
+            return n <= 514 || (n <= 960 && chain > 64) ? 2222 : n <= 960 ? 2241 : 0;
+        }
+        if (work <= 2800) return 4122;
+        if (n <= 120) return 2424;
+        if (n <= 300) return n <= 170 && chain >= 100 ? 4224 : 0;
+        if (n <= 340) return 4122;
+        return n <= 860 || (S >= 3000 && n <= 2700) ? 2241 : 0;
+    }
+    if (D == 96) {
+        if (nk > 740) return 0;
+        if (!causal) return nk <= 48 ? 2214 : nk <= 86 ? 4224 : 4122;
+        if (n <= 365) return 2214;
+        if (nk <= 200) return S <= 550 ? 0 : 4224;
+        return chain <= 440 ? 4122 : 4224;
+    }
+    if (D == 128 && group == 1) {
+        if (causal) {
+            if (work <= 240) return 4141;
+            if (n <= 200) return n <= 80 ? 2214 : 4224;
+            return n > 514 && n <= 994 ? 2241 : 0;
+        }
+        if (n <= 168) return S <= 90 ? 4141 : S <= 160 ? 4122 : S <= 480 || n <= 92 ? 2214 : 4224;
+        if (work <= 3000) return 4141;
+        return work > 6150 && (n <= 900 || (n <= 2000 && S >= 1500)) ? 2241 : 0;
+    }
+    if (D == 128) {
+        if (nk <= (causal ? 54 : 42)) return 2214;
+        if (!causal) return work <= 2290 ? 4122 : nk <= 73 ? 4224 : nk <= 230 ? 0 : 4141;
+        return chain <= 175 || (nk <= 384 && n > 1300) ? 0 : nk <= 384 ? 4224 : 4141;
+    }
+    if (group == 1) return n <= 90 ? (S <= 64 ? 4120 : 2212) : n <= (causal ? 800 : 2000) ? 4120 : 0;
+    if (nk <= (S <= 64 ? 60 : 51)) return 2212;
+    if (nk <= 75 && S > 64) return 4223;
+    if (causal && nk >= 240) return 0;
+    if (chain > 80 && nk < (causal ? 240 : chain > 400 ? 130 : 100)) return 4223;
+    return nk <= 500 ? 4120 : 0;
+}
+
+template <typename T, int D, int NWQ, int NSQ, int NWK, int NSK>
+int launch_bwd_joint_form(const BwdLaunchArgs &a)
+{
+    // (forms with streams of keys have the loop over a group compiled in)
+    if constexpr (NSK == 1)
+        if (a.group == 1) return launch_bwd_joint_nw<T, D, NWQ, NSQ, NWK, NSK, false>(a);
+    return launch_bwd_joint_nw<T, D, NWQ, NSQ, NWK, NSK, true>(a);
+}
+
+template <typename T, int D>
+int launch_bwd_joint(const BwdLaunchArgs &a, int form)
+{
+    const int err = launch_bwd_stats<T, D>(a);
+    if (err != 0) return err;
+    if constexpr (D == 160) {
+        if (form == 4120) return launch_bwd_joint_form<T, D, 4, 1, 2, 1>(a);
+        return form == 4223 ? launch_bwd_joint_form<T, D, 4, 2, 2, 2>(a) : launch_bwd_joint_form<T, D, 2, 2, 1, 2>(a);
+    } else {
+        if (form == 2241) return launch_bwd_joint_form<T, D, 2, 2, 4, 1>(a);
+        if (form == 4122) return launch_bwd_joint_form<T, D, 4, 1, 2, 2>(a);
+        if constexpr (D <= 96)
+            if (form == 2222) return launch_bwd_joint_form<T, D, 2, 2, 2, 2>(a);
+        if constexpr (D >= 96)
+            if (form == 4224) return launch_bwd_joint_form<T, D, 4, 2, 2, 4>(a);
+        if constexpr (D == 64) {
+            if (form == 2418) return launch_bwd_joint_form<T, D, 2, 4, 1, 8>(a);
+            if (form == 4114) return launch_bwd_joint_form<T, D, 4, 1, 1, 4>(a);
+            if (form == 1414) return launch_bwd_joint_form<T, D, 1, 4, 1, 4>(a);
+        } else if constexpr (D == 96) {
+            if (form == 2424) return launch_bwd_joint_form<T, D, 2, 4, 2, 4>(a);
+        } else {
+            if (form == 4141) return launch_bwd_joint_form<T, D, 4, 1, 4, 1>(a);
+        }
+        return launch_bwd_joint_form<T, D, 2, 2, 1, 4>(a);
+    }
+}
+
 template <typename T, int D>
 int launch_bwd(const BwdLaunchArgs &a)
 {
@@ -176,6 +269,7 @@ int launch_bwd(const BwdLaunchArgs &a)
         if (a.group == 1 && a.S <= 256 && bwd_in_one_launch(D, a.BH, a.S))
             return a.S <= 64 ? launch_bwd_short_nw<T, D, 2>(a) : a.S <= 128 ? launch_bwd_short_nw<T, D, 4>(a) : launch_bwd_short_nw<T, D, 8>(a);
     }
+    if (const int form = pick_bwd_joint(D, a.causal != 0, a.BH, a.group, a.S)) return launch_bwd_joint<T, D>(a, form);
     // one query head per key/value head keeps the kernels without the loop over a group
     return a.group == 1 ? launch_bwd_passes<T, D, false>(a) : launch_bwd_passes<T, D, true>(a);
 }

@@ -103,8 +103,8 @@ template <int D, int TS, int MODE> constexpr int bwd_stream_bytes() { return 4 *
 // NS: streams.  NS groups of NW wavefronts share the resident rows and take every NS-th tile of the chain each (over the
 // heads of a group), in LDS slots of their own; at the end their sums are added in the order of the streams.  For passes
 // of few workgroups, whose wavefronts would wait through the whole chain alone (the choice and its figures: pick_bwd_form).
-// The dQ pass runs first: it has the query rows, so it computes their statistics (Delta_i, and LSE_i in log2 units) in
-// its prologue and leaves them in `stats` for the keys-resident passes.
+// Launched by itself the dQ pass runs first: it has the query rows, so it computes their statistics (Delta_i, and LSE_i in log2
+// units) in its prologue and leaves them in `stats` for the other.  HAVE_STATS: they are there already (sdpa_bwd_joint_kernel.h).
 template <typename T, int D, int NW, int NS, int TS, int MODE, bool GRP, bool R2LDS, bool HAVE_STATS>
 __device__ __forceinline__ void
 bwd_pass(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
