@@ -72,11 +72,11 @@ template <int STRIDE, bool TWO> __device__ __forceinline__ void short_read_block
 }
 #undef TSDPA_RD_TR
 
-template <typename T, int D, int NW>
+template <typename T, int D, int NW, bool CAUSAL>
 __global__ void __launch_bounds__(NW * 64, 2)
 sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ dout,
                       const T *__restrict__ o, const float *__restrict__ lse, T *__restrict__ dq, T *__restrict__ dk,
-                      T *__restrict__ dv, int S, float c, float scale, uint32_t rsign, int causal)
+                      T *__restrict__ dv, int S, float c, float scale, uint32_t rsign)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using E = Elem<T>;
@@ -115,7 +115,7 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
             load_unit(first ? q_rsrc : do_rsrc, lds + (first ? 0 : W::NSLOT * TILE) + slot * TILE, first ? u : u - U, j * 32);
         }
     };
-    const bool short_rows = causal || S <= kBwdShortRow;       // (their Delta comes from its definition: see the general kernel)
+    const bool short_rows = CAUSAL || S <= kBwdShortRow;       // (their Delta comes from its definition: see the general kernel)
 
     // ---- prologue: K into the LDS, the first tile (or the first rows of V, for the short rows' Delta) beside it
     {
@@ -149,18 +149,7 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
         row_ptr[i] = lds + G::at(l32, 2 * G::rp_kk(i) + g);
         TSDPA_OPAQUE(row_ptr[i]);
     }
-    // (`stats`: LDS address of -Delta of the lane's rows to start from, or 0)
-    auto products = [&](int at, const vec8 (&rf)[KK], f32x16 &acc, int stats = 0) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-        if (stats != 0) {
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const f32x4 md = *(TSDPA_LDS f32x4 *)(lds + stats + r4 * 32);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[r4 * 4 + e] = md[e];
-            }
-        }
+    auto products = [&](int at, const vec8 (&rf)[KK], f32x16 &acc) __attribute__((always_inline)) {
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
             const u32x4 raw = lds_read128(row_ptr[G::rp(kk)] + at + G::rp_imm(kk));
@@ -190,10 +179,12 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
                     qf[kk] = __builtin_bit_cast(vec8, raw);
                     df[kk] = *(const vec8 *)(drow + kk * 16);
                 }
-                const int thi = causal ? row_c : S - 1;
+                const int thi = CAUSAL ? row_c : S - 1;
                 float sum = 0.f;
                 for (int j = 0; j < kBwdShortRow / 32 && j < nb; ++j) {
                     f32x16 sacc, dpacc;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) sacc[i] = dpacc[i] = 0.f;
                     products(W::KBASE + j * TILE, qf, sacc);
                     products(j * TILE, df, dpacc);
 #pragma unroll
@@ -280,6 +271,10 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
                 acc[db] = E::mfma(__builtin_bit_cast(vec8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)), x[ks], acc[db]);
             }
     };
+    // Keys past the end (lanes of the last block, with copies of the last key's rows): their rows of dK and dV are not stored, and
+    // their dS, which other lanes' dQ would meet, is not written: the buffers hold zeros there.  (Under a mask per weight the
+    // last block's wavefront took 160 vector instructions for the weights of a tile instead of 64, and held up the others at
+    // every barrier: B=64 H=12 S=197 59.5 us.)
     vec8 pb[2], xb[2];
     auto weights = [&](int j, const f32x16 &sacc, const f32x16 &dpacc, auto mask_tag) __attribute__((always_inline)) {
         constexpr bool MASK = decltype(mask_tag)::value;
@@ -290,8 +285,7 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int i = r4 * 4 + e, qrow = j * 32 + r4 * 8 + g * 4 + e;
-                // a key past the end, or (causal) one after the query
-                const bool masked = MASK && (row >= S || (causal && qrow < row));
+                const bool masked = MASK && qrow < row;             // a key after the query
                 const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], c, -st_lse[e]));
                 const float x = p * dpacc[i];
                 pb[i >> 3][i & 7] = (T)(masked ? 0.f : p);
@@ -301,6 +295,9 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
     };
     const int ds_w0 = W::DSBASE + W::ds_at(row, g);            // run r4 of this lane's key: chunk r4 ^ f, as an XOR of the address
     const lds_ptr ds_r = lds + W::DSBASE;
+    if (row >= S)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *(TSDPA_LDS u32x2 *)(lds + (i >> 2) * W::DSBUF + (ds_w0 ^ ((i & 3) << 4))) = u32x2{0u, 0u};
 
     int slot = 0;
     const int qh0 = NW == 8 ? wave / 4 : 0;       // KTREG: the first half of the tile's queries that this wavefront has blocks in
@@ -310,19 +307,30 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
         const int ahead = j + W::NSLOT - 1, free_slot = (slot + W::NSLOT - 1) % W::NSLOT;
         if (W::KTREG || ahead < nb) load_tile(ahead, free_slot);   // (KTREG: also past the end, for the count of the wait below)
         const int at = slot * TILE, ds_buf = (j & 1) * W::DSBUF;
-        if (wave < nb && (!causal || j >= wave)) {
+        if (wave < nb && (!CAUSAL || j >= wave)) {
+            // (dP starts from -Delta; no branch between the two chains of MFMAs, which fill each other's waits)
             f32x16 sacc, dpacc;
-            products(at, rf1, sacc);
-            products(W::NSLOT * TILE + at, rf2, dpacc, W::STATS + (NW * 32 + j * 32 + g * 4) * 4);
-            if (wave * 32 + 32 > S || (causal && j == wave)) weights(j, sacc, dpacc, std::true_type{});
-            else                                             weights(j, sacc, dpacc, std::false_type{});
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                vec4 x;
+                const f32x4 md = *(TSDPA_LDS f32x4 *)(lds + W::STATS + (NW * 32 + j * 32 + g * 4) * 4 + r4 * 32);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = xb[r4 >> 1][(r4 & 1) * 4 + e];
-                *(TSDPA_LDS vec4 *)(lds + ds_buf + (ds_w0 ^ (r4 << 4))) = x;
+                for (int e = 0; e < 4; ++e) {
+                    sacc[r4 * 4 + e] = 0.f;
+                    dpacc[r4 * 4 + e] = md[e];
+                }
             }
+            products(at, rf1, sacc);
+            products(W::NSLOT * TILE + at, rf2, dpacc);
+            if (CAUSAL && j == wave) weights(j, sacc, dpacc, std::true_type{});
+            else                     weights(j, sacc, dpacc, std::false_type{});
+            if (row < S)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    vec4 x;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = xb[r4 >> 1][(r4 & 1) * 4 + e];
+                    *(TSDPA_LDS vec4 *)(lds + ds_buf + (ds_w0 ^ (r4 << 4))) = x;
+                }
             // dV^T += dO^T P, dK^T += Q^T dS
             if constexpr (W::KTREG) {
                 i16x4 x[16];
@@ -345,7 +353,7 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
         }
         tile_barrier();
         // dQ of the tile: [16 columns][16 queries] += K^T dS^T over the keys (causal: up to the tile's own)
-        const int kbs = causal ? j + 1 : nb;
+        const int kbs = CAUSAL ? j + 1 : nb;
         auto put = [&](const f32x4 &acc, int db, int qh) __attribute__((always_inline)) {
             const int qrow = j * 32 + qh * 16 + l16;
             vec4 out;
@@ -363,18 +371,19 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
                 const uint32_t lo = (ds_lo + ds_buf) ^ (h << 5), hi = (ds_hi + ds_buf) ^ (h << 5);
 #pragma unroll
                 for (int i = 0; i < NKB; i += 4) short_read_blocks<2048, NW == 2>(x + 2 * i, lo + i * 2048, hi + i * 2048);
-                f32x4 acc[W::NDB];
+                // two chains per block, even and odd key blocks; without the mask all of them in one run (dS past the end is zero)
+                f32x4 acc[W::NDB][2];
 #pragma unroll
-                for (int d = 0; d < W::NDB; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int d = 0; d < W::NDB; ++d) acc[d][0] = acc[d][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kb = 0; kb < NW; ++kb) {
-                    if (kb >= kbs) break;
+                    if (CAUSAL && kb >= kbs) break;
                     const vec8 b = __builtin_bit_cast(vec8, __builtin_shufflevector(x[2 * kb], x[2 * kb + 1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-                    for (int d = 0; d < W::NDB; ++d) acc[d] = Elem16<T>::mfma(kt[d][kb], b, acc[d]);
+                    for (int d = 0; d < W::NDB; ++d) acc[d][kb & 1] = Elem16<T>::mfma(kt[d][kb], b, acc[d][kb & 1]);
                 }
 #pragma unroll
-                for (int d = 0; d < W::NDB; ++d) put(acc[d], (wave + d * NW) % (D / 16), qh0 + h);
+                for (int d = 0; d < W::NDB; ++d) put(acc[d][0] + acc[d][1], (wave + d * NW) % (D / 16), qh0 + h);
             }
         } else {
 #pragma unroll 1
@@ -426,9 +435,9 @@ sdpa_bwd_short_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
 #endif
 }
 
-template <typename T, int D, int NW> int launch_bwd_short_nw(const BwdLaunchArgs &a)
+template <typename T, int D, int NW, bool CAUSAL> int launch_bwd_short_mask(const BwdLaunchArgs &a)
 {
-    auto kern = sdpa_bwd_short_kernel<T, D, NW>;
+    auto kern = sdpa_bwd_short_kernel<T, D, NW, CAUSAL>;
     constexpr int lds_bytes = BwdShortGeom<D, NW>::LDS_BYTES;
     static_assert(lds_bytes <= 160 * 1024, "LDS of a CU");
     static std::once_flag once;
@@ -438,8 +447,13 @@ template <typename T, int D, int NW> int launch_bwd_short_nw(const BwdLaunchArgs
     });
     if (attr_err != hipSuccess) return (int)attr_err;
     hipLaunchKernelGGL(kern, dim3((unsigned)a.BH), dim3(NW * 64), lds_bytes, a.stream, (const T *)a.q, (const T *)a.k, (const T *)a.v,
-                       (const T *)a.dout, (const T *)a.o, a.lse, (T *)a.dq, (T *)a.dk, (T *)a.dv, a.S, a.c, a.scale, a.rsign, a.causal);
+                       (const T *)a.dout, (const T *)a.o, a.lse, (T *)a.dq, (T *)a.dk, (T *)a.dv, a.S, a.c, a.scale, a.rsign);
     return (int)hipGetLastError();
+}
+
+template <typename T, int D, int NW> int launch_bwd_short_nw(const BwdLaunchArgs &a)
+{
+    return a.causal ? launch_bwd_short_mask<T, D, NW, true>(a) : launch_bwd_short_mask<T, D, NW, false>(a);
 }
 
 }  // namespace tsdpa
