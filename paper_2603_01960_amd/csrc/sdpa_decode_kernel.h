@@ -272,23 +272,51 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
             }
         }
         __syncthreads();
-        // two columns per thread, eight runs' loads in flight
-        for (int x = tid; x < S * (D / 2); x += NW * 64) {
-            const int row = x / (D / 2);
-            float s0 = 0.f, s1 = 0.f;
-#pragma unroll 8
-            for (int s = 0; s < splits; ++s) {
-                const float w = wgt[s * S + row];
-                const Pair part = get(po + (size_t)s * S * D + (size_t)x * 2);
-                if (!(w < 0.f)) {
-                    s0 += w * part.x;
-                    s1 += w * part.y;
-                }
+        // Eight runs' loads in flight; the last batch, if it is not full, loads its first run again.  What bounds this part is the
+        // number of round trips past the L2, so a thread has two columns where that takes all of them in one pass, and else four.
+        // (The whole call in us, remainder run by run and two columns at all times -> this: 8 heads, one row of D = 64 in 7 runs 9.2 ->
+        // 7.6, in 12 8.2 -> 7.4, in 8 or 16 level; 8 rows of D = 160 in 7 runs 14.7 -> 12.1; 30 heads, 4 rows of D = 128 in 7
+        // 13.3 -> 12.0.  Four columns at all times cost 0.4 to 1 us at 8 and 16 runs, and several threads per four columns, which
+        // share the runs, 0.3 us more up to 16.)
+        auto combine = [&](auto pairs) {
+            constexpr int P = pairs;
+            for (int x = tid; x < S * (D / 2 / P); x += NW * 64) {
+                const int row = x / (D / 2 / P);
+                float sum[2 * P] = {};
+                auto batch = [&](int s0, auto whole) {
+                    Pair part[8][P];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const float *at = po + (size_t)(whole || s0 + i < splits ? s0 + i : s0) * S * D + (size_t)x * (2 * P);
+#pragma unroll
+                        for (int p = 0; p < P; ++p) part[i][p] = get(at + 2 * p);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        if (!whole && s0 + i >= splits) break;
+                        const float w = wgt[(s0 + i) * S + row];
+                        if (!(w < 0.f)) {
+#pragma unroll
+                            for (int p = 0; p < P; ++p) {
+                                sum[2 * p] += w * part[i][p].x;
+                                sum[2 * p + 1] += w * part[i][p].y;
+                            }
+                        }
+                    }
+                };
+                int s0 = 0;
+                for (; s0 + 8 <= splits; s0 += 8) batch(s0, std::true_type{});
+                if (s0 < splits) batch(s0, std::false_type{});
+                const float inv = wgt[splits * S + row];
+                typedef T Out __attribute__((ext_vector_type(2 * P)));
+                Out out;
+#pragma unroll
+                for (int c = 0; c < 2 * P; ++c) out[c] = (T)(sum[c] * inv);
+                *(Out *)(o + (size_t)head * S * D + (size_t)x * (2 * P)) = out;
             }
-            const float inv = wgt[splits * S + row];
-            typedef T vec2 __attribute__((ext_vector_type(2)));
-            *(vec2 *)(o + (size_t)head * S * D + (size_t)x * 2) = vec2{(T)(s0 * inv), (T)(s1 * inv)};
-        }
+        };
+        if (S * (D / 2) <= NW * 64) combine(std::integral_constant<int, 1>{});
+        else combine(std::integral_constant<int, 2>{});
     };
 
     // this workgroup's run of tiles: [t0, t0 + n)
@@ -590,10 +618,7 @@ template <typename T, int D, int NQ, int NW, bool PAGED> int launch_decode_one(c
 
 template <typename T, int D, int NQ> int launch_decode_rows(const LaunchArgs &a)
 {
-    // Up to one workgroup per CU: eight wavefronts each (two workgroups of four per CU hold as many beyond that): level on
-    // large caches, 256 heads of 2048 keys 52.5 -> 48.4 us
-    // (with less than a tile per wavefront to do, four)
-    if (a.BH * a.splits <= 256 && a.Skv / a.splits >= 8 * kDecodeTile)
+    if (decode_waves(a.BH, a.splits, a.Skv) == 8)
         return a.block_table ? launch_decode_one<T, D, NQ, 8, true>(a) : launch_decode_one<T, D, NQ, 8, false>(a);
     return a.block_table ? launch_decode_one<T, D, NQ, 4, true>(a) : launch_decode_one<T, D, NQ, 4, false>(a);
 }

@@ -31,6 +31,14 @@ struct LaunchArgs {
     hipStream_t stream;
 };
 
+// Wavefronts per workgroup of the decoding kernel.  Up to one workgroup per CU eight (two workgroups of four per CU hold as
+// many beyond that): level on large caches, 256 heads of 2048 keys 52.5 -> 48.4 us.  With less than a tile of 32 keys per
+// wavefront to do, four.
+inline int decode_waves(int heads, int splits, int Skv)
+{
+    return (long long)heads * splits <= 256 && Skv / splits >= 256 ? 8 : 4;
+}
+
 // Chunks in which causal_tile (sdpa_fwd_kernel.h) takes the heads: heads per XCD and chunk (0: the plain order, head
 // after head), and heads of the first chunk.  `tiles` workgroups per head, `stream_bytes` of streamed operands per head.
 // From timings of every chunk size on 24 shapes (us, plain order -> this rule):

@@ -195,11 +195,16 @@ unsigned long long call_ticket()
 constexpr int kDecodeRows = 32;
 
 // Splits of a decoding step (BF16, cold cache, us; s = splits): one workgroup per CU in all, of runs of at least 128 keys.
-// From half as many key/value heads as CUs on, none: a pass is then as fast without the second look at the states (256
-// heads of 8192 keys: s1 177, s2 181, s4 185; lengths from a quarter of that: 127, 131-133, 130-132; 160 heads of 1024:
-// 18.0 / 22.5 / 23.5; 96 heads of 3000: 28.1 / 24.2 / 25.9; 32 heads of 8192: s4 30.9, s8 27.4, s16 28.5).
-int pick_splits_decode(int BH, int Skv)
+// None where a workgroup is through a head's K about as soon as it could be through the second look at the states: 105000
+// elements, or 200000 with more than 64 heads, where the CUs are nearly full without (one split / the best of more: 12 heads
+// of 1608 keys D = 64 6.9 / 7.8; 15 of 627 D = 128 7.4 / 7.9; 64 of 746 D = 128 9.5 / 10.6; 70 of 2048 D = 96 12.8 / 14.3; 24
+// heads of 772 D = 160, past the line, 10.4 / 9.3).  Nor from half as many key/value heads as CUs on: a pass is then as fast
+// (256 heads of 8192 keys: s1 177, s2 181, s4 185; lengths from a quarter of that: 127, 131-133, 130-132; 160 heads of 1024:
+// 18.0 / 22.5 / 23.5; 96 heads of 3000: 28.1 / 24.2 / 25.9; 32 heads of 8192: s4 30.9, s8 27.4, s16 28.5; 84 heads of 4096,
+// all full: s2 29.4, s3 30.4, and with lengths from a tenth of that s2 47.2, s3 38.1 for 66 of 8127).
+int pick_splits_decode(int BH, int Skv, int D)
 {
+    if ((int64_t)Skv * D <= (BH > 64 ? 200000 : 105000)) return 1;
     const int most = Skv > 256 ? (Skv + 127) / 128 : 1;
     int want = BH >= 128 ? 1 : BH > 64 ? 2 : 256 / BH;
     if (want > most) want = most;
@@ -219,12 +224,18 @@ void pick_tile_kv(long long heads, int Sq, int Skv, int D, int *tm, int *tn);
 // 8192 from 32) the plain form's 128 rows per tile load win back what the shorter chain gains.
 int pick_streams_kv(long long heads, int rows, int Skv, int D, int *tm)
 {
-    // (the decoding kernel below that, and on 17 to 32 rows of many heads or very long caches: 8 heads of 32 rows, 1000 keys
-    // D = 64 9.1 us there, 7.3 here, 62 heads D = 160 22.9 / 14.6, 62 of 4096 keys D = 128 28.8 / 24.7, but 128 of 4096 51.6 / 66,
-    // ... and few heads of few keys at D = 160 11.7 / 13.4)
-    if (rows <= 16 || (rows <= kDecodeRows && (heads > 64 || (D == 160 && heads <= 16 && Skv < 2048)))) return 1;
+    if (rows <= 16) return 1;
     const long long n = heads * (((long long)rows + 127) / 128), n32 = heads * (((long long)rows + 31) / 32);
     auto form = [&](int r, int streams) { *tm = r; return streams; };
+    // 17 to 32 rows, where the decoding kernel is the other choice (us, decoding kernel at its best split -> here): 72 heads of
+    // 512 keys D = 128 13.3 -> 8.9, 2048 keys 21.2 -> 17.9; 112 heads of 256 keys D = 160 13.6 -> 9.2, 4096 keys 64.6 -> 58.4
+    // (both in two splits); 224 of 1024 27.0 -> 24.1 (D = 128); 48 of 64 keys 8.2 -> 7.5 (D = 160).  Past 256 workgroups only
+    // D = 64 has two on a CU (320 heads of 512 keys 11.7 -> 9.9, D = 128 21.4 -> 22.6), and there long caches of many heads are
+    // the decoding kernel's (160 heads of 4096 keys 32.8 / 36.1)
+    if (rows <= kDecodeRows && (n > 64 || Skv <= 64)) {
+        const bool pays = Skv <= 4096 && (n <= 128 || (Skv <= 2048 && D == 64 && n <= 512) || (D > 64 && n <= 256));
+        return pays ? form(32, 4) : 1;
+    }
     if (n <= 64) {
         const bool pays = Skv <= 4096 ? Skv > 64 : n32 <= 32 || (Skv <= 8192 && (D == 64 || (D <= 128 && n32 <= 128)));
         return pays ? form(32, 4) : 1;
@@ -239,12 +250,17 @@ int default_splits(int BH, int rows, int Skv, int D)
 {
     int tile_m;
     const bool streams = pick_streams_kv(BH, rows, Skv, D, &tile_m) > 1;
-    if (rows <= kDecodeRows && !streams) return pick_splits_decode(BH, Skv);
+    if (rows <= kDecodeRows && !streams) return pick_splits_decode(BH, Skv, D);
     if (streams) {
-        // one workgroup per CU in all, once a stream has sixteen tiles to share (the states of a split cost a second kernel)
+        // one workgroup per CU in all, once a stream has sixteen tiles to share (the states of a split cost a second kernel).  Up to
+        // 32 rows: not before a head's K is as much as the decoding kernel splits (112 heads of 2048 keys D = 64 s1 13.1, s2 14.9),
+        // but four from 1024 keys on at D = 160 (8 heads s1 12.8, s4 10.8; 27 heads 15.6 / 13.8; at D = 128 9.4 / 9.8)
         const long long wg = (long long)BH * ((rows + tile_m - 1) / tile_m);
-        const long long want = tile_m > 32 || Skv < 2048 ? 1 : 256 / wg;
-        return want < 1 ? 1 : want > 16 ? 16 : (int)want;
+        if (tile_m > 32 || (rows <= kDecodeRows && BH > 64 && (int64_t)Skv * D <= 200000)) return 1;
+        const bool short_wide = D == 160 && rows <= kDecodeRows && BH <= 64 && Skv >= 1024 && Skv < 2048;
+        if (Skv < 2048 && !short_wide) return 1;
+        const long long most = short_wide ? 4 : 16, want = 256 / wg;
+        return want < 1 ? 1 : want > most ? (int)most : (int)want;
     }
     int tm, tn;
     pick_tile_kv(BH, rows, Skv, D, &tm, &tn);
@@ -623,9 +639,11 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     }
     const bool decode = heuristic_tile && rows <= kDecodeRows && a.streams <= 1;
     // The decoding kernel combines the runs itself while they are few: a mark (8 bytes) per run must fit a head's part of o,
-    // and past about 64 states per head the one workgroup that does it is slower than the merge kernel's many (8 heads, 4
-    // rows: 8 runs of 128 keys 7.9 us against 10.5 with two kernels, 16 runs level, 32 runs of 256 keys 15.2 against 13.3)
-    if (decode && splits > 1 && splits <= rows * D / 4 && splits * rows <= 64) a.ticket = call_ticket();
+    // and past about 64 states per head, or four columns for each thread, the one workgroup that does it is slower than the
+    // merge kernel's many (8 heads, 4 rows: 8 runs of 128 keys 7.9 us against 10.5 with two kernels, 16 runs level, 32 runs of
+    // 256 keys 15.2 against 13.3; 24 heads, 8 rows of D = 160, 8 runs of 97 keys 11.0 against 9.3)
+    if (decode && splits > 1 && splits <= rows * D / 4 && splits * rows <= 64 && rows * D <= 256 * tsdpa::decode_waves(a.BH, splits, Skv))
+        a.ticket = call_ticket();
     if (decode) {
         err = dtype == TSDPA_F16 ? tsdpa::launch_decode_f16(D, a) : tsdpa::launch_decode_bf16(D, a);
     } else if (dtype == TSDPA_F16) {

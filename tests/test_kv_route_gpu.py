@@ -1,0 +1,35 @@
+"""Calls of the cache entry points around the lines where their route changes: a decoding step in one run or several (by a
+head's K and by the heads), combined by its own workgroups or by the merge kernel (runs just below, at and past the eight that
+are loaded at once), and 17 to 32 query rows in streams of K/V tiles or in the decoding kernel, against the float64 oracle with
+the usual forward tolerances."""
+import pytest
+
+import test_sdpa_kv_gpu as kv
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads,D,Skv", [(1, 64, 1640), (1, 64, 1641), (3, 160, 656), (3, 160, 657), (65, 96, 2083), (65, 96, 2084),
+                                         (85, 128, 1600), (86, 128, 1600), (127, 64, 3200), (128, 64, 3200)])
+def test_one_run_or_several(heads, D, Skv):
+    for Sq, dtype in ((1, "bf16"), (8, "f16")):
+        q, k, v = kv.make_q_kv(1, heads, Sq, Skv, D, dtype, seed=7000 + Skv)
+        kv.check_kv(q, k, v, dtype, causal=True, tag="default runs")
+
+
+@pytest.mark.parametrize("D,Sq", [(64, 1), (96, 5), (128, 8), (160, 6), (160, 7), (128, 17), (64, 31)])
+def test_runs_combined_in_batches(D, Sq):
+    """Up to four columns per thread and 64 states (rows x runs) a head's last workgroup combines the runs."""
+    q, k, v = kv.make_q_kv(1, 3, Sq, 2300, D, "bf16", seed=7100 + D)
+    for splits in (2, 7, 8, 9, 15, 16, 17, 33):
+        kv.check_kv(q, k, v, "bf16", splits=splits, tag="runs")
+    kv.check_kv_lens(4, 6, 3, Sq, 2300, D, "bf16", [0, 40, 700, 2299], False, 9)     # runs without keys
+
+
+@pytest.mark.parametrize("heads,rows,Skv,D", [(2, 17, 33, 160), (64, 32, 64, 96), (65, 32, 64, 96), (16, 32, 300, 160), (5, 24, 1023, 160),
+                                              (64, 20, 1030, 160), (128, 17, 515, 128), (129, 32, 200, 64), (512, 17, 90, 64), (513, 17, 90, 64),
+                                              (256, 18, 70, 128), (257, 18, 70, 128), (66, 20, 4096, 64), (66, 20, 4097, 64), (70, 32, 1300, 160)])
+def test_seventeen_to_thirty_two_rows(heads, rows, Skv, D):
+    q, k, v = kv.make_q_kv(1, heads, rows, Skv, D, "f16", seed=7200 + heads)
+    kv.check_kv(q, k, v, "f16", causal=True, tag="few rows")
+    kv.check_kv_lens(2, heads, heads // 2 if heads % 2 == 0 else heads, rows // 2, Skv, D, "bf16", [Skv // 3, Skv], False, 0)
