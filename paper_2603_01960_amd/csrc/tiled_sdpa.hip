@@ -308,6 +308,26 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
                        int tile_m, int tile_n, unsigned flags,
                        int splits, void *workspace, unsigned long long workspace_bytes);
 
+// Combines the states of a call's splits (a.BH heads of a.S rows).  Each kernel in the form that loads no more than the splits
+// need: see its header.
+template <typename T> static void launch_merge(const tsdpa::LaunchArgs &a, void *o, bool wide, int D)
+{
+    using namespace tsdpa;
+    if (wide) {
+        static_assert(kMergeLanes * kMergePerLane >= TSDPA_MAX_SPLITS, "every split needs a thread");
+        const auto kernel = a.splits <= 4 * kMergeLanes ? sdpa_merge_wide_kernel<T, 4>
+                          : a.splits <= 8 * kMergeLanes ? sdpa_merge_wide_kernel<T, 8> : sdpa_merge_wide_kernel<T, kMergePerLane>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)a.S, (unsigned)a.BH), dim3(D / 4, kMergeLanes), 0, a.stream,
+                           (const float *)a.ws, (T *)o, a.lse, D, a.splits);
+        return;
+    }
+    const unsigned rows = (unsigned)((int64_t)a.BH * a.S);     // below 2^30: see validate_shape_kv
+    const dim3 block(D / 4, 256 / (D / 4));
+    const auto kernel = a.splits <= 4 ? sdpa_merge_kernel<T, 4> : a.splits <= 8 ? sdpa_merge_kernel<T, 8> : sdpa_merge_kernel<T, 0>;
+    hipLaunchKernelGGL(kernel, dim3((rows + block.y - 1) / block.y), block, 0, a.stream,
+                       (const float *)a.ws, (T *)o, a.lse, rows, (unsigned)a.S, D, a.splits);
+}
+
 extern "C" {
 
 int tiled_sdpa_version(void) { return kVersion; }
@@ -670,25 +690,10 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     // 128 2-3 us less for the call, level at D = 160).  With thousands of
     // rows the walking threads are many enough to hide it themselves and launch an eighth of the threads
     // (8 splits of 8192 rows: 47 us per call against 55 us).
-    if (splits > 1 && (splits > 8 || decode || (splits >= 4 && out_rows * D <= 131072)) && out_rows <= 2048) {
-        static_assert(tsdpa::kMergeLanes * tsdpa::kMergePerLane >= TSDPA_MAX_SPLITS, "every split needs a thread");
-        const dim3 block(D / 4, tsdpa::kMergeLanes);
-        if (dtype == TSDPA_F16)
-            hipLaunchKernelGGL(tsdpa::sdpa_merge_wide_kernel<_Float16>, dim3((unsigned)out_rows), block, 0, (hipStream_t)stream,
-                               (const float *)workspace, (_Float16 *)o, lse, B * Hkv, rows, D, splits);
-        else
-            hipLaunchKernelGGL(tsdpa::sdpa_merge_wide_kernel<__bf16>, dim3((unsigned)out_rows), block, 0, (hipStream_t)stream,
-                               (const float *)workspace, (__bf16 *)o, lse, B * Hkv, rows, D, splits);
-        if (hipGetLastError() != hipSuccess) return TSDPA_ERR_LAUNCH;
-    } else if (splits > 1) {
-        const size_t threads = out_rows * (D / 4);
-        const unsigned blocks = (unsigned)((threads + 255) / 256);
-        if (dtype == TSDPA_F16)
-            hipLaunchKernelGGL(tsdpa::sdpa_merge_kernel<_Float16>, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
-                               (const float *)workspace, (_Float16 *)o, lse, B * Hkv, rows, D, splits);
-        else
-            hipLaunchKernelGGL(tsdpa::sdpa_merge_kernel<__bf16>, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
-                               (const float *)workspace, (__bf16 *)o, lse, B * Hkv, rows, D, splits);
+    if (splits > 1) {
+        const bool wide = (splits > 8 || decode || (splits >= 4 && out_rows * D <= 131072)) && out_rows <= 2048;
+        if (dtype == TSDPA_F16) launch_merge<_Float16>(a, o, wide, D);
+        else launch_merge<__bf16>(a, o, wide, D);
         if (hipGetLastError() != hipSuccess) return TSDPA_ERR_LAUNCH;
     }
     return TSDPA_OK;
