@@ -366,11 +366,11 @@ def bench_kv(pkg, torch, args, tile, flags):
     if roofline["bound"] == "hbm" and not args.no_ceilings:
         roofline["hbm_read_ceiling_GBs"] = hbm_read_ceiling(pkg, torch)
         roofline["frac_of_hbm_read_ceiling"] = round(roofline["achieved"] / roofline["hbm_read_ceiling_GBs"], 4)
-    rows = G * Sq                       # (17 to 32 rows: the decoding kernel where the heads are many)
-    kernel = ("sdpa_fwd_kernel<KV>" if tile or rows > 32 else "sdpa_decode_kernel" if rows <= 16 or B * Hkv > 64 else
+    rows = G * Sq                       # (17 to 32 rows: the decoding kernel where the heads are many or the cache long)
+    kernel = ("sdpa_fwd_kernel<KV>" if tile or rows > 32 else "sdpa_decode_kernel" if rows <= 16 else
               "sdpa_decode_kernel or sdpa_fwd_kernel<KV>")
-    if splits > 1:                      # (the decoding kernel combines up to 64 states per head itself)
-        kernel += " + sdpa_merge_kernel" if rows > 16 or splits * rows > 64 or tile else ""
+    if splits > 1:                      # (the decoding kernel combines up to 32 states per head itself)
+        kernel += " + sdpa_merge_kernel" if rows > 8 or splits * rows > 32 or tile else ""
     roofline.update({"traffic": None, "kernel": kernel,
                      "ms_avg_both_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
                      "compulsory_hbm_bytes_per_launch": comp_bytes})

@@ -659,10 +659,12 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     }
     const bool decode = heuristic_tile && rows <= kDecodeRows && a.streams <= 1;
     // The decoding kernel combines the runs itself while they are few: a mark (8 bytes) per run must fit a head's part of o,
-    // and past about 64 states per head, or four columns for each thread, the one workgroup that does it is slower than the
-    // merge kernel's many (8 heads, 4 rows: 8 runs of 128 keys 7.9 us against 10.5 with two kernels, 16 runs level, 32 runs of
-    // 256 keys 15.2 against 13.3; 24 heads, 8 rows of D = 160, 8 runs of 97 keys 11.0 against 9.3)
-    if (decode && splits > 1 && splits <= rows * D / 4 && splits * rows <= 64 && rows * D <= 256 * tsdpa::decode_waves(a.BH, splits, Skv))
+    // and past 32 states per head, eight rows, or four columns for each thread, the one workgroup that does it is slower than the
+    // merge kernel's many (time with the marks / with two kernels, over 300 shapes: one row 0.95 at 2 runs, 0.97 at 8, 1.04 at 20;
+    // up to four rows 0.95, 0.99, 1.07; up to eight 0.99 at 2, 1.05 at 8; 9 to 16 rows 1.20 at 2; 24 heads, 8 rows of D = 160, 8
+    // runs of 97 keys 11.0 us against 9.3)
+    if (decode && splits > 1 && rows <= 8 && splits * rows <= 32 && splits <= rows * D / 4 &&
+        rows * D <= 256 * tsdpa::decode_waves(a.BH, splits, Skv))
         a.ticket = call_ticket();
     if (decode) {
         err = dtype == TSDPA_F16 ? tsdpa::launch_decode_f16(D, a) : tsdpa::launch_decode_bf16(D, a);

@@ -17,9 +17,9 @@ def test_one_run_or_several(heads, D, Skv):
         kv.check_kv(q, k, v, dtype, causal=True, tag="default runs")
 
 
-@pytest.mark.parametrize("D,Sq", [(64, 1), (96, 5), (128, 8), (160, 6), (160, 7), (128, 17), (64, 31)])
-def test_runs_combined_in_batches(D, Sq):
-    """Up to four columns per thread and 64 states (rows x runs) a head's last workgroup combines the runs."""
+@pytest.mark.parametrize("D,Sq", [(64, 1), (160, 1), (96, 2), (128, 4), (96, 5), (160, 6), (160, 8), (128, 9), (64, 16)])
+def test_runs_combined(D, Sq):
+    """Few rows and runs are combined by a head's last workgroup, the others by the merge kernel."""
     q, k, v = kv.make_q_kv(1, 3, Sq, 2300, D, "bf16", seed=7100 + D)
     for splits in (2, 7, 8, 9, 15, 16, 17, 33):
         kv.check_kv(q, k, v, "bf16", splits=splits, tag="runs")
