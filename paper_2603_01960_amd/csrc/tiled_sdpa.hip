@@ -155,12 +155,18 @@ int validate_shape(int B, int H, int S, int D, int dtype)
 // or more (long caches: more loads in flight pay), else for one per CU, never cutting runs shorter
 // than 4 tiles for up to 64 query rows or 16 tiles beyond (each split of a query tile writes and the
 // merge re-reads T_M x D floats, which a short run does not amortise).
+// Of 128-row tiles a CU holds two and no more, and what exceeds two per CU is another round, mostly empty: so as many splits as
+// stay within the first, and from 342 tiles on, where two splits are a round and a third and more, two on long caches only, whose
+// unequal entries gain from shorter runs (us, rounded up -> this: 156 tiles of 4520 keys D = 128 4 splits 96.9 -> 3 splits 78.2;
+// 153 of 8834 D = 64 57.1 -> 50.3; 248 of 6113 D = 160 3 splits 203 -> 2 splits 158; 196 of 14584 D = 96 183 -> 163; 464 of 2048
+// D = 128 2 splits 88.1 -> 1 split 68.1; the other way, lengths from a tenth of the capacity: 216 of 32768 D = 160 459 -> 485,
+// 160 of 8649 D = 64 50.4 -> 56.0).
 int pick_splits(int BH, int Sq, int Skv, int tm, int tn)
 {
     const int64_t base = (int64_t)BH * ((Sq + tm - 1) / tm);
     const int64_t tiles = (Skv + tn - 1) / tn;
     if (base <= 0 || base >= 512) return 1;
-    int64_t want = (512 + base - 1) / base;
+    int64_t want = tm != 128 ? (512 + base - 1) / base : base <= 256 ? 512 / base : base > 341 && Skv < 8192 ? 1 : 2;
     if (tiles / want < 16) {
         want = (256 + base - 1) / base;
         const int64_t shortest = Sq <= 64 ? 4 : 16;
@@ -294,7 +300,9 @@ void pick_tile_kv(long long heads, int Sq, int Skv, int D, int *tm, int *tn)
 {
     // (up to 32 rows the decoding kernel takes over, whose tile is its own)
     *tm = Sq <= 64 ? 64 : 128;
-    *tn = Skv >= 512 ? 64 : 32;
+    // (D = 128: 64-row tiles on short caches too, 1.3 to 1.5 times as fast: 42 heads of 512 rows, 128
+    // keys 11.7 -> 7.8 us, 210 of 920 rows, 230 keys 68.3 -> 48.0)
+    *tn = Skv >= 512 || D == 128 ? 64 : 32;
     // D = 160: 32-row tiles are level or ahead (3-10 %) until the query block is long (2048 rows: 64-row tiles
     // 2-5 % ahead) or its 128-row tiles are fewer than the CUs (15 % ahead at one head's 512 or 1024 rows)
     if (D == 160) *tn = (Sq >= 2048 || (Sq >= 128 && Skv >= 512 && heads * ((Sq + 127) / 128) < 256)) ? 64 : 32;
@@ -607,11 +615,11 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
         }
     }
     // Long query blocks against a dense cache of one length, no mask, no split: the 256-row query tile of the
-    // square problem, under the same conditions (with 256 such workgroups the 128-row tile has 512 and is not
-    // split either, so the split count does not depend on this choice)
+    // square problem, under the same conditions.  (Where the last 256 rows of the heads are half empty, 256 such workgroups can
+    // be fewer than 512 of 128 rows, which then fill the chip in one round.)
     if (heuristic_tile && splits == 1 && block_table == nullptr && kv_lens == nullptr &&
         !(flags & TSDPA_FLAG_CAUSAL) && D >= 96 && rows >= (D == 160 ? 1024 : D == 96 ? 4096 : 2048) &&
-        (int64_t)B * Hkv * ((rows + 255) / 256) >= 256) {
+        (int64_t)B * Hkv * ((rows + 255) / 256) >= 256 && (Skv < 1985 || (int64_t)B * Hkv * ((rows + 127) / 128) >= 512)) {
         tile_m = 256;
         tile_n = 64;
     }

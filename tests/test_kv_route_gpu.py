@@ -33,3 +33,11 @@ def test_seventeen_to_thirty_two_rows(heads, rows, Skv, D):
     q, k, v = kv.make_q_kv(1, heads, rows, Skv, D, "f16", seed=7200 + heads)
     kv.check_kv(q, k, v, "f16", causal=True, tag="few rows")
     kv.check_kv_lens(2, heads, heads // 2 if heads % 2 == 0 else heads, rows // 2, Skv, D, "bf16", [Skv // 3, Skv], False, 0)
+
+
+# 128-row query tiles around two per CU: (heads, rows, Skv, D), one or more splits of the key range
+@pytest.mark.parametrize("heads,rows,Skv,D", [(27, 1100, 1100, 64), (30, 1100, 1060, 96), (38, 1100, 2050, 64), (2, 200, 100, 128),
+                                              (65, 128, 511, 128), (3, 300, 33, 128), (85, 129, 2100, 64), (86, 257, 2100, 64), (171, 129, 2100, 64)])
+def test_chunks_around_two_tiles_per_cu(heads, rows, Skv, D):
+    q, k, v = kv.make_q_kv(1, heads, rows, Skv, D, "bf16", seed=7300 + rows)
+    kv.check_kv(q, k, v, "bf16", causal=Skv >= rows, tag="chunk")
