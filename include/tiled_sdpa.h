@@ -219,7 +219,7 @@ int tiled_sdpa_fwd_kvcache(const void *q, const void *k, const void *v, void *o,
  *   minus the workspace.  Results are bit-identical to tiled_sdpa_fwd_kvcache with the same tile and
  *   split count: the same kernels run.
  *   Limit: tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, n) <= TSDPA_STATIC_SCRATCH_BYTES, n being `splits`
- *   or the heuristic's count for splits = 0; beyond it the call enqueues nothing and returns
+ *   or the heuristic's count for splits = 0 (which is smaller here where the default count does not fit); beyond it the call enqueues nothing and returns
  *   TSDPA_ERR_STATIC_SCRATCH (pass fewer splits, or use tiled_sdpa_fwd_kvcache).  n = 1 needs no scratch.
  *   Nothing in the buffer has to start at zero: every word the second kernel reads is written by the
  *   first kernel of the same call; its contents after a call are unspecified.

@@ -151,30 +151,50 @@ int validate_shape(int B, int H, int S, int D, int dtype)
 }
 
 // Splits along the key axis (from timings on MI355X).  None when the query tiles alone give every CU
-// two workgroups.  Otherwise aim for two workgroups per CU if every split then still streams 16 tiles
-// or more (long caches: more loads in flight pay), else for one per CU, never cutting runs shorter
-// than 4 tiles for up to 64 query rows or 16 tiles beyond (each split of a query tile writes and the
+// two workgroups.  64- and 256-row query tiles (and the fewest splits that the library settles for): two workgroups per CU if
+// every split then still streams 16 tiles or more (long caches: more loads in flight pay), else one per CU, never cutting runs
+// shorter than 4 tiles for up to 64 query rows or 16 tiles beyond (each split of a query tile writes and the
 // merge re-reads T_M x D floats, which a short run does not amortise).
-// Of 128-row tiles a CU holds two and no more, and what exceeds two per CU is another round, mostly empty: so as many splits as
-// stay within the first, and from 342 tiles on, where two splits are a round and a third and more, two on long caches only, whose
-// unequal entries gain from shorter runs (us, rounded up -> this: 156 tiles of 4520 keys D = 128 4 splits 96.9 -> 3 splits 78.2;
-// 153 of 8834 D = 64 57.1 -> 50.3; 248 of 6113 D = 160 3 splits 203 -> 2 splits 158; 196 of 14584 D = 96 183 -> 163; 464 of 2048
-// D = 128 2 splits 88.1 -> 1 split 68.1; the other way, lengths from a tenth of the capacity: 216 of 32768 D = 160 459 -> 485,
-// 160 of 8649 D = 64 50.4 -> 56.0).
-int pick_splits(int BH, int Sq, int Skv, int tm, int tn)
+int round_splits(int64_t base, int64_t tiles, int Sq)
 {
-    const int64_t base = (int64_t)BH * ((Sq + tm - 1) / tm);
-    const int64_t tiles = (Skv + tn - 1) / tn;
-    if (base <= 0 || base >= 512) return 1;
-    int64_t want = tm != 128 ? (512 + base - 1) / base : base <= 256 ? 512 / base : base > 341 && Skv < 8192 ? 1 : 2;
+    int64_t want = (512 + base - 1) / base;
     if (tiles / want < 16) {
         want = (256 + base - 1) / base;
         const int64_t shortest = Sq <= 64 ? 4 : 16;
         const int64_t most = tiles / shortest > 1 ? tiles / shortest : 1;
         if (want > most) want = most;
     }
-    if (want > TSDPA_MAX_SPLITS) want = TSDPA_MAX_SPLITS;
-    return (int)want;
+    return (int)(want > TSDPA_MAX_SPLITS ? TSDPA_MAX_SPLITS : want);
+}
+
+// 128-row query tiles: the count of the least cost, in steps of 64 keys.  A CU holds two workgroups and no more, so the grid runs
+// in rounds of 512, each as long as a run; a last round (or the only one) that gives a CU one workgroup at most takes
+// 0.74 of that.  Then a run's prologue (0.7), the merge kernel (2.3), the states that it reads (6.7 for every 512 tiles) and its
+// walk over the splits (0.19 each).  The constants are a fit to 700 calls, each timed at every split count (BF16; 8 to 511 tiles,
+// 1500 to 40000 keys, lengths from all, half and a tenth of the capacity on): on average 1.4 % behind the best count, where 512 /
+// tiles rounded up was 15.6 % and rounded down 5.3 % (us, up / down / this: 20 tiles of 11576 keys 20.1 / 20.1 / 19.7, 16 of
+// 11000 27.5 / 27.5 / 22.9, 144 of 16384, lengths from a tenth, 78.1 / 92.8 / 83.7, 156 of 4520 97 / 78 / 78).  Behind the former by more than
+// 10 %: 8 of the 700, most of them with lengths from a tenth of the capacity.  Up to four rounds (8 would be 0.1 % ahead at twice
+// the workspace) of runs of 512 keys or more.
+int pick_splits(int BH, int Sq, int Skv, int tm, int tn, bool fewest = false)
+{
+    const int64_t base = (int64_t)BH * ((Sq + tm - 1) / tm);
+    const int tiles = (int)(((int64_t)Skv + tn - 1) / tn);
+    if (base <= 0 || base >= 512) return 1;
+    if (tm != 128 || fewest) return round_splits(base, tiles, Sq);
+    int best = 1;
+    double least = 0;
+    for (int n = 1; n <= TSDPA_MAX_SPLITS && (n == 1 || (n * (int)base <= 2048 && tiles / n * tn >= 512)); ++n) {
+        const int grid = n * (int)base, last = grid % 512;
+        const double rounds = grid / 512 + (last > 256 ? 1.0 : last > 0 ? 0.74 : 0.0);
+        const double run = ((tiles + n - 1) / n * tn) * (1.0 / 64);
+        const double cost = rounds * (run + 0.7) + (n == 1 ? 0.0 : 2.3 + 6.7 * grid / 512 + 0.19 * n);
+        if (n == 1 || cost < least) {
+            best = n;
+            least = cost;
+        }
+    }
+    return best;
 }
 
 // A 64-bit number that no other call of any process has had, as far as chance goes: a counter from a random start,
@@ -252,7 +272,7 @@ int pick_streams_kv(long long heads, int rows, int Skv, int D, int *tm)
 }
 
 // Splits of a cache call whose tile is left to the library too.
-int default_splits(int BH, int rows, int Skv, int D)
+int default_splits(int BH, int rows, int Skv, int D, bool fewest = false)
 {
     int tile_m;
     const bool streams = pick_streams_kv(BH, rows, Skv, D, &tile_m) > 1;
@@ -270,7 +290,7 @@ int default_splits(int BH, int rows, int Skv, int D)
     }
     int tm, tn;
     pick_tile_kv(BH, rows, Skv, D, &tm, &tn);
-    return pick_splits(BH, rows, Skv, tm, tn);
+    return pick_splits(BH, rows, Skv, tm, tn, fewest);
 }
 
 int validate_shape_kv(int B, int H, int Sq, int Skv, int D, int dtype, unsigned flags)
@@ -538,9 +558,13 @@ int tiled_sdpa_fwd_kvcache_static(const void *q, const void *k, const void *v, v
     if (splits < 0 || splits > TSDPA_MAX_SPLITS) return TSDPA_ERR_BAD_SPLITS;
     if ((int64_t)(H / Hkv) * Sq > (int64_t)std::numeric_limits<int>::max()) return TSDPA_ERR_BAD_SHAPE;
     if (splits == 0) {
-        if (tile_m == 0 && tile_n == 0) splits = default_splits(B * Hkv, (H / Hkv) * Sq, Skv, D);
-        else if (!valid_tile_kv(tile_m, tile_n, false)) return TSDPA_ERR_BAD_TILE;
-        else splits = pick_splits(B * Hkv, (H / Hkv) * Sq, Skv, tile_m, tile_n);
+        if (!(tile_m == 0 && tile_n == 0) && !valid_tile_kv(tile_m, tile_n, false)) return TSDPA_ERR_BAD_TILE;
+        // (the count that runs best, or the smaller one if only that fits the buffer)
+        for (const bool fewest : {false, true}) {
+            splits = tile_m == 0 ? default_splits(B * Hkv, (H / Hkv) * Sq, Skv, D, fewest)
+                                 : pick_splits(B * Hkv, (H / Hkv) * Sq, Skv, tile_m, tile_n, fewest);
+            if (tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits) <= (unsigned long long)TSDPA_STATIC_SCRATCH_BYTES) break;
+        }
     }
     const unsigned long long need = tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits);
     if (need > (unsigned long long)TSDPA_STATIC_SCRATCH_BYTES) return TSDPA_ERR_STATIC_SCRATCH;

@@ -41,3 +41,29 @@ def test_seventeen_to_thirty_two_rows(heads, rows, Skv, D):
 def test_chunks_around_two_tiles_per_cu(heads, rows, Skv, D):
     q, k, v = kv.make_q_kv(1, heads, rows, Skv, D, "bf16", seed=7300 + rows)
     kv.check_kv(q, k, v, "bf16", causal=Skv >= rows, tag="chunk")
+
+
+def test_long_caches_in_few_tiles():
+    """Splits of one CU's two workgroups each, runs of 512 keys and more."""
+    from paper_2603_01960_amd import binding
+    for D, Skv in ((64, 8200), (160, 8321)):
+        q, k, v = kv.make_q_kv(1, 3, 400, Skv, D, "bf16", seed=7400 + D)
+        n = binding.kv_default_splits(1, 3, 400, Skv, D, binding.BF16)
+        assert n > 1 and n * 12 <= 2048 and Skv // n >= 512
+        kv.check_kv(q, k, v, "bf16", causal=True, tag="long cache")
+
+
+def test_without_a_workspace_the_count_is_one_that_fits():
+    """26 heads of 128 rows at D = 160: the default count's states exceed the library's own buffer, a smaller count's do not."""
+    import torch
+    from paper_2603_01960_amd import binding
+    H, Sq, Skv, D = 26, 128, 12000, 160
+    n = binding.kv_default_splits(1, H, Sq, Skv, D, binding.BF16)
+    assert binding.kv_workspace_bytes(1, H, Sq, D, n) > binding.STATIC_SCRATCH_BYTES
+    g = torch.Generator("cuda").manual_seed(7500)
+    q, k, v = (torch.randn((1, H, s, D), device="cuda", generator=g).bfloat16() for s in (Sq, Skv, Skv))
+    o = torch.full_like(q, float("nan"))
+    st = binding.tiled_sdpa_fwd_kvcache_static(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None, None, 1, H, H, Sq, Skv, D,
+                                               float("nan"), binding.BF16, torch.cuda.current_stream().cuda_stream, 0, 0, 0, 0)
+    assert st == 0, binding.status_string(st)
+    assert torch.equal(o, binding.sdpa_kv(q, k, v, splits=10))       # one workgroup per CU: 256 / 26, rounded up
