@@ -169,24 +169,25 @@ int round_splits(int64_t base, int64_t tiles, int Sq)
 
 // 128-row query tiles: the count of the least cost, in steps of 64 keys.  A CU holds two workgroups and no more, so the grid runs
 // in rounds of 512, each as long as a run; a last round (or the only one) that gives a CU one workgroup at most takes
-// 0.74 of that.  Then a run's prologue (0.7), the merge kernel (2.3), the states that it reads (6.7 for every 512 tiles) and its
-// walk over the splits (0.19 each).  The constants are a fit to 700 calls, each timed at every split count (BF16; 8 to 511 tiles,
-// 1500 to 40000 keys, lengths from all, half and a tenth of the capacity on): on average 1.4 % behind the best count, where 512 /
-// tiles rounded up was 15.6 % and rounded down 5.3 % (us, up / down / this: 20 tiles of 11576 keys 20.1 / 20.1 / 19.7, 16 of
-// 11000 27.5 / 27.5 / 22.9, 144 of 16384, lengths from a tenth, 78.1 / 92.8 / 83.7, 156 of 4520 97 / 78 / 78).  Behind the former by more than
-// 10 %: 8 of the 700, most of them with lengths from a tenth of the capacity.  Up to four rounds (8 would be 0.1 % ahead at twice
-// the workspace) of runs of 512 keys or more.
-int pick_splits(int BH, int Sq, int Skv, int tm, int tn, bool fewest = false)
+// 0.72 of that, at D = 160 0.9 (two splits against one: 204 tiles of 3776 keys there 0.76 of the time, 252 of 3648 keys at D = 64
+// 0.98).  Then a run's prologue (0.7), the merge kernel (2.3), the states that it reads (6.7 for every 512 tiles) and its walk over
+// the splits (0.19 each).  The constants are a fit to 700 calls, each timed at every split count (BF16; 8 to 511 tiles, 1500 to 40000
+// keys, lengths from all, half and a tenth of the capacity on): on average 1.3 % behind the best count, where 512 / tiles rounded
+// up was 15.6 % and rounded down 5.3 % (us, up / down / this: 16 tiles of 11000 keys 27.5 / 27.5 / 22.9, 144 of 16384, lengths from a
+// tenth, 78 / 93 / 84, 156 of 4520 97 / 78 / 78).  Behind the former by more than 10 %: 7 of the 700, most of them with lengths from a
+// tenth of the capacity.  Up to four rounds (eight would be 0.1 % ahead at twice the workspace) of runs of 512 keys or more.
+int pick_splits(int BH, int Sq, int Skv, int D, int tm, int tn, bool fewest = false)
 {
     const int64_t base = (int64_t)BH * ((Sq + tm - 1) / tm);
     const int tiles = (int)(((int64_t)Skv + tn - 1) / tn);
     if (base <= 0 || base >= 512) return 1;
     if (tm != 128 || fewest) return round_splits(base, tiles, Sq);
+    const double alone = D == 160 ? 0.9 : 0.72;
     int best = 1;
     double least = 0;
     for (int n = 1; n <= TSDPA_MAX_SPLITS && (n == 1 || (n * (int)base <= 2048 && tiles / n * tn >= 512)); ++n) {
         const int grid = n * (int)base, last = grid % 512;
-        const double rounds = grid / 512 + (last > 256 ? 1.0 : last > 0 ? 0.74 : 0.0);
+        const double rounds = grid / 512 + (last > 256 ? 1.0 : last > 0 ? alone : 0.0);
         const double run = ((tiles + n - 1) / n * tn) * (1.0 / 64);
         const double cost = rounds * (run + 0.7) + (n == 1 ? 0.0 : 2.3 + 6.7 * grid / 512 + 0.19 * n);
         if (n == 1 || cost < least) {
@@ -290,7 +291,7 @@ int default_splits(int BH, int rows, int Skv, int D, bool fewest = false)
     }
     int tm, tn;
     pick_tile_kv(BH, rows, Skv, D, &tm, &tn);
-    return pick_splits(BH, rows, Skv, tm, tn, fewest);
+    return pick_splits(BH, rows, Skv, D, tm, tn, fewest);
 }
 
 int validate_shape_kv(int B, int H, int Sq, int Skv, int D, int dtype, unsigned flags)
@@ -514,7 +515,7 @@ int tiled_sdpa_kv_tile_splits(int B, int H, int Sq, int Skv, int D, int dtype, u
     const int st = tiled_sdpa_kv_default_splits(B, H, Sq, Skv, D, dtype, flags, splits);
     if (st != TSDPA_OK || (int64_t)B * H * Sq == 0 || (tile_m == 0 && tile_n == 0)) return st;
     if (!valid_tile_kv(tile_m, tile_n, false)) return TSDPA_ERR_BAD_TILE;
-    *splits = pick_splits(B * H, Sq, Skv, tile_m, tile_n);
+    *splits = pick_splits(B * H, Sq, Skv, D, tile_m, tile_n);
     return TSDPA_OK;
 }
 
@@ -562,7 +563,7 @@ int tiled_sdpa_fwd_kvcache_static(const void *q, const void *k, const void *v, v
         // (the count that runs best, or the smaller one if only that fits the buffer)
         for (const bool fewest : {false, true}) {
             splits = tile_m == 0 ? default_splits(B * Hkv, (H / Hkv) * Sq, Skv, D, fewest)
-                                 : pick_splits(B * Hkv, (H / Hkv) * Sq, Skv, tile_m, tile_n, fewest);
+                                 : pick_splits(B * Hkv, (H / Hkv) * Sq, Skv, D, tile_m, tile_n, fewest);
             if (tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits) <= (unsigned long long)TSDPA_STATIC_SCRATCH_BYTES) break;
         }
     }
@@ -634,7 +635,7 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
         if (!heuristic_tile) {
             // the tile's own count, unless the workspace holds the states of the default count only (a caller may have sized it by
             // tiled_sdpa_kv_default_splits, which speaks of forms that an explicit tile never takes)
-            const int own = pick_splits(B * Hkv, rows, Skv, tile_m, tile_n);
+            const int own = pick_splits(B * Hkv, rows, Skv, D, tile_m, tile_n);
             if (own <= splits || (workspace && workspace_bytes >= tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, own))) splits = own;
         }
     }
