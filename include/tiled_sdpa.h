@@ -273,7 +273,9 @@ int tiled_sdpa_kv_default_splits(int B, int H, int Sq, int Skv, int D, int dtype
 int tiled_sdpa_kv_tile_splits(int B, int H, int Sq, int Skv, int D, int dtype, unsigned flags, int tile_m, int tile_n, int *splits);
 
 /* Workspace bytes tiled_sdpa_fwd_kv needs for `splits` >= 1 (a value from tiled_sdpa_kv_default_splits,
- * or the caller's own): B*H*splits*Sq*(D+2) floats.  0 for splits <= 1 or negative arguments. */
+ * or the caller's own): B*H*splits*Sq*(D+2) floats.  0 for splits <= 1 or negative arguments.
+ * The counts above are at most 2048 workgroups of 128 rows (170 MB at D = 160), and, but for 33 to 64 rows per key/value head,
+ * never fewer for a longer cache: a workspace sized for the capacity serves every shorter length with splits = 0. */
 unsigned long long tiled_sdpa_kv_workspace_bytes(int B, int H, int Sq, int D, int splits);
 
 /*

@@ -174,8 +174,11 @@ int round_splits(int64_t base, int64_t tiles, int Sq)
 // the splits (0.19 each).  The constants are a fit to 700 calls, each timed at every split count (BF16; 8 to 511 tiles, 1500 to 40000
 // keys, lengths from all, half and a tenth of the capacity on): on average 1.3 % behind the best count, where 512 / tiles rounded
 // up was 15.6 % and rounded down 5.3 % (us, up / down / this: 16 tiles of 11000 keys 27.5 / 27.5 / 22.9, 144 of 16384, lengths from a
-// tenth, 78 / 93 / 84, 156 of 4520 97 / 78 / 78).  Behind the former by more than 10 %: 7 of the 700, most of them with lengths from a
+// tenth, 78 / 93 / 84, 156 of 4520 97 / 78 / 78).  Behind the former by more than 10 %: 6 of the 700, most of them with lengths from a
 // tenth of the capacity.  Up to four rounds (eight would be 0.1 % ahead at twice the workspace) of runs of 512 keys or more.
+// A longer cache never gets fewer splits, so that a workspace sized for the capacity serves every length on the way there: the
+// cost is keys * a(n) + b(n) with b growing in n, and the counts that 512 keys per run leave out are the largest.  (With runs
+// rounded up to whole tiles, which gained nothing on the 700 calls, 24 tiles had 21 splits at 15872 keys and 20 at 16384.)
 int pick_splits(int BH, int Sq, int Skv, int D, int tm, int tn, bool fewest = false)
 {
     const int64_t base = (int64_t)BH * ((Sq + tm - 1) / tm);
@@ -185,10 +188,10 @@ int pick_splits(int BH, int Sq, int Skv, int D, int tm, int tn, bool fewest = fa
     const double alone = D == 160 ? 0.9 : 0.72;
     int best = 1;
     double least = 0;
-    for (int n = 1; n <= TSDPA_MAX_SPLITS && (n == 1 || (n * (int)base <= 2048 && tiles / n * tn >= 512)); ++n) {
+    for (int n = 1; n <= TSDPA_MAX_SPLITS && (n == 1 || (n * (int)base <= 2048 && Skv / n >= 512)); ++n) {
         const int grid = n * (int)base, last = grid % 512;
         const double rounds = grid / 512 + (last > 256 ? 1.0 : last > 0 ? alone : 0.0);
-        const double run = ((tiles + n - 1) / n * tn) * (1.0 / 64);
+        const double run = Skv / (64.0 * n);
         const double cost = rounds * (run + 0.7) + (n == 1 ? 0.0 : 2.3 + 6.7 * grid / 512 + 0.19 * n);
         if (n == 1 || cost < least) {
             best = n;
@@ -280,10 +283,12 @@ int default_splits(int BH, int rows, int Skv, int D, bool fewest = false)
     if (rows <= kDecodeRows && !streams) return pick_splits_decode(BH, Skv, D);
     if (streams) {
         // one workgroup per CU in all, once a stream has sixteen tiles to share (the states of a split cost a second kernel).  Up to
-        // 32 rows: not before a head's K is as much as the decoding kernel splits (112 heads of 2048 keys D = 64 s1 13.1, s2 14.9),
-        // but four from 1024 keys on at D = 160 (8 heads s1 12.8, s4 10.8; 27 heads 15.6 / 13.8; at D = 128 9.4 / 9.8)
+        // 32 rows: with more than 64 heads what the decoding kernel has, which takes over as the cache grows (112 heads of 2048 keys D =
+        // 64 s1 13.1, s2 14.9), but four from 1024 keys on at D = 160 (8 heads s1 12.8, s4 10.8; 27 heads 15.6 / 13.8; at D = 128
+        // 9.4 / 9.8)
         const long long wg = (long long)BH * ((rows + tile_m - 1) / tile_m);
-        if (tile_m > 32 || (rows <= kDecodeRows && BH > 64 && (int64_t)Skv * D <= 200000)) return 1;
+        if (rows <= kDecodeRows && BH > 64) return Skv < 2048 ? 1 : pick_splits_decode(BH, Skv, D);
+        if (tile_m > 32) return 1;
         const bool short_wide = D == 160 && rows <= kDecodeRows && BH <= 64 && Skv >= 1024 && Skv < 2048;
         if (Skv < 2048 && !short_wide) return 1;
         const long long most = short_wide ? 4 : 16, want = 256 / wg;
