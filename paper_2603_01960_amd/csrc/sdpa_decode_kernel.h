@@ -156,8 +156,9 @@ template <> struct DecodeRead<160> {
 #undef TSDPA_RD_V
 #undef TSDPA_RD_WAIT
 
-// PAGED: a descriptor per tile (see the forward kernel's paged variant).
-template <typename T, int D, int NQ, int NW, bool PAGED>
+// PAGED: a descriptor per tile (see the forward kernel's paged variant).  HALVES: each weight multiplied as two 16-bit halves,
+// see pick_halves (an instantiation of its own: the code alone costs the shortest calls 0.3 us).
+template <typename T, int D, int NQ, int NW, bool PAGED, bool HALVES>
 __global__ void __launch_bounds__(NW * 64, 2)
 sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v,
                    T *o, float *__restrict__ lse, int S, int heads, float c, float tau, uint32_t qsign, int causal,
@@ -448,7 +449,7 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
         vptr[i] = __builtin_bit_cast(uint32_t, vslot) + v_row * G::ROW + ((i ^ G::vx(v_row)) << 5) + (lane & 3) * 8;
 
     // weights of one tile and their sum, this lane's share
-    vec8 pb[NQ];
+    vec8 pb[NQ], ph[NQ];                          // (HALVES: half of each, rounded, and what that leaves of it)
     auto exponentials = [&](const f32x4 (&s)[2], int nq, int key0) __attribute__((always_inline)) {
         float sum = 0.f;
 #pragma unroll
@@ -458,7 +459,8 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
                 float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][e], c, -m_ref[nq]));
                 if (key0 + b * 16 + e > klim[nq]) p = 0.f;
                 sum += p;
-                pb[nq][b * 4 + e] = (T)p;
+                pb[nq][b * 4 + e] = (T)(HALVES ? 0.5f * p : p);
+                if constexpr (HALVES) ph[nq][b * 4 + e] = (T)(p - (float)pb[nq][b * 4 + e]);
             }
         return sum;
     };
@@ -518,7 +520,10 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
         for (int db = 0; db < DB; ++db) {
             const i16x8 a = __builtin_shufflevector(vf[db][0], vf[db][1], 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
-            for (int nq = 0; nq < NQ; ++nq) oacc[nq][db] = E::mfma(__builtin_bit_cast(vec8, a), pb[nq], oacc[nq][db]);
+            for (int nq = 0; nq < NQ; ++nq) {
+                oacc[nq][db] = E::mfma(__builtin_bit_cast(vec8, a), pb[nq], oacc[nq][db]);
+                if constexpr (HALVES) oacc[nq][db] = E::mfma(__builtin_bit_cast(vec8, a), ph[nq], oacc[nq][db]);
+            }
         }
         cur = next;
     }
@@ -599,9 +604,9 @@ sdpa_decode_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__
 #endif
 }
 
-template <typename T, int D, int NQ, int NW, bool PAGED> int launch_decode_one(const LaunchArgs &a)
+template <typename T, int D, int NQ, int NW, bool PAGED, bool HALVES> int launch_decode_one(const LaunchArgs &a)
 {
-    auto kern = sdpa_decode_kernel<T, D, NQ, NW, PAGED>;
+    auto kern = sdpa_decode_kernel<T, D, NQ, NW, PAGED, HALVES>;
     constexpr int lds_bytes = NW * 2 * DecodeGeom<D>::TILE;
     static_assert(NW * NQ * 16 * D * 4 <= lds_bytes, "the states of all wavefronts must fit");
     static std::once_flag once;
@@ -616,20 +621,26 @@ template <typename T, int D, int NQ, int NW, bool PAGED> int launch_decode_one(c
     return (int)hipGetLastError();
 }
 
-template <typename T, int D, int NQ> int launch_decode_rows(const LaunchArgs &a)
+template <typename T, int D, int NQ, bool HALVES> int launch_decode_rows(const LaunchArgs &a)
 {
     if (decode_waves(a.BH, a.splits, a.Skv) == 8)
-        return a.block_table ? launch_decode_one<T, D, NQ, 8, true>(a) : launch_decode_one<T, D, NQ, 8, false>(a);
-    return a.block_table ? launch_decode_one<T, D, NQ, 4, true>(a) : launch_decode_one<T, D, NQ, 4, false>(a);
+        return a.block_table ? launch_decode_one<T, D, NQ, 8, true, HALVES>(a) : launch_decode_one<T, D, NQ, 8, false, HALVES>(a);
+    return a.block_table ? launch_decode_one<T, D, NQ, 4, true, HALVES>(a) : launch_decode_one<T, D, NQ, 4, false, HALVES>(a);
+}
+
+template <typename T, int D> int launch_decode_dim(const LaunchArgs &a)
+{
+    if (a.S > 16) return launch_decode_rows<T, D, 2, false>(a);
+    return a.halves ? launch_decode_rows<T, D, 1, true>(a) : launch_decode_rows<T, D, 1, false>(a);
 }
 
 template <typename T> int launch_decode(int D, const LaunchArgs &a)
 {
     switch (D) {
-        case 64: return a.S <= 16 ? launch_decode_rows<T, 64, 1>(a) : launch_decode_rows<T, 64, 2>(a);
-        case 96: return a.S <= 16 ? launch_decode_rows<T, 96, 1>(a) : launch_decode_rows<T, 96, 2>(a);
-        case 128: return a.S <= 16 ? launch_decode_rows<T, 128, 1>(a) : launch_decode_rows<T, 128, 2>(a);
-        default: return a.S <= 16 ? launch_decode_rows<T, 160, 1>(a) : launch_decode_rows<T, 160, 2>(a);
+        case 64: return launch_decode_dim<T, 64>(a);
+        case 96: return launch_decode_dim<T, 96>(a);
+        case 128: return launch_decode_dim<T, 128>(a);
+        default: return launch_decode_dim<T, 160>(a);
     }
 }
 

@@ -21,7 +21,7 @@ constexpr int kLdsPerCU = 160 * 1024;
 // halves and move them back and forth (or to scratch) inside the loop.
 template <int D, int NW, int TN> constexpr int waves_per_simd() { return (TN == 32 && D <= 128) ? 3 : 2; }
 
-template <typename T, int D, int NW, int TN, int KV = 0, int NS = 1>     // KV: 0 square, 1 dense cache, 2 paged cache; NS streams
+template <typename T, int D, int NW, int TN, int KV = 0, int NS = 1>     // KV: 0 square, 1 dense cache, 2 paged cache, 3 and 4 these with halved weights; NS streams
 int launch_one(const LaunchArgs &a)
 {
     constexpr int WPS = NS > 1 ? 2 : waves_per_simd<D, NW, TN>();
@@ -90,7 +90,10 @@ template <typename T, int D, int KV>
 int launch_streams(int tile_m, const LaunchArgs &a)
 {
     switch (tile_m * 10 + a.streams) {
-        case 324: return launch_one<T, D, 1, 32, KV, 4>(a);
+        case 324:
+            if constexpr (KV != 0 && D < 160)
+                if (a.halves) return launch_one<T, D, 1, 32, KV + 2, 4>(a);
+            return launch_one<T, D, 1, 32, KV, 4>(a);
         case 642: return launch_one<T, D, 2, 32, KV, 2>(a);
         case 1282:
             if constexpr (KV == 0) return launch_one<T, D, 4, 32, KV, 2>(a);

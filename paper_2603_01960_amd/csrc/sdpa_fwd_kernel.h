@@ -193,7 +193,8 @@ constexpr float kNoWeight = -__FLT_MAX__;
 // buffer descriptor of its own, based at its page and as long as the tile has valid rows.
 // KVM: 0 = the paper's square problem, 1 = the general kernel over a dense cache, 2 = over a paged cache
 // (an instantiation of its own: the per-tile descriptors cost scalar registers in the loop, which the
-// latency-bound small decoding shapes of the dense path would pay for too).
+// latency-bound small decoding shapes of the dense path would pay for too).  3, 4: the same two, each weight multiplied
+// as two 16-bit halves, for the few query rows of a decoding step (pick_halves).
 // TILE: rows T_N of a K/V tile, plus 1000 * (NS - 1).  NS > 1: NS streams of NW wavefronts each work on
 // the same query rows; stream s takes the tiles s, s + NS, ... into LDS slots of its own, and the streams' states (o, m,
 // l of Eqs. 2-4) are combined through the LDS at the end, in their order.  For launches of few workgroups: the chain of tiles
@@ -210,7 +211,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 int batches, Divisor by_batches)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub; the body uses device-only types
-    constexpr bool KV = KVM != 0, PAGED = KVM == 2;
+    constexpr bool KV = KVM != 0, PAGED = KVM == 2 || KVM == 4, HALVES = KVM >= 3;
     constexpr int TN = TILE % 1000, NS = 1 + TILE / 1000;
     using E = Elem<T>;
     using vec8 = typename E::vec8;
@@ -560,6 +561,8 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
     };
     // p = 2^(s*c - m_ref); Eq. 3 sums the unrounded FP32 p (this lane's share of the tile is returned),
     // the PV product uses the 16-bit rounded p, left in pb as MFMA B-operands
+    // (HALVES: half of it rounded, and what that leaves, in ph)
+    vec8 ph[HALVES ? NB : 1][2];
     auto exponentials = [&](f32x16 (&sacc)[NB], int row0, vec8 (&pb)[NB][2], auto mask_tag) __attribute__((always_inline)) {
         constexpr bool MASK = decltype(mask_tag)::value;
         const int key0 = row0 + g * 4;
@@ -574,7 +577,8 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                 }
                 if (nb == 0 && i < 4) psum[i] = p;        // four partial sums: short dependency chains
                 else psum[i & 3] += p;
-                pb[nb][i >> 3][i & 7] = (T)p;
+                pb[nb][i >> 3][i & 7] = (T)(HALVES ? 0.5f * p : p);
+                if constexpr (HALVES) ph[nb][i >> 3][i & 7] = (T)(p - (float)pb[nb][i >> 3][i & 7]);
             }
         return (psum[0] + psum[1]) + (psum[2] + psum[3]);
     };
@@ -593,6 +597,7 @@ sdpa_fwd_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__res
                     i16x4 hi = lds_read_tr16(p0 + 8 * G::ROW);
                     i16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                     oacc[db] = E::mfma(__builtin_bit_cast(vec8, a), pb[nb][ks], oacc[db]);
+                    if constexpr (HALVES) oacc[db] = E::mfma(__builtin_bit_cast(vec8, a), ph[nb][ks], oacc[db]);
                 }
     };
 

@@ -25,6 +25,7 @@ struct LaunchArgs {
     int max_blocks, block_shift;
     int tile_rot;      // kv = 1, dense cache: 1 = every workgroup starts its sweep over the unmasked tiles at a tile of its own
     int batches;       // kv = 1: batch entries (BH / heads_per_batch)
+    int halves;        // kv = 1, at most 32 rows: 1 = each weight goes into the output product as two 16-bit halves (pick_halves)
     unsigned long long ticket; // decoding kernel, splits > 1: a number of this call alone (never 0) if it combines the runs itself, else 0
     int streams;       // kv = 0: streams of K/V tiles per workgroup (0 or 1: the plain form)
     int rows_per_head; // kv = 1: query positions per query head; S / rows_per_head query heads are folded into the S rows

@@ -228,13 +228,14 @@ constexpr int kDecodeRows = 32;
 // None where a workgroup is through a head's K about as soon as it could be through the second look at the states: 105000
 // elements, or 200000 with more than 64 heads, where the CUs are nearly full without (one split / the best of more: 12 heads
 // of 1608 keys D = 64 6.9 / 7.8; 15 of 627 D = 128 7.4 / 7.9; 64 of 746 D = 128 9.5 / 10.6; 70 of 2048 D = 96 12.8 / 14.3; 24
-// heads of 772 D = 160, past the line, 10.4 / 9.3).  Nor from half as many key/value heads as CUs on: a pass is then as fast
+// heads of 772 D = 160, past the line, 10.4 / 9.3; with more than 16 rows several runs are ahead: 10 heads of 20 rows, 621 keys
+// D = 160 13.9 / 10.8).  Nor from half as many key/value heads as CUs on: a pass is then as fast
 // (256 heads of 8192 keys: s1 177, s2 181, s4 185; lengths from a quarter of that: 127, 131-133, 130-132; 160 heads of 1024:
 // 18.0 / 22.5 / 23.5; 96 heads of 3000: 28.1 / 24.2 / 25.9; 32 heads of 8192: s4 30.9, s8 27.4, s16 28.5; 84 heads of 4096,
 // all full: s2 29.4, s3 30.4, and with lengths from a tenth of that s2 47.2, s3 38.1 for 66 of 8127).
-int pick_splits_decode(int BH, int Skv, int D)
+int pick_splits_decode(int BH, int rows, int Skv, int D)
 {
-    if ((int64_t)Skv * D <= (BH > 64 ? 200000 : 105000)) return 1;
+    if (rows <= 16 && (int64_t)Skv * D <= (BH > 64 ? 200000 : 105000)) return 1;
     const int most = Skv > 256 ? (Skv + 127) / 128 : 1;
     int want = BH >= 128 ? 1 : BH > 64 ? 2 : 256 / BH;
     if (want > most) want = most;
@@ -257,11 +258,14 @@ int pick_streams_kv(long long heads, int rows, int Skv, int D, int *tm)
     if (rows <= 16) return 1;
     const long long n = heads * (((long long)rows + 127) / 128), n32 = heads * (((long long)rows + 31) / 32);
     auto form = [&](int r, int streams) { *tm = r; return streams; };
-    // 17 to 32 rows, where the decoding kernel is the other choice (us, decoding kernel at its best split -> here): 72 heads of
-    // 512 keys D = 128 13.3 -> 8.9, 2048 keys 21.2 -> 17.9; 112 heads of 256 keys D = 160 13.6 -> 9.2, 4096 keys 64.6 -> 58.4
-    // (both in two splits); 224 of 1024 27.0 -> 24.1 (D = 128); 48 of 64 keys 8.2 -> 7.5 (D = 160).  Past 256 workgroups only
+    // 17 to 32 rows, where the decoding kernel is the other choice (us, decoding kernel -> here, weights in halves): 69
+    // heads of 607 keys D = 96 17.7 -> 10.3, 92 of 1450 21.5 -> 17.9; 157 of 292 keys D = 128 13.2 -> 10.3; 147 of 309 keys D = 64
+    // 8.4 -> 7.0; 112 heads of 256 keys D = 160 13.6 -> 9.2, 48 of 64 keys 8.2 -> 7.5.  Past 256 workgroups only
     // D = 64 has two on a CU (320 heads of 512 keys 11.7 -> 9.9, D = 128 21.4 -> 22.6), and there long caches of many heads are
-    // the decoding kernel's (160 heads of 4096 keys 32.8 / 36.1)
+    // the decoding kernel's (160 heads of 4096 keys 32.8 / 36.1).  D = 160 past 256 keys: the same kernel has no registers for
+    // two halves of each weight (21 to 48 spilled, 8.9 -> 11.8), and whole ones leave a larger error than the decoding kernel's
+    // runs (16 heads of 23 rows, 807 keys, FP16 2.86e-4 / 2.53e-4).
+    if (rows <= kDecodeRows && D == 160 && Skv > 256 && (n > 64 || (n <= 16 && Skv < 2048))) return 1;
     if (rows <= kDecodeRows && (n > 64 || Skv <= 64)) {
         const bool pays = Skv <= 4096 && (n <= 128 || (Skv <= 2048 && D == 64 && n <= 512) || (D > 64 && n <= 256));
         return pays ? form(32, 4) : 1;
@@ -275,19 +279,33 @@ int pick_streams_kv(long long heads, int rows, int Skv, int D, int *tm)
     return n <= (Skv < 1024 ? 160 : 192) ? form(64, 2) : 1;
 }
 
+// Whether a call of up to 32 rows multiplies each weight as two 16-bit halves, half of it rounded and what that leaves, so that the
+// rounding is half as coarse.  (Halves rather than the rounded weight and its remainder: both are positive, so that an infinite
+// value stays one.)  The weights of a run are rounded against the greatest score of its first tile, which itself is exact; a
+// wavefront that takes its keys in several runs thus rounds less than one that takes them all.  So where one run, or streams, took
+// the place of the decoding kernel's runs of a tile or two per wavefront, the error was 5 to 18 % larger, and is smaller this way
+// (BF16, 16 heads, 2 rows, 744 keys, D = 96 in six runs 1.96e-3, in one 2.32e-3, this way 1.81e-3).  The calls take 0 to
+// 4 % longer for it (us: 7 heads, 2 rows, 365 keys D = 64 in several runs 6.7, in one 4.6, this way 4.7; 68 heads, 26 rows, 1607 keys
+// in the decoding kernel 16.3, in streams 14.7, this way 15.5).
+bool pick_halves(int BH, int rows, int Skv, int D, int splits, int streams)
+{
+    if (Skv <= 256) return false;                 // (one run of a tile or two at all times)
+    return streams > 1 ? rows <= kDecodeRows && BH > 64 && D < 160 : rows <= 16 && splits == 1 && BH < 128;
+}
+
 // Splits of a cache call whose tile is left to the library too.
 int default_splits(int BH, int rows, int Skv, int D, bool fewest = false)
 {
     int tile_m;
     const bool streams = pick_streams_kv(BH, rows, Skv, D, &tile_m) > 1;
-    if (rows <= kDecodeRows && !streams) return pick_splits_decode(BH, Skv, D);
+    if (rows <= kDecodeRows && !streams) return pick_splits_decode(BH, rows, Skv, D);
     if (streams) {
         // one workgroup per CU in all, once a stream has sixteen tiles to share (the states of a split cost a second kernel).  Up to
         // 32 rows: with more than 64 heads what the decoding kernel has, which takes over as the cache grows (112 heads of 2048 keys D =
         // 64 s1 13.1, s2 14.9), but four from 1024 keys on at D = 160 (8 heads s1 12.8, s4 10.8; 27 heads 15.6 / 13.8; at D = 128
         // 9.4 / 9.8)
         const long long wg = (long long)BH * ((rows + tile_m - 1) / tile_m);
-        if (rows <= kDecodeRows && BH > 64) return Skv < 2048 ? 1 : pick_splits_decode(BH, Skv, D);
+        if (rows <= kDecodeRows && BH > 64) return Skv < 2048 ? 1 : pick_splits_decode(BH, rows, Skv, D);
         if (tile_m > 32) return 1;
         const bool short_wide = D == 160 && rows <= kDecodeRows && BH <= 64 && Skv >= 1024 && Skv < 2048;
         if (Skv < 2048 && !short_wide) return 1;
@@ -696,6 +714,7 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
         }
     }
     const bool decode = heuristic_tile && rows <= kDecodeRows && a.streams <= 1;
+    a.halves = (decode || a.streams > 1) && pick_halves(a.BH, rows, Skv, D, splits, a.streams) ? 1 : 0;
     // The decoding kernel combines the runs itself while they are few: a mark (8 bytes) per run must fit a head's part of o,
     // and past 32 states per head, eight rows, or four columns for each thread, the one workgroup that does it is slower than the
     // merge kernel's many (time with the marks / with two kernels, over 300 shapes: one row 0.95 at 2 runs, 0.97 at 8, 1.04 at 20;

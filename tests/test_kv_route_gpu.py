@@ -67,3 +67,56 @@ def test_without_a_workspace_the_count_is_one_that_fits():
                                                float("nan"), binding.BF16, torch.cuda.current_stream().cuda_stream, 0, 0, 0, 0)
     assert st == 0, binding.status_string(st)
     assert torch.equal(o, binding.sdpa_kv(q, k, v, splits=10))       # one workgroup per CU: 256 / 26, rounded up
+
+
+# One run where the decoding kernel had several, and streams of more than 64 heads, multiply each weight as two 16-bit halves (the
+# largest weight of a wavefront is exact anyway, and wavefronts with a tile or two each had many of those).  The least error is the
+# rounding of the result, measured on the exact one; rounded weights add as much again (in the squares), weights rounded in
+# halves a quarter of that: sqrt(1.25).  At D = 160 the decoding kernel keeps its runs of a tile per wavefront past 256 keys:
+# weights rounded but for the largest of 32 normal scores, 27 % of the sum of squares, so sqrt(1 + 0.73).  3 % for the
+# spread of a few hundred values.
+HALVES = 1.118
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("heads,rows,Skv,D,rounded", [
+    (16, 2, 744, 96, HALVES), (2, 8, 1473, 64, HALVES), (7, 16, 760, 128, HALVES), (9, 1, 635, 160, HALVES), (36, 5, 257, 128, HALVES),
+    (70, 2, 2040, 96, HALVES),
+    (20, 3, 260, 160, HALVES), (72, 20, 512, 128, HALVES), (112, 32, 385, 96, HALVES), (72, 24, 900, 64, HALVES), (65, 17, 257, 64, HALVES),
+    (66, 20, 3000, 128, HALVES), (3, 24, 717, 160, 1.315), (16, 23, 807, 160, 1.315)])
+def test_error_of_few_rows(heads, rows, Skv, D, rounded, paged):
+    import torch
+    from paper_2603_01960_amd import binding
+    for dtype in (torch.bfloat16, torch.float16):
+        g = torch.Generator("cuda").manual_seed(7600 + heads)
+        q, k, v = (torch.randn((1, heads, n, D), device="cuda", generator=g).to(dtype) for n in (rows, Skv, Skv))
+        if paged:
+            block, pages = 64, -(-Skv // 64)
+            pool = torch.full((2, pages, heads, block, D), float("nan"), device="cuda", dtype=dtype)
+            for side, x in zip(pool, (k, v)):
+                for i in range(pages):
+                    part = x[0, :, i * block:(i + 1) * block]
+                    side[pages - 1 - i, :, :part.shape[1]] = part
+            table = torch.arange(pages - 1, -1, -1, device="cuda", dtype=torch.int32)[None].contiguous()
+            o = binding.sdpa_paged(q, pool[0], pool[1], torch.tensor([Skv], device="cuda", dtype=torch.int32), table)
+        else:
+            o = binding.sdpa_kv(q, k, v)
+        err = least = 0.0
+        for h in range(heads):
+            want = (q[0, h].double() @ k[0, h].double().t().contiguous() * D ** -0.5).softmax(-1) @ v[0, h].double()
+            err += ((o[0, h].double() - want) ** 2).sum().item()
+            least += ((want.to(dtype).double() - want) ** 2).sum().item()
+        assert err ** 0.5 <= 1.03 * rounded * least ** 0.5, f"{dtype} {(err / least) ** 0.5:.3f} times the rounding of the result"
+
+
+def test_an_infinite_value_stays_one():
+    import torch
+    from paper_2603_01960_amd import binding
+    for heads, rows, Skv, D in ((3, 4, 600, 96), (70, 20, 600, 64)):
+        for dtype in (torch.bfloat16, torch.float16):
+            g = torch.Generator("cuda").manual_seed(7700)
+            q, k, v = (torch.randn((1, heads, n, D), device="cuda", generator=g).to(dtype) for n in (rows, Skv, Skv))
+            v[0, :, 300, 5] = float("inf")
+            o = binding.sdpa_kv(q, k, v)
+            assert (o[..., 5] == float("inf")).all()
+            assert torch.isfinite(o[..., :5]).all() and torch.isfinite(o[..., 6:]).all()
