@@ -386,12 +386,12 @@ def bench_kv(pkg, torch, args, tile, flags):
 
 def bwd_kernels(D, heads, S, grouped):
     """(kernels of a backward call, products of S x S x D that they execute per query head): one launch for short sequences of
-    whole heads (bwd_in_one_launch of csrc/sdpa_bwd_inst.h), else scores and dP once per pass: 7 products."""
+    whole heads (bwd_in_one_launch of csrc/sdpa_bwd_pick.h), else scores and dP once per pass: 7 products."""
     if D <= 96 and not grouped and S <= 256:
         rounds = -(-heads // 256)
         if S <= (128 if D == 64 else 64) or (heads >= 110 and (D == 64 or S <= 128 or 10 * heads >= 7 * 256 * rounds)):
             return "sdpa_bwd_short_kernel", 5
-    # (one grid after the statistics, or launches of their own: pick_bwd_joint of csrc/sdpa_bwd_inst.h)
+    # (one grid after the statistics, or launches of their own: pick_bwd_joint of csrc/sdpa_bwd_pick.h)
     return "sdpa_bwd_joint_kernel, or sdpa_bwd_kernel<dQ> + " + ("sdpa_bwd_pair_kernel" if D == 160 else "sdpa_bwd_kernel<dK+dV>"), 7
 
 

@@ -3,8 +3,8 @@
 // As launches of their own (sdpa_bwd_kernel.h) the two passes run one after the other, and where neither fills the card, or
 // fills it with an uneven last round, the CUs wait: two launches of one round each, both as long as their longest chain of
 // tiles.  In one grid they share the card.  Then the dQ pass cannot leave the statistics for the other any more; a launch
-// before them computes them (3 us on small problems; on large ones the time to read O and dO, which is why those keep the
-// passes apart: pick_bwd_joint in sdpa_bwd_inst.h).
+// before them computes them (3 us on small problems; on large ones the time to read O and dO, which is why most of those keep the
+// passes apart: pick_bwd_joint in sdpa_bwd_pick.h).
 // BF16, us per call, passes apart -> one grid: one head S = 1159 D = 64 20.9 -> 14.1, D = 128 34.4 -> 21.4, D = 160 52.7 -> 22.3;
 // two entries of 16 heads over 2, S = 57, D = 128 20.4 -> 17.7; 8 heads over 2, S = 1346, D = 128 78 -> 60; 65 heads of S = 679, G = 4,
 // D = 64 71.5 -> 58; 30 heads over 2, S = 2969, D = 128 277 -> 238.
