@@ -70,17 +70,14 @@ int launch_bwd_pass(const BwdLaunchArgs &a)
     return launch_bwd_pass_nw<T, D, MODE, GRP, Sh::NW, 1, Sh::TS[MODE], Sh::WPS[MODE]>(a);
 }
 
-// The dK + dV pass at D = 160 as a launch of its own (large problems: pick_bwd_joint).  Two pairs, two workgroups per CU, 2-10 %
-// ahead of four on causal and short problems; four pairs, which read a tile once for 128 keys, 3-4 % ahead on long ones without the
-// mask (32 heads of S = 8192, us: 2084 / 2002); two pairs and two streams where up to 400 tiles of 128 keys have chains that run
-// over a group's heads (four entries of 16 heads over 4, S = 2048, causal: 374 / 305).
 template <typename T, int D, bool GRP>
 int launch_bwd_pairs(const BwdLaunchArgs &a)
 {
-    const long long nk = (long long)(a.BH / a.group) * ((a.S + 127) / 128), chain = (long long)a.group * ((a.S + 31) / 32);
-    if (nk <= 400 && chain > 140) return launch_bwd_pair<T, D, 2, 2, true>(a);
-    if (!a.causal && a.S >= 600) return launch_bwd_pair<T, D, 4, 1, GRP>(a);
-    return launch_bwd_pair<T, D, 2, 1, GRP>(a);
+    switch (pick_bwd_pairs(a.causal != 0, a.BH, a.group, a.S)) {
+        case 22: return launch_bwd_pair<T, D, 2, 2, true>(a);
+        case 41: return launch_bwd_pair<T, D, 4, 1, GRP>(a);
+        default: return launch_bwd_pair<T, D, 2, 1, GRP>(a);
+    }
 }
 
 template <typename T, int D, bool GRP>

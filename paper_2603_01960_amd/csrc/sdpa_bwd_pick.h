@@ -61,6 +61,17 @@ inline bool bwd_in_one_launch(int D, int heads, int S)
     return heads * 10 >= (heads + 255) / 256 * 256 * 7;
 }
 
+// The dK + dV pass at D = 160 as a launch of its own (large problems: pick_bwd_joint), pairs and streams as two digits.  Two pairs,
+// two workgroups per CU, 2-10 % ahead of four on causal and short problems; four pairs, which read a tile once for 128 keys, 3-4 %
+// ahead on long ones without the mask (32 heads of S = 8192, us: 2084 / 2002); two pairs and two streams where up to 400 tiles
+// of 128 keys have chains that run over a group's heads (four entries of 16 heads over 4, S = 2048, causal: 374 / 305).
+inline int pick_bwd_pairs(bool causal, int heads, int group, int S)
+{
+    const long long nk = (long long)(heads / group) * ((S + 127) / 128), chain = (long long)group * ((S + 31) / 32);
+    if (nk <= 400 && chain > 140) return 22;
+    return !causal && S >= 600 ? 41 : 21;
+}
+
 // The form of the joint grid: wavefronts along the rows and streams of the dQ pass, then of the dK + dV pass (D = 160: pairs and
 // streams), as four digits; 0: the passes as launches of their own.  `nk`: workgroups of 128 keys; n: those and the ones of 128
 // queries; `chain`: the 32-row steps of a workgroup of keys, over the query heads of its group; work: their product.  The lines are

@@ -1,7 +1,7 @@
-"""The backward passes split their streamed tiles over up to eight streams per workgroup where the workgroups are few, and the
-number of streams and of resident rows follows from the head dim, the mask, the workgroups and the length of the chain of
-tiles: every form, the plain one included, at lengths around its tiles (32 streamed rows, 32 to 128 resident ones) and with fewer tiles than
-streams, against float64 gradients."""
+"""The backward pass at lengths around its tiles (32 streamed rows, 32 to 128 resident ones), with fewer tiles than streams, few and
+many workgroups, short and long chains of tiles and grouped heads, against float64 gradients.  Which kernels the cases meet follows
+from pick_bwd_joint and pick_bwd_form (csrc/sdpa_bwd_pick.h); together with those of test_bwd_joint_gpu.py they meet every one that
+some call takes (test_bwd_pick_host.py)."""
 import pytest
 import torch
 
@@ -31,8 +31,8 @@ CASES = [(1, 1, 65), (3, 1, 96), (2, 1, 97), (5, 1, 300), (2, 1, 2049), (1, 8, 3
          (3, 1, 1), (2, 1, 16), (5, 1, 32), (4, 1, 33), (2, 1, 64), (3, 1, 100), (2, 1, 128), (130, 1, 129), (120, 1, 160), (256, 1, 197),
          (112, 1, 224), (115, 1, 255), (111, 1, 256),
          (7, 1, 2100), (35, 2, 257), (45, 1, 515), (25, 1, 1030), (16, 4, 513), (13, 1, 2050), (20, 1, 2048),
-         # one stream, the tiles of a group's heads one head after the other (more than 400 workgroups of keys): odd and even tile
-         # counts, full and ragged; 256 resident rows per workgroup at D = 128 without the mask
+         # many workgroups of grouped heads, the tiles of a group's heads one head after the other: odd and even tile counts, full and
+         # ragged
          (105, 2, 513), (140, 3, 300), (135, 2, 384), (205, 4, 160), (64, 2, 1024), (66, 2, 1100)]
 
 

@@ -1,6 +1,6 @@
 """The backward pass in one grid for dQ and dK + dV, and its dK + dV pass by pairs of wavefronts at D = 160: every form of either
 (wavefronts along the rows and streams of both passes, by the workgroups and the length of their chains of tiles), and the
-first shapes that launch the passes by themselves, with one tile, odd and even numbers of them, more streams than tiles, ragged ends
+passes in launches of their own, with one tile, odd and even numbers of them, more streams than tiles, ragged ends
 and chains that run on into the next query head, against float64."""
 import pytest
 import torch
@@ -22,7 +22,11 @@ CASES = [(64, 1, 1, 257), (64, 3, 1, 300), (64, 45, 1, 290), (64, 48, 1, 300),  
          (160, 1, 1, 65), (160, 3, 1, 97), (160, 9, 1, 160), (160, 1, 3, 31), (160, 2, 8, 45), (160, 5, 4, 70), (160, 90, 4, 145),
          (160, 20, 3, 300), (160, 26, 8, 257), (160, 30, 2, 290), (160, 19, 3, 545), (160, 30, 8, 1090),
          (160, 1, 1, 1), (160, 2, 1, 33), (160, 260, 1, 40), (160, 90, 1, 129), (160, 400, 1, 65), (160, 120, 2, 150),
-         (160, 64, 1, 897), (160, 90, 4, 290), (160, 210, 1, 385), (160, 210, 1, 601)]
+         (160, 64, 1, 897), (160, 90, 4, 290), (160, 210, 1, 385), (160, 210, 1, 601),
+         # passes in launches of their own, in every form of either, and what else the lines above leave out: test_bwd_pick_host.py
+         # finds the kernels that some call takes and no case meets
+         (64, 15, 2, 2564), (96, 17, 2, 130), (96, 260, 1, 130), (96, 22, 1, 680), (96, 4, 1, 1923), (96, 13, 1, 1154), (96, 5, 2, 770),
+         (96, 112, 1, 67), (128, 17, 2, 129), (128, 134, 4, 33), (128, 86, 1, 1037), (128, 2, 1, 5601), (128, 15, 1, 1158), (128, 16, 4, 1024)]
 
 
 @pytest.mark.parametrize("causal", [False, True])

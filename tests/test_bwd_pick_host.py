@@ -1,4 +1,5 @@
-"""Which kernels a backward call takes (csrc/sdpa_bwd_pick.h), evaluated on the host."""
+"""Which kernels a backward call takes (csrc/sdpa_bwd_pick.h), evaluated on the host: the large calls that keep the passes apart, and
+that the cases of the GPU tests between them meet every kernel that some call takes."""
 import ctypes
 import shutil
 import subprocess
@@ -13,6 +14,18 @@ EXPORTS = r"""
 using namespace tsdpa;
 extern "C" {
 int joint(int D, int causal, int heads, int group, int S) { return pick_bwd_joint(D, causal != 0, heads, group, S); }
+int one_launch(int D, int heads, int S) { return bwd_in_one_launch(D, heads, S); }
+int pairs(int causal, int heads, int group, int S) { return pick_bwd_pairs(causal != 0, heads, group, S); }
+// wavefronts along the rows and streams of a pass in a launch of its own, as two digits
+int apart(int D, int causal, int keys, int heads, int group, int S)
+{
+    const long long own = keys ? heads / group : heads;
+    if (D == 96 || D == 128) {
+        const BwdForm f = pick_bwd_form(D, causal != 0, keys != 0, own * ((S + 127) / 128), (keys ? group : 1) * ((S + 31LL) / 32));
+        if (f.ns > 1) return f.nw * 10 + f.ns;
+    }
+    return D == 128 && !causal && bwd_wide_rows(own, S) ? 81 : 41;
+}
 }
 """
 
@@ -28,6 +41,21 @@ def pick(tmp_path_factory):
     return ctypes.CDLL(str(at / "pick.so"))
 
 
+def kernels(pick, D, causal, hkv, G, S):
+    """The kernels of a call, as launch_bwd (csrc/sdpa_bwd_inst.h) takes them; the forms with streams of keys, and the passes with
+    streams, are one kernel for grouped and other heads."""
+    heads = hkv * G
+    if D <= 96 and G == 1 and S <= 256 and pick.one_launch(D, heads, S):
+        return {("one launch", D, 2 if S <= 64 else 4 if S <= 128 else 8, causal)}
+    form = pick.joint(D, causal, heads, G, S)
+    if form:
+        return {("joint", D, form, "any heads" if form % 10 > 1 else "grouped" if G > 1 else "ungrouped")}
+    heads_of = lambda f: "any heads" if f % 10 > 1 else "grouped" if G > 1 else "ungrouped"
+    dq = pick.apart(D, causal, 0, heads, G, S)
+    dkv = pick.pairs(causal, heads, G, S) if D == 160 else pick.apart(D, causal, 1, heads, G, S)
+    return {("dQ", D, dq, heads_of(dq)), ("dK + dV", D, dkv, heads_of(dkv))}
+
+
 def test_large_grouped_calls_keep_the_passes_apart(pick):
     """Where the launch for the statistics of the query rows costs more than one grid gains."""
     for hkv, G, S in ((96, 4, 4096), (40, 4, 8192), (16, 8, 16384)):
@@ -36,3 +64,22 @@ def test_large_grouped_calls_keep_the_passes_apart(pick):
     for D, causal, hkv, G, S in ((64, 0, 99, 2, 512), (64, 0, 117, 2, 1241), (64, 0, 44, 2, 2048), (96, 0, 30, 2, 2048),
                                  (64, 1, 77, 4, 3879), (96, 1, 108, 2, 256)):
         assert pick.joint(D, causal, hkv * G, G, S) == 0
+
+
+def test_the_gpu_cases_meet_every_kernel(pick):
+    from test_bwd_forms_gpu import CASES as forms
+    from test_bwd_joint_gpu import CASES as joint
+
+    met = {k for causal in (False, True) for D, hkv, G, S in [*joint, *((D, *c) for D in (64, 96, 128, 160) for c in forms)]
+           for k in kernels(pick, D, causal, hkv, G, S)}
+    heads = sorted({round(1.15 ** i) for i in range(51)})
+    lengths = sorted({round(16 * 1.1 ** i) for i in range(73)} | {1, 32, 33, 64, 65, 128, 129, 256, 257, 512, 1024, 2048, 4096, 8192})
+    missed = {}
+    for D in (64, 96, 128, 160):
+        for causal in (False, True):
+            for G in (1, 2, 3, 4, 8, 16):
+                for hkv in heads:
+                    for S in lengths:
+                        for k in kernels(pick, D, causal, hkv, G, S) - met:
+                            missed.setdefault(k, (causal, hkv, G, S))
+    assert not missed, f"kernels that no case meets, each with a call that takes it: {missed}"

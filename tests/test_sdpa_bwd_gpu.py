@@ -120,8 +120,7 @@ def test_rows_that_see_one_or_two_keys(D, dtype):
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_many_heads_of_a_few_hundred_rows_at_D128(dtype):
-    """At D = 128 without the causal mask the passes take 256 resident rows per workgroup once that gives 256
-    workgroups: 128 heads of 257 ... 700 rows do, with a ragged last tile, and are small enough to check in full."""
+    """128 heads of 257 ... 700 rows, with a ragged last tile: many workgroups, and small enough to check in full."""
     for B, H, S in ((8, 16, 300), (2, 64, 257), (4, 32, 545)):
         q, k, v = make_qkv(B, H, S, 128, dtype, seed=13100 + S)
         do = make_dout(q.shape, dtype, 13150 + S)
