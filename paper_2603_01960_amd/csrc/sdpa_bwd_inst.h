@@ -64,7 +64,7 @@ int launch_bwd_pass(const BwdLaunchArgs &a)
             return f.ns == 2 ? launch_bwd_pass_nw<T, D, MODE, true, 2, 2, 32, 2>(a) : launch_bwd_pass_nw<T, D, MODE, true, 2, 4, 32, 2>(a);
         }
     }
-    if constexpr (D == 128) {
+    if constexpr (D == 128 && (MODE == BWD_DQ || !GRP)) {     // (dK + dV of as many grouped heads: the joint grid)
         if (!a.causal && bwd_wide_rows(heads, a.S)) return launch_bwd_pass_nw<T, D, MODE, GRP, 8, 1, Sh::TS[MODE], Sh::WPS[MODE]>(a);
     }
     return launch_bwd_pass_nw<T, D, MODE, GRP, Sh::NW, 1, Sh::TS[MODE], Sh::WPS[MODE]>(a);
@@ -105,10 +105,14 @@ int launch_bwd_joint(const BwdLaunchArgs &a, int form)
     const int err = launch_bwd_stats<T, D>(a);
     if (err != 0) return err;
     if constexpr (D == 160) {
-        if (form == 4120) return launch_bwd_joint_form<T, D, 4, 1, 2, 1>(a);
-        return form == 4223 ? launch_bwd_joint_form<T, D, 4, 2, 2, 2>(a) : launch_bwd_joint_form<T, D, 2, 2, 1, 2>(a);
+        if (form == 4121) return launch_bwd_joint_form<T, D, 4, 1, 2, 1>(a);
+        return form == 4222 ? launch_bwd_joint_form<T, D, 4, 2, 2, 2>(a) : launch_bwd_joint_form<T, D, 2, 2, 1, 2>(a);
     } else {
-        if (form == 2241) return launch_bwd_joint_form<T, D, 2, 2, 4, 1>(a);
+        if constexpr (D == 64) {
+            if (form == 2241) return launch_bwd_joint_form<T, D, 2, 2, 4, 1>(a);
+        } else {                                  // (never picked for grouped heads there)
+            if (form == 2241 && a.group == 1) return launch_bwd_joint_nw<T, D, 2, 2, 4, 1, false>(a);
+        }
         if (form == 4122) return launch_bwd_joint_form<T, D, 4, 1, 2, 2>(a);
         if constexpr (D <= 96)
             if (form == 2222) return launch_bwd_joint_form<T, D, 2, 2, 2, 2>(a);

@@ -21,7 +21,7 @@ inline BwdForm pick_bwd_form(int D, bool causal, bool keys_resident, long long n
 {
     const BwdForm plain{4, 1};
     if (chain <= 2) return plain;
-    if (n <= 64) return !keys_resident && chain <= 8 ? BwdForm{2, 2} : BwdForm{1, 4};
+    if (n <= 64) return BwdForm{1, 4};
     if (n <= 128) return causal && chain >= 128 ? BwdForm{1, 4} : BwdForm{2, chain >= 32 ? 4 : 2};
     if (n <= 256) {
         if (!causal) return chain >= (keys_resident ? 16 : 32) ? BwdForm{4, 2} : plain;
@@ -78,7 +78,7 @@ inline int pick_bwd_pairs(bool causal, int heads, int group, int S)
 // those of timings of every form on 6100 shapes (BF16; one to sixteen query heads per key/value head, S = 16 ... 16384).  What decides:
 //   * few workgroups: a wavefront per 32 keys with tiles of its own (..14; D = 160 ..12), whose chains are the shortest, while the CUs
 //     hold all of its workgroups; where a group's heads make the chains long, eight streams at D = 64 (2418);
-//   * more of them: workgroups that share tiles, 64 keys in two or four streams (4122, 2222, 2424, 4224) or 128 (2241, 4141, 4120),
+//   * more of them: workgroups that share tiles, 64 keys in two or four streams (4122, 2222, 2424, 4224) or 128 (2241, 4141, 4121),
 //     the form that comes out just below a whole number of workgroups per CU;
 //   * many workgroups: the passes apart, which are level there or ahead and save reading O and dO once more (us, joint / apart: D = 64, 64
 //     heads over 32 of S = 8192 9073 / 8654, 88 over 44 of S = 2048 364 / 333; D = 96, 60 over 30 of S = 2048 350 / 306).  But D = 128
@@ -156,12 +156,12 @@ inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
         if (causal) return chain > 260 || (group >= 3 && S > 650) ? 4224 : 0;
         return chain > 150 || n <= 260 ? 4224 : 0;
     }
-    if (group == 1) return n <= 90 ? (S <= 64 ? 4120 : 2212) : n <= (causal ? 800 : 2000) ? 4120 : 0;
+    if (group == 1) return n <= 90 ? (S <= 64 ? 4121 : 2212) : n <= (causal ? 800 : 2000) ? 4121 : 0;
     if (nk <= (S <= 64 ? 60 : 51)) return 2212;
-    if (nk <= 75 && S > 64) return 4223;
+    if (nk <= 75 && S > 64) return 4222;
     if (causal && nk >= 240) return 0;
-    if (chain > 80 && nk < (causal ? 240 : chain > 400 ? 130 : 100)) return 4223;
-    return nk <= 500 ? 4120 : 0;
+    if (chain > 80 && nk < (causal ? 240 : chain > 400 ? 130 : 100)) return 4222;
+    return nk <= 500 ? 4121 : 0;
 }
 
 }  // namespace tsdpa
