@@ -663,11 +663,14 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
         }
     }
     // Long query blocks against a dense cache of one length, no mask, no split: the 256-row query tile of the
-    // square problem, under the same conditions.  (Where the last 256 rows of the heads are half empty, 256 such workgroups can
-    // be fewer than 512 of 128 rows, which then fill the chip in one round.)
+    // square problem, under the same conditions.  Not where its workgroups begin a second round that 128-row ones, two per CU,
+    // do without, the last 256 rows of the heads being half empty (us, 256 rows / 128: 29 heads of 2100 rows, D = 128, 1024 keys
+    // 54.9 / 33.3, 4096 keys 188 / 113; 13 of 4900, D = 96, 4096 keys 159 / 93; 52 of 1100, D = 160, 4096 keys 253 / 154; one
+    // round of either, 16 of 3900, D = 128, 4096 keys 111.9 / 113.1).
+    const int64_t wide = (int64_t)B * Hkv * ((rows + 255) / 256);
     if (heuristic_tile && splits == 1 && block_table == nullptr && kv_lens == nullptr &&
         !(flags & TSDPA_FLAG_CAUSAL) && D >= 96 && rows >= (D == 160 ? 1024 : D == 96 ? 4096 : 2048) &&
-        (int64_t)B * Hkv * ((rows + 255) / 256) >= 256 && (Skv < 1985 || (int64_t)B * Hkv * ((rows + 127) / 128) >= 512)) {
+        (wide == 256 || (wide > 256 && (int64_t)B * Hkv * ((rows + 127) / 128) >= 512))) {
         tile_m = 256;
         tile_n = 64;
     }

@@ -43,6 +43,14 @@ def test_chunks_around_two_tiles_per_cu(heads, rows, Skv, D):
     kv.check_kv(q, k, v, "bf16", causal=Skv >= rows, tag="chunk")
 
 
+# no mask: 128 rows per workgroup where 256 begin a second round with the last rows half empty, 256 where either is one round
+@pytest.mark.parametrize("heads,rows,Skv,D", [(52, 1100, 70, 160), (37, 1600, 33, 160), (16, 3900, 65, 160), (29, 2100, 64, 128), (16, 3901, 40, 128),
+                                              (13, 4900, 50, 96), (8, 8000, 45, 96), (30, 2300, 70, 128)])
+def test_long_query_blocks_without_a_mask(heads, rows, Skv, D):
+    q, k, v = kv.make_q_kv(1, heads, rows, Skv, D, "bf16", seed=7350 + rows)
+    kv.check_kv(q, k, v, "bf16", splits=1, tag="long block")
+
+
 def test_long_caches_in_few_tiles():
     """Splits of one CU's two workgroups each, runs of 512 keys and more."""
     from paper_2603_01960_amd import binding
