@@ -64,7 +64,7 @@ int launch_bwd_pass(const BwdLaunchArgs &a)
             return f.ns == 2 ? launch_bwd_pass_nw<T, D, MODE, true, 2, 2, 32, 2>(a) : launch_bwd_pass_nw<T, D, MODE, true, 2, 4, 32, 2>(a);
         }
     }
-    if constexpr (D == 128 && (MODE == BWD_DQ || !GRP)) {     // (dK + dV of as many grouped heads: the joint grid)
+    if constexpr (D == 128) {
         if (!a.causal && bwd_wide_rows(heads, a.S)) return launch_bwd_pass_nw<T, D, MODE, GRP, 8, 1, Sh::TS[MODE], Sh::WPS[MODE]>(a);
     }
     return launch_bwd_pass_nw<T, D, MODE, GRP, Sh::NW, 1, Sh::TS[MODE], Sh::WPS[MODE]>(a);

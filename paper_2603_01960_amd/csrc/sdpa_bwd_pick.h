@@ -82,17 +82,25 @@ inline int pick_bwd_pairs(bool causal, int heads, int group, int S)
 //     the form that comes out just below a whole number of workgroups per CU;
 //   * many workgroups: the passes apart, which are level there or ahead and save reading O and dO once more (us, joint / apart: D = 64, 64
 //     heads over 32 of S = 8192 9073 / 8654, 88 over 44 of S = 2048 364 / 333; D = 96, 60 over 30 of S = 2048 350 / 306).  But D = 128
-//     with grouped heads, where 4141 is level or ahead at any size (20 heads of S = 4096 over eight queries each 3846 / 4349, 64 over
-//     16 of S = 8192, causal, 3186 / 3614), and D = 64 and 96 without the mask on long
+//     with grouped heads, where 4141 is ahead at any size (80 heads over 20 of S = 4096 2005 / 2206, 48 over 12 of S = 8192 4731 / 4825,
+//     64 over 16 of S = 8192, causal, 3287 / 3383) unless the passes' workgroups of keys come in whole rounds without the mask (64 over
+//     16 of S = 8192 6285 / 6239, of S = 4096 1602 / 1589; level at S = 2048, 433 / 440 at S = 1024), and D = 64 and 96 without the mask on long
 //     chains up to the lines below (12 to 20 % just past whole rounds of the passes' workgroups).
 // On 1470 other shapes this choice is 2.0 % from the best of all forms on average, and 0.89, 0.88, 0.87 and 0.64 of the time of the
 // two passes with streams in each (D = 160: three passes) that went before; more than 10 % behind those on 7, more than 3 % on 37.
+// On 589 shapes of 64 to 1024 full key tiles, powers of two, D = 64 to 128: 0.97 of that time, more than 10 % behind on 2, 3 % on 37.
 inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
 {
     const long long tiles = (S + 127) / 128, nk = heads / group * tiles, n = nk + heads * tiles;
     const long long chain = (long long)group * ((S + 31) / 32), work = nk * chain;
     // 2214 with its workgroups of 32 keys and of 64 queries on a CU each
     const bool spread = heads / group * (long long)((S + 31) / 32) + heads * (long long)((S + 63) / 64) <= 256;
+    // the passes in forms of their own (pick_bwd_form) are whole rounds: long chains then gain nothing from one grid (us, joint / apart:
+    // four heads over 2 of S = 8192, causal, D = 96 281 / 213, D = 128 358 / 286; 32 heads of S = 2048, D = 128 225 / 213)
+    const bool even = chain > 24 && (nk == 128 || nk == 256 || nk % 512 == 0);
+    if (D == 64 && !causal && even && nk >= 512) return 0;
+    if (D == 96 && even && (group == 1 || !causal || nk <= 256)) return 0;
+    if (D == 128 && even && (group == 1 || nk == (causal ? 256 : 128) || (causal && group == 2 && nk == 128))) return 0;
     if (D == 64 && group == 1) {
         if (S <= 256) return n <= 330 || (n <= 440 && S <= 190) ? 4122 : causal ? 2241 : 0;
         if (causal) {
@@ -110,7 +118,7 @@ inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
             return nk > 580 ? 0 : chain <= 600 ? 4122 : 4114;
         }
         if (nk <= 110) return chain > 350 ? 2214 : S > 620 ? 1414 : nk <= 80 ? 4114 : 4122;
-        if (nk <= 310) return n <= 870 && S > 270 ? 2222 : 4122;
+        if (nk <= 310) return nk == 256 ? 2241 : n <= 870 && S > 270 ? 2222 : 4122;
         return S > 2300 && nk <= 1200 ? 2241 : 0;
     }
     if (D == 96 && group == 1) {
@@ -151,7 +159,7 @@ inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
     }
     if (D == 128) {
         if (nk <= (group == 2 ? 32 : 40)) return chain <= 6 ? 4122 : 2214;
-        if (nk > (causal ? 290 : 150)) return 4141;
+        if (nk > (causal ? 290 : 150)) return !causal && nk % 512 == 0 && S > 1920 ? 0 : 4141;
         if (chain <= 6) return 4141;
         if (causal) return chain > 260 || (group >= 3 && S > 650) ? 4224 : 0;
         return chain > 150 || n <= 260 ? 4224 : 0;
