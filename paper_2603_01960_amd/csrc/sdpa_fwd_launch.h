@@ -132,7 +132,8 @@ int launch_bf16_d160(int tile_m, int tile_n, const LaunchArgs &a);
 int launch_decode_f16(int D, const LaunchArgs &a);
 int launch_decode_bf16(int D, const LaunchArgs &a);
 
-// Backward pass: the dQ pass (queries resident; row statistics on the way), then dK and dV (keys resident).
+// Backward pass: dQ (queries resident) and dK + dV (keys resident) in one grid after the row statistics, or one after the other with
+// the statistics on the way, or whole heads in one launch (sdpa_bwd_pick.h).
 int launch_bwd_f16_d64(const BwdLaunchArgs &a);
 int launch_bwd_f16_d96(const BwdLaunchArgs &a);
 int launch_bwd_f16_d128(const BwdLaunchArgs &a);
