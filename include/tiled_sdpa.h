@@ -275,7 +275,8 @@ int tiled_sdpa_kv_tile_splits(int B, int H, int Sq, int Skv, int D, int dtype, u
 /* Workspace bytes tiled_sdpa_fwd_kv needs for `splits` >= 1 (a value from tiled_sdpa_kv_default_splits,
  * or the caller's own): B*H*splits*Sq*(D+2) floats.  0 for splits <= 1 or negative arguments.
  * The counts above are at most 2048 workgroups of 128 rows (170 MB at D = 160), and, but for 33 to 64 rows per key/value head,
- * never fewer for a longer cache: a workspace sized for the capacity serves every shorter length with splits = 0. */
+ * never fewer for a longer cache: a workspace sized for the capacity serves every shorter length with splits = 0.  Where a call with
+ * splits = 0 is given less, it takes a smaller count (512 workgroups in all, rounded up) if that fits. */
 unsigned long long tiled_sdpa_kv_workspace_bytes(int B, int H, int Sq, int D, int splits);
 
 /*

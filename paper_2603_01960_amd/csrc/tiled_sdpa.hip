@@ -307,7 +307,7 @@ int default_splits(int BH, int rows, int Skv, int D, bool fewest = false)
         const long long wg = (long long)BH * ((rows + tile_m - 1) / tile_m);
         if (rows <= kDecodeRows && BH > 64) return Skv < 2048 ? 1 : pick_splits_decode(BH, rows, Skv, D);
         if (tile_m > 32) return 1;
-        const bool short_wide = D == 160 && rows <= kDecodeRows && BH <= 64 && Skv >= 1024 && Skv < 2048;
+        const bool short_wide = !fewest && D == 160 && rows <= kDecodeRows && BH <= 64 && Skv >= 1024 && Skv < 2048;
         if (Skv < 2048 && !short_wide) return 1;
         const long long most = short_wide ? 4 : 16, want = 256 / wg;
         return want < 1 ? 1 : want > most ? (int)most : (int)want;
@@ -660,6 +660,12 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
             // tiled_sdpa_kv_default_splits, which speaks of forms that an explicit tile never takes)
             const int own = pick_splits(B * Hkv, rows, Skv, D, tile_m, tile_n);
             if (own <= splits || (workspace && workspace_bytes >= tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, own))) splits = own;
+        }
+        // (the count that runs best, or the smaller one if only that fits what the caller gave, be it nothing)
+        const unsigned long long given = workspace ? workspace_bytes : 0;
+        if (tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits) > given) {
+            const int few = heuristic_tile ? default_splits(B * Hkv, rows, Skv, D, true) : pick_splits(B * Hkv, rows, Skv, D, tile_m, tile_n, true);
+            if (tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, few) <= given) splits = few;
         }
     }
     // Long query blocks against a dense cache of one length, no mask, no split: the 256-row query tile of the

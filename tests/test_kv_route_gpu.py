@@ -61,6 +61,28 @@ def test_long_caches_in_few_tiles():
         kv.check_kv(q, k, v, "bf16", causal=True, tag="long cache")
 
 
+@pytest.mark.parametrize("heads,rows,Skv,D,given", [(20, 24, 1500, 160, 1), (64, 32, 1024, 160, 1), (202, 128, 1432, 160, 1), (103, 200, 1346, 160, 1),
+                                                    (13, 300, 9000, 96, 7), (26, 128, 12000, 160, 10)])
+def test_a_workspace_for_fewer_states_is_taken(heads, rows, Skv, D, given):
+    """splits = 0 with a workspace (or none) that holds `given` states per tile, fewer than the default count's."""
+    import torch
+    from paper_2603_01960_amd import binding
+    assert binding.kv_default_splits(1, heads, rows, Skv, D, binding.BF16) > given
+    size = binding.kv_workspace_bytes(1, heads, rows, D, given)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda") if size else None
+    g = torch.Generator("cuda").manual_seed(7450)
+    q, k, v = (torch.randn((1, heads, s, D), device="cuda", generator=g).bfloat16() for s in (rows, Skv, Skv))
+    o = torch.full_like(q, float("nan"))
+    st = binding.load_library().tiled_sdpa_fwd_kv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None, 1, heads, rows, Skv, D, float("nan"),
+                                                  binding.BF16, torch.cuda.current_stream().cuda_stream, 0, 0, 0, 0,
+                                                  ws.data_ptr() if size else None, size)
+    assert st == 0, binding.status_string(st)
+    torch.testing.assert_close(o.float(), binding.sdpa_kv(q, k, v).float(), rtol=2e-2, atol=2e-2)
+    st = binding.load_library().tiled_sdpa_fwd_kv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None, 1, heads, rows, Skv, D, float("nan"),
+                                                  binding.BF16, torch.cuda.current_stream().cuda_stream, 0, 0, 0, given + 1, ws.data_ptr() if size else None, size)
+    assert st != 0                                # a count of the caller's own is not lowered
+
+
 def test_without_a_workspace_the_count_is_one_that_fits():
     """26 heads of 128 rows at D = 160: the default count's states exceed the library's own buffer, a smaller count's do not."""
     import torch
