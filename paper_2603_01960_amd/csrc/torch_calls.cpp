@@ -320,11 +320,13 @@ PyObject *call_sdpa_kv(PyObject *, PyObject *const *args, Py_ssize_t n)
         const int dtype = element_type(q);
         at::Tensor out = output(args[7], q, "out must match q in shape, dtype, device and be contiguous"), lse;
         if (with_lse) lse = empty(s.slice(0, 3), at::kFloat, q);
-        if (splits == 0) {
+        const bool heuristic = splits == 0;
+        if (heuristic) {
             const int st = heuristic_splits(B, H, Hkv, Sq, Skv, D, dtype, flags, H != Hkv, tile, &splits);
             if (st != TSDPA_OK) return PyLong_FromLong(st);
         }
         const Workspace ws(args[8], tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits), q);
+        if (heuristic && args[8] != Py_None) splits = 0;      // (what fits the caller's buffer: the library decides)
         const Launch on(q);
         const int st = without_gil(tiled_sdpa_fwd_kvcache, data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr, lens,
                                               B, H, Hkv, Sq, Skv, D, scale, dtype, on.stream, tile.m, tile.n, flags, splits,
@@ -371,13 +373,15 @@ PyObject *call_sdpa_paged(PyObject *, PyObject *const *args, Py_ssize_t n)
         const int max_blocks = (int)table.size(1), dtype = element_type(q);
         at::Tensor out = output(args[9], q, "out must match q in shape, dtype, device and be contiguous"), lse;
         if (with_lse) lse = empty(s.slice(0, 3), at::kFloat, q);
-        if (splits == 0) {
+        const bool heuristic = splits == 0;
+        if (heuristic) {
             const int64_t rows = (int64_t)max_blocks * block_rows;
             if (rows > std::numeric_limits<int>::max()) return PyLong_FromLong(TSDPA_ERR_BAD_SHAPE);
             const int st = heuristic_splits(B, H, Hkv, Sq, rows > 1 ? (int)rows : 1, D, dtype, flags, true, tile, &splits);
             if (st != TSDPA_OK) return PyLong_FromLong(st);
         }
         const Workspace ws(args[10], tiled_sdpa_kv_workspace_bytes(B, H, Sq, D, splits), q);
+        if (heuristic && args[10] != Py_None) splits = 0;
         const Launch on(q);
         const int st = without_gil(tiled_sdpa_fwd_paged, data(q), data(k), data(v), data(out), with_lse ? (float *)data(lse) : nullptr,
                                             (const int *)data(lens), (const int *)data(table), B, H, Hkv, Sq, max_blocks,

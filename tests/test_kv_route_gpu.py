@@ -78,6 +78,8 @@ def test_a_workspace_for_fewer_states_is_taken(heads, rows, Skv, D, given):
                                                   ws.data_ptr() if size else None, size)
     assert st == 0, binding.status_string(st)
     torch.testing.assert_close(o.float(), binding.sdpa_kv(q, k, v).float(), rtol=2e-2, atol=2e-2)
+    if size:
+        assert torch.equal(binding.sdpa_kv(q, k, v, workspace=ws), o)
     st = binding.load_library().tiled_sdpa_fwd_kv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None, 1, heads, rows, Skv, D, float("nan"),
                                                   binding.BF16, torch.cuda.current_stream().cuda_stream, 0, 0, 0, given + 1, ws.data_ptr() if size else None, size)
     assert st != 0                                # a count of the caller's own is not lowered
