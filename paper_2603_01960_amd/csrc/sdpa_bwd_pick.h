@@ -86,9 +86,10 @@ inline int pick_bwd_pairs(bool causal, int heads, int group, int S)
 //     64 over 16 of S = 8192, causal, 3287 / 3383) unless the passes' workgroups of keys come in whole rounds without the mask (64 over
 //     16 of S = 8192 6285 / 6239, of S = 4096 1602 / 1589; level at S = 2048, 433 / 440 at S = 1024), and D = 64 and 96 without the mask on long
 //     chains up to the lines below (12 to 20 % just past whole rounds of the passes' workgroups).
-// On 1470 other shapes this choice is 2.0 % from the best of all forms on average, and 0.89, 0.88, 0.87 and 0.64 of the time of the
-// two passes with streams in each (D = 160: three passes) that went before; more than 10 % behind those on 7, more than 3 % on 37.
-// On 589 shapes of 64 to 1024 full key tiles, powers of two, D = 64 to 128: 0.97 of that time, more than 10 % behind on 2, 3 % on 37.
+// On 1473 other shapes (profiles/sdpa_bwd_joint_forms.csv) this choice is 1.9 % from the best of all forms on average, and 0.89, 0.88,
+// 0.87 and 0.64 of the time of the two passes with streams in each (D = 160: three passes) that went before; more than 10 % behind
+// those on 7, more than 3 % on 36.  On 589 of 64 to 1024 full key tiles, powers of two, D = 64 to 128: 0.97 of that time, more than
+// 10 % behind on 2, 3 % on 33.
 inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
 {
     const long long tiles = (S + 127) / 128, nk = heads / group * tiles, n = nk + heads * tiles;
@@ -114,10 +115,10 @@ inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
     if (D == 64) {
         if (nk <= 34) return chain <= 35 ? 4114 : 2418;
         if (causal) {
-            if (nk <= 130) return S <= 270 ? (group <= 3 ? 4122 : 4114) : chain <= 260 ? 2214 : 2418;
-            return nk > 580 ? 0 : chain <= 600 ? 4122 : 4114;
+            if (nk <= 130) return S <= 270 ? (group <= 3 ? 4122 : 4114) : chain <= 260 || nk > 64 ? 2214 : 2418;
+            return nk > 580 ? 0 : group == 2 && S > 900 ? 2222 : chain <= 600 ? 4122 : 4114;
         }
-        if (nk <= 110) return chain > 350 ? 2214 : S > 620 ? 1414 : nk <= 80 ? 4114 : 4122;
+        if (nk <= 110) return chain > 350 || (S > 620 && group > 2) ? 2214 : S > 620 ? 1414 : nk <= 80 ? 4114 : 4122;
         if (nk <= 310) return nk == 256 ? 2241 : n <= 870 && S > 270 ? 2222 : 4122;
         return S > 2300 && nk <= 1200 ? 2241 : 0;
     }
