@@ -416,7 +416,7 @@ def bench_bwd(pkg, torch, args, flags):
     dout = torch.randn(*q.shape, dtype=torch.float32, generator=g).to(q.dtype).cuda()
     o, lse = pkg.sdpa_kv(qd, kd, vd, causal=causal, return_lse=True) if Hkv != w.H else pkg.sdpa(qd, kd, vd, causal=causal, return_lse=True)
     grads = (torch.empty_like(qd), torch.empty_like(kd), torch.empty_like(kd))
-    ws = torch.empty(pkg.bwd_workspace_bytes(w.B, w.H, w.S), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(pkg.bwd_full_workspace_bytes(w.B, w.H, Hkv, w.S, w.D, causal), dtype=torch.uint8, device="cuda")
     run = lambda: pkg.sdpa_backward(qd, kd, vd, o, dout, lse, causal=causal, workspace=ws, grads=grads)
     for _ in range(args.warmup):
         run()
@@ -435,6 +435,9 @@ def bench_bwd(pkg, torch, args, flags):
     flops = 2.5 * w.flops * (0.5 if causal else 1.0)
     tf = flops / (ms * 1e-3) / 1e12
     kernels, products = bwd_kernels(w.D, w.B * w.H, w.S, Hkv != w.H)
+    chain = ws.numel() > pkg.bwd_workspace_bytes(w.B, w.H, w.S)        # room for sums of dQ: five products
+    if chain:
+        kernels, products = "sdpa_bwd_stats_kernel + sdpa_bwd_chain_kernel", 5
     print(json.dumps({
         "metric": "SDPA backward TFLOP/s (10*B*H*S^2*D / t)", "value": round(flops / (wall_ms * 1e-3) / 1e12, 2),
         "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(wall_ms, 5),
@@ -444,7 +447,7 @@ def bench_bwd(pkg, torch, args, flags):
         "roofline": {"bound": "mfma", "achieved": round(tf, 2), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tf / PEAK_MFMA_TFLOPS, 4),
                      # both kernels of a call, FETCH_SIZE + WRITE_SIZE scaled (profiles/sdpa_bwd_C4_C2.md)
-                     "traffic": 1621.4e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H) else None,
+                     "traffic": 1621.4e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H and not chain) else None,
                      "kernel": kernels, "ms_avg_all_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
                      "executed_mfma_flops_per_launch": flops * products / 5.0}}), flush=True)
 

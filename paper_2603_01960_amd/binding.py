@@ -29,6 +29,7 @@ EXPORTS = (
     "tiled_sdpa_bwd",
     "tiled_sdpa_bwd_gqa",
     "tiled_sdpa_bwd_workspace_bytes",
+    "tiled_sdpa_bwd_full_workspace_bytes",
     "tiled_sdpa_default_tile",
     "tiled_sdpa_tune_tile",
     "tiled_sdpa_fwd_kv",
@@ -99,6 +100,8 @@ def load_library():
     lib.tiled_sdpa_bwd_gqa.argtypes = [vp] * 9 + [ci, ci, ci, ci, ci, cf, ci, ctypes.c_uint, vp, ctypes.c_ulonglong, vp]
     lib.tiled_sdpa_bwd_workspace_bytes.restype = ctypes.c_ulonglong
     lib.tiled_sdpa_bwd_workspace_bytes.argtypes = [ci, ci, ci]
+    lib.tiled_sdpa_bwd_full_workspace_bytes.restype = ctypes.c_ulonglong
+    lib.tiled_sdpa_bwd_full_workspace_bytes.argtypes = [ci, ci, ci, ci, ci, ctypes.c_uint]
     lib.tiled_sdpa_probe_hbm_read.restype = ci
     lib.tiled_sdpa_probe_hbm_read.argtypes = [vp, ctypes.c_ulonglong, vp, ctypes.POINTER(ctypes.c_double), vp]
     lib.tiled_sdpa_probe_mfma.restype = ci
@@ -300,6 +303,11 @@ def sdpa_paged(q, k_pages, v_pages, kv_lens, block_table, causal: bool = False, 
 
 def bwd_workspace_bytes(B: int, H: int, S: int) -> int:
     return int(load_library().tiled_sdpa_bwd_workspace_bytes(B, H, S))
+
+
+def bwd_full_workspace_bytes(B: int, H: int, Hkv: int, S: int, D: int, causal: bool = False) -> int:
+    """Workspace with which the backward pass is fastest; see tiled_sdpa_bwd_full_workspace_bytes."""
+    return int(load_library().tiled_sdpa_bwd_full_workspace_bytes(B, H, Hkv, S, D, FLAG_CAUSAL if causal else 0))
 
 
 def tiled_sdpa_bwd(q_ptr, k_ptr, v_ptr, o_ptr, dout_ptr, lse_ptr, dq_ptr, dk_ptr, dv_ptr, B, H, S, D, scale,

@@ -36,8 +36,15 @@ FLAGS = [
 ILP_SCHED = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
 
 
+# The five-product backward keeps dK and dV in accumulation registers by itself and everything else out of them:
+# left to its own choice, the compiler puts the results of all matrix instructions there once one is, and copies.
+MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+
+
 def extra_flags(src: Path) -> list[str]:
     name = src.name
+    if name.startswith("sdpa_bwd_chain_"):
+        return MFMA_VGPR
     if name.startswith("sdpa_fwd_") and name.endswith("_tn64.hip") and "_d160_" not in name:
         return ILP_SCHED
     if name.startswith("sdpa_bwd_") and not name.endswith("_d128.hip"):

@@ -1,0 +1,6 @@
+// Backward in five products: element type f16, head dim 96.
+#include "sdpa_bwd_chain_kernel.h"
+
+namespace tsdpa {
+int launch_bwd_chain_f16_d96(const BwdLaunchArgs &a, int per_claim) { return launch_bwd_chain<_Float16, 96>(a, per_claim); }
+}  // namespace tsdpa

@@ -17,11 +17,13 @@ namespace tsdpa {
 // Statistics of all query rows, -Delta and LSE in log2 units, into `stats`.  Four lanes per row, 64 rows per workgroup, from
 // workgroup `short_heads` on; the workgroups before it take Delta of the rows that see at most kBwdShortRow keys from its
 // definition, one per query head: wavefront 2 * b + j pairs the queries 32b ... with the keys 32j ... .
-template <typename T, int D>
+// TILED (for sdpa_bwd_chain_kernel.h): `pitch` rows per head, of which those past S get weights of 0; and `nclear` words at `clear` are cleared.
+template <typename T, int D, bool TILED>
 __global__ void __launch_bounds__(256)
 sdpa_bwd_stats_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ dout,
                       const T *__restrict__ o, const float *__restrict__ lse, float *__restrict__ stats, int rows, int S,
-                      Divisor by_S, int group, float c, uint32_t rsign, int causal, unsigned stat_bytes, int short_heads)
+                      Divisor by_S, int group, float c, uint32_t rsign, int causal, unsigned stat_bytes, int short_heads,
+                      unsigned *__restrict__ clear, int nclear, int pitch)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using E = Elem<T>;
@@ -29,6 +31,16 @@ sdpa_bwd_stats_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
     constexpr int KK = D / 16, CPL = D / 32;      // k-steps; 16-byte chunks per lane of a quarter row
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float *lse2 = (float *)((char *)stats + stat_bytes);
+    if constexpr (TILED) {
+        for (int i = (int)blockIdx.x * 256 + tid; i < nclear; i += (int)gridDim.x * 256) clear[i] = 0;
+        for (int h = (int)blockIdx.x; h < rows / S; h += (int)gridDim.x)
+            if (tid < pitch - S) {
+                stats[(size_t)h * pitch + S + tid] = 0.f;
+                lse2[(size_t)h * pitch + S + tid] = __builtin_inff();
+            }
+    } else {
+        pitch = S;
+    }
     if ((int)blockIdx.x < short_heads) {
         __shared__ float part[4][32];
         const int head = blockIdx.x, g = lane >> 5, l32 = lane & 31, qb = wave >> 1, kb = wave & 1;
@@ -64,8 +76,8 @@ sdpa_bwd_stats_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
         if (g == 0) part[wave][l32] = sum;
         __syncthreads();
         if (kb == 0 && g == 0 && row < S) {
-            stats[(size_t)head * S + row] = -(sum + part[wave + 1][l32]);
-            lse2[(size_t)head * S + row] = l2;
+            stats[(size_t)head * pitch + row] = -(sum + part[wave + 1][l32]);
+            lse2[(size_t)head * pitch + row] = l2;
         }
         return;
     }
@@ -87,8 +99,9 @@ sdpa_bwd_stats_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
     delta += __shfl_xor(delta, 1);
     delta += __shfl_xor(delta, 2);
     if (part == 0 && !(short_heads > 0 && row - divide(row, by_S) * S < kBwdShortRow)) {
-        stats[row] = -delta;
-        lse2[row] = l2;
+        const size_t at = TILED ? (size_t)row + (size_t)divide(row, by_S) * (pitch - S) : row;
+        stats[at] = -delta;
+        lse2[at] = l2;
     }
 #endif
 }
@@ -165,14 +178,14 @@ template <typename T, int D, int NWQ, int NSQ, int NWK, int NSK, bool GRP> int l
     return (int)hipGetLastError();
 }
 
-template <typename T, int D> int launch_bwd_stats(const BwdLaunchArgs &a)
+template <typename T, int D, bool TILED = false> int launch_bwd_stats(const BwdLaunchArgs &a, unsigned *clear = nullptr, int nclear = 0, int pitch = 0)
 {
     const int rows = a.BH * a.S;
     const int short_heads = a.causal || a.S <= kBwdShortRow ? a.BH : 0;
     const int rest = a.S <= kBwdShortRow ? 0 : (rows + 63) / 64;
-    hipLaunchKernelGGL((sdpa_bwd_stats_kernel<T, D>), dim3(short_heads + rest), dim3(256), 0, a.stream, (const T *)a.q,
+    hipLaunchKernelGGL((sdpa_bwd_stats_kernel<T, D, TILED>), dim3(short_heads + rest), dim3(256), 0, a.stream, (const T *)a.q,
                        (const T *)a.k, (const T *)a.v, (const T *)a.dout, (const T *)a.o, a.lse, a.stats, rows, a.S,
-                       divisor((uint32_t)a.S), a.group, a.c, a.rsign, a.causal, a.stat_bytes, short_heads);
+                       divisor((uint32_t)a.S), a.group, a.c, a.rsign, a.causal, a.stat_bytes, short_heads, clear, nclear, pitch);
     return (int)hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 // Which kernels a backward call takes, by its sizes: host rules without device code, so that a host program can evaluate them too.
 #pragma once
+#include <stddef.h>
 
 namespace tsdpa {
 
@@ -171,6 +172,81 @@ inline int pick_bwd_joint(int D, bool causal, int heads, int group, int S)
     if (causal && nk >= 240) return 0;
     if (chain > 80 && nk < (causal ? 240 : chain > 400 ? 130 : 100)) return 4222;
     return nk <= 500 ? 4121 : 0;
+}
+
+// ---- five products, dQ summed from block to block (sdpa_bwd_chain_kernel.h)
+constexpr int kChainWaves = 4, kChainKeys = 64 * kChainWaves;       // wavefronts and keys of a workgroup
+constexpr int kChainGroups = 256, kChainXcds = 16;                  // workgroups: one per CU; XCDs that a hardware id can name
+constexpr int kChainFlag = 32;                                      // words from one progress counter to the next: a cache line each
+constexpr int kChainQueueBytes = 128 * (1 + kChainXcds);
+
+// Where its workspace holds what: the queue and the claims of every XCD and the progress counters (zero at the start), the row statistics,
+// 32 rows per tile, and the sums.  An XCD's workgroups look at the places of all its claims and of one past the end each at most.
+struct ChainLayout {
+    int nT, nB, nclaims, max_slots;
+    unsigned stat_bytes;
+    size_t zero_bytes, stats_at, part_at, bytes;
+};
+inline ChainLayout chain_layout(int heads, int group, int S, int D, int per_claim)
+{
+    ChainLayout l{};
+    const int HK = heads / group;
+    l.nT = (S + 31) / 32;
+    l.nB = (S + kChainKeys - 1) / kChainKeys;
+    l.nclaims = (HK + per_claim - 1) / per_claim;
+    l.max_slots = l.nclaims + kChainGroups + 1;
+    l.zero_bytes = kChainQueueBytes + (size_t)kChainXcds * l.max_slots * 4 + (size_t)HK * l.nB * kChainWaves * kChainFlag * 4;
+    l.stats_at = (l.zero_bytes + 255) & ~(size_t)255;
+    l.stat_bytes = (unsigned)((size_t)heads * l.nT * 32 * 4);
+    l.part_at = (l.stats_at + 2 * (size_t)l.stat_bytes + 255) & ~(size_t)255;
+    l.bytes = l.part_at + (size_t)heads * l.nT * 32 * D * 4;
+    return l;
+}
+
+// Key/value heads that an XCD claims at a time if a call takes the five products, else 0.  In steps of 256 keys by 32 queries, one per workgroup:
+// `ideal` is the call's work dealt over 256 CUs (causal: half the plane), `cost` what its workgroups take, who get blocks of 256 keys
+// by whole heads per XCD:
+//   * rounds of 32 blocks; causal, where the blocks of a head get shorter, all blocks of the XCD dealt over its 32 CUs, but no less than the
+//     longest block of the last claim, which starts when the claims before it are through;
+//   * four steps of prologue and epilogue per round, and a step per block that follows another of its head at the same time: the fewer
+//     heads in a claim, the more;
+//   * 2.2 % for every doubling of the claim's blocks beyond two per CU, of which the L2 holds less.
+// (us, claims of 1, 2, 4, 8 heads, D = 128 causal: 64 heads S = 8192 2908, 2800, 2868, 2925; S = 2048 277, 268, 238, 240.)
+// The step itself is 0.75 ... 0.85 of the two passes' time for the same work, which leaves the lines below (us, passes / five products, BF16;
+// ideal / cost):
+//   D = 128  64 heads S = 1024 121 / 116 (0.8), 60 heads 116 / 115 (0.75), 32 heads S = 2048 221 / 206 (0.84), 16 heads S = 8192 1638 / 1336 (0.96);
+//            causal 128 heads S = 1024 152 / 151 (0.67), 64 heads S = 2048 259 / 238 (0.8), 16 heads S = 8192 903 / 713 (0.91);
+//   D = 96   64 heads S = 1024 96 / 95 (0.8), 32 heads S = 2048 176 / 167 (0.84); causal 128 heads S = 1024 120 / 120, 64 heads S = 2048 198 / 184;
+//   D = 64   (what a wavefront issues beside the products weighs twice as much) 128 heads S = 1024 125 / 127 (0.84), 16 heads S = 4096 228 / 234
+//            (0.87), 64 heads S = 2048 231 / 213 (0.89); causal 64 heads S = 2048 137 / 136 (0.8), 32 heads S = 4096 248 / 231 (0.89),
+//            grouped 64 over 16 heads S = 8192 1798 / 1901 (0.96).
+// D = 160 has no registers for it.  At most 2 GiB of sums, and 1 GiB per group of heads (the range of their descriptor).
+constexpr size_t kChainMostBytes = (size_t)2 << 30;
+inline int pick_bwd_chain(int D, bool causal, int heads, int group, int S)
+{
+    const long long HK = heads / group, nT = ((long long)S + 31) / 32, nB = ((long long)S + kChainKeys - 1) / kChainKeys;
+    if (D == 160 || (D == 64 && causal && group > 1) || HK * nB < 128) return 0;
+    if (heads * nT * 32 * D * 4 > (long long)kChainMostBytes || group * nT * 32 * D * 4 >= 1ll << 30) return 0;
+    const long long per_head = group * (causal ? nB * nT - 4 * nB * (nB - 1) : nB * nT);     // steps (causal: blocks of nT, nT - 8, ... tiles)
+    long long pick = 0, least = 0;                // cost times 1000
+    for (long long m = 1; m <= (HK + 7) / 8 && m <= 32; ++m) {
+        const long long most = ((HK + m - 1) / m + 7) / 8 * m, rounds = (most * nB + 31) / 32;      // heads of the XCD that gets the most
+        const long long links = nB < (32 + m - 1) / m ? nB : (32 + m - 1) / m;
+        long long cost = rounds * group * nT + links;
+        if (causal) {
+            const long long share = (most * per_head + 31) / 32, last = (most - m) * per_head / 32 + group * nT + links;
+            cost = share > last ? share : last;
+        }
+        cost = (cost + 4 * rounds) * 1000;
+        for (long long b = m * nB; b >= 128; b /= 2) cost += cost / 45;
+        if (pick == 0 || cost < least) {
+            pick = m;
+            least = cost;
+        }
+    }
+    const long long ideal = HK * S * group * nT / (causal ? 2 : 1);      // times 256 * 256
+    const int line = D == 64 ? 87 : causal && group > 1 ? 85 : D == 96 ? (causal ? 79 : 83) : causal ? 76 : 78;      // per cent
+    return ideal * 100 * 1000 >= least * 65536 * line ? (int)pick : 0;
 }
 
 }  // namespace tsdpa

@@ -28,14 +28,6 @@ namespace tsdpa {
 
 constexpr int kDecodeTile = 32;                   // keys per tile
 
-template <typename T> struct Elem16;
-template <> struct Elem16<_Float16> {
-    static __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
-};
-template <> struct Elem16<__bf16> {
-    static __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-};
-
 // LDS layout of a K or V tile: 32 rows of D values, unpadded; 16-byte chunks are permuted within each row.
 //   K (16 lanes read one chunk of 16 consecutive rows): as in the forward kernel.
 //   V (the transposing read has 32 lanes fetch the same 32 bytes of 8 consecutive rows): 32-byte block b of row r at

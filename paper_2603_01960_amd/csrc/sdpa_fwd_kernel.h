@@ -58,6 +58,15 @@ template <> struct Elem<__bf16> {
     }
 };
 
+// 16 x 16 blocks over 32 products
+template <typename T> struct Elem16;
+template <> struct Elem16<_Float16> {
+    static __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+};
+template <> struct Elem16<__bf16> {
+    static __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+};
+
 __device__ __forceinline__ u32x4 lds_read128(lds_ptr p) { return *(TSDPA_LDS u32x4 *)p; }
 __device__ __forceinline__ void lds_write128(lds_ptr p, u32x4 x) { *(TSDPA_LDS u32x4 *)p = x; }
 // 16 lanes x 4 consecutive 16-bit values, transposed across the 16 lanes: lane i receives, as

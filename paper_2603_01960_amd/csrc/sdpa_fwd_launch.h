@@ -108,6 +108,7 @@ struct BwdLaunchArgs {
     void *dq, *dk, *dv;
     float *stats;            // workspace, two halves of [BH*S + slack]: Delta, then LSE in log2 units
     unsigned stat_bytes;     // bytes of one half
+    void *chain;             // workspace of the five products (chain_layout in sdpa_bwd_pick.h)
     int BH, S;               // query heads (B * H) and rows per head
     int group;               // query heads per key/value head (1: k, v, dk, dv have BH heads too; else BH / group)
     float c;                 // |scale| * log2(e)
@@ -142,5 +143,13 @@ int launch_bwd_bf16_d64(const BwdLaunchArgs &a);
 int launch_bwd_bf16_d96(const BwdLaunchArgs &a);
 int launch_bwd_bf16_d128(const BwdLaunchArgs &a);
 int launch_bwd_bf16_d160(const BwdLaunchArgs &a);
+
+// ... in five products (per_claim: key/value heads that an XCD takes at a time)
+int launch_bwd_chain_f16_d64(const BwdLaunchArgs &a, int per_claim);
+int launch_bwd_chain_f16_d96(const BwdLaunchArgs &a, int per_claim);
+int launch_bwd_chain_f16_d128(const BwdLaunchArgs &a, int per_claim);
+int launch_bwd_chain_bf16_d64(const BwdLaunchArgs &a, int per_claim);
+int launch_bwd_chain_bf16_d96(const BwdLaunchArgs &a, int per_claim);
+int launch_bwd_chain_bf16_d128(const BwdLaunchArgs &a, int per_claim);
 
 }  // namespace tsdpa

@@ -10,6 +10,7 @@
 #include <mutex>
 #include <random>
 
+#include "sdpa_bwd_pick.h"
 #include "sdpa_fwd_launch.h"
 #include "sdpa_merge_kernel.h"
 
@@ -767,12 +768,34 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
     return TSDPA_OK;
 }
 
+// Where the workspace of the five products begins within the caller's (behind the statistics that every other form keeps), and the
+// bytes of both.
+static unsigned long long chain_at(int BH, int S)
+{
+    return (2ull * ((unsigned long long)BH * S + tsdpa::kBwdStatPad) * sizeof(float) + 255) & ~255ull;
+}
+static unsigned long long chain_workspace(int BH, int group, int S, int D, int per_claim)
+{
+    return chain_at(BH, S) + tsdpa::chain_layout(BH, group, S, D, per_claim).bytes;
+}
+
 extern "C" {
 
 unsigned long long tiled_sdpa_bwd_workspace_bytes(int B, int H, int S)
 {
     if (B < 0 || H < 0 || S < 0) return 0;
     return 2ull * ((unsigned long long)B * H * S + tsdpa::kBwdStatPad) * sizeof(float);
+}
+
+unsigned long long tiled_sdpa_bwd_full_workspace_bytes(int B, int H, int Hkv, int S, int D, unsigned flags)
+{
+    if (B < 0 || H < 0 || S < 0) return 0;
+    const unsigned long long least = tiled_sdpa_bwd_workspace_bytes(B, H, S);
+    if (validate_shape(B, H, S, D, TSDPA_F16) != TSDPA_OK || Hkv <= 0 || H % Hkv != 0 || (int64_t)B * H * S == 0 ||
+        (int64_t)B * H * S >= ((int64_t)1 << 29))
+        return least;
+    const int per_claim = tsdpa::pick_bwd_chain(D, (flags & TSDPA_FLAG_CAUSAL) != 0, B * H, H / Hkv, S);
+    return per_claim > 0 ? chain_workspace(B * H, H / Hkv, S, D, per_claim) : least;
 }
 
 int tiled_sdpa_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
@@ -821,7 +844,23 @@ int tiled_sdpa_bwd_gqa(const void *q, const void *k, const void *v, const void *
     a.causal = (flags & TSDPA_FLAG_CAUSAL) ? 1 : 0;
     a.stream = (hipStream_t)stream;
     int err;
-    if (dtype == TSDPA_F16) {
+    const int per_claim = tsdpa::pick_bwd_chain(D, a.causal != 0, a.BH, a.group, S);
+    if (per_claim > 0 && workspace_bytes >= chain_workspace(a.BH, a.group, S, D, per_claim)) {
+        a.chain = (char *)workspace + chain_at(a.BH, S);
+        if (dtype == TSDPA_F16) {
+            switch (D) {
+                case 64: err = tsdpa::launch_bwd_chain_f16_d64(a, per_claim); break;
+                case 96: err = tsdpa::launch_bwd_chain_f16_d96(a, per_claim); break;
+                default: err = tsdpa::launch_bwd_chain_f16_d128(a, per_claim); break;
+            }
+        } else {
+            switch (D) {
+                case 64: err = tsdpa::launch_bwd_chain_bf16_d64(a, per_claim); break;
+                case 96: err = tsdpa::launch_bwd_chain_bf16_d96(a, per_claim); break;
+                default: err = tsdpa::launch_bwd_chain_bf16_d128(a, per_claim); break;
+            }
+        }
+    } else if (dtype == TSDPA_F16) {
         switch (D) {
             case 64: err = tsdpa::launch_bwd_f16_d64(a); break;
             case 96: err = tsdpa::launch_bwd_f16_d96(a); break;

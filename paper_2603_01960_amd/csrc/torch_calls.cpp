@@ -209,6 +209,7 @@ struct Workspace {
     at::Tensor held;
     void *ptr = nullptr;
     unsigned long long bytes = 0;
+    Workspace() = default;
     // the caller's buffer, or `need` bytes of torch's.  The kernels write to it as to one range of bytes: it has to be that,
     // and on the device of the call (of a call that needs none it is not looked at)
     Workspace(PyObject *obj, unsigned long long need, const at::Tensor &like)
@@ -443,7 +444,18 @@ PyObject *call_sdpa_backward(PyObject *, PyObject *const *args, Py_ssize_t n)
             Py_DECREF(seq);
         }
         const int B = (int)s[0], H = (int)s[1], S = (int)s[2], D = (int)s[3];
-        const Workspace ws(args[8], tiled_sdpa_bwd_workspace_bytes(B, H, S), q);
+        const unsigned long long least = tiled_sdpa_bwd_workspace_bytes(B, H, S);
+        Workspace ws;
+        if (args[8] == Py_None) {
+            // (without memory for the sums of dQ the call takes the passes that need none)
+            const unsigned long long full = tiled_sdpa_bwd_full_workspace_bytes(B, H, (int)t[1], S, D, flags);
+            try {
+                ws = Workspace(args[8], full, q);
+            } catch (const c10::OutOfMemoryError &) {
+                if (full == least) throw;
+            }
+        }
+        if (!ws.ptr) ws = Workspace(args[8], least, q);
         const Launch on(q);
         const int st = without_gil(tiled_sdpa_bwd_gqa, data(q), data(k), data(v), data(o), data(dout), (const float *)data(lse), data(grad[0]),
                                           data(grad[1]), data(grad[2]), B, H, (int)t[1], S, D, scale, dtype, flags, ws.ptr,

@@ -1,0 +1,99 @@
+"""The backward pass in five products, whose dQ is summed from block to block of 256 keys (csrc/sdpa_bwd_chain_kernel.h): ragged ends of
+tiles and blocks, one and several rounds of blocks, heads that eight does not divide, grouped heads, both masks, both
+types, against float64; a second call gives the same bits, and a workspace of the least size the passes that need no sums."""
+import pytest
+import torch
+
+from test_bwd_forms_gpu import CASES as FORMS
+from test_bwd_forms_gpu import _reference
+from test_bwd_joint_gpu import CASES as JOINT
+
+pytestmark = pytest.mark.gpu
+
+# (D, key/value heads, query heads per key/value head, S, causal)
+CASES = [(64, 128, 1, 2048, False), (64, 62, 1, 2041, False), (64, 32, 4, 2048, False), (64, 32, 1, 4096, True), (64, 16, 1, 8170, True),
+         (96, 64, 1, 2048, False), (96, 64, 2, 1000, False), (96, 31, 1, 3999, True), (96, 32, 3, 4070, True), (96, 24, 1, 5100, False),
+         (128, 64, 1, 1024, False), (128, 62, 1, 2041, False), (128, 64, 3, 1000, False), (128, 64, 1, 2048, True), (128, 62, 1, 2017, True),
+         (128, 16, 1, 8129, False), (128, 15, 1, 8190, True), (128, 32, 2, 4095, True)]
+
+
+@pytest.mark.parametrize("D,hkv,G,S,causal", CASES)
+def test_gradients_summed_from_block_to_block(D, hkv, G, S, causal):
+    from paper_2603_01960_amd import binding
+    full, least = binding.bwd_full_workspace_bytes(1, hkv * G, hkv, S, D, causal), binding.bwd_workspace_bytes(1, hkv * G, S)
+    assert full > least                           # else the call takes other kernels
+    for dtype, tol in ((torch.float16, 2e-3), (torch.bfloat16, 1.6e-2)):       # times the gradient's size, as for every form
+        g = torch.Generator("cuda").manual_seed(100 * S + hkv)
+        draw = lambda h: torch.randn((1, h, S, D), device="cuda", generator=g).to(dtype)
+        q, k, v, dout = draw(hkv * G), draw(hkv), draw(hkv), draw(hkv * G)
+        o, lse = binding.sdpa_kv(q, k, v, causal, return_lse=True)
+        grads = tuple(torch.full_like(t, float("nan")) for t in (q, k, v))
+        workspace = torch.full((-(-full // 4),), -1, dtype=torch.int32, device="cuda")     # (nothing in it is taken for zero)
+        binding.sdpa_backward(q, k, v, o, dout, lse, causal, grads=grads, workspace=workspace)
+        again = binding.sdpa_backward(q, k, v, o, dout, lse, causal)
+        passes = binding.sdpa_backward(q, k, v, o, dout, lse, causal, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+        for h in {0, hkv - 1}:
+            hq = slice(h * G, (h + 1) * G)
+            want = _reference(q[:, hq], k[:, h:h + 1], v[:, h:h + 1], dout[:, hq], causal)
+            for name, got, other, ref in zip(("dq", "dk", "dv"), (grads[0][:, hq], grads[1][:, h:h + 1], grads[2][:, h:h + 1]),
+                                             (passes[0][:, hq], passes[1][:, h:h + 1], passes[2][:, h:h + 1]), want):
+                err = (got.double() - ref).abs().max().item()
+                bound = tol * max(1.0, ref.abs().max().item())
+                assert err <= bound, f"{name} {dtype} heads={hkv}x{G} S={S} causal={causal}: {err} > {bound}"
+                # no less precise than the passes: both round dS and P once to 16 bits and sum in FP32 (2-norm, 2 % for the order)
+                assert (got.double() - ref).norm() <= 1.02 * (other.double() - ref).norm(), f"{name} {dtype}"
+        assert all(torch.isfinite(t).all() for t in grads)
+        assert all(torch.equal(a, b) for a, b in zip(grads, again))   # no sum depends on who finishes first
+
+
+def test_passes_where_the_workspace_has_no_room_for_the_sums():
+    """The cases of the passes that take the five products when torch allocates the workspace, with one of the least size."""
+    from paper_2603_01960_amd import binding
+    taken = 0
+    for causal in (False, True):
+        for D, hkv, G, S in [*JOINT, *((D, *c) for D in (64, 96, 128) for c in FORMS)]:
+            least = binding.bwd_workspace_bytes(1, hkv * G, S)
+            if binding.bwd_full_workspace_bytes(1, hkv * G, hkv, S, D, causal) == least:
+                continue
+            taken += 1
+            g = torch.Generator("cuda").manual_seed(S + hkv)
+            draw = lambda h: torch.randn((1, h, S, D), device="cuda", generator=g).bfloat16()
+            q, k, v, dout = draw(hkv * G), draw(hkv), draw(hkv), draw(hkv * G)
+            o, lse = binding.sdpa_kv(q, k, v, causal, return_lse=True)
+            grads = binding.sdpa_backward(q, k, v, o, dout, lse, causal, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+            want = _reference(q[:, -G:], k[:, -1:], v[:, -1:], dout[:, -G:], causal)
+            for name, got, ref in zip(("dq", "dk", "dv"), (grads[0][:, -G:], grads[1][:, -1:], grads[2][:, -1:]), want):
+                err = (got.double() - ref).abs().max().item()
+                assert err <= 1.6e-2 * max(1.0, ref.abs().max().item()), f"{name} D={D} heads={hkv}x{G} S={S} causal={causal}: {err}"
+    assert taken > 0
+
+
+def test_recorded_into_a_graph_and_on_two_streams():
+    """The counters of a call are cleared by a kernel of its own: every replay, and two calls under way at once, give the eager bits."""
+    from paper_2603_01960_amd import binding
+    g = torch.Generator("cuda").manual_seed(5)
+    q, k, v, dout = (torch.randn((1, 64, 2048, 128), device="cuda", generator=g).bfloat16() for _ in range(4))
+    o, lse = binding.sdpa(q, k, v, True, return_lse=True)
+    full = binding.bwd_full_workspace_bytes(1, 64, 64, 2048, 128, True)
+    assert full > binding.bwd_workspace_bytes(1, 64, 2048)
+    want = binding.sdpa_backward(q, k, v, o, dout, lse, True)
+    sets = [(torch.full((full,), 255, dtype=torch.uint8, device="cuda"), tuple(torch.empty_like(t) for t in (q, k, v))) for _ in range(2)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in sets]
+    for _ in range(3):
+        for (workspace, grads), stream in zip(sets, streams):
+            with torch.cuda.stream(stream):
+                binding.sdpa_backward(q, k, v, o, dout, lse, True, workspace=workspace, grads=grads)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for _, grads in sets for a, b in zip(grads, want))
+    workspace, grads = sets[0]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        binding.sdpa_backward(q, k, v, o, dout, lse, True, workspace=workspace, grads=grads)
+    for _ in range(4):
+        for t in grads:
+            t.fill_(float("nan"))
+        workspace.fill_(170)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(grads, want))
