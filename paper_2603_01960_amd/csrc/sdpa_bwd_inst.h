@@ -135,8 +135,15 @@ template <typename T, int D>
 int launch_bwd(const BwdLaunchArgs &a)
 {
     if constexpr (D <= 96) {
-        if (a.group == 1 && a.S <= 256 && bwd_in_one_launch(D, a.BH, a.S))
+        if (a.group == 1 && a.S <= 256 && bwd_in_one_launch(D, a.BH, a.S)) {
+            // A workgroup that takes several heads hides one's loads behind another's work.  Up to 256 heads there is nothing to hide and its
+            // prologue costs more (us, a workgroup per head -> that: 256 heads of 197 rows 17.6 -> 18.3, 200 of 256 20.1 -> 20.2), from 257 on
+            // it gains (257 of 256 34.8 -> 34.7, 300 of 129 23.5 -> 23.2, more above 512: see there).  At up to 128 rows several workgroups
+            // share a CU and do the same for each other.
+            if constexpr (D == 64)
+                if (a.S > 128 && a.BH > 256) return launch_bwd_heads<T>(a);
             return a.S <= 64 ? launch_bwd_short_nw<T, D, 2>(a) : a.S <= 128 ? launch_bwd_short_nw<T, D, 4>(a) : launch_bwd_short_nw<T, D, 8>(a);
+        }
     }
     if (const int form = pick_bwd_joint(D, a.causal != 0, a.BH, a.group, a.S)) return launch_bwd_joint<T, D>(a, form);
     // one query head per key/value head keeps the kernels without the loop over a group

@@ -10,8 +10,10 @@
 // that ends its part of tile j, while others are already in tile j + 1 (two dS buffers).
 // What bounds it: per tile and wavefront about 640 cycles of MFMA and 500 of vector work at D = 64 that overlap only across
 // the two wavefronts of a SIMD (more would not fit 256 registers), and prologue and epilogue, which nothing overlaps where
-// eight wavefronts fill the CU.
+// eight wavefronts fill the CU; with more such heads than CUs sdpa_bwd_heads_kernel below overlaps them.
 #pragma once
+#include <mutex>
+
 #include "sdpa_bwd_kernel.h"
 #include "sdpa_decode_kernel.h"
 
@@ -41,6 +43,16 @@ template <int D, int NW> struct BwdShortGeom {
         const int f = (((key >> 2) & 1) << 1) | ((key >> 3) & 1);
         return key * 64 + (((q4 >> 1) ^ f) << 4) + (((q4 & 1) ^ ((key >> 4) & 1)) << 3);
     }
+};
+
+// LDS of sdpa_bwd_heads_kernel: three Q tiles, three dO tiles, LSE in log2 units and -Delta of 256 rows, two dS buffers, K, V and O of a head.
+struct BwdHeadsGeom {
+    using G = BwdGeom<64>;
+    static constexpr int U = 4, TILE = G::bytes(32), BLOCK = G::bytes(256), DSBUF = 256 * 64;
+    static constexpr int DO = 3 * TILE, STATS = 6 * TILE, DS = STATS + 2 * 256 * 4, HEAD = DS + 2 * DSBUF;
+    static constexpr int LDS_BYTES = HEAD + 3 * BLOCK;
+    static __host__ __device__ constexpr int ds_at(int key, int q4) { return BwdShortGeom<64, 8>::ds_at(key, q4); }
+    static_assert(256 * G::OROW <= 2 * DSBUF && DS % 1024 == 0, "dK and dV are turned where dS was; its chunks are XORed");
 };
 
 // Sixteen (or eight) transposing reads and the wait for them in one block of inline assembly.  Left to the compiler, which
@@ -454,6 +466,317 @@ template <typename T, int D, int NW, bool CAUSAL> int launch_bwd_short_mask(cons
 template <typename T, int D, int NW> int launch_bwd_short_nw(const BwdLaunchArgs &a)
 {
     return a.causal ? launch_bwd_short_mask<T, D, NW, true>(a) : launch_bwd_short_mask<T, D, NW, false>(a);
+}
+
+// The same for sequences of 129 ... 256 rows at D = 64 and more heads than CUs: a workgroup per CU takes one head after another and
+// fetches the next head's K, V and O into the LDS while it works on the present one, two load instructions per wavefront and tile; the
+// next head's first tiles and dO rows are on their way while dK and dV are stored.  As a workgroup per head, whose eight wavefronts
+// fill the CU, a head spent 13 of its 35 thousand clocks on the arrival of those, every CU at the same time, and 18 in the loop
+// with the memory idle.  us per call, BF16, a workgroup per head -> this: 768 heads of 197 rows
+// 54.2 -> 51.1 (causal 52.9 -> 46.5), 1030 of 130 55.9 -> 52.4 (62.1 -> 54.0), 520 of 160 36.9 -> 34.3 (40.6 -> 35.7), 600 of 225
+// 51.7 -> 49.6 (54.9 -> 50.2), 384 of 256 35.8 -> 35.3 (38.0 -> 36.4).  What bounds it: the loop as above, now with the memory at work
+// beside it, and the prologue of a workgroup's first head.
+template <typename T, bool CAUSAL>
+__global__ void __launch_bounds__(512, 2)
+sdpa_bwd_heads_kernel(const T *__restrict__ q, const T *__restrict__ k, const T *__restrict__ v, const T *__restrict__ dout,
+                      const T *__restrict__ o, const float *__restrict__ lse, T *__restrict__ dq, T *__restrict__ dk,
+                      T *__restrict__ dv, int heads, int S, float c, float scale, uint32_t rsign)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int D = 64, NW = 8;
+    using E = Elem<T>;
+    using vec8 = typename E::vec8;
+    using vec4 = typename E::vec4;
+    using G = BwdGeom<D>;
+    using W = BwdHeadsGeom;
+    constexpr int KK = D / 16, DB = D / 32, U = W::U, TILE = W::TILE, ROW16 = G::bytes(16);
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const lds_ptr lds = (lds_ptr)smem;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 5, l32 = lane & 31, t = lane >> 4, l16 = lane & 15;
+    const int row = wave * 32 + l32, row_c = row < S ? row : S - 1;        // this lane's key, and its query in the statistics
+    const int nb = (S + 31) / 32;                 // 32-row blocks of the sequence
+
+    // (rows past the sequence read as zero and are not written)
+    auto rsrc_of = [&](const T *p, int head) __attribute__((always_inline)) {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(p + (size_t)head * S * D), (short)0, S * G::GROW, 0x00020000);
+    };
+    // a unit of eight rows; of a wavefront's units all have odd or all even numbers
+    const int goff = (lane >> 3) * G::GROW + (((lane & 7) ^ G::swz((wave & 1) * 8 + (lane >> 3))) << 4);
+    auto load_unit = [&](__amdgpu_buffer_rsrc_t rsrc, uint32_t dst, int unit) __attribute__((always_inline)) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(dst), "v"(goff), "s"(rsrc), "s"(unit * 1024));
+    };
+    // Q and dO of tile j of the head behind rsrc: one unit per wavefront, of Q or of dO
+    const T *const mine = wave < 4 ? q : dout;
+    const uint32_t mine_at = lds0 + (wave < 4 ? 0 : W::DO) + (wave & 3) * 1024;
+    auto load_tile = [&](__amdgpu_buffer_rsrc_t rsrc, int j, int slot) __attribute__((always_inline)) {
+        load_unit(rsrc, mine_at + slot * TILE, j * U + (wave & 3));
+    };
+    // K, V and O of the head behind the three descriptors: part j of nb, two units per wavefront (the last ones more than once, so that
+    // every part has two)
+    auto fetch = [&](__amdgpu_buffer_rsrc_t k_rsrc, __amdgpu_buffer_rsrc_t v_rsrc, __amdgpu_buffer_rsrc_t o_rsrc, int j) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int at = j * 16 + i * 8 + wave, u = at < 12 * nb ? at : 12 * nb - 8 + wave;
+            const int x = (u >= 4 * nb) + (u >= 8 * nb), uu = u - x * 4 * nb;
+            load_unit(x == 0 ? k_rsrc : x == 1 ? v_rsrc : o_rsrc, lds0 + W::HEAD + x * W::BLOCK + uu * 1024, uu);
+        }
+    };
+    lds_ptr row_ptr[G::NRP];
+#pragma unroll
+    for (int i = 0; i < G::NRP; ++i) {
+        row_ptr[i] = lds + G::at(l32, 2 * G::rp_kk(i) + g);
+        TSDPA_OPAQUE(row_ptr[i]);
+    }
+    auto operand = [&](int at, int kk) __attribute__((always_inline)) { return lds_read128(row_ptr[G::rp(kk)] + at + G::rp_imm(kk)); };
+    auto products = [&](int at, const vec8 (&rf)[KK], f32x16 &acc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) acc = E::mfma(__builtin_bit_cast(vec8, operand(at, kk)), rf[kk], acc);
+    };
+    const int t_row = g * 4 + (l16 >> 2), t_chunk = (t & 1) * 2 + ((lane & 3) >> 1), k_row = 4 * t + (l16 >> 2);
+    uint32_t tr_lo[G::NTP], tr_hi[G::NTP];
+#pragma unroll
+    for (int i = 0; i < G::NTP; ++i) {
+        tr_lo[i] = lds0 + G::at(t_row, i * 4 + t_chunk) + (lane & 1) * 8;
+        tr_hi[i] = lds0 + G::at(t_row + 8, i * 4 + t_chunk) + (lane & 1) * 8;
+        TSDPA_OPAQUE(tr_lo[i]);
+        TSDPA_OPAQUE(tr_hi[i]);
+    }
+    // dQ: block of 16 columns wave % 4, queries (wave / 4) * 16 ...
+    const int qh = wave / 4, cb = wave & 3;
+    const uint32_t ds_lo = lds0 + W::DS + W::ds_at(k_row, qh * 4 + (l16 & 3)), ds_hi = lds0 + W::DS + W::ds_at(k_row + 16, qh * 4 + (l16 & 3));
+    const uint32_t kt_at = lds0 + W::HEAD + G::at(k_row, cb * 2 + ((l16 & 3) >> 1)) + (l16 & 1) * 8;
+    const int ds_w0 = W::DS + W::ds_at(row, g);   // run r4 of this lane's key: chunk r4 ^ f, as an XOR of the address
+
+    int head = blockIdx.x;
+    u32x4 drow[KK];                               // dO of the lane's row, and its LSE
+    float lse_r;
+    auto load_rows = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) drow[kk] = *(const u32x4 *)(dout + ((size_t)h * S + row_c) * D + kk * 16 + g * 8);
+        lse_r = lse[(size_t)h * S + row_c];
+    };
+    auto t_rsrc = rsrc_of(mine, head);
+    {
+        const auto k_rsrc = rsrc_of(k, head), v_rsrc = rsrc_of(v, head), o_rsrc = rsrc_of(o, head);
+        for (int j = 0; j < nb; ++j) fetch(k_rsrc, v_rsrc, o_rsrc, j);
+    }
+    load_tile(t_rsrc, 0, 0);
+    load_tile(t_rsrc, 1, 1);
+    load_rows(head);
+    int slot = 0;                                 // of the head's first tile; tiles follow one another also across heads
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    for (;;) {
+        const int next = head + (int)gridDim.x;
+        const bool more = next < heads;
+        const auto n_rsrc = rsrc_of(mine, next), k_rsrc = rsrc_of(k, next), v_rsrc = rsrc_of(v, next), o_rsrc = rsrc_of(o, next);
+        const size_t off = (size_t)head * S * D;
+        __syncthreads();
+        // ---- K and V rows of this wavefront (the sign of a negative scale goes into K's), K^T of its dQ blocks
+        vec8 rf1[KK], rf2[KK], kt[NW];
+        float delta_r = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            rf1[kk] = __builtin_bit_cast(vec8, operand(W::HEAD + wave * TILE, kk) ^ rsign);
+            rf2[kk] = __builtin_bit_cast(vec8, operand(W::HEAD + W::BLOCK + wave * TILE, kk));
+            const vec8 x = __builtin_bit_cast(vec8, operand(W::HEAD + 2 * W::BLOCK + wave * TILE, kk)), y = __builtin_bit_cast(vec8, drow[kk]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) delta_r += (float)x[e] * (float)y[e];
+        }
+        delta_r = pair_sum(delta_r);
+        const float lse2 = lse_r * 1.44269504088896340736f;
+        {
+            i16x4 x[2 * NW];
+#pragma unroll
+            for (int n = 0; n < NW; n += 4) short_read_blocks<2 * ROW16, false>(x + 2 * n, kt_at + n * 2 * ROW16, kt_at + (n * 2 + 1) * ROW16);
+#pragma unroll
+            for (int kb = 0; kb < NW; ++kb) {
+                // (blocks past the end are whatever the LDS holds; their dS is zero)
+                const u32x4 raw = __builtin_bit_cast(u32x4, __builtin_shufflevector(x[2 * kb], x[2 * kb + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+                kt[kb] = __builtin_bit_cast(vec8, kb < nb ? raw : u32x4{0u, 0u, 0u, 0u});
+            }
+        }
+        if constexpr (CAUSAL) {
+            // rows that see at most kBwdShortRow keys: Delta from its definition (see the general kernel); their Q is in the first tiles
+            if (wave * 32 < kBwdShortRow) {
+                vec8 qf[KK], df[KK];
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    qf[kk] = __builtin_bit_cast(vec8, operand((slot + wave) % 3 * TILE, kk) ^ rsign);
+                    df[kk] = __builtin_bit_cast(vec8, drow[kk]);
+                }
+                float sum = 0.f;
+                for (int j = 0; j < kBwdShortRow / 32; ++j) {
+                    f32x16 sacc, dpacc;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) sacc[i] = dpacc[i] = 0.f;
+                    products(W::HEAD + j * TILE, qf, sacc);
+                    products(W::HEAD + W::BLOCK + j * TILE, df, dpacc);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int key = j * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
+                        if (key <= row_c) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], c, -lse2)) * dpacc[i];
+                    }
+                }
+                delta_r = pair_sum(sum);
+            }
+        }
+        if (g == 0) {
+            TSDPA_LDS float *st = (TSDPA_LDS float *)(lds + W::STATS);
+            st[row] = row < S ? lse2 : INFINITY;
+            st[NW * 32 + row] = row < S ? -delta_r : 0.f;
+        }
+        // dS of keys past the end is never written: zero
+        if (row >= S)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) *(TSDPA_LDS u32x2 *)(lds + (i >> 2) * W::DSBUF + (ds_w0 ^ ((i & 3) << 4))) = u32x2{0u, 0u};
+        __syncthreads();                          // (K, V and O are through: the next head's may come)
+
+        f32x16 acc_k[DB], acc_v[DB];
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc_k[db][i] = acc_v[db][i] = 0.f;
+        vec8 pb[2], xb[2];
+        auto weights = [&](int j, const f32x16 &sacc, const f32x16 &dpacc, auto mask_tag) __attribute__((always_inline)) {
+            constexpr bool MASK = decltype(mask_tag)::value;
+            const lds_ptr st = lds + W::STATS + (j * 32 + g * 4) * 4;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const f32x4 st_lse = *(TSDPA_LDS f32x4 *)(st + r4 * 32);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = r4 * 4 + e, qrow = j * 32 + r4 * 8 + g * 4 + e;
+                    const bool masked = MASK && qrow < row;             // a key after the query
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[i], c, -st_lse[e]));
+                    const float x = p * dpacc[i];
+                    pb[i >> 3][i & 7] = (T)(masked ? 0.f : p);
+                    xb[i >> 3][i & 7] = (T)(masked ? 0.f : x);
+                }
+            }
+        };
+        for (int j = 0; j < nb; ++j) {
+            const bool own = j + 2 < nb;
+            if (own || more) load_tile(own ? t_rsrc : n_rsrc, own ? j + 2 : j + 2 - nb, slot == 0 ? 2 : slot - 1);
+            if (more) fetch(k_rsrc, v_rsrc, o_rsrc, j);
+            const int at = slot * TILE, ds_buf = (j & 1) * W::DSBUF;
+            if (wave < nb && (!CAUSAL || j >= wave)) {
+                f32x16 sacc, dpacc;
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const f32x4 md = *(TSDPA_LDS f32x4 *)(lds + W::STATS + (NW * 32 + j * 32 + g * 4) * 4 + r4 * 32);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        sacc[r4 * 4 + e] = 0.f;
+                        dpacc[r4 * 4 + e] = md[e];
+                    }
+                }
+                products(at, rf1, sacc);
+                products(W::DO + at, rf2, dpacc);
+                if (CAUSAL && j == wave) weights(j, sacc, dpacc, std::true_type{});
+                else                     weights(j, sacc, dpacc, std::false_type{});
+                if (row < S)
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) {
+                        vec4 x;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[e] = xb[r4 >> 1][(r4 & 1) * 4 + e];
+                        *(TSDPA_LDS vec4 *)(lds + ds_buf + (ds_w0 ^ (r4 << 4))) = x;
+                    }
+                // dV^T += dO^T P, dK^T += Q^T dS
+                i16x4 x[16];
+                short_read_tiles<W::DO, ROW16>(x, tr_lo[0] + at, tr_hi[0] + at, tr_lo[1] + at, tr_hi[1] + at);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) {
+                        auto both = [&](int i) __attribute__((always_inline)) {
+                            return __builtin_bit_cast(vec8, __builtin_shufflevector(x[i], x[i + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+                        };
+                        acc_v[db] = E::mfma(both((ks * 2 + db) * 2), pb[ks], acc_v[db]);
+                        acc_k[db] = E::mfma(both(8 + (ks * 2 + db) * 2), xb[ks], acc_k[db]);
+                    }
+            }
+            // The next tile, requested a step ago, has landed when nothing but what was requested after it is outstanding: two units of
+            // the next head then, the tile after the next and two more units now (a store of dQ may count as well: then more has landed).
+            // In the last head the tile after the next is all there is.
+            if (more) asm volatile("s_waitcnt vmcnt(5) lgkmcnt(0)" : : : "memory");
+            else if (own) asm volatile("s_waitcnt vmcnt(1) lgkmcnt(0)" : : : "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
+            __builtin_amdgcn_s_barrier();
+            slot = slot == 2 ? 0 : slot + 1;
+            // dQ of the tile: [16 columns][16 queries] += K^T dS^T over the keys (causal: up to the tile's own)
+            i16x4 x[2 * NW];
+#pragma unroll
+            for (int i = 0; i < NW; i += 4) short_read_blocks<2048, false>(x + 2 * i, ds_lo + ds_buf + i * 2048, ds_hi + ds_buf + i * 2048);
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int kb = 0; kb < NW; ++kb) {
+                if (CAUSAL && kb > j) break;
+                const vec8 b = __builtin_bit_cast(vec8, __builtin_shufflevector(x[2 * kb], x[2 * kb + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+                acc[kb & 1] = Elem16<T>::mfma(kt[kb], b, acc[kb & 1]);
+            }
+            const int qrow = j * 32 + qh * 16 + l16;
+            vec4 out;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[e] = (T)((acc[0][e] + acc[1][e]) * scale);
+            if (qrow < S) *(vec4 *)(dq + off + (size_t)qrow * D + cb * 16 + t * 4) = out;
+        }
+        // ---- the next head's rows, and dK and dV through the place of dS as whole rows (the barrier: dS is read)
+        if (more) load_rows(next);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
+        auto store = [&](const f32x16 (&acc)[DB], float factor, T *dst) __attribute__((always_inline)) {
+            constexpr int OCPR = G::OROW / 16, CMASK = OCPR - 1;
+            const lds_ptr ow = lds + W::DS + wave * (32 * G::OROW);
+            const auto rsrc = rsrc_of(dst, head);
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    vec4 val;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) val[e] = (T)(acc[db][q4 * 4 + e] * factor);
+                    *(TSDPA_LDS vec4 *)(ow + l32 * G::OROW + (((db * 4 + q4) ^ (l32 & CMASK)) << 4) + g * 8) = val;
+                }
+            constexpr int RPI = 64 / OCPR;
+#pragma unroll
+            for (int i = 0; i < 32 / RPI; ++i) {
+                const int r = i * RPI + lane / OCPR, cc = lane % OCPR;
+                const u32x4 val = lds_read128(ow + r * G::OROW + ((cc ^ (r & CMASK)) << 4));
+                __builtin_amdgcn_raw_buffer_store_b128(val, rsrc, r * G::GROW + cc * 16, wave * 32 * G::GROW, 0);        // (rows >= S: dropped)
+            }
+        };
+        store(acc_k, scale, dk);
+        store(acc_v, 1.0f, dv);                   // (same region: it is private to the wavefront, whose LDS operations complete in order)
+        if (!more) break;
+        // everything of the next head has landed; the eight stores may be on their way
+        asm volatile("s_waitcnt vmcnt(8)" : : : "memory");
+        head = next;
+        t_rsrc = n_rsrc;
+    }
+#endif
+}
+
+template <typename T, bool CAUSAL> int launch_bwd_heads_mask(const BwdLaunchArgs &a)
+{
+    auto kern = sdpa_bwd_heads_kernel<T, CAUSAL>;
+    static_assert(BwdHeadsGeom::LDS_BYTES <= 160 * 1024, "LDS of a CU");
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] {
+        attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, BwdHeadsGeom::LDS_BYTES);
+    });
+    if (attr_err != hipSuccess) return (int)attr_err;
+    hipLaunchKernelGGL(kern, dim3(256), dim3(512), BwdHeadsGeom::LDS_BYTES, a.stream, (const T *)a.q, (const T *)a.k, (const T *)a.v,
+                       (const T *)a.dout, (const T *)a.o, a.lse, (T *)a.dq, (T *)a.dk, (T *)a.dv, a.BH, a.S, a.c, a.scale, a.rsign);
+    return (int)hipGetLastError();
+}
+
+template <typename T> int launch_bwd_heads(const BwdLaunchArgs &a)
+{
+    return a.causal ? launch_bwd_heads_mask<T, true>(a) : launch_bwd_heads_mask<T, false>(a);
 }
 
 }  // namespace tsdpa
