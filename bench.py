@@ -390,7 +390,7 @@ def bwd_kernels(D, heads, S, grouped):
     if D <= 96 and not grouped and S <= 256:
         rounds = -(-heads // 256)
         if S <= (128 if D == 64 else 64) or (heads >= 110 and (D == 64 or S <= 128 or 10 * heads >= 7 * 256 * rounds)):
-            return "sdpa_bwd_short_kernel", 5
+            return "sdpa_bwd_heads_kernel" if D == 64 and S > 128 and heads > 256 else "sdpa_bwd_short_kernel", 5
     # (one grid after the statistics, or launches of their own: pick_bwd_joint of csrc/sdpa_bwd_pick.h)
     return "sdpa_bwd_joint_kernel, or sdpa_bwd_kernel<dQ> + " + ("sdpa_bwd_pair_kernel" if D == 160 else "sdpa_bwd_kernel<dK+dV>"), 7
 
@@ -447,7 +447,7 @@ def bench_bwd(pkg, torch, args, flags):
         "roofline": {"bound": "mfma", "achieved": round(tf, 2), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tf / PEAK_MFMA_TFLOPS, 4),
                      # both kernels of a call, FETCH_SIZE + WRITE_SIZE scaled (profiles/sdpa_bwd_C4_C2.md)
-                     "traffic": 1621.4e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H and not chain) else None,
+                     "traffic": 7979e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H and chain) else None,
                      "kernel": kernels, "ms_avg_all_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
                      "executed_mfma_flops_per_launch": flops * products / 5.0}}), flush=True)
 
