@@ -769,14 +769,15 @@ static int fwd_kv_impl(const void *q, const void *k, const void *v, void *o, flo
 }
 
 // Where the workspace of the five products begins within the caller's (behind the statistics that every other form keeps), and the
-// bytes of both.
-static unsigned long long chain_at(int BH, int S)
+// bytes of both wherever the caller's begins.  At an address that 256 divides: a cache line of two tiles' sums, read for the first of
+// them, would still be in the CU's cache, with what the second one's place held then, when that one's turn comes.
+static uintptr_t chain_at(uintptr_t workspace, int BH, int S)
 {
-    return (2ull * ((unsigned long long)BH * S + tsdpa::kBwdStatPad) * sizeof(float) + 255) & ~255ull;
+    return (workspace + 2 * ((size_t)BH * S + tsdpa::kBwdStatPad) * sizeof(float) + 255) & ~(uintptr_t)255;
 }
 static unsigned long long chain_workspace(int BH, int group, int S, int D, int per_claim)
 {
-    return chain_at(BH, S) + tsdpa::chain_layout(BH, group, S, D, per_claim).bytes;
+    return chain_at(256 - 16, BH, S) + tsdpa::chain_layout(BH, group, S, D, per_claim).bytes;
 }
 
 extern "C" {
@@ -846,7 +847,7 @@ int tiled_sdpa_bwd_gqa(const void *q, const void *k, const void *v, const void *
     int err;
     const int per_claim = tsdpa::pick_bwd_chain(D, a.causal != 0, a.BH, a.group, S);
     if (per_claim > 0 && workspace_bytes >= chain_workspace(a.BH, a.group, S, D, per_claim)) {
-        a.chain = (char *)workspace + chain_at(a.BH, S);
+        a.chain = (void *)chain_at((uintptr_t)workspace, a.BH, S);
         if (dtype == TSDPA_F16) {
             switch (D) {
                 case 64: err = tsdpa::launch_bwd_chain_f16_d64(a, per_claim); break;

@@ -68,6 +68,23 @@ def test_passes_where_the_workspace_has_no_room_for_the_sums():
     assert taken > 0
 
 
+def test_workspace_that_begins_in_the_middle_of_a_cache_line():
+    """A workspace needs no more than 16 bytes of alignment; the sums then still keep to cache lines of their own."""
+    from paper_2603_01960_amd import binding
+    g = torch.Generator("cuda").manual_seed(6)
+    q, k, v, dout = (torch.randn((1, 64, 2048, 128), device="cuda", generator=g).bfloat16() for _ in range(4))
+    o, lse = binding.sdpa(q, k, v, True, return_lse=True)
+    full = binding.bwd_full_workspace_bytes(1, 64, 64, 2048, 128, True)
+    room = torch.full((full + 512,), 255, dtype=torch.uint8, device="cuda")
+    base = -room.data_ptr() % 256
+    want = binding.sdpa_backward(q, k, v, o, dout, lse, True, workspace=room[base:base + full])
+    for shift in (16, 112, 240):
+        room.fill_(255)
+        got = binding.sdpa_backward(q, k, v, o, dout, lse, True, workspace=room[base + shift:base + shift + full])
+        assert all(torch.equal(a, b) for a, b in zip(want, got)), f"begins {shift} bytes into a line"
+        assert (room[:base + shift] == 255).all() and (room[base + shift + full:] == 255).all()
+
+
 def test_recorded_into_a_graph_and_on_two_streams():
     """The counters of a call are cleared by a kernel of its own: every replay, and two calls under way at once, give the eager bits."""
     from paper_2603_01960_amd import binding
