@@ -327,10 +327,12 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
         // One query tile.  Vector memory operations of a step, in their order: PARTS loads of sums, the counter's store, the flag's load, the loads
         // of the tile after the next (NLD, and one of wavefront 0), PARTS stores.
         // Masks: none; the diagonal (and the end of the keys); the end of the keys, past which a lane's rows of dK and dV are garbage that is not
-        // stored, so that only its dS has to be zero.
-        enum { NONE, DIAGONAL, END };
+        // stored, so that only its dS has to be zero; the diagonal in a ragged last tile of queries, whose rows past the end have weights of zero
+        // by their LSE, but a score of 0 * inf with a key of infinities.
+        enum { NONE, DIAGONAL, END, TAIL };
         auto step = [&](auto mask_tag) __attribute__((always_inline)) {
-            constexpr bool MASK = decltype(mask_tag)::value == DIAGONAL, LAST = decltype(mask_tag)::value == END;
+            constexpr bool ROWS = decltype(mask_tag)::value == TAIL, MASK = ROWS || decltype(mask_tag)::value == DIAGONAL;
+            constexpr bool LAST = decltype(mask_tag)::value == END;
             f32x16 s[2], dp[2], delta;
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[0][i] = s[1][i] = 0.f;
@@ -384,12 +386,18 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
                 const int key = w0 + kb * 32 + (lane & 31);
                 return (key >= S ? 0x7fffffff : causal ? key : 0) - (lane >> 5) * 4;
             };
+            // ... and of those that do, the first this many exist
+            auto seeing = [&](int kb) __attribute__((always_inline)) -> unsigned {
+                const int key = w0 + kb * 32 + (lane & 31);
+                return key >= S ? 0u : causal ? S - key : S;
+            };
             auto weight = [&](int kb, int r4) __attribute__((always_inline)) {
                 const int lo = MASK ? hidden(kb) : 0;
+                const unsigned row = ROWS ? (unsigned)(j * TS + r4 * 8) - (unsigned)lo : 0u, rows = ROWS ? seeing(kb) : 0u;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][r4 * 4 + e], c, -lse[r4][e]));
-                    p4[kb][r4][e] = MASK && j * TS + r4 * 8 + e < lo ? 0.f : p;
+                    p4[kb][r4][e] = (ROWS ? row + e >= rows : MASK && j * TS + r4 * 8 + e < lo) ? 0.f : p;
                 }
                 pw[kb][r4] = __builtin_bit_cast(u32x2, __builtin_convertvector(p4[kb][r4], vec4));
             };
@@ -565,6 +573,7 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
         const bool end = !causal && r0 + KEYS > S;
         const int jd = causal ? j0 + KEYS / TS : j0;             // tiles from here on are behind the diagonal
         for (int h = 0; h < group; ++h) {
+            if (S % TS != 0) step(std::integral_constant<int, TAIL>{});
             if (end)
                 while (j >= j0) step(std::integral_constant<int, END>{});
             while (j >= jd) step(std::integral_constant<int, NONE>{});

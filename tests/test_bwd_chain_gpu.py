@@ -68,6 +68,30 @@ def test_passes_where_the_workspace_has_no_room_for_the_sums():
     assert taken > 0
 
 
+@pytest.mark.parametrize("D,hkv,G,S,causal", [(64, 62, 1, 2041, False), (96, 31, 1, 3999, True), (128, 62, 1, 2041, False), (128, 32, 2, 4095, True)])
+def test_keys_of_infinities(D, hkv, G, S, causal):
+    """A key whose score is -inf for every query has gradients of zero, also where rows past the end, whose score with it is NaN (0 * inf),
+    lie in the last tile.  (dQ is NaN in its column, 0 * inf, of the rows that see it and, under the mask, ahead of it in its tile.)"""
+    from paper_2603_01960_amd import binding
+    g = torch.Generator("cuda").manual_seed(S + D)
+    draw = lambda h: torch.randn((1, h, S, D), device="cuda", generator=g).half()
+    q, k, v, dout = draw(hkv * G), draw(hkv), draw(hkv), draw(hkv * G)
+    q[..., 0] = q[..., 0].abs() + 0.1
+    keys = [S // 2, S - 300]
+    k[0, hkv - 1, keys, 0] = float("-inf")
+    o, lse = binding.sdpa_kv(q, k, v, causal, return_lse=True)
+    assert torch.isfinite(o).all() and torch.isfinite(lse).all()
+    assert binding.bwd_full_workspace_bytes(1, hkv * G, hkv, S, D, causal) > binding.bwd_workspace_bytes(1, hkv * G, S)
+    grads = binding.sdpa_backward(q, k, v, o, dout, lse, causal)
+    passes = binding.sdpa_backward(q, k, v, o, dout, lse, causal,
+                                   workspace=torch.empty(binding.bwd_workspace_bytes(1, hkv * G, S), dtype=torch.uint8, device="cuda"))
+    for name, got, ref in zip(("dq", "dk", "dv"), grads, passes):
+        assert torch.isfinite(got[..., 1:]).all() and torch.isfinite(ref[..., 1:]).all(), name
+        assert name == "dq" or (torch.isfinite(got).all() and torch.isfinite(ref).all()), name
+        assert (got - ref).nan_to_num().abs().max() <= 4e-3 * max(1.0, ref.nan_to_num().abs().max()), name       # (2e-3 of each to float64)
+    assert (grads[1][0, hkv - 1, keys] == 0).all() and (grads[2][0, hkv - 1, keys] == 0).all()
+
+
 def test_workspace_that_begins_in_the_middle_of_a_cache_line():
     """A workspace needs no more than 16 bytes of alignment; the sums then still keep to cache lines of their own."""
     from paper_2603_01960_amd import binding
