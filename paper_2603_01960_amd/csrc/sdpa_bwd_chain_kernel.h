@@ -65,20 +65,6 @@ struct ChainArgs {
     float c, scale;
 };
 
-// HBM -> LDS, 16 or 4 bytes per lane.  (m0 needs one other instruction before it is used.)
-__device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t dst, int voff, int soff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff));
-}
-__device__ __forceinline__ void lds_load4(__amdgpu_buffer_rsrc_t rsrc, uint32_t dst, int voff, int soff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff));
-}
-// ... past the L2
-__device__ __forceinline__ void lds_load4_agent(__amdgpu_buffer_rsrc_t rsrc, uint32_t dst)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen sc1 lds" : : "s"(dst), "v"(0), "s"(rsrc));
-}
 // all but the last N vector memory operations are complete
 template <int N> __device__ __forceinline__ void wait_all_but() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
 __device__ __forceinline__ void wait_all()

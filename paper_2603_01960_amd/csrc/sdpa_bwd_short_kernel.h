@@ -506,7 +506,7 @@ sdpa_bwd_heads_kernel(const T *__restrict__ q, const T *__restrict__ k, const T 
     // a unit of eight rows; of a wavefront's units all have odd or all even numbers
     const int goff = (lane >> 3) * G::GROW + (((lane & 7) ^ G::swz((wave & 1) * 8 + (lane >> 3))) << 4);
     auto load_unit = [&](__amdgpu_buffer_rsrc_t rsrc, uint32_t dst, int unit) __attribute__((always_inline)) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(dst), "v"(goff), "s"(rsrc), "s"(unit * 1024));
+        lds_load16(rsrc, dst, goff, unit * 1024);
     };
     // Q and dO of tile j of the head behind rsrc: one unit per wavefront, of Q or of dO
     const T *const mine = wave < 4 ? q : dout;

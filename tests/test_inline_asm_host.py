@@ -1,0 +1,72 @@
+"""What the compiler cannot know of instructions written in assembly, checked on its own output (no GPU): which registers they write, and the
+wait states that the hardware wants between two instructions, which the compiler inserts for its own instructions only.  Small kernels that put the
+wrappers where their neighbours are closest, and the kernels that use them."""
+import re
+import shutil
+import subprocess
+from pathlib import Path
+
+import pytest
+
+CSRC = Path(__file__).resolve().parents[1] / "paper_2603_01960_amd" / "csrc"
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+pytestmark = pytest.mark.skipif(not Path(HIPCC).exists(), reason="hipcc not available")
+
+PRELUDE = '#include "sdpa_bwd_chain_kernel.h"\nusing namespace tsdpa;\n'
+
+
+def assembly(src: Path, out: Path):
+    """The instructions of a translation unit, [(name, operands, written in assembly)], labels as names with a colon."""
+    from paper_2603_01960_amd import build as lib_build
+    subprocess.run([HIPCC, *lib_build.FLAGS, *lib_build.extra_flags(src), "-S", "--cuda-device-only", str(src), "-o", str(out)],
+                   check=True, capture_output=True, timeout=600)
+    code, by_hand = [], False
+    for line in out.read_text().split("\n"):
+        if "#ASMSTART" in line or "#ASMEND" in line:
+            by_hand = "#ASMSTART" in line
+            continue
+        line = line.split(";")[0].strip()
+        if not line or (line.startswith(".") and not line.endswith(":")):
+            continue
+        name, _, rest = line.partition(" ")
+        operands = [x.strip() for x in rest.split(",")] if rest else []
+        if operands:
+            operands[-1:] = operands[-1].split()          # (modifiers)
+        code.append((name, operands, by_hand))
+    return code
+
+
+def probe(tmp_path, body):
+    """Assembly of a kernel, built with the flags of the five-product backward."""
+    src = tmp_path / "sdpa_bwd_chain_probe.hip"
+    src.write_text(PRELUDE + body)
+    return assembly(src, tmp_path / "probe.s")
+
+
+def test_m0_of_the_compilers_loads_survives_a_load_in_assembly(tmp_path):
+    """A load to the LDS takes its address from m0, which the compiler sets once for loads to the same place: not past a load in assembly."""
+    code = probe(tmp_path, r"""
+__global__ void loads(int *p, int bytes, int at, int other)
+{
+    extern __shared__ unsigned char smem[];
+    const lds_ptr lds = (lds_ptr)smem;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, bytes, 0x00020000);
+    const int voff = threadIdx.x * 4;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + at), 4, voff, 0, 0, 0);
+    lds_load16(rsrc, other, voff, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + at), 4, voff, 64, 0, 0);
+    lds_load4(rsrc, other, voff, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + at), 4, voff, 128, 0, 0);
+    lds_load4_agent(rsrc, other);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (TSDPA_LDS void *)(lds + at), 4, voff, 192, 0, 0);
+}
+""")
+    loads = set_by = 0
+    for name, operands, by_hand in code:
+        if operands and operands[0] == "m0":
+            set_by = by_hand
+        if name.startswith("buffer_load") and "lds" in operands:
+            loads += 1
+            assert set_by == by_hand, f"load {loads} has the m0 of the one before it"
+    assert loads == 7
