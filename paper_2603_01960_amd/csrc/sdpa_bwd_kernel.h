@@ -91,23 +91,25 @@ enum { BWD_DQ = 0, BWD_DKV = 1 };
 constexpr int kBwdShortRow = 64;
 
 // HBM -> LDS loads in assembly, 16 or 4 bytes per lane, for kernels that count their loads themselves: left to the compiler, the first
-// transposing read waits for all of them.  (m0 needs one other instruction before it is used.  That it is written has to be said: the
-// compiler keeps the m0 of its own loads to the LDS from one to the next.  Its warning that m0 is reserved is about registers that it
-// would restore, which nothing here relies on.)
+// transposing read waits for all of them.
+//   * That m0 is written has to be said: the compiler keeps the m0 of its own loads to the LDS from one to the next.  (Its warning that m0
+//     is reserved is about registers that it would restore, which nothing here relies on.)
+//   * A memory instruction must not follow a vector instruction that writes one of its scalar registers by less than five wait states, and
+//     the compiler, which reads spilled ones back with v_readlane, does not look into assembly: the instructions before the load make five.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t dst, int voff, int soff)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
 }
 __device__ __forceinline__ void lds_load4(__amdgpu_buffer_rsrc_t rsrc, uint32_t dst, int voff, int soff)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, %3 offen lds" : : "s"(dst), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
 }
 // ... past the L2
 __device__ __forceinline__ void lds_load4_agent(__amdgpu_buffer_rsrc_t rsrc, uint32_t dst)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen sc1 lds" : : "s"(dst), "v"(0), "s"(rsrc) : "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen sc1 lds" : : "s"(dst), "v"(0), "s"(rsrc) : "m0");
 }
 #pragma clang diagnostic pop
 

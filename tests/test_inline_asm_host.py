@@ -4,6 +4,7 @@ wrappers where their neighbours are closest, and the kernels that use them."""
 import re
 import shutil
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 from pathlib import Path
 
 import pytest
@@ -12,6 +13,9 @@ CSRC = Path(__file__).resolve().parents[1] / "paper_2603_01960_amd" / "csrc"
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
 pytestmark = pytest.mark.skipif(not Path(HIPCC).exists(), reason="hipcc not available")
+
+# translation units with kernels that use them
+UNITS = [CSRC / f"sdpa_bwd_{x}.hip" for t in ("f16", "bf16") for x in (f"chain_{t}_d64", f"chain_{t}_d96", f"chain_{t}_d128", f"{t}_d64")]
 
 PRELUDE = '#include "sdpa_bwd_chain_kernel.h"\nusing namespace tsdpa;\n'
 
@@ -44,6 +48,45 @@ def probe(tmp_path, body):
     return assembly(src, tmp_path / "probe.s")
 
 
+@pytest.fixture(scope="module")
+def units(tmp_path_factory):
+    at = tmp_path_factory.mktemp("units")
+    with ThreadPoolExecutor(len(UNITS)) as pool:
+        return dict(zip((u.name for u in UNITS), pool.map(lambda u: assembly(u, at / (u.stem + ".s")), UNITS)))
+
+
+def registers(operand):
+    """{("s", 4), ("s", 5)} of s[4:5]"""
+    m = re.match(r"([vas])(?:(\d+)|\[(\d+):(\d+)\])$", operand)
+    if not m:
+        return set()
+    first, last = (m[2], m[2]) if m[2] else (m[3], m[4])
+    return {(m[1], i) for i in range(int(first), int(last) + 1)}
+
+
+def before(code, at, states):
+    """The instructions up to `states` wait states before instruction `at`, nearest first.  (Straight back in the listing: what stands between
+    an instruction in assembly and its neighbours does so on every way to it.)"""
+    i = at - 1
+    while i >= 0 and states > 0:
+        name, operands, _ = code[i]
+        if not name.endswith(":"):
+            yield code[i]
+            states -= int(operands[0]) + 1 if name == "s_nop" else 1
+        i -= 1
+
+
+def late_scalars(code):
+    """Memory instructions in assembly less than five wait states after a vector instruction that writes a scalar register they read."""
+    found, seen = [], 0
+    for i, (name, operands, by_hand) in enumerate(code):
+        if by_hand and name.startswith("buffer_"):
+            seen += 1
+            used = {r for x in operands for r in registers(x) if r[0] == "s"}
+            found += [(code[i], other) for other in before(code, i, 5) if other[0].startswith("v_") and registers(other[1][0]) & used]
+    return found, seen
+
+
 def test_m0_of_the_compilers_loads_survives_a_load_in_assembly(tmp_path):
     """A load to the LDS takes its address from m0, which the compiler sets once for loads to the same place: not past a load in assembly."""
     code = probe(tmp_path, r"""
@@ -70,3 +113,25 @@ __global__ void loads(int *p, int bytes, int at, int other)
             loads += 1
             assert set_by == by_hand, f"load {loads} has the m0 of the one before it"
     assert loads == 7
+
+
+def test_loads_in_assembly_wait_for_scalar_registers_that_vector_instructions_write(tmp_path, units):
+    code = probe(tmp_path, r"""
+__global__ void loads(const int *words, int lane, int dst)
+{
+    const int x = words[threadIdx.x];
+    auto word = [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, lane + i); };
+    auto rsrc = [&](int i) __attribute__((always_inline)) {
+        void *at = (void *)((unsigned long long)(unsigned)word(i) | (unsigned long long)(unsigned)word(i + 1) << 32);
+        return __builtin_amdgcn_make_buffer_rsrc(at, (short)0, word(i + 2), 0x00020000);
+    };
+    lds_load16(rsrc(0), dst, 0, word(3));
+    lds_load4(rsrc(4), dst, 0, word(7));
+    lds_load4_agent(rsrc(8), dst);
+}
+""")
+    found, seen = late_scalars(code)
+    assert seen == 3 and not found, found
+    for name, code in units.items():
+        found, seen = late_scalars(code)
+        assert seen > 0 and not found, f"{name}: {found}"
