@@ -74,16 +74,19 @@ __device__ __forceinline__ void wait_all()
     asm volatile("" ::: "memory");
 }
 
-// acc += a b with the accumulator in the registers that only matrix instructions reach
+// acc0 += a b0, acc1 += a b1 with the accumulators in the registers that only matrix instructions reach.  A matrix instruction must not
+// read a register less than two wait states after a vector instruction has written it, and the compiler, which may put a copy of an
+// operand anywhere, does not look into assembly: the instruction before the products makes two.  (It costs 7 clocks: by pairs of
+// products 0.6 % of a call, one by one 2 to 3 % at D = 64.)
 template <typename T> struct AccMfma;
 template <> struct AccMfma<_Float16> {
-    static __device__ __forceinline__ void run(f32x16 &acc, f16x8 a, f16x8 b) {
-        asm("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    static __device__ __forceinline__ void run(f32x16 &acc0, f32x16 &acc1, f16x8 a, f16x8 b0, f16x8 b1) {
+        asm("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %2, %3, %0\n\tv_mfma_f32_32x32x16_f16 %1, %2, %4, %1" : "+a"(acc0), "+a"(acc1) : "v"(a), "v"(b0), "v"(b1));
     }
 };
 template <> struct AccMfma<__bf16> {
-    static __device__ __forceinline__ void run(f32x16 &acc, bf16x8 a, bf16x8 b) {
-        asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    static __device__ __forceinline__ void run(f32x16 &acc0, f32x16 &acc1, bf16x8 a, bf16x8 b0, bf16x8 b1) {
+        asm("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\tv_mfma_f32_32x32x16_bf16 %1, %2, %4, %1" : "+a"(acc0), "+a"(acc1) : "v"(a), "v"(b0), "v"(b1));
     }
 };
 
@@ -465,8 +468,7 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
                     hf[i + 2 - 2 * DB] = tr_frag(0, i + 2 - 2 * DB);
                     read_qk(i + 2 - 2 * DB);
                 }
-                AccMfma<T>::run(dv[0][i % DB], tf[i], frag(pw[0], i / DB));
-                AccMfma<T>::run(dv[1][i % DB], tf[i], frag(pw[1], i / DB));
+                AccMfma<T>::run(dv[0][i % DB], dv[1][i % DB], tf[i], frag(pw[0], i / DB), frag(pw[1], i / DB));
                 if (i < 4) grad(1, i);
                 fence();
             }
@@ -492,7 +494,7 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
                     read_qk(ks + 2);
                     read_qd(ks + 2);
                 }
-                constexpr int NDK = 4 * DB;       // dK products: key block i & 1, fragment i / 2
+                constexpr int NDK = 4 * DB;       // dK products: key block i & 1, fragment i / 2, by pairs
 #pragma unroll
                 for (int i = ks * NDK / KS; i < (ks + 1) * NDK / KS; ++i)
                     if (i % 2 == 0 && i / 2 + 2 < 2 * DB) hf[i / 2 + 2] = tr_frag(0, i / 2 + 2);
@@ -508,7 +510,7 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
                 }
 #pragma unroll
                 for (int i = ks * NDK / KS; i < (ks + 1) * NDK / KS; ++i)
-                    AccMfma<T>::run(dk[i & 1][i / 2 % DB], hf[i / 2], frag(xw[i & 1], i / 2 / DB));
+                    if (i % 2 == 1) AccMfma<T>::run(dk[0][i / 2 % DB], dk[1][i / 2 % DB], hf[i / 2], frag(xw[0], i / 2 / DB), frag(xw[1], i / 2 / DB));
                 if (ks == KS - 4) load_next();
                 fence();
             }

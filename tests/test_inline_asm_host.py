@@ -87,6 +87,18 @@ def late_scalars(code):
     return found, seen
 
 
+def late_operands(code):
+    """Matrix instructions in assembly less than two wait states after a vector instruction that writes a register they read."""
+    found, seen = [], 0
+    for i, (name, operands, by_hand) in enumerate(code):
+        if by_hand and name.startswith("v_mfma"):
+            seen += 1
+            used = set().union(*(registers(x) for x in operands[1:]))
+            found += [(code[i], other) for other in before(code, i, 2)
+                      if other[0].startswith("v_") and not other[0].startswith("v_mfma") and registers(other[1][0]) & used]
+    return found, seen
+
+
 def test_m0_of_the_compilers_loads_survives_a_load_in_assembly(tmp_path):
     """A load to the LDS takes its address from m0, which the compiler sets once for loads to the same place: not past a load in assembly."""
     code = probe(tmp_path, r"""
@@ -135,3 +147,30 @@ __global__ void loads(const int *words, int lane, int dst)
     for name, code in units.items():
         found, seen = late_scalars(code)
         assert seen > 0 and not found, f"{name}: {found}"
+
+
+@pytest.mark.parametrize("vec,elem", [("f16x8", "_Float16"), ("bf16x8", "__bf16")])
+def test_matrix_instructions_in_assembly_wait_for_operands_that_vector_instructions_write(tmp_path, vec, elem):
+    code = probe(tmp_path, r"""
+__global__ void products(const u32x4 *in, float *out, unsigned x)
+{
+    f32x16 acc0, acc1;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc0[i] = acc1[i] = 0.f;
+    const u32x4 a = in[threadIdx.x], b = in[threadIdx.x + 64];
+    for (int i = 0; i < 3; ++i) AccMfma<ELEM>::run(acc0, acc1, __builtin_bit_cast(VEC, a ^ (x + i)), __builtin_bit_cast(VEC, b ^ (x - i)),
+                                                   __builtin_bit_cast(VEC, b + (x ^ i)));
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum += acc0[i] * acc1[i];
+    out[threadIdx.x] = sum;
+}
+""".replace("VEC", vec).replace("ELEM", elem))
+    found, seen = late_operands(code)
+    assert seen >= 2 and not found, found
+
+
+def test_matrix_instructions_of_the_kernels_wait_for_their_operands(units):
+    for name, code in units.items():
+        found, seen = late_operands(code)
+        assert (seen > 0) == ("chain" in name) and not found, f"{name}: {found}"
