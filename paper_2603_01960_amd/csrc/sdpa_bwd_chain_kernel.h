@@ -90,6 +90,17 @@ template <> struct AccMfma<__bf16> {
     }
 };
 
+// Accumulators of such products, for others to read from here on: no product moves behind the wait and no reader ahead of it, which is
+// longer than the 19 states that the longest product takes.
+template <int N> __device__ __forceinline__ void settle(f32x16 (&a)[2][N], f32x16 (&b)[2][N])
+{
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) asm volatile("" : "+a"(a[i / N][i % N]), "+a"(b[i / N][i % N]));
+    asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) asm volatile("" : "+a"(a[i / N][i % N]), "+a"(b[i / N][i % N]));
+}
+
 template <typename T, int D>
 __global__ void __launch_bounds__(kChainWaves * 64, 1)
 sdpa_bwd_chain_kernel(const ChainArgs by_value)
@@ -576,7 +587,7 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
         __syncthreads();                          // every wavefront past its last LDS read
 
         // ---- dK and dV, turned through the LDS
-        asm volatile("s_nop 15\n\ts_nop 15");     // the last products into the accumulators are done
+        settle(dk, dv);
         auto store = [&](const f32x16 (&acc)[DB], int kb, float factor, T *dst) __attribute__((always_inline)) {
             constexpr int OCPR = G::OROW / 16, CMASK = OCPR - 1;
             const lds_ptr ow = lds + wave * (32 * G::OROW);

@@ -23,8 +23,9 @@ PRELUDE = '#include "sdpa_bwd_chain_kernel.h"\nusing namespace tsdpa;\n'
 def assembly(src: Path, out: Path):
     """The instructions of a translation unit, [(name, operands, written in assembly)], labels as names with a colon."""
     from paper_2603_01960_amd import build as lib_build
-    subprocess.run([HIPCC, *lib_build.FLAGS, *lib_build.extra_flags(src), "-S", "--cuda-device-only", str(src), "-o", str(out)],
-                   check=True, capture_output=True, timeout=600)
+    done = subprocess.run([HIPCC, *lib_build.FLAGS, *lib_build.extra_flags(src), "-S", "--cuda-device-only", str(src), "-o", str(out)],
+                          capture_output=True, text=True, timeout=600)
+    assert done.returncode == 0, done.stderr
     code, by_hand = [], False
     for line in out.read_text().split("\n"):
         if "#ASMSTART" in line or "#ASMEND" in line:
@@ -99,6 +100,18 @@ def late_operands(code):
     return found, seen
 
 
+def early_results(code):
+    """Instructions of the compiler's that touch an accumulator less than 19 wait states after a matrix instruction in assembly that writes it."""
+    found, seen = [], 0
+    for i, (_, operands, by_hand) in enumerate(code):
+        touched = {r for x in operands for r in registers(x) if r[0] == "a"}
+        if not by_hand and touched:
+            seen += 1
+            found += [(code[i], other) for other in before(code, i, 19)
+                      if other[2] and other[0].startswith("v_mfma") and registers(other[1][0]) & touched]
+    return found, seen
+
+
 def test_m0_of_the_compilers_loads_survives_a_load_in_assembly(tmp_path):
     """A load to the LDS takes its address from m0, which the compiler sets once for loads to the same place: not past a load in assembly."""
     code = probe(tmp_path, r"""
@@ -150,27 +163,32 @@ __global__ void loads(const int *words, int lane, int dst)
 
 
 @pytest.mark.parametrize("vec,elem", [("f16x8", "_Float16"), ("bf16x8", "__bf16")])
-def test_matrix_instructions_in_assembly_wait_for_operands_that_vector_instructions_write(tmp_path, vec, elem):
+def test_matrix_instructions_in_assembly_keep_their_distances(tmp_path, vec, elem):
     code = probe(tmp_path, r"""
 __global__ void products(const u32x4 *in, float *out, unsigned x)
 {
-    f32x16 acc0, acc1;
+    f32x16 k[2][1], v[2][1];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc0[i] = acc1[i] = 0.f;
+    for (int i = 0; i < 16; ++i) k[0][0][i] = k[1][0][i] = v[0][0][i] = v[1][0][i] = 0.f;
     const u32x4 a = in[threadIdx.x], b = in[threadIdx.x + 64];
-    for (int i = 0; i < 3; ++i) AccMfma<ELEM>::run(acc0, acc1, __builtin_bit_cast(VEC, a ^ (x + i)), __builtin_bit_cast(VEC, b ^ (x - i)),
-                                                   __builtin_bit_cast(VEC, b + (x ^ i)));
+    auto made = [&](const u32x4 &y) __attribute__((always_inline)) { return __builtin_bit_cast(VEC, y); };
+    for (unsigned i = 0; i < 3; ++i) AccMfma<ELEM>::run(k[0][0], k[1][0], made(a ^ (x + i)), made(b ^ (x - i)), made(b + (x ^ i)));
+    AccMfma<ELEM>::run(v[0][0], v[1][0], made(a), made(a), made(b));
+    settle(k, v);
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sum += acc0[i] * acc1[i];
+    for (int i = 0; i < 16; ++i) sum += k[0][0][i] * k[1][0][i] + v[0][0][i] * v[1][0][i];
     out[threadIdx.x] = sum;
 }
 """.replace("VEC", vec).replace("ELEM", elem))
-    found, seen = late_operands(code)
-    assert seen >= 2 and not found, found
+    for check in (late_operands, early_results):
+        found, seen = check(code)
+        assert seen >= 2 and not found, f"{check.__name__}: {found}"
 
 
-def test_matrix_instructions_of_the_kernels_wait_for_their_operands(units):
+@pytest.mark.parametrize("check", [late_operands, early_results])
+def test_matrix_instructions_of_the_kernels_keep_their_distances(units, check):
     for name, code in units.items():
-        found, seen = late_operands(code)
-        assert (seen > 0) == ("chain" in name) and not found, f"{name}: {found}"
+        if "chain" in name:
+            found, seen = check(code)
+            assert seen > 0 and not found, f"{name}: {found}"
