@@ -78,15 +78,26 @@ __device__ __forceinline__ void wait_all()
 // read a register less than two wait states after a vector instruction has written it, and the compiler, which may put a copy of an
 // operand anywhere, does not look into assembly: the instruction before the products makes two.  (It costs 7 clocks: by pairs of
 // products 0.6 % of a call, one by one 2 to 3 % at D = 64.)
+//   * Of the 64 keys only the first `keys`, a multiple of 32 or less than one.  (As a branch of the compiler's, the accumulators moved at every join.)
 template <typename T> struct AccMfma;
 template <> struct AccMfma<_Float16> {
     static __device__ __forceinline__ void run(f32x16 &acc0, f32x16 &acc1, f16x8 a, f16x8 b0, f16x8 b1) {
         asm("s_nop 1\n\tv_mfma_f32_32x32x16_f16 %0, %2, %3, %0\n\tv_mfma_f32_32x32x16_f16 %1, %2, %4, %1" : "+a"(acc0), "+a"(acc1) : "v"(a), "v"(b0), "v"(b1));
     }
+    static __device__ __forceinline__ void run(f32x16 &acc0, f32x16 &acc1, f16x8 a, f16x8 b0, f16x8 b1, int keys) {
+        asm("s_cmp_lt_i32 %5, 32\n\ts_cbranch_scc1 .Lhidden%=\n\tv_mfma_f32_32x32x16_f16 %0, %2, %3, %0\n\t"
+            "s_cmp_lt_i32 %5, 64\n\ts_cbranch_scc1 .Lhidden%=\n\tv_mfma_f32_32x32x16_f16 %1, %2, %4, %1\n.Lhidden%=:"
+            : "+a"(acc0), "+a"(acc1) : "v"(a), "v"(b0), "v"(b1), "s"(keys) : "scc");
+    }
 };
 template <> struct AccMfma<__bf16> {
     static __device__ __forceinline__ void run(f32x16 &acc0, f32x16 &acc1, bf16x8 a, bf16x8 b0, bf16x8 b1) {
         asm("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\tv_mfma_f32_32x32x16_bf16 %1, %2, %4, %1" : "+a"(acc0), "+a"(acc1) : "v"(a), "v"(b0), "v"(b1));
+    }
+    static __device__ __forceinline__ void run(f32x16 &acc0, f32x16 &acc1, bf16x8 a, bf16x8 b0, bf16x8 b1, int keys) {
+        asm("s_cmp_lt_i32 %5, 32\n\ts_cbranch_scc1 .Lhidden%=\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\t"
+            "s_cmp_lt_i32 %5, 64\n\ts_cbranch_scc1 .Lhidden%=\n\tv_mfma_f32_32x32x16_bf16 %1, %2, %4, %1\n.Lhidden%=:"
+            : "+a"(acc0), "+a"(acc1) : "v"(a), "v"(b0), "v"(b1), "s"(keys) : "scc");
     }
 };
 
@@ -455,6 +466,13 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
             auto frag = [&](const u32x2 (&w)[4], int ks) __attribute__((always_inline)) -> vec8 {
                 return __builtin_bit_cast(vec8, u32x4{w[2 * ks][0], w[2 * ks][1], w[2 * ks + 1][0], w[2 * ks + 1][1]});
             };
+            // products of dV or dK with the wavefront's 64 keys.  Without the blocks of 32 that no query of the tile sees: their weights are
+            // zero, which a row of infinities would turn into NaN.
+            const int visible_keys = causal ? j * TS + TS - w0 : 64;
+            auto add = [&](f32x16 (&acc)[2][DB], int db, vec8 a, const u32x2 (&w)[2][4], int ks) __attribute__((always_inline)) {
+                if constexpr (MASK) AccMfma<T>::run(acc[0][db], acc[1][db], a, frag(w[0], ks), frag(w[1], ks), visible_keys);
+                else                AccMfma<T>::run(acc[0][db], acc[1][db], a, frag(w[0], ks), frag(w[1], ks));
+            };
             constexpr int KS = SMALL ? KEYS / 32 : KEYS / 16;
             vec8 qk[KS][NKP], qd[KS][SMALL ? NDP : 1];
             auto read_qk = [&](int ks) __attribute__((always_inline)) {
@@ -479,7 +497,7 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
                     hf[i + 2 - 2 * DB] = tr_frag(0, i + 2 - 2 * DB);
                     read_qk(i + 2 - 2 * DB);
                 }
-                AccMfma<T>::run(dv[0][i % DB], dv[1][i % DB], tf[i], frag(pw[0], i / DB), frag(pw[1], i / DB));
+                add(dv, i % DB, tf[i], pw, i / DB);
                 if (i < 4) grad(1, i);
                 fence();
             }
@@ -521,7 +539,7 @@ sdpa_bwd_chain_kernel(const ChainArgs by_value)
                 }
 #pragma unroll
                 for (int i = ks * NDK / KS; i < (ks + 1) * NDK / KS; ++i)
-                    if (i % 2 == 1) AccMfma<T>::run(dk[0][i / 2 % DB], dk[1][i / 2 % DB], hf[i / 2], frag(xw[0], i / 2 / DB), frag(xw[1], i / 2 / DB));
+                    if (i % 2 == 1) add(dk, i / 2 % DB, hf[i / 2], xw, i / 2 / DB);
                 if (ks == KS - 4) load_next();
                 fence();
             }

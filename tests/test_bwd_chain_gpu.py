@@ -138,3 +138,32 @@ def test_recorded_into_a_graph_and_on_two_streams():
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(grads, want))
+
+
+@pytest.mark.parametrize("D,hkv,G,S", [(64, 16, 1, 8170), (96, 31, 1, 3999), (96, 32, 3, 4070), (128, 64, 1, 2048), (128, 62, 1, 2017), (128, 32, 2, 4095)])
+def test_rows_of_nan_stay_with_the_keys_they_see(D, hkv, G, S):
+    """Under the mask a query row that is not finite, in Q (with O and LSE) or in dO, changes nothing for the keys behind its tile of 32, nor
+    for the other query rows that come before it or belong to other heads."""
+    from paper_2603_01960_amd import binding
+    g = torch.Generator("cuda").manual_seed(S - D)
+    draw = lambda h: torch.randn((1, h, S, D), device="cuda", generator=g).bfloat16()
+    q, k, v, dout = draw(hkv * G), draw(hkv), draw(hkv), draw(hkv * G)
+    assert binding.bwd_full_workspace_bytes(1, hkv * G, hkv, S, D, True) > binding.bwd_workspace_bytes(1, hkv * G, S)
+    o, lse = binding.sdpa_kv(q, k, v, True, return_lse=True)
+    want = binding.sdpa_backward(q, k, v, o, dout, lse, True)
+    last = hkv * G - 1
+    # a first block's first tile and its last one, a wavefront's second 32 keys, tiles of the last block
+    for row in (5, 255, 1067, S - 200, S - 1):
+        for where in ("q", "dout"):
+            q1, d1 = q.clone(), dout.clone()
+            (q1 if where == "q" else d1)[0, last, row] = float("nan")
+            o1, lse1 = binding.sdpa_kv(q1, k, v, True, return_lse=True) if where == "q" else (o, lse)
+            dq, dk, dv = binding.sdpa_backward(q1, k, v, o1, d1, lse1, True)
+            behind = (row // 32 + 1) * 32
+            assert torch.isnan(dv[0, -1, :row + 1]).all()
+            assert torch.equal(dk[0, -1, behind:], want[1][0, -1, behind:]), f"dk, {where} row {row}"
+            assert torch.equal(dv[0, -1, behind:], want[2][0, -1, behind:]), f"dv, {where} row {row}"
+            assert torch.equal(dk[0, :-1], want[1][0, :-1]) and torch.equal(dv[0, :-1], want[2][0, :-1])
+            others = torch.arange(S, device="cuda") != row
+            assert torch.equal(dq[0, last, others], want[0][0, last, others]), f"dq, {where} row {row}"
+            assert torch.equal(dq[0, :last], want[0][0, :last])
