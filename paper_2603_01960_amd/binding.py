@@ -322,6 +322,12 @@ def sdpa_backward(q, k, v, o, dout, lse, causal: bool = False, scale=None, *, wo
     (``return_lse=True``) for the same q, k, v, causal and scale.  ``grads=(dq, dk, dv)`` and
     ``workspace`` let the caller own the buffers; otherwise torch allocates them.
 
+    The workspace that torch allocates is :func:`bwd_full_workspace_bytes`: for large calls at D = 64, 96 and 128 FP32 sums of dQ, twice
+    the bytes of q and at most 2.3 GB (in a captured graph they stay with the graph).  If it cannot be had, and with a caller's workspace of at
+    least :func:`bwd_workspace_bytes` but less than that, the call takes kernels without such sums: 0.9 of the speed, the gradients differ
+    in their last bits.  The same workspace size always gives the same bits; a program that needs them to not depend on
+    the memory that is free passes a workspace.
+
     Grouped heads: k, v [B, Hkv, S, D] with H a multiple of Hkv (the forward of ``sdpa_kv`` at Sq = Skv);
     dk, dv then have the shape of k and hold the sum over the query heads of each group."""
     return _checked(_calls().sdpa_backward(q, k, v, o, dout, lse, causal, scale, workspace, grads))

@@ -68,6 +68,30 @@ def test_passes_where_the_workspace_has_no_room_for_the_sums():
     assert taken > 0
 
 
+def test_passes_where_torch_has_no_memory_for_the_sums():
+    """With less memory left than the sums need, but enough for the statistics, the call gives what a workspace of the least size does."""
+    from paper_2603_01960_amd import binding
+    g = torch.Generator("cuda").manual_seed(7)
+    q, k, v, dout = (torch.randn((2, 64, 2048, 128), device="cuda", generator=g).bfloat16() for _ in range(4))
+    o, lse = binding.sdpa(q, k, v, True, return_lse=True)
+    full, least = binding.bwd_full_workspace_bytes(2, 64, 64, 2048, 128, True), binding.bwd_workspace_bytes(2, 64, 2048)
+    assert full > 128 << 20 and least < 16 << 20
+    want = binding.sdpa_backward(q, k, v, o, dout, lse, True, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    sums = binding.sdpa_backward(q, k, v, o, dout, lse, True)
+    grads = tuple(torch.empty_like(t) for t in (q, k, v))
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(full, dtype=torch.uint8, device="cuda")
+        binding.sdpa_backward(q, k, v, o, dout, lse, True, grads=grads)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert all(torch.equal(a, b) for a, b in zip(grads, want))
+    assert not all(torch.equal(a, b) for a, b in zip(grads, sums))       # (so it was the other form)
+
+
 @pytest.mark.parametrize("D,hkv,G,S,causal", [(64, 62, 1, 2041, False), (96, 31, 1, 3999, True), (128, 62, 1, 2041, False), (128, 32, 2, 4095, True)])
 def test_keys_of_infinities(D, hkv, G, S, causal):
     """A key whose score is -inf for every query has gradients of zero, also where rows past the end, whose score with it is NaN (0 * inf),
