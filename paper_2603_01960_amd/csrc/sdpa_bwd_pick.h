@@ -212,14 +212,22 @@ inline ChainLayout chain_layout(int heads, int group, int S, int D, int per_clai
 //     heads in a claim, the more;
 //   * 2.2 % for every doubling of the claim's blocks beyond two per CU, of which the L2 holds less.
 // (us, claims of 1, 2, 4, 8 heads, D = 128 causal: 64 heads S = 8192 2908, 2800, 2868, 2925; S = 2048 277, 268, 238, 240.)
-// The step itself is 0.75 ... 0.85 of the two passes' time for the same work, which leaves the lines below (us, passes / five products, BF16;
-// ideal / cost):
-//   D = 128  64 heads S = 1024 121 / 116 (0.8), 60 heads 116 / 115 (0.75), 32 heads S = 2048 221 / 206 (0.84), 16 heads S = 8192 1638 / 1336 (0.96);
-//            causal 128 heads S = 1024 152 / 151 (0.67), 64 heads S = 2048 259 / 238 (0.8), 16 heads S = 8192 903 / 713 (0.91);
-//   D = 96   64 heads S = 1024 96 / 95 (0.8), 32 heads S = 2048 176 / 167 (0.84); causal 128 heads S = 1024 120 / 120, 64 heads S = 2048 198 / 184;
-//   D = 64   (what a wavefront issues beside the products weighs twice as much) 128 heads S = 1024 125 / 127 (0.84), 16 heads S = 4096 228 / 234
-//            (0.87), 64 heads S = 2048 231 / 213 (0.89); causal 64 heads S = 2048 137 / 136 (0.8), 32 heads S = 4096 248 / 231 (0.89),
-//            grouped 64 over 16 heads S = 8192 1798 / 1901 (0.96).
+// The step itself is 0.75 ... 0.9 of the two passes' time for the same work, which leaves the first of the lines below (us, passes / five
+// products, mean of both types and of several runs; ideal / cost):
+//   D = 128  64 heads S = 1024 117 / 114 (0.80), 32 heads S = 2048 213 / 201 (0.84), 16 heads S = 3777 383 / 346 (0.80); causal 230 heads S = 2048
+//            892 / 898 (0.77), 64 heads S = 2048 249 / 232 (0.80); grouped, causal 192 over 64 heads S = 2304 888 / 888 (0.86);
+//   D = 96   32 heads S = 2048 174 / 170 (0.84), 128 heads S = 1024 178 / 171 (0.87); causal 64 heads S = 2779 327 / 334 (0.83), 128 heads S = 3456
+//            968 / 935 (0.87);
+//   D = 64   (what a wavefront issues beside the products weighs twice as much) 8 heads S = 8192 460 / 464 (0.88), 128 heads S = 2048 462 / 439
+//            (0.93), 64 heads S = 8192 3476 / 3279 (0.98); causal 32 heads S = 8192 896 / 847 (0.93); grouped, causal not at all (64 over 16
+//            heads S = 8192 1798 / 1901, 0.96).
+// Where the step is short, at D = 64, and causal at D = 96, a call has to reach a second line as well, with eight or four more steps of
+// prologue and epilogue per round and a quarter of the steps of a claim's start for every claim that follows another: D = 64, 384 over 128
+// heads S = 512 101 / 105, 1648 over 206 heads S = 1408 2818 / 3004, causal 128 heads S = 4096 962 / 987; D = 96, causal, 64 heads S = 2432 260 / 269,
+// 222 heads S = 2048 666 / 687.
+// Timed on 1943 shapes above the first lines, most within a tenth: 34 of them are below the second ones (mean of five products / passes 1.01);
+// the others are at 0.915 on average, 18 of them above 1.02 (the worst 92 over 23 heads S = 4992, causal, D = 128, 1.08).  One box and
+// the next differ by 3 % in that quotient.
 // D = 160 has no registers for it.  At most 2 GiB of sums, and 1 GiB per group of heads (the range of their descriptor).
 constexpr size_t kChainMostBytes = (size_t)2 << 30;
 inline int pick_bwd_chain(int D, bool causal, int heads, int group, int S)
@@ -228,7 +236,7 @@ inline int pick_bwd_chain(int D, bool causal, int heads, int group, int S)
     if (D == 160 || (D == 64 && causal && group > 1) || HK * nB < 128) return 0;
     if (heads * nT * 32 * D * 4 > (long long)kChainMostBytes || group * nT * 32 * D * 4 >= 1ll << 30) return 0;
     const long long per_head = group * (causal ? nB * nT - 4 * nB * (nB - 1) : nB * nT);     // steps (causal: blocks of nT, nT - 8, ... tiles)
-    long long pick = 0, least = 0;                // cost times 1000
+    long long pick = 0, least = 0, more = 0;      // costs times 1000
     for (long long m = 1; m <= (HK + 7) / 8 && m <= 32; ++m) {
         const long long most = ((HK + m - 1) / m + 7) / 8 * m, rounds = (most * nB + 31) / 32;      // heads of the XCD that gets the most
         const long long links = nB < (32 + m - 1) / m ? nB : (32 + m - 1) / m;
@@ -242,11 +250,15 @@ inline int pick_bwd_chain(int D, bool causal, int heads, int group, int S)
         if (pick == 0 || cost < least) {
             pick = m;
             least = cost;
+            more = (D == 64 ? 8000 : 4000) * rounds + 250 * links * (most / m - 1);
         }
     }
     const long long ideal = HK * S * group * nT / (causal ? 2 : 1);      // times 256 * 256
-    const int line = D == 64 ? 87 : causal && group > 1 ? 85 : D == 96 ? (causal ? 79 : 83) : causal ? 76 : 78;      // per cent
-    return ideal * 100 * 1000 >= least * 65536 * line ? (int)pick : 0;
+    auto reaches = [&](long long cost, int line) { return ideal * 1000 * 1000 >= cost * 65536 * line; };      // (per mille)
+    if (!reaches(least, D == 64 ? (!causal && group >= 4 ? 875 : 870) : causal && group > 1 ? 850 : D == 96 ? (causal ? 790 : 830) : causal ? 760 : 780)) return 0;
+    if (D == 64 && !reaches(least + more, causal ? 800 : group > 1 ? 805 : 750)) return 0;
+    if (D == 96 && causal && group == 1 && !reaches(least + more, 728)) return 0;
+    return (int)pick;
 }
 
 }  // namespace tsdpa

@@ -15,6 +15,7 @@ using namespace tsdpa;
 extern "C" {
 int joint(int D, int causal, int heads, int group, int S) { return pick_bwd_joint(D, causal != 0, heads, group, S); }
 int one_launch(int D, int heads, int S) { return bwd_in_one_launch(D, heads, S); }
+int chain(int D, int causal, int heads, int group, int S) { return pick_bwd_chain(D, causal != 0, heads, group, S); }
 int pairs(int causal, int heads, int group, int S) { return pick_bwd_pairs(causal != 0, heads, group, S); }
 // wavefronts along the rows and streams of a pass in a launch of its own, as two digits
 int apart(int D, int causal, int keys, int heads, int group, int S)
@@ -64,6 +65,17 @@ def test_large_grouped_calls_keep_the_passes_apart(pick):
     for D, causal, hkv, G, S in ((64, 0, 99, 2, 512), (64, 0, 117, 2, 1241), (64, 0, 44, 2, 2048), (96, 0, 30, 2, 2048),
                                  (64, 1, 77, 4, 3879), (96, 1, 108, 2, 256)):
         assert pick.joint(D, causal, hkv * G, G, S) == 0
+
+
+def test_calls_that_five_products_make_slower_keep_the_passes(pick):
+    """Shapes at which they took 1.01 to 1.07 of the passes' time, on average over both types; others near by, at which they take 0.89 to 0.98, keep them."""
+    for D, causal, hkv, G, S in ((64, 0, 128, 3, 512), (64, 0, 128, 4, 512), (64, 0, 64, 2, 1024), (64, 0, 142, 4, 2048), (64, 0, 192, 1, 1024), (64, 0, 206, 8, 1408),
+                                 (64, 0, 256, 4, 1371), (64, 1, 63, 1, 4664), (64, 1, 128, 1, 4096), (64, 1, 128, 1, 4160), (96, 1, 64, 1, 2432),
+                                 (96, 1, 124, 1, 2432), (96, 1, 128, 1, 2048), (96, 1, 222, 1, 2048), (96, 1, 240, 1, 2048)):
+        assert pick.chain(D, causal, hkv * G, G, S) == 0, (D, causal, hkv, G, S)
+    for D, causal, hkv, G, S in ((64, 0, 128, 2, 1024), (64, 0, 32, 3, 1936), (64, 0, 128, 1, 2048), (64, 1, 32, 1, 4096), (64, 1, 32, 1, 8192), (96, 1, 128, 1, 3456),
+                                 (128, 1, 64, 1, 2048), (128, 0, 64, 1, 1024)):
+        assert pick.chain(D, causal, hkv * G, G, S) > 0, (D, causal, hkv, G, S)
 
 
 def test_the_gpu_cases_meet_every_kernel(pick):
