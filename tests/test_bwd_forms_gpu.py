@@ -8,12 +8,12 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-def _reference(q, k, v, dout, causal):
+def _reference(q, k, v, dout, causal, scale=None):
     """Gradients of Eq. 1 in float64; k and v repeated over the heads of a group, their gradients summed."""
     G = q.shape[1] // k.shape[1]
     q, dout = q.double(), dout.double()
     kr, vr = (t.double().repeat_interleave(G, 1) for t in (k, v))
-    scale = q.shape[-1] ** -0.5
+    scale = q.shape[-1] ** -0.5 if scale is None else scale
     s = (q @ kr.transpose(2, 3).contiguous()) * scale
     if causal:
         s = s.masked_fill(torch.ones(s.shape[-2:], dtype=torch.bool, device=s.device).triu(1), float("-inf"))

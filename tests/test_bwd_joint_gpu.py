@@ -27,7 +27,7 @@ CASES = [(64, 1, 1, 257), (64, 3, 1, 300), (64, 45, 1, 290), (64, 48, 1, 300),  
          # finds the kernels that some call takes and no case meets
          (64, 15, 2, 2564), (96, 17, 2, 130), (96, 260, 1, 130), (96, 22, 1, 680), (96, 4, 1, 1923), (96, 13, 1, 1154), (96, 5, 2, 770),
          (96, 112, 1, 67), (128, 17, 2, 129), (128, 134, 4, 33), (128, 86, 1, 1037), (128, 2, 1, 5601), (128, 15, 1, 1158), (128, 16, 4, 1024),
-         (128, 32, 2, 2040)]
+         (128, 32, 2, 2040), (96, 12, 1, 964), (96, 203, 1, 129)]
 
 
 @pytest.mark.parametrize("causal", [False, True])

@@ -42,11 +42,15 @@ def pick(tmp_path_factory):
     return ctypes.CDLL(str(at / "pick.so"))
 
 
-def kernels(pick, D, causal, hkv, G, S):
-    """The kernels of a call, as launch_bwd (csrc/sdpa_bwd_inst.h) takes them; the forms with streams of keys, and the passes with
-    streams, are one kernel for grouped and other heads."""
+def kernels(pick, D, causal, hkv, G, S, sums=True):
+    """The kernels of a call, as tiled_sdpa_bwd_gqa (csrc/tiled_sdpa.hip) and launch_bwd (csrc/sdpa_bwd_inst.h) take them, with a workspace for the
+    sums of dQ or without; the forms with streams of keys, and the passes with streams, are one kernel for grouped and other heads."""
     heads = hkv * G
+    if sums and pick.chain(D, causal, heads, G, S):
+        return {("five products", D)}
     if D <= 96 and G == 1 and S <= 256 and pick.one_launch(D, heads, S):
+        if D == 64 and S > 128 and heads > 256:
+            return {("heads one after another", causal)}
         return {("one launch", D, 2 if S <= 64 else 4 if S <= 128 else 8, causal)}
     form = pick.joint(D, causal, heads, G, S)
     if form:
@@ -79,11 +83,30 @@ def test_calls_that_five_products_make_slower_keep_the_passes(pick):
 
 
 def test_the_gpu_cases_meet_every_kernel(pick):
+    """In either type: the forms' cases alternate between the types, the others run in both."""
+    from test_bwd_chain_gpu import CASES as chain
     from test_bwd_forms_gpu import CASES as forms
     from test_bwd_joint_gpu import CASES as joint
 
-    met = {k for causal in (False, True) for D, hkv, G, S in [*joint, *((D, *c) for D in (64, 96, 128, 160) for c in forms)]
-           for k in kernels(pick, D, causal, hkv, G, S)}
+    met = set()
+    add = lambda types, kinds: met.update((t, k) for t in types for k in kinds)
+    both = ("f16", "bf16")
+    for causal in (False, True):
+        for D, hkv, G, S in joint:
+            add(both, kernels(pick, D, causal, hkv, G, S))
+        for D in (64, 96, 128, 160):
+            for i, (hkv, G, S) in enumerate(forms):
+                add(both[i % 2:i % 2 + 1], kernels(pick, D, causal, hkv, G, S))
+        # test_passes_where_the_workspace_has_no_room_for_the_sums
+        for D, hkv, G, S in [*joint, *((D, *c) for D in (64, 96, 128) for c in forms)]:
+            if pick.chain(D, causal, hkv * G, G, S):
+                add(both, kernels(pick, D, causal, hkv, G, S, sums=False))
+        # test_one_head_after_another
+        for heads, S in ((257, 256), (768, 197)):
+            add(both, kernels(pick, 64, causal, heads, 1, S))
+    for D, hkv, G, S, causal in chain:
+        assert kernels(pick, D, causal, hkv, G, S) == {("five products", D)}
+        add(both, kernels(pick, D, causal, hkv, G, S))
     heads = sorted({round(1.15 ** i) for i in range(51)})
     lengths = sorted({round(16 * 1.1 ** i) for i in range(73)} | {1, 32, 33, 64, 65, 128, 129, 256, 257, 512, 1024, 2048, 4096, 8192})
     missed = {}
@@ -92,6 +115,9 @@ def test_the_gpu_cases_meet_every_kernel(pick):
             for G in (1, 2, 3, 4, 8, 16):
                 for hkv in heads:
                     for S in lengths:
-                        for k in kernels(pick, D, causal, hkv, G, S) - met:
-                            missed.setdefault(k, (causal, hkv, G, S))
+                        for sums in (True, False):
+                            for k in kernels(pick, D, causal, hkv, G, S, sums):
+                                for t in both:
+                                    if (t, k) not in met:
+                                        missed.setdefault((t, k), (causal, hkv, G, S, sums))
     assert not missed, f"kernels that no case meets, each with a call that takes it: {missed}"

@@ -105,3 +105,35 @@ def test_main_loop_of_the_headline_kernels_touches_no_scratch_memory(dtype, tmp_
         square = re.search(r"ELi0EEEv", name) is not None
         assert with_mfma <= 2 and len(loops) - with_mfma <= (1 if square else 0), \
             f"{name}: {len(loops)} loops in the assembly, {with_mfma} with MFMAs (a load wrapped in a descriptor loop?)"
+
+
+@pytest.mark.skipif(not Path(HIPCC).exists(), reason="hipcc not available")
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_backward_kernels_that_count_their_loads_touch_no_scratch_memory_in_their_loops(dtype, tmp_path):
+    """The five products keep 256 accumulators and 256 other registers per lane and write the step out: nothing may be spilled.  Of the one-launch
+    backward of many heads a few values of a head's prologue may be, but nothing in its loop over the tiles."""
+    from paper_2603_01960_amd import build as lib_build
+
+    def assembly(name):
+        src, asm = CSRC / f"{name}.hip", tmp_path / f"{name}.s"
+        subprocess.run([HIPCC, *lib_build.FLAGS, *lib_build.extra_flags(src), "-S", "--cuda-device-only", str(src), "-o", str(asm)],
+                       check=True, capture_output=True, timeout=600)
+        return asm.read_text()
+
+    for D in (64, 96, 128):
+        text = assembly(f"sdpa_bwd_chain_{dtype}_d{D}")
+        body = text[re.search(r"^_ZN5tsdpa21sdpa_bwd_chain_kernel\S+:", text, re.M).start():]
+        assert "scratch_" not in body[:body.index("s_endpgm")], f"D = {D}"
+    text = assembly(f"sdpa_bwd_{dtype}_d64")
+    checked = 0
+    for m in re.finditer(r"^_ZN5tsdpa21sdpa_bwd_heads_kernel\S+:", text, re.M):
+        body = text[m.start():]
+        inner, mfma, scratch = False, 0, 0
+        for line in body[:body.index("s_endpgm")].split("\n"):
+            if re.match(r"^(\.LBB\d+_\d+:|; %bb\.\d+:)", line):
+                inner = "Depth=2" in line
+            mfma += inner and "v_mfma" in line
+            scratch += inner and "scratch_" in line
+        assert mfma > 0 and scratch == 0, f"{scratch} scratch accesses in the loop over the tiles"
+        checked += 1
+    assert checked == 2
