@@ -447,7 +447,7 @@ def bench_bwd(pkg, torch, args, flags):
         "roofline": {"bound": "mfma", "achieved": round(tf, 2), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tf / PEAK_MFMA_TFLOPS, 4),
                      # both kernels of a call, FETCH_SIZE + WRITE_SIZE scaled (profiles/sdpa_bwd_C4_C2.md)
-                     "traffic": 7979e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H and chain) else None,
+                     "traffic": 8535e6 if (w.name == "C4" and dtype == "bf16" and not causal and Hkv == w.H and chain) else None,
                      "kernel": kernels, "ms_avg_all_kernels": round(ms, 5), "algorithmic_flops_per_launch": flops,
                      "executed_mfma_flops_per_launch": flops * products / 5.0}}), flush=True)
 

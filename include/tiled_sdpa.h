@@ -295,7 +295,7 @@ unsigned long long tiled_sdpa_kv_workspace_bytes(int B, int H, int Sq, int D, in
  *                      bytes (two FP32 values per query row); caller-owned, used only during this call's
  *                      kernels, so calls that may overlap on the GPU need distinct workspaces.  With
  *                      tiled_sdpa_bwd_full_workspace_bytes bytes or more a large call takes five products
- *                      instead of seven (about 0.85 of the time).
+ *                      instead of seven (0.9 of the time on average).
  * Kernels enqueued on `stream`: dQ, which also leaves the row statistics in the workspace, or a kernel for these alone (Delta_i = <dO_i, O_i> and
  * LSE_i in log2 units; for query rows that see at most 64 keys -- S <= 64, or the first 64 rows under the causal mask --
  * Delta_i by its definition sum_j P_ij dP_ij in FP32, because on such rows the rounding of the 16-bit o inside
@@ -303,8 +303,11 @@ unsigned long long tiled_sdpa_kv_workspace_bytes(int B, int H, int Sq, int D, in
  * that was not computed before.  Sequences of up to 256 rows
  * at D = 64 and 96 with H = Hkv may take one kernel for all of it, which leaves the workspace alone.  No sum crosses
  * workgroups there.  With the full workspace, a kernel for the statistics and one for all three gradients, in which the parts of a
- * query row's dQ are summed across workgroups in a fixed order.  Results are deterministic either way; the two orders of summation
- * differ in the last bits.  Validation order: dtype, D, shape, empty problem, null pointers, alignment,
+ * query row's dQ are summed across workgroups in a fixed order.  Results are deterministic either way, and depend on
+ * workspace_bytes only by which of the two it is: their orders of summation differ in the last bits.
+ * Values that are not finite: under the causal mask a row of q (with its o and lse) or dout that holds one may make NaN of dk and dv of keys that
+ * it does not see, up to 127 rows behind it (full workspace: to the end of its 32 rows, counted from row 0), and a row of k of the dq of
+ * as many rows before it.  Validation order: dtype, D, shape, empty problem, null pointers, alignment,
  * scale, workspace, launch.
  */
 int tiled_sdpa_bwd(const void *q, const void *k, const void *v, const void *o, const void *dout,
@@ -331,7 +334,7 @@ int tiled_sdpa_bwd_gqa(const void *q, const void *k, const void *v, const void *
 unsigned long long tiled_sdpa_bwd_workspace_bytes(int B, int H, int S);
 
 /* Workspace bytes with which tiled_sdpa_bwd (Hkv = H) and tiled_sdpa_bwd_gqa are fastest: for large problems at D = 64, 96 and 128 room for
- * FP32 sums of dQ, about 4*B*H*S*D bytes and at most 2.2 GB; otherwise what tiled_sdpa_bwd_workspace_bytes says.  flags as for the
+ * FP32 sums of dQ, about 4*B*H*S*D bytes and at most 2.3 GB; otherwise what tiled_sdpa_bwd_workspace_bytes says.  flags as for the
  * call.  Never fails: for arguments that the call refuses, the latter too. */
 unsigned long long tiled_sdpa_bwd_full_workspace_bytes(int B, int H, int Hkv, int S, int D, unsigned flags);
 

@@ -9,21 +9,22 @@
 //
 // Who waits for whom: a workgroup takes its blocks by ticket, and waits only for blocks of lower tickets, which by then have a
 // workgroup that runs.  Whatever the order and the number of workgroups on the card, the lowest unfinished block waits for nobody, so
-// every wait ends.  The sums pass through the L2 of one XCD (12 KB or more per step and workgroup each way: past the L2, at agent scope, the whole
+// every wait ends.  The sums pass through the L2 of one XCD (8, 12 or 16 KB by head dim per step and workgroup each way: past the L2, at agent scope, the whole
 // pass takes 1.3 to 1.5 times as long): an XCD claims whole key/value heads, and its workgroups, which ask the hardware where they
 // are, take the blocks of its claims only.  A block starts by invalidating its CU's cache, in which a line of a sum could
 // be left from an earlier block; within a block each line is read once.  Progress counters are written and read at agent scope, after the
 // sums they stand for have been acknowledged.
 //
-// What bounds it: the matrix pipe under the power limit, with 5 instead of 7 products, at 0.55 to 0.65 of the pipe's cycles.  One wavefront
+// What bounds it: the matrix pipe under the power limit, with 5 instead of 7 products, at 0.57 of the pipe's cycles (64 heads S = 8192, D = 128).  One wavefront
 // per SIMD (512 registers: 256 accumulators that only matrix instructions touch, 256 others) and 64 keys per wavefront halve the LDS
 // reads per product against two wavefronts of 32 keys (which took 5.5 ms in the shape below, without the sums).  What a single wavefront
 // issues beside its products is then what limits it (a vector instruction takes 5.8 clocks, an exponential 12, a scalar one 5, a transposing
 // read 9, a product 32), so that the step is written out: reads two products ahead, the exponentials under the second half of
 // the scores and the first half of dP, dS under the second half and dV, dQ's reads under dK.  Fences keep that order; the loads to the LDS are written in
 // assembly, or the compiler would wait for all of them at the first transposing read.
-// BF16, D = 128, us per call, two passes -> this: 64 heads S = 8192 6040 -> 5270, S = 2048 412 -> 355, 8 heads S = 16384 3015 -> 2455,
-// 16 over 4 heads of four entries S = 4096 1536 -> 1277; causal 64 heads S = 8192 3134 -> 2700, S = 4096 832 -> 746.
+// BF16, us per call, two passes -> this: D = 128, 64 heads S = 8192 6237 -> 5433, S = 2048 423 -> 369, 8 heads S = 16384 3107 -> 2613,
+// 16 over 4 heads of four entries S = 4096 1572 -> 1334; causal 64 heads S = 8192 3263 -> 2820, S = 4096 855 -> 792; D = 96, 32 heads S = 4096
+// 629 -> 546; D = 64, 64 heads S = 2048 233 -> 224.
 #pragma once
 #include <mutex>
 #include "sdpa_bwd_joint_kernel.h"

@@ -228,7 +228,7 @@ inline ChainLayout chain_layout(int heads, int group, int S, int D, int per_clai
 // Timed on 1943 shapes above the first lines, most within a tenth: 34 of them are below the second ones (mean of five products / passes 1.01);
 // the others are at 0.915 on average, 18 of them above 1.02 (the worst 92 over 23 heads S = 4992, causal, D = 128, 1.08).  One box and
 // the next differ by 3 % in that quotient.
-// D = 160 has no registers for it.  At most 2 GiB of sums, and 1 GiB per group of heads (the range of their descriptor).
+// D = 160 has no registers for 64 keys per wavefront (320 accumulators); with 32 it would, which is not built.  At most 2 GiB of sums, and 1 GiB per group of heads (the range of their descriptor).
 constexpr size_t kChainMostBytes = (size_t)2 << 30;
 inline int pick_bwd_chain(int D, bool causal, int heads, int group, int S)
 {

@@ -472,9 +472,10 @@ template <typename T, int D, int NW> int launch_bwd_short_nw(const BwdLaunchArgs
 // fetches the next head's K, V and O into the LDS while it works on the present one, two load instructions per wavefront and tile; the
 // next head's first tiles and dO rows are on their way while dK and dV are stored.  As a workgroup per head, whose eight wavefronts
 // fill the CU, a head spent 13 of its 35 thousand clocks on the arrival of those, every CU at the same time, and 18 in the loop
-// with the memory idle.  us per call, BF16, a workgroup per head -> this: 768 heads of 197 rows
-// 54.2 -> 51.1 (causal 52.9 -> 46.5), 1030 of 130 55.9 -> 52.4 (62.1 -> 54.0), 520 of 160 36.9 -> 34.3 (40.6 -> 35.7), 600 of 225
-// 51.7 -> 49.6 (54.9 -> 50.2), 384 of 256 35.8 -> 35.3 (38.0 -> 36.4).  What bounds it: the loop as above, now with the memory at work
+// with the memory idle.  us per call, BF16, a workgroup per head -> this, the same tensors again and
+// again (24 sets of them in turn, so that they come from memory): 768 heads of 197 rows 50.9 -> 44.9 (56.6 -> 51.7), causal 53.8 -> 47.4
+// (60.1 -> 51.3), 1030 of 130 56.2 -> 51.3 (61.5 -> 52.7), 520 of 160 36.8 -> 33.7 (40.5 -> 36.3), 384 of 256 35.8 -> 34.4 (40.6 -> 38.3).
+// What bounds it: the loop as above, now with the memory at work
 // beside it, and the prologue of a workgroup's first head.
 template <typename T, bool CAUSAL>
 __global__ void __launch_bounds__(512, 2)
