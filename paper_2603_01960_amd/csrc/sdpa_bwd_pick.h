@@ -254,7 +254,7 @@ inline int pick_bwd_chain(int D, bool causal, int heads, int group, int S)
         }
     }
     const long long ideal = HK * S * group * nT / (causal ? 2 : 1);      // times 256 * 256
-    auto reaches = [&](long long cost, int line) { return ideal * 1000 * 1000 >= cost * 65536 * line; };      // (per mille)
+    auto reaches = [&](long long cost, int line) { return ideal * 15625 >= cost * 1024 * line; };        // line per mille, both sides over 64
     if (!reaches(least, D == 64 ? (!causal && group >= 4 ? 875 : 870) : causal && group > 1 ? 850 : D == 96 ? (causal ? 790 : 830) : causal ? 760 : 780)) return 0;
     if (D == 64 && !reaches(least + more, causal ? 800 : group > 1 ? 805 : 750)) return 0;
     if (D == 96 && causal && group == 1 && !reaches(least + more, 728)) return 0;
