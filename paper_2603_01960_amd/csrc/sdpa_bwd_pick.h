@@ -226,7 +226,7 @@ inline ChainLayout chain_layout(int heads, int group, int S, int D, int per_clai
 // heads S = 512 101 / 105, 1648 over 206 heads S = 1408 2818 / 3004, causal 128 heads S = 4096 962 / 987; D = 96, causal, 64 heads S = 2432 260 / 269,
 // 222 heads S = 2048 666 / 687.
 // Timed on 1943 shapes above the first lines, most within a tenth: 34 of them are below the second ones (mean of five products / passes 1.01);
-// the others are at 0.915 on average, 18 of them above 1.02 (the worst 92 over 23 heads S = 4992, causal, D = 128, 1.08).  One box and
+// the others are at 0.915 on average, 18 of them above 1.02 (the worst 92 over 23 heads S = 4992, causal, D = 128, 1.08).  One card and
 // the next differ by 3 % in that quotient.
 // D = 160 has no registers for 64 keys per wavefront (320 accumulators); with 32 it would, which is not built.  At most 2 GiB of sums, and 1 GiB per group of heads (the range of their descriptor).
 constexpr size_t kChainMostBytes = (size_t)2 << 30;
